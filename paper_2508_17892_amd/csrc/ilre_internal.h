@@ -13,6 +13,17 @@ constexpr int kHeadDim = ILRE_HEAD_DIM;
 constexpr int kNumCU = 256;  // MI355X: 256 compute units in 8 XCDs
 constexpr int kNumXCD = 8;
 
+// Asynchronous 16-byte-per-lane copy from a buffer resource straight into LDS: lane l of the
+// wavefront lands at lds_addr + 16*l; bytes past the resource's num_records read as zero.  Tracked
+// by vmcnt.  Issued as inline assembly so that the compiler's conservative alias handling does not
+// put a full vmcnt wait in front of every later LDS read.
+typedef __attribute__((ext_vector_type(4))) int i32x4;
+__device__ __forceinline__ void lds_dma16(i32x4 rsrc, unsigned lds_addr, int voffset)
+{
+    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voffset), "s"(rsrc)
+                 : "memory", "m0");
+}
+
 // ---------------------------------------------------------------- scoring (Eq. 4 / Eq. 5)
 
 // How one scoring pass is cut into workgroups.  A workgroup owns (kv head g, query block qb,
@@ -104,8 +115,8 @@ struct SelectLayout {
     size_t active;    // uint32 [ceil(L / kSelFine)]: fine chunks left after pruning
     size_t cells;     // float: the max-pooled cell arrays, one per max kernel (kSelMaxAvg)
     size_t picked;    // uint32 [ILRE_MAX_BUDGET] the allocated tokens in the order they were taken, then their count
-    size_t seed;      // kSelWindowMax: uint32 rank[kCandCap], int32 dom_left[kCandCap], int32 dom_right[kCandCap]
-    size_t cand;      // uint64 [n][kCandCap]; kSelWindowMax: [1 + n][kCandCap], list 0 the seeds, then a token list per kernel size
+    size_t seed;      // kSelWindowMax, by rank: uint32 token[kCandCap], uint32 distances to the outranking neighbours[kCandCap]
+    size_t cand;      // uint64 [n][kCandCap], one list per combination (kSelWindowMax: one, the seeds)
     size_t tie;       // uint64: per combination two ping-pong lists of boundary elements, each as long as its source
     size_t total;
 };

@@ -106,17 +106,6 @@ __device__ __forceinline__ void row_update(const f32x16 &acc, float c, float &m,
     for (int v = 0; v < 16; ++v) z[v & 3] += fast_exp2(fmaf(s[v], c, nm));
 }
 
-// Asynchronous 16-byte-per-lane copy from a buffer resource straight into LDS: lane l of the
-// wavefront lands at lds_addr + 16*l; bytes past the resource's num_records read as zero.  Tracked
-// by vmcnt.  Issued as inline assembly so that the compiler's conservative alias handling does not
-// put a full vmcnt wait in front of every later LDS read.
-typedef __attribute__((ext_vector_type(4))) int i32x4;
-__device__ __forceinline__ void lds_dma16(i32x4 rsrc, unsigned lds_addr, int voffset)
-{
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voffset), "s"(rsrc)
-                 : "memory", "m0");
-}
-
 __device__ __forceinline__ float quad_swap1(float x)  // lanes 0<->1, 2<->3 of every quad
 {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1, 0xF, 0xF, true));

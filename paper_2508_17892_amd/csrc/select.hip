@@ -25,10 +25,11 @@
 //                compacted) to what is needed -- in the window-max form only while it is longer than
 //                kSelSmall, extra candidates rank last and are harmless; in the printed form to
 //                exactly K_m elements -- and joins the candidates
-//   allocate_ranked   one workgroup walks the combinations in order over their rank-ordered token lists: a
-//                token already allocated (LDS hash set) is skipped, the first B_j others are taken
-//   emit_sorted  the allocated set in ascending order behind the sink part (each token counts the
-//                tokens below it)
+//   allocate_walk   one workgroup walks the combinations in order over their ranked cells: the allocated set is
+//                a bitmap in LDS, tokens that it holds are skipped, the first B_j others are taken; the ascending
+//                output is then read off the bitmap
+//   emit_sorted  contexts whose bitmap does not fit the LDS: the allocated set in ascending order (each token
+//                counts the tokens below it)
 //
 // The window-max form does not pool while it scans.  With B' = min(B, L), only the B' best raw scores by
 // (score descending, token ascending), the "seeds", can decide anything: the K_j-th largest pooled value
@@ -42,11 +43,10 @@
 //   seed_rank    per seed: its rank among the seeds (counting: a wavefront's lanes share out the staged keys
 //                and compare them with its four seeds) and the nearest seed that outranks it on either side
 //                (a scan of the raw scores around it, 16 lanes a seed: whatever outranks a seed is a seed)
-//   seed_lists   one workgroup per kernel size: seed u owns the tokens whose window holds u and no seed
-//                that outranks u, an interval [max(u-r, a+r+1), min(u+r, b-r-1)]; their pooled value is
-//                u's score.  Seeds in rank order, each interval ascending, is the kernel size's ranked
-//                token list; its first K_j tokens are written out
-//   allocate_ranked   the walk over those lists (shared with the printed form)
+//   allocate_walk   for kernel size j seed u owns the tokens whose window holds u and no seed that outranks u, an
+//                interval [max(u-r, a+r+1), min(u+r, b-r-1)]; their pooled value is u's score.  Seeds in rank
+//                order, each interval ascending, is the kernel size's ranked token list: the walk takes the
+//                intervals as they are, no list is written
 //
 // Long contexts in the window-max form (L >= 4M and >= 1024 tokens per budgeted token) start with a
 // pruning pre-pass: the maximum of every fine chunk (one streaming read of the scores), the 22-bit
@@ -61,16 +61,16 @@
 // the same key gives them once the element index is replaced by the token index.
 #include "ilre_internal.h"
 
+#include <type_traits>
+
 namespace ilre {
 namespace {
 
-constexpr int kThreads = 1024;                    // refine, seed_lists: one large workgroup
+constexpr int kThreads = 1024;                    // sel_init, refine: one large workgroup
 constexpr int kPoolThreads = 256;                 // pooling passes: four wavefronts, one fine chunk each
 constexpr int kPoolWaves = kPoolThreads / 64;
 constexpr int kPerThread = kSelFine / 64;         // 4 tokens per lane
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
-constexpr int kHashSlots = 16384;                 // >= 2 * ILRE_MAX_BUDGET
-constexpr int kKeysPerThread = kCandCap / kThreads;
 
 // Per-combination description, host -> sel_init (by value), which copies it into the control blocks.
 struct SelParams {
@@ -123,6 +123,16 @@ __device__ __forceinline__ uint32_t wave_scan_add(uint32_t x)  // inclusive pref
     x += (uint32_t)ILRE_DPP(0, x, 0x118, 0xF);  // row_shr:8
     x += (uint32_t)ILRE_DPP(0, x, 0x142, 0xA);  // row_bcast:15 into rows 1 and 3
     x += (uint32_t)ILRE_DPP(0, x, 0x143, 0xC);  // row_bcast:31 into rows 2 and 3
+    return x;
+}
+__device__ __forceinline__ uint32_t wave_scan_max(uint32_t x)  // inclusive running maximum over the 64 lanes
+{
+    x = max(x, (uint32_t)ILRE_DPP(0, x, 0x111, 0xF));
+    x = max(x, (uint32_t)ILRE_DPP(0, x, 0x112, 0xF));
+    x = max(x, (uint32_t)ILRE_DPP(0, x, 0x114, 0xF));
+    x = max(x, (uint32_t)ILRE_DPP(0, x, 0x118, 0xF));
+    x = max(x, (uint32_t)ILRE_DPP(0, x, 0x142, 0xA));
+    x = max(x, (uint32_t)ILRE_DPP(0, x, 0x143, 0xC));
     return x;
 }
 __device__ __forceinline__ uint32_t wave_total(uint32_t scanned)  // lane 63 of an inclusive scan, in every lane
@@ -821,37 +831,9 @@ __global__ __launch_bounds__(kThreads) void refine(SelCtrl *ctrl, uint64_t *cand
             __syncthreads();
         }
     }
-    // The allocation walk wants tokens: element e stands for tokens e*m .. e*m+m-1, in that order.  The
-    // token list (uint32, total * m <= kCandCap entries) takes over the storage of the key list.
-    uint32_t *tokens = (uint32_t *)cand_j;
-    const uint32_t m = ctrl[j].cell;
-    for (uint32_t r = threadIdx.x; r < total * m; r += kThreads) {
-        const uint32_t el = r / m;
-        tokens[r] = key_token(srt[el]) * m + (r - el * m);
-    }
-}
-
-__device__ __forceinline__ uint32_t hash_slot(uint32_t token) { return (token * 0x9E3779B1u) >> 18; }
-
-// The allocated set I of Algorithm 1 as an open-addressing hash set of token indices in LDS.
-__device__ __forceinline__ bool is_allocated(const uint32_t *table, uint32_t token)
-{
-    uint32_t s = hash_slot(token);
-    while (true) {
-        const uint32_t t = table[s];
-        if (t == kEmpty) return false;
-        if (t == token) return true;
-        s = (s + 1) & (kHashSlots - 1);
-    }
-}
-__device__ __forceinline__ void mark_allocated(uint32_t *table, uint32_t token)
-{
-    uint32_t s = hash_slot(token);
-    while (true) {
-        const uint32_t old = atomicCAS(&table[s], kEmpty, token);
-        if (old == kEmpty || old == token) break;
-        s = (s + 1) & (kHashSlots - 1);
-    }
+    // The allocation walk wants the elements in rank order; the list (uint32) takes over the storage of the keys.
+    uint32_t *ranked = (uint32_t *)cand_j;
+    for (uint32_t r = threadIdx.x; r < total; r += kThreads) ranked[r] = key_token(srt[r]);
 }
 
 // Last step of the allocation: the sink indices, then the nsel allocated tokens in ascending order, then -1
@@ -901,169 +883,453 @@ __global__ __launch_bounds__(kEmitThreads) void emit_sorted(const uint32_t *pick
     }
 }
 
+// The allocated set I of Algorithm 1 as a bitmap over the body's tokens, 32 tokens a word.  Up to kBitmapTokens
+// tokens the whole bitmap lies in LDS (128 KiB at 1M tokens); beyond that LDS holds an open-addressing table of
+// the words that have a bit set: at most ILRE_MAX_BUDGET of them, half of its slots.
+constexpr int kBitmapChunk = 256;                      // words a wavefront turns into output at a time
+constexpr int kBitmapChunks = 136;                     // 136 KiB of the compute unit's 160
+constexpr int kBitmapTokens = kBitmapChunks * kBitmapChunk * 32;
+constexpr int kWordSlots = 16384;
+static_assert(kWordSlots >= 2 * ILRE_MAX_BUDGET, "the word table stays half empty");
+
+template <bool HASHED>
+struct TokenSet {
+    uint32_t *key, *mask;  // HASHED: word index and bits per slot; otherwise mask[word]
+    static __device__ __forceinline__ uint32_t slot_of(uint32_t word) { return (word * 0x9E3779B1u) >> 18; }
+    __device__ __forceinline__ uint32_t get(uint32_t word) const
+    {
+        if (!HASHED) return mask[word];
+        uint32_t s = slot_of(word);
+        while (true) {
+            const uint32_t k = key[s];
+            if (k == word) return mask[s];
+            if (k == kEmpty) return 0u;
+            s = (s + 1) & (kWordSlots - 1);
+        }
+    }
+    __device__ __forceinline__ void set(uint32_t word, uint32_t bits) const
+    {
+        if (!HASHED) {
+            atomicOr(&mask[word], bits);
+            return;
+        }
+        uint32_t s = slot_of(word);
+        while (true) {
+            const uint32_t old = atomicCAS(&key[s], kEmpty, word);
+            if (old == kEmpty || old == word) break;
+            s = (s + 1) & (kWordSlots - 1);
+        }
+        atomicOr(&mask[s], bits);
+    }
+};
+
+// bits of word w that lie in the token interval [first, last]
+__device__ __forceinline__ uint32_t interval_bits(uint32_t w, uint32_t first, uint32_t last)
+{
+    uint32_t m = 0xFFFFFFFFu;
+    if (w == first >> 5) m &= 0xFFFFFFFFu << (first & 31);
+    if (w == last >> 5) m &= 0xFFFFFFFFu >> (31 - (last & 31));
+    return m;
+}
+
 // LDS writes of this wavefront done, then the workgroup barrier; global loads in flight stay in flight.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// Algorithm 1's walk, printed form.  refine left combination j's candidate tokens in rank order (a
-// uint32 list in the storage of cand[j]).  Wavefront w owns the ranks [w*64*per,
-// (w+1)*64*per), lane l the ranks w*64*per + 64*i + l.  Each wavefront counts its free tokens with
-// ballots, one exchange through LDS gives every wavefront the number of free tokens ranked ahead of
-// it, and the first B_j free tokens are taken.  The next combination's tokens are fetched meanwhile.
-constexpr int kRankThreads = 1024;
-constexpr int kRankWaves = kRankThreads / 64;
-constexpr int kRankG = 5;                                                           // tokens of a lane are handled in groups
-constexpr int kRankGroups = (kCandCap / kRankThreads + kRankG - 1) / kRankG;
-constexpr int kRankPer = kRankGroups * kRankG;                                      // tokens per lane at most
-static_assert(kRankPer <= 64, "free tokens of a lane are kept in a 64-bit mask");
+// Algorithm 1's walk.  Combination j offers its tokens as ranked intervals that do not overlap -- in the window-max
+// form the tokens each seed owns, seeds in rank order; in the printed form the tokens of each cell, cells in rank
+// order -- and takes the first B_j of them, in that order and ascending inside an interval, that the set does not
+// hold yet.  A thread looks at kWalkPer neighbouring intervals: the free tokens in one are a population count of one
+// or two words of the set, a scan over the workgroup gives every interval the number of free tokens ranked ahead of
+// it, and those up to the share's end are marked, a word at a time.
+//
+// Bound: the chain of dependent LDS round trips and instructions per combination (gather, scan, exchange, marks) on
+// one compute unit, about 1300 cycles.  Hence the gathers of a thread's intervals are in flight together, no atomic
+// returns a value, a combination's numbers come from a register lane, its list is in LDS before it is needed, and
+// there is one scan and two barriers per 1024 intervals.  Two wavefronts a SIMD: with one (four intervals a thread)
+// nothing hides the LDS latency, with four (one interval a thread) the scan is repeated by as many.
+// Measured (kernel trace): 48 printed combinations at budget 4096 on 128K tokens 135.9 -> 36.8 us, on 1M 124 -> 40.6 us,
+// four kernel sizes at budget 4096 on 32K tokens 11.4 us and five on 1M 20.2 us, where the predecessor took 15.0 and
+// 19.5 us and two more kernels of 5.7 - 9.5 us each (one to write every kernel size's ranked tokens out, one to put the
+// result in order); it walked single tokens through a hash set, a wavefront's round trip per token and probe.
+constexpr int kWalkThreads = 512;
+constexpr int kWalkWaves = kWalkThreads / 64;
+constexpr int kWalkPer = 2;                                                   // intervals a thread looks at in one pass
+constexpr int kWalkSpan = kWalkThreads * kWalkPer;                            // intervals per pass
+constexpr int kWalkPasses = kCandCap / kWalkSpan;                             // passes a list may need
+constexpr int kWalkAhead = 4;                                                 // cells: passes fetched ahead
+static_assert(kCandCap % kWalkSpan == 0, "whole passes");
+static_assert(ILRE_MAX_POOL_KERNELS <= 64, "a lane holds a combination's numbers");
+constexpr int kRingBytes = kWalkAhead * kWalkSpan * (int)sizeof(uint32_t);    // also holds a 16-bit word number per place in the output
+static_assert(kRingBytes >= ILRE_MAX_BUDGET * (int)sizeof(uint16_t) && (kWalkAhead & (kWalkAhead - 1)) == 0, "the ring's memory is used again");
+static_assert(kBitmapTokens / 32 < 65536 && ILRE_MAX_BUDGET < 65536, "16-bit word numbers and places");
 
-__global__ __launch_bounds__(kRankThreads) void allocate_ranked(const SelCtrl *ctrl, const uint64_t *cand, int n, int n_out,
-                                                                uint32_t *picked, uint32_t *picked_n)
+// What the intervals of a list are.
+enum WalkItems {
+    kWalkSeeds,      // tokens owned by a seed: found from its position, its outranking neighbours and the window radius
+    kWalkWordCells,  // cells of 1, 2, 4 .. 32 tokens: inside one word of the set
+    kWalkCells       // cells of any size
+};
+
+struct WalkArgs {
+    int n, n_out, sink;
+    uint32_t len;                             // tokens of the body
+    uint32_t share[ILRE_MAX_POOL_KERNELS];    // B_j
+    uint32_t reach[ILRE_MAX_POOL_KERNELS];    // window radius, or tokens per cell
+    uint32_t cells[ILRE_MAX_POOL_KERNELS];    // cells: length of the list (>= 1)
+    const SelCtrl *ctrl;                      // seeds: their number
+    const uint32_t *pos, *dom;                // seeds, by rank: token, and the distances to its outranking neighbours
+    const uint64_t *cand;                     // cells: per combination the ranked cells, uint32
+    uint32_t *picked, *picked_n;              // HASHED: the allocated tokens in the order they are taken
+    int32_t *out_idx, *out_count;
+};
+
+// the lowest `n` set bits of x
+__device__ __forceinline__ uint32_t lowest_bits(uint32_t x, uint32_t n)
+{
+    uint32_t keep = 0;
+    for (; n; --n) {
+        keep |= x & (0u - x);
+        x &= x - 1;
+    }
+    return keep;
+}
+
+// position of set bit number k (counted from 0) of x
+__device__ __forceinline__ uint32_t nth_set_bit(uint32_t x, uint32_t k)
+{
+    uint32_t at = 0;
+#pragma unroll
+    for (int half = 16; half > 0; half >>= 1) {
+        const uint32_t c = __popc(x & ((1u << half) - 1u));
+        const bool up = k >= c;
+        k -= up ? c : 0u;
+        x >>= up ? half : 0;
+        at += up ? half : 0;
+    }
+    return at;
+}
+
+template <int ITEMS, bool HASHED>
+__global__ __launch_bounds__(kWalkThreads) void allocate_walk(const WalkArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    uint32_t *table = (uint32_t *)smem;  // kHashSlots
-    uint32_t *sel = table + kHashSlots;  // ILRE_MAX_BUDGET tokens
-    __shared__ uint32_t wfree[2][kRankWaves];  // free tokens per wavefront, two generations
-    __shared__ uint32_t c_share[ILRE_MAX_POOL_KERNELS], c_tokens[ILRE_MAX_POOL_KERNELS];
+    __shared__ uint32_t wsum[2][kWalkWaves];
+    __shared__ uint32_t chunk_n[kBitmapChunks];
+    constexpr bool SEEDS = ITEMS == kWalkSeeds;
+    const TokenSet<HASHED> set{(uint32_t *)smem, (uint32_t *)smem + (HASHED ? kWordSlots : 0)};
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t chunks = (a.len + 32 * kBitmapChunk - 1) / (32 * kBitmapChunk);
 
-    for (int i = threadIdx.x; i < kHashSlots; i += kRankThreads) table[i] = kEmpty;
-    if ((int)threadIdx.x < n) {
-        c_share[threadIdx.x] = ctrl[threadIdx.x].share;
-        c_tokens[threadIdx.x] = ctrl[threadIdx.x].total_n * ctrl[threadIdx.x].cell;  // <= kCandCap by the host's limits
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint64_t lanes_below = (1ull << lane) - 1ull;
-    __syncthreads();
-    // At most (shares before j) tokens are allocated when combination j runs, so its B_j free tokens
-    // are among its first (shares up to and including j) ranked ones: the rest is never looked at.
-    if (threadIdx.x == 0) {
-        uint32_t upto = 0;
-        for (int j = 0; j < n; ++j) {
-            upto += c_share[j];
-            if (upto < c_tokens[j]) c_tokens[j] = upto;
+    // combination j's numbers are lane j's: a readlane away, where memory would be a round trip per combination
+    uint32_t l_share = a.share[lane], l_reach = a.reach[lane], l_cells = SEEDS ? 0u : a.cells[lane];
+    asm volatile("" : "+v"(l_share), "+v"(l_reach), "+v"(l_cells));  // wait for them here, not behind every fetch of the loop
+    auto of = [](uint32_t x, int j) { return (uint32_t)__builtin_amdgcn_readlane((int)x, j); };
+
+    // The seeds serve every kernel size: a thread keeps the ones it looks at in registers.
+    uint32_t seed[SEEDS ? kWalkPasses : 1][kWalkPer], dom[SEEDS ? kWalkPasses : 1][kWalkPer];
+    uint32_t nseeds = 0;
+    if (SEEDS) {
+        nseeds = a.ctrl[0].total_n;
+#pragma unroll
+        for (int p = 0; p < kWalkPasses; ++p) {
+            const int r2 = p * kWalkThreads + tid;
+            const uint2 x = ((const uint2 *)a.pos)[r2], d = ((const uint2 *)a.dom)[r2];
+            seed[p][0] = x.x, seed[p][1] = x.y;
+            dom[p][0] = d.x, dom[p][1] = d.y;
         }
+#pragma unroll
+        for (int p = 0; p < kWalkPasses; ++p)
+#pragma unroll
+            for (int i = 0; i < kWalkPer; ++i)
+                if ((uint32_t)((p * kWalkThreads + tid) * kWalkPer + i) >= nseeds) seed[p][i] = dom[p][i] = 0;  // owns nothing at any radius
     }
-    __syncthreads();
-
-    // Loads are unconditional from a clamped slot of the list's storage, so that all are in flight
-    // together; a whole group of kRankG tokens a lane is fetched when any of it is needed.
-    auto fetch = [&](int j, uint32_t(&raw)[kRankPer]) {
-        const uint32_t *list = (const uint32_t *)(cand + (size_t)j * kCandCap);
-        const uint32_t per = (c_tokens[j] + kRankThreads - 1) / kRankThreads;
-        const uint32_t base = (uint32_t)wave * per * 64u + (uint32_t)lane;
-#pragma unroll
-        for (int g = 0; g < kRankGroups; ++g) {
-            if ((uint32_t)(g * kRankG) < per) {  // uniform
-#pragma unroll
-                for (int u = 0; u < kRankG; ++u) {
-                    const uint32_t r = base + 64u * (g * kRankG + u);
-                    raw[g * kRankG + u] = list[r < (uint32_t)kCandCap ? r : (uint32_t)kCandCap - 1u];
-                }
-            }
+    const uint32_t clear = HASHED ? kWordSlots : chunks * kBitmapChunk;
+    uint32_t *ring = set.mask + clear;  // cells: kWalkAhead passes of kWalkSpan cells
+    // Cells come in a list per combination, written by other compute units a kernel ago: fetching one takes longer than
+    // walking one, so kWalkAhead passes are under way, copied straight into LDS.  A wavefront fetches what its own
+    // lanes look at, so its own wait is all the synchronisation there is.  (fj, fbase) is the next pass to fetch; past
+    // the last one the last list is fetched again.
+    const unsigned ring_lds = (unsigned)(size_t)(__attribute__((address_space(3))) uint32_t *)ring;
+    int fj = 0;
+    uint32_t fbase = 0;
+    auto fetch = [&](int slot) {
+        const unsigned long long list = (unsigned long long)((const uint32_t *)(a.cand + (size_t)fj * kCandCap) + fbase + wave * 64 * kWalkPer);
+        i32x4 rsrc;
+        rsrc[0] = __builtin_amdgcn_readfirstlane((int)(unsigned)list);
+        rsrc[1] = __builtin_amdgcn_readfirstlane((int)((unsigned)(list >> 32) & 0xFFFFu));
+        rsrc[2] = 64 * kWalkPer * (int)sizeof(uint32_t);
+        rsrc[3] = 0x00020000;
+        if (lane < 64 * kWalkPer / 4)
+            lds_dma16(rsrc, __builtin_amdgcn_readfirstlane(ring_lds + (unsigned)((slot * kWalkSpan + wave * 64 * kWalkPer) * sizeof(uint32_t))), lane * 16);
+        fbase += kWalkSpan;
+        if (fbase >= of(l_cells, fj)) {
+            fbase = 0;
+            if (fj + 1 < a.n) ++fj;
         }
     };
+    // the oldest pass under way has arrived (HASHED: so have the notes, which are stores of the same counter)
+    auto arrived = [&](int slot, uint32_t(&x)[kWalkPer]) {
+        if (HASHED)
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        else
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kWalkAhead - 1) : "memory");
+        const uint2 v = *(const uint2 *)&ring[slot * kWalkSpan + tid * kWalkPer];
+        x[0] = v.x;
+        x[1] = v.y;
+    };
+    if (!SEEDS && a.n > 0) {
+#pragma unroll
+        for (int d = 0; d < kWalkAhead; ++d) fetch(d);
+    }
 
-    uint32_t tok[kRankPer], nxt[kRankPer];
-    if (n > 0) fetch(0, nxt);
-    uint32_t nsel = 0;
+    for (uint32_t i = tid * 4; i < clear; i += kWalkThreads * 4) {
+        if (HASHED) *(uint4 *)&set.key[i] = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
+        *(uint4 *)&set.mask[i] = make_uint4(0, 0, 0, 0);
+    }
+    lds_barrier();
+
+    uint32_t nsel = 0, taken = 0, share = 0, reach = 0;
+    bool wide = false;  // an interval may touch more than two words
     int gen = 0;
-    for (int j = 0; j < n; ++j) {
+    auto start = [&](int j) {
+        share = min(of(l_share, j), (uint32_t)a.n_out - nsel);
+        reach = of(l_reach, j);
+        wide = ITEMS != kWalkWordCells && (SEEDS ? 2 * reach + 1 : reach) > 33;
+        taken = 0;
+    };
+    // one pass: this thread's two neighbouring intervals, of which the ones from `cn` on (cells) do not exist
+    auto pass = [&](uint32_t base, uint32_t cn, const uint32_t(&it)[kWalkPer], const uint32_t(&dm)[kWalkPer]) __attribute__((always_inline)) {
+        uint32_t first[kWalkPer], last[kWalkPer], mask0[kWalkPer], mask1[kWalkPer], free0[kWalkPer], free1[kWalkPer], nfree[kWalkPer];
 #pragma unroll
-        for (int i = 0; i < kRankPer; ++i) tok[i] = nxt[i];
-        if (j + 1 < n) fetch(j + 1, nxt);
-        uint32_t share = c_share[j];
-        if ((uint32_t)n_out - nsel < share) share = (uint32_t)n_out - nsel;
-        if (share == 0) continue;  // uniform
-        const uint32_t cn = c_tokens[j];
-        const uint32_t per = (cn + kRankThreads - 1) / kRankThreads;
-        const uint32_t base = (uint32_t)wave * per * 64u + (uint32_t)lane;
-
-        // Per group: the hash-set probes of all its tokens advance together, one round of LDS reads
-        // per step of the longest probe chain, then the wavefront's count by ballots.
-        uint64_t free_bits = 0;
-        uint32_t run = 0;
+        for (int i = 0; i < kWalkPer; ++i) {
+            bool some;
+            if (SEEDS) {
+                // the tokens whose window holds the seed and nothing that outranks it
+                const int32_t r = (int32_t)reach, at = (int32_t)it[i];
+                const int32_t l = min(min(r, (int32_t)(dm[i] & 0xFFFFu) - r - 1), at);
+                const int32_t e = min(min(r, (int32_t)(dm[i] >> 16) - r - 1), (int32_t)a.len - 1 - at);
+                some = l + e >= 0;
+                first[i] = some ? (uint32_t)(at - l) : 0u;
+                last[i] = some ? (uint32_t)(at + e) : 0u;
+            } else {
+                some = base + tid * kWalkPer + i < cn;
+                first[i] = some ? it[i] * reach : 0u;
+                last[i] = first[i] + reach - 1;
+            }
+            if (ITEMS == kWalkWordCells) {
+                mask0[i] = (0xFFFFFFFFu >> (32 - reach)) << (first[i] & 31);
+            } else {
+                mask0[i] = interval_bits(first[i] >> 5, first[i], last[i]);
+                mask1[i] = some && last[i] >> 5 > first[i] >> 5 ? interval_bits((first[i] >> 5) + 1, first[i], last[i]) : 0u;
+            }
+            mask0[i] = some ? mask0[i] : 0u;
+        }
 #pragma unroll
-        for (int g = 0; g < kRankGroups; ++g) {
-            if ((uint32_t)(g * kRankG) < per) {  // uniform
-                uint32_t slot[kRankG];
-                uint32_t pend = 0;
+        for (int i = 0; i < kWalkPer; ++i) {
+            free0[i] = set.get(first[i] >> 5);
+            if (ITEMS != kWalkWordCells) free1[i] = set.get(min((first[i] >> 5) + 1, last[i] >> 5));
+        }
 #pragma unroll
-                for (int u = 0; u < kRankG; ++u) {
-                    const int i = g * kRankG + u;
-                    slot[u] = hash_slot(tok[i]);
-                    if ((uint32_t)i < per && base + 64u * i < cn) pend |= 1u << u;
-                }
-                while (__any(pend != 0)) {
-                    uint32_t seen_tok[kRankG];
-#pragma unroll
-                    for (int u = 0; u < kRankG; ++u) seen_tok[u] = table[slot[u]];
-#pragma unroll
-                    for (int u = 0; u < kRankG; ++u) {
-                        if ((pend >> u) & 1u) {
-                            if (seen_tok[u] == kEmpty) {
-                                free_bits |= 1ull << (g * kRankG + u);
-                                pend &= ~(1u << u);
-                            } else if (seen_tok[u] == tok[g * kRankG + u]) {
-                                pend &= ~(1u << u);
-                            } else {
-                                slot[u] = (slot[u] + 1) & (kHashSlots - 1);
-                            }
-                        }
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < kRankG; ++u) run += (uint32_t)__popcll(__ballot((free_bits >> (g * kRankG + u)) & 1ull));
+        for (int i = 0; i < kWalkPer; ++i) {
+            free0[i] = ~free0[i] & mask0[i];
+            nfree[i] = __popc(free0[i]);
+            if (ITEMS != kWalkWordCells) {
+                free1[i] = ~free1[i] & mask1[i];
+                nfree[i] += __popc(free1[i]);
             }
         }
-        if (lane == 0) wfree[gen][wave] = run;
+        if (wide) {  // uniform
+#pragma unroll
+            for (int i = 0; i < kWalkPer; ++i)
+                if (mask0[i])
+                    for (uint32_t w = (first[i] >> 5) + 2; w <= last[i] >> 5; ++w) nfree[i] += __popc(~set.get(w) & interval_bits(w, first[i], last[i]));
+        }
+        const uint32_t mine = nfree[0] + nfree[1];
+        static_assert(kWalkPer == 2, "two intervals a thread");
+        const uint32_t upto = wave_scan_add(mine);
+        if (lane == 63) wsum[gen][wave] = upto;
         lds_barrier();
-        uint32_t before = 0, total_free = 0;
-#pragma unroll
-        for (int w = 0; w < kRankWaves; ++w) {
-            const uint32_t c = wfree[gen][w];
-            if (w < wave) before += c;
-            total_free += c;
-        }
+        // the wavefronts' totals, one a lane, summed along the row of eight
+        static_assert(kWalkWaves == 8, "three steps sum eight wavefronts' totals");
+        uint32_t ws = wsum[gen][lane & (kWalkWaves - 1)];
+        ws += (uint32_t)ILRE_DPP(0, ws, 0x111, 0xF);
+        ws += (uint32_t)ILRE_DPP(0, ws, 0x112, 0xF);
+        ws += (uint32_t)ILRE_DPP(0, ws, 0x114, 0xF);
+        const uint32_t total = of(ws, kWalkWaves - 1);
+        uint32_t before = upto - mine + (wave ? of(ws, wave - 1) : 0u);
         gen ^= 1;
-        const uint32_t take = share < total_free ? share : total_free;
-        const uint32_t quota = take > before ? take - before : 0u;  // of this wavefront's free tokens, in rank order
-        uint32_t seen = 0;
+        const uint32_t room = share - taken;
+        auto note = [&](uint32_t w, uint32_t bits, uint32_t &at) {  // only where the output cannot be read off the set
+            for (; bits; bits &= bits - 1) a.picked[at++] = w * 32 + (uint32_t)__ffs((int)bits) - 1;
+        };
 #pragma unroll
-        for (int g = 0; g < kRankGroups; ++g) {
-            if ((uint32_t)(g * kRankG) < per && seen < quota) {  // uniform
-#pragma unroll
-                for (int u = 0; u < kRankG; ++u) {
-                    const int i = g * kRankG + u;
-                    const bool fr = (free_bits >> i) & 1ull;
-                    const uint64_t mask = __ballot(fr);
-                    const uint32_t pos = seen + (uint32_t)__popcll(mask & lanes_below);
-                    if (fr && pos < quota) {
-                        sel[nsel + before + pos] = tok[i];
-                        mark_allocated(table, tok[i]);
+        for (int i = 0; i < kWalkPer; ++i) {
+            const uint32_t w0 = first[i] >> 5;
+            uint32_t quota = room > before ? room - before : 0u, at = nsel + taken + before;
+            if (quota < nfree[i]) {  // the share ends in (or before) this interval: the lowest tokens of it are taken
+                const uint32_t c0 = __popc(free0[i]);
+                if (quota < c0) free0[i] = lowest_bits(free0[i], quota);
+                if (ITEMS != kWalkWordCells) free1[i] = quota > c0 ? lowest_bits(free1[i], min(quota - c0, (uint32_t)__popc(free1[i]))) : 0u;
+            }
+            if (free0[i]) set.set(w0, free0[i]);
+            if (HASHED) note(w0, free0[i], at);
+            if (ITEMS != kWalkWordCells) {
+                if (free1[i]) set.set(w0 + 1, free1[i]);
+                if (HASHED) note(w0 + 1, free1[i], at);
+                if (wide && mask0[i]) {
+                    uint32_t more = min(quota, nfree[i]) - __popc(free0[i]) - __popc(free1[i]);
+                    for (uint32_t w = w0 + 2; more; ++w) {
+                        uint32_t bits = ~set.get(w) & interval_bits(w, first[i], last[i]);
+                        if ((uint32_t)__popc(bits) > more) bits = lowest_bits(bits, more);
+                        more -= __popc(bits);
+                        if (bits) set.set(w, bits);
+                        if (HASHED) note(w, bits, at);
                     }
-                    seen += (uint32_t)__popcll(mask);
                 }
             }
+            before += nfree[i];
         }
-        nsel += take;
-        lds_barrier();  // the set is complete before the next combination probes it
+        taken += min(total, room);
+    };
+    if (SEEDS) {
+        for (int j = 0; j < a.n; ++j) {
+            start(j);
+#pragma unroll
+            for (int p = 0; p < kWalkPasses; ++p)
+                if (taken < share && (uint32_t)(p * kWalkSpan) < nseeds) pass(0, 0, seed[p], dom[p]);
+            nsel += taken;
+            lds_barrier();  // the set is complete before the next kernel size counts in it
+        }
+    } else {
+        uint32_t base = 0, it[kWalkPer];
+        int j = 0, slot = 0;
+        if (a.n > 0) {
+            start(0);
+            arrived(0, it);
+        }
+        while (j < a.n) {
+            const uint32_t cn = of(l_cells, j);
+            if (taken < share) pass(base, cn, it, dom[0]);
+            fetch(slot);
+            slot = (slot + 1) & (kWalkAhead - 1);
+            arrived(slot, it);
+            base += kWalkSpan;
+            if (base >= cn) {  // the list is done
+                nsel += taken;
+                lds_barrier();
+                base = 0;
+                if (++j < a.n) start(j);
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing writes into the ring any more
+    }
+    if (HASHED) {
+        if (tid == 0) *a.picked_n = nsel;
+        return;
+    }
+
+    // Ascending output straight from the bitmap.  The tokens per chunk (a lane counts four neighbouring words) and
+    // their running sum place every word's first token; the place notes the word.  Then one lane a place: the nearest
+    // noted place at or before its own is at most 31 back and names the word, the distance the bit in it.
+    // All of it is latency: kEmitBatch chunks (groups of 64 places) of a wavefront advance together.
+    constexpr int kEmitBatch = 4;
+    // per place in the output: the word (number + 1) whose first token goes there, or 0
+    uint16_t *slot_word = (uint16_t *)ring;
+    __syncthreads();  // every wavefront is done with the ring
+    for (uint32_t i = tid * 8; i < (uint32_t)a.n_out; i += kWalkThreads * 8) *(uint4 *)&slot_word[i] = make_uint4(0, 0, 0, 0);
+    auto words4 = [&](uint32_t c) {  // the lane's four words of a chunk, none past the last chunk
+        return c < chunks ? *(const uint4 *)&set.mask[c * kBitmapChunk + 4 * lane] : make_uint4(0, 0, 0, 0);
+    };
+    for (uint32_t c0 = wave; c0 < chunks; c0 += kWalkWaves * kEmitBatch) {
+        uint32_t sum[kEmitBatch];
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) {
+            const uint4 x = words4(c0 + b * kWalkWaves);
+            sum[b] = __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w);
+        }
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) sum[b] = wave_scan_add(sum[b]);
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b)
+            if (lane == 63 && c0 + b * kWalkWaves < chunks) chunk_n[c0 + b * kWalkWaves] = sum[b];
     }
     __syncthreads();
-    // the allocated tokens, in the order they were taken, for emit_sorted
-    for (uint32_t i = threadIdx.x; i < nsel; i += kRankThreads) picked[i] = sel[i];
-    if (threadIdx.x == 0) *picked_n = nsel;
+    // every wavefront sums the chunks before each of its own by itself (lane l holds chunks l, l + 64, l + 128)
+    uint32_t cn[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) cn[i] = (uint32_t)(lane + 64 * i) < chunks ? chunk_n[lane + 64 * i] : 0u;
+    static_assert(kBitmapChunks <= 3 * 64, "three chunks a lane");
+    for (uint32_t c0 = wave; c0 < chunks; c0 += kWalkWaves * kEmitBatch) {
+        uint4 x[kEmitBatch];
+        uint32_t n3[kEmitBatch], at[kEmitBatch];
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) {
+            const uint32_t c = c0 + b * kWalkWaves;
+            x[b] = words4(c);
+            n3[b] = __popc(x[b].x) + __popc(x[b].y) + __popc(x[b].z) + __popc(x[b].w);
+            at[b] = ((uint32_t)lane < c ? cn[0] : 0u) + ((uint32_t)lane + 64 < c ? cn[1] : 0u) + ((uint32_t)lane + 128 < c ? cn[2] : 0u);
+        }
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) at[b] = wave_total(wave_scan_add(at[b])) + wave_scan_add(n3[b]) - n3[b];
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) {
+            const uint32_t w = (c0 + b * kWalkWaves) * kBitmapChunk + 4 * lane;
+            if (x[b].x) slot_word[at[b]] = (uint16_t)(w + 1);
+            at[b] += __popc(x[b].x);
+            if (x[b].y) slot_word[at[b]] = (uint16_t)(w + 2);
+            at[b] += __popc(x[b].y);
+            if (x[b].z) slot_word[at[b]] = (uint16_t)(w + 3);
+            at[b] += __popc(x[b].z);
+            if (x[b].w) slot_word[at[b]] = (uint16_t)(w + 4);
+        }
+    }
+    __syncthreads();
+    int32_t *out = a.out_idx + a.sink;
+    // a wavefront's places lie side by side: the last note of one group of 64 serves the next
+    const uint32_t span = (nsel + kWalkThreads - 1) / kWalkThreads * 64, s_begin = wave * span, s_end = min(s_begin + span, nsel);
+    auto note_of = [&](uint32_t s) {  // place and word in one number, larger for a later place
+        const uint32_t x = s < nsel ? slot_word[s] : 0u;
+        return x ? (s & 0xFFFFu) << 16 | x : 0u;
+    };
+    uint32_t carry = 0;
+    if (s_begin >= 64 && s_begin < nsel) carry = wave_total(wave_scan_max(note_of(s_begin - 64 + lane)));
+    for (uint32_t s0 = s_begin; s0 < s_end; s0 += 64 * kEmitBatch) {
+        uint32_t note[kEmitBatch], bits[kEmitBatch];
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) note[b] = note_of(s0 + 64 * b + lane);
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) note[b] = wave_scan_max(note[b]);
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) {
+            note[b] = max(note[b], carry);
+            carry = wave_total(note[b]);
+            bits[b] = set.mask[(note[b] & 0xFFFFu) - 1u];  // (place 0 is noted: there is always one)
+        }
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) {
+            const uint32_t s = s0 + 64 * b + lane;
+            if (s < s_end) out[s] = (int32_t)(((note[b] & 0xFFFFu) - 1u) * 32 + nth_set_bit(bits[b], s - (note[b] >> 16)) + (uint32_t)a.sink);
+        }
+    }
+    for (uint32_t i = tid; i < (uint32_t)a.sink; i += kWalkThreads) a.out_idx[i] = (int32_t)i;
+    for (uint32_t i = nsel + tid; i < (uint32_t)a.n_out; i += kWalkThreads) out[i] = -1;
+    if (tid == 0 && a.out_count) *a.out_count = a.sink + (int32_t)nsel;
 }
 
 
 // ---------------------------------------------------------------- window-max form: seeds
 
-// Per seed u (one of the ns best raw scores, keys distinct): rank[u] = number of seeds with a larger key,
-// and the nearest token on either side, within `reach` tokens, whose key is larger (-1 / -1 if none; such a
-// token is itself a seed, the seeds being the best keys).  A wavefront owns four seeds.  For the count its
+// Per seed (one of the ns best raw scores, keys distinct): its rank = the number of seeds with a larger key, and
+// the distances to the nearest token on either side, within `reach` tokens, whose key is larger (such a token is
+// itself a seed, the seeds being the best keys; kNoDom if there is none).  Written in rank order, the two distances
+// as the halves of a word.  A wavefront owns four seeds.  For the count its
 // lanes read disjoint parts of the staged key list (every LDS word is fetched once per wavefront) and
 // compare them with all four keys; for the scan 16 lanes share a seed and split its neighbourhood.
 constexpr int kSeedRankThreads = 512;  // 32 seeds a workgroup
+constexpr uint32_t kNoDom = 0x7FFF;    // farther than two radii: binds no kernel size
+static_assert(kNoDom > ILRE_MAX_POOL_KERNEL, "reach is twice the largest radius");
 __global__ __launch_bounds__(kSeedRankThreads) void seed_rank(const float *scores, int64_t L, const SelCtrl *sc, const uint64_t *seeds,
-                                                              int reach, uint32_t *rank, int32_t *dom_left, int32_t *dom_right)
+                                                              int reach, uint32_t *by_rank, uint32_t *dom)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     uint64_t *all = (uint64_t *)smem;  // every seed's key, staged once per workgroup (kCandCap at most)
@@ -1104,93 +1370,23 @@ __global__ __launch_bounds__(kSeedRankThreads) void seed_rank(const float *score
     const uint32_t cnt = grp == 0 ? wtot[0] : (grp == 1 ? wtot[1] : (grp == 2 ? wtot[2] : wtot[3]));
     const int64_t pos = (int64_t)key_token(key);
     // nearest outranking token: distance d = 1 .. reach, 16 distances a round, both sides at once
-    int32_t left = -1, right = -1;
+    uint32_t left = kNoDom, right = kNoDom;
     for (int d0 = 1; d0 <= reach; d0 += 16) {
         const int d = d0 + sub;
         const int64_t pl = pos - d, pr = pos + d;
         const bool hit_l = d <= reach && pl >= 0 && make_key(scores[pl < 0 ? 0 : pl], (uint32_t)(pl < 0 ? 0 : pl)) > key;
         const bool hit_r = d <= reach && pr < L && make_key(scores[pr < L ? pr : L - 1], (uint32_t)(pr < L ? pr : L - 1)) > key;
         // lowest lane of this 16-lane group with a hit = smallest distance
-        const uint64_t bl = __ballot(left < 0 && hit_l), br = __ballot(right < 0 && hit_r);
+        const uint64_t bl = __ballot(left == kNoDom && hit_l), br = __ballot(right == kNoDom && hit_r);
         const int shift = (threadIdx.x & 63) & ~15;
         const uint32_t ml = (uint32_t)(bl >> shift) & 0xFFFFu, mr = (uint32_t)(br >> shift) & 0xFFFFu;
-        if (left < 0 && ml) left = (int32_t)(pos - (d0 + __ffs((int)ml) - 1));
-        if (right < 0 && mr) right = (int32_t)(pos + (d0 + __ffs((int)mr) - 1));
-        if (left >= 0 && right >= 0) break;  // uniform within the group; ballots are wave-wide but only read per group
+        if (left == kNoDom && ml) left = (uint32_t)(d0 + __ffs((int)ml) - 1);
+        if (right == kNoDom && mr) right = (uint32_t)(d0 + __ffs((int)mr) - 1);
+        if (left != kNoDom && right != kNoDom) break;  // uniform within the group; ballots are wave-wide but only read per group
     }
     if (sub == 15) {
-        rank[u] = cnt;
-        dom_left[u] = left;
-        dom_right[u] = right;
-    }
-}
-
-// One workgroup per kernel size j: the first K_j tokens of its ranked token list (uint32, in the storage of
-// cand list 1 + j) and its control block for the walk.  LDS: lo[kCandCap] and the running token counts
-// pre[kCandCap], both indexed by seed rank.
-struct SeedParams {
-    int n;
-    uint32_t radius[ILRE_MAX_POOL_KERNELS], share[ILRE_MAX_POOL_KERNELS], want[ILRE_MAX_POOL_KERNELS];
-};
-__global__ __launch_bounds__(kThreads) void seed_lists(const SeedParams prm, int64_t L, const SelCtrl *sc, const uint64_t *seeds,
-                                                       const uint32_t *rank, const int32_t *dom_left, const int32_t *dom_right,
-                                                       SelCtrl *kctrl, uint64_t *cand)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    int32_t *lo = (int32_t *)smem;
-    uint32_t *pre = (uint32_t *)(lo + kCandCap);
-    __shared__ uint32_t wsum[kThreads / 64];
-    const int j = blockIdx.x;
-    const uint32_t ns = sc->total_n;
-    const int64_t r = prm.radius[j];
-    for (uint32_t u = threadIdx.x; u < ns; u += kThreads) {
-        const int64_t pos = (int64_t)key_token(seeds[u]);
-        const int64_t a = dom_left[u], b = dom_right[u];
-        int64_t first = pos - r, last = pos + r;
-        if (first < 0) first = 0;
-        if (last > L - 1) last = L - 1;
-        if (a >= 0 && a + r + 1 > first) first = a + r + 1;
-        if (b >= 0 && b - r - 1 < last) last = b - r - 1;
-        const uint32_t rk = rank[u];
-        lo[rk] = (int32_t)first;
-        pre[rk] = last >= first ? (uint32_t)(last - first + 1) : 0u;
-    }
-    __syncthreads();
-    // inclusive running sum of the interval lengths in rank order: thread t owns ranks t*kKeysPerThread ..
-    uint32_t own[kKeysPerThread], sum = 0;
-#pragma unroll
-    for (int k = 0; k < kKeysPerThread; ++k) {
-        const uint32_t i = threadIdx.x * kKeysPerThread + k;
-        own[k] = i < ns ? pre[i] : 0u;
-        sum += own[k];
-    }
-    uint32_t total;
-    uint32_t run = block_scan_inclusive<kThreads>(sum, wsum, total) - sum;
-#pragma unroll
-    for (int k = 0; k < kKeysPerThread; ++k) {
-        const uint32_t i = threadIdx.x * kKeysPerThread + k;
-        run += own[k];
-        if (i < ns) pre[i] = run;
-    }
-    __syncthreads();
-    const uint32_t want = prm.want[j] < total ? prm.want[j] : total;
-    uint32_t *tokens = (uint32_t *)(cand + (size_t)(1 + j) * kCandCap);
-    for (uint32_t i = threadIdx.x; i < want; i += kThreads) {
-        // the seed whose interval holds ranked token i: the first rank with pre[rank] > i
-        uint32_t lo_r = 0, hi_r = ns - 1;
-        while (lo_r < hi_r) {
-            const uint32_t mid = (lo_r + hi_r) >> 1;
-            if (pre[mid] > i) hi_r = mid; else lo_r = mid + 1;
-        }
-        const uint32_t before = lo_r ? pre[lo_r - 1] : 0u;
-        tokens[i] = (uint32_t)lo[lo_r] + (i - before);
-    }
-    if (threadIdx.x == 0) {
-        SelCtrl c{};
-        c.share = prm.share[j];
-        c.total_n = want;
-        c.cell = 1;
-        kctrl[j] = c;
+        by_rank[cnt] = (uint32_t)pos;
+        dom[cnt] = left | (right << 16);
     }
 }
 
@@ -1238,7 +1434,7 @@ SelectLayout make_select_layout(const SelectJob &job)
     lay.hist = off;
     off = up(off + 2 * (size_t)(nh + 1) * kSelBins * sizeof(uint32_t));
     lay.ctrl = off;
-    off = up(off + (size_t)(nh + 1 + (window ? n : 0)) * sizeof(SelCtrl));
+    off = up(off + (size_t)(nh + 1) * sizeof(SelCtrl));
     lay.done = off;
     off = up(off + 2 * (size_t)(nh + 1) * sizeof(uint32_t));
     lay.cmax = off;
@@ -1257,9 +1453,9 @@ SelectLayout make_select_layout(const SelectJob &job)
     lay.picked = off;
     off = up(off + ((size_t)ILRE_MAX_BUDGET + 64) * sizeof(uint32_t));
     lay.seed = off;
-    off = up(off + (window ? 3 * (size_t)kCandCap * sizeof(uint32_t) : 0));
+    off = up(off + (window ? 2 * (size_t)kCandCap * sizeof(uint32_t) : 0));
     lay.cand = off;
-    off = up(off + (size_t)(window ? n + 1 : n) * kCandCap * sizeof(uint64_t));
+    off = up(off + (size_t)nh * kCandCap * sizeof(uint64_t));
     lay.tie = off;
     off = up(off + ntie * sizeof(uint64_t));
     lay.total = off;
@@ -1273,18 +1469,20 @@ namespace {
 hipError_t set_select_attributes()
 {
     static hipError_t status = [] {
-        constexpr int kAllocLds = kHashSlots * (int)sizeof(uint32_t) + ILRE_MAX_BUDGET * (int)sizeof(uint32_t);
+        constexpr int kWalkLds = kBitmapTokens / 8 + kRingBytes;
+        static_assert(kWalkLds >= 2 * kWordSlots * (int)sizeof(uint32_t) + kRingBytes, "the word table fits where the bitmap does");
         constexpr int kPoolLdsMax = kPoolWaves * 2 * (kSelFine + 2 * (ILRE_MAX_AVG_KERNEL > ILRE_MAX_POOL_KERNEL ? ILRE_MAX_AVG_KERNEL : ILRE_MAX_POOL_KERNEL)) * (int)sizeof(float);
         constexpr int kSortLdsMax = 16384 * (int)sizeof(uint64_t);  // >= ILRE_MAX_BUDGET + 1 keys, padded to a power of two
-        constexpr int kSeedLds = 2 * kCandCap * (int)sizeof(uint32_t);
         constexpr int kSeedRankLds = kCandCap * (int)sizeof(uint64_t);
         hipError_t e;
-        if ((e = hipFuncSetAttribute((const void *)allocate_ranked, hipFuncAttributeMaxDynamicSharedMemorySize, kAllocLds)) != hipSuccess) return e;
+        for (const void *walk : {(const void *)allocate_walk<kWalkSeeds, false>, (const void *)allocate_walk<kWalkSeeds, true>,
+                                 (const void *)allocate_walk<kWalkWordCells, false>, (const void *)allocate_walk<kWalkWordCells, true>,
+                                 (const void *)allocate_walk<kWalkCells, false>, (const void *)allocate_walk<kWalkCells, true>})
+            if ((e = hipFuncSetAttribute(walk, hipFuncAttributeMaxDynamicSharedMemorySize, kWalkLds)) != hipSuccess) return e;
         if ((e = hipFuncSetAttribute((const void *)pool_hist<1>, hipFuncAttributeMaxDynamicSharedMemorySize, kPoolLdsMax)) != hipSuccess) return e;
         if ((e = hipFuncSetAttribute((const void *)pool_hist<2>, hipFuncAttributeMaxDynamicSharedMemorySize, kPoolLdsMax)) != hipSuccess) return e;
         if ((e = hipFuncSetAttribute((const void *)collect, hipFuncAttributeMaxDynamicSharedMemorySize, kPoolLdsMax)) != hipSuccess) return e;
         if ((e = hipFuncSetAttribute((const void *)refine, hipFuncAttributeMaxDynamicSharedMemorySize, kSortLdsMax)) != hipSuccess) return e;
-        if ((e = hipFuncSetAttribute((const void *)seed_lists, hipFuncAttributeMaxDynamicSharedMemorySize, kSeedLds)) != hipSuccess) return e;
         if ((e = hipFuncSetAttribute((const void *)seed_rank, hipFuncAttributeMaxDynamicSharedMemorySize, kSeedRankLds)) != hipSuccess) return e;
         return hipSuccess;
     }();
@@ -1304,8 +1502,31 @@ uint32_t clamp_u32(uint32_t x, uint32_t lo, uint32_t hi) { return x < lo ? lo : 
 // about one resident round of workgroups over all combinations.
 constexpr uint32_t kHistGrid = 2560, kCollectGrid = 8192;
 
-// Window-max form: the seeds (best raw scores), their ranks and neighbours, one ranked token list per
-// kernel size, the walk.
+// The walk and its ascending output: straight from the bitmap where it fits the LDS, else through the list of
+// allocated tokens, which emit_sorted puts in order.
+template <int ITEMS>
+void launch_walk(WalkArgs &w, const SelectJob &job, int n_out, unsigned char *ws, const SelectLayout &lay, int32_t *out_idx,
+                 int32_t *out_count, hipStream_t s)
+{
+    w.n_out = n_out;
+    w.sink = job.sink;
+    w.len = (uint32_t)job.L;
+    w.picked = (uint32_t *)(ws + lay.picked);
+    w.picked_n = w.picked + ILRE_MAX_BUDGET;
+    w.out_idx = out_idx;
+    w.out_count = out_count;
+    if (job.L <= kBitmapTokens) {
+        const size_t chunks = ((size_t)job.L + 32 * kBitmapChunk - 1) / (32 * kBitmapChunk);
+        const size_t lds = chunks * kBitmapChunk * sizeof(uint32_t) + kRingBytes;
+        hipLaunchKernelGGL((allocate_walk<ITEMS, false>), dim3(1), dim3(kWalkThreads), lds, s, w);
+    } else {
+        hipLaunchKernelGGL((allocate_walk<ITEMS, true>), dim3(1), dim3(kWalkThreads), 2 * (size_t)kWordSlots * sizeof(uint32_t) + kRingBytes, s, w);
+        hipLaunchKernelGGL(emit_sorted, dim3((unsigned)((n_out + kEmitPerBlock - 1) / kEmitPerBlock) + 1u), dim3(kEmitThreads), 0, s,
+                           w.picked, w.picked_n, n_out, job.sink, out_idx, out_count);
+    }
+}
+
+// Window-max form: the seeds (best raw scores), their ranks and neighbours, the walk.
 hipError_t launch_select_window(const float *scores, const SelectJob &job, int32_t *out_idx, int32_t *out_count,
                                 unsigned char *ws, const SelectLayout &lay, hipStream_t s, const FusedScores *fused)
 {
@@ -1313,15 +1534,11 @@ hipError_t launch_select_window(const float *scores, const SelectJob &job, int32
     const int n = job.combos();
     const int n_out = (int)(job.budget < L ? job.budget : L);
     uint32_t *hist = (uint32_t *)(ws + lay.hist);
-    SelCtrl *ctrl = (SelCtrl *)(ws + lay.ctrl);  // [0] the seed combination, [1] the pruning pre-pass, [2 ..] the kernel sizes
+    SelCtrl *ctrl = (SelCtrl *)(ws + lay.ctrl);  // [0] the seed combination, [1] the pruning pre-pass
     uint32_t *done = (uint32_t *)(ws + lay.done);
-    uint64_t *cand = (uint64_t *)(ws + lay.cand);  // list 0: the seeds' keys; list 1 + j: kernel size j's ranked tokens
+    uint64_t *cand = (uint64_t *)(ws + lay.cand);  // the seeds' keys
     uint64_t *tie = (uint64_t *)(ws + lay.tie);
-    uint32_t *rank = (uint32_t *)(ws + lay.seed);
-    int32_t *dom_left = (int32_t *)(rank + kCandCap), *dom_right = dom_left + kCandCap;
-    const size_t alloc_lds = (size_t)kHashSlots * sizeof(uint32_t) + (size_t)ILRE_MAX_BUDGET * sizeof(uint32_t);
-    uint32_t *picked = (uint32_t *)(ws + lay.picked), *picked_n = picked + ILRE_MAX_BUDGET;
-    const dim3 emit_grid((unsigned)((n_out + kEmitPerBlock - 1) / kEmitPerBlock) + 1u);
+    uint32_t *by_rank = (uint32_t *)(ws + lay.seed), *dom = by_rank + kCandCap;
 
     // the seed combination: window 1 on the scores, the n_out best wanted
     SelParams prm{};
@@ -1332,23 +1549,20 @@ hipError_t launch_select_window(const float *scores, const SelectJob &job, int32
     prm.want[0] = (uint32_t)n_out;
     prm.len[0] = (uint32_t)L;
     prm.cell[0] = 1;
-    // B_c: floor(B / n), the first B mod n kernel sizes one more.  K_j: what the earlier shares could have
-    // taken plus the own share.
-    SeedParams sp{};
-    sp.n = n;
+    // B_c: floor(B / n), the first B mod n kernel sizes one more
+    WalkArgs walk{};
+    walk.n = n;
     const int base = job.budget / n, rem = job.budget % n;
-    int64_t before = 0;
     int r_max = 0;
     for (int j = 0; j < n; ++j) {
-        const int share = base + (j < rem ? 1 : 0);
         const int r = (job.max_kernels[j] - 1) / 2;
-        const int64_t want = before + share < n_out ? before + share : n_out;
-        sp.radius[j] = (uint32_t)r;
-        sp.share[j] = (uint32_t)share;
-        sp.want[j] = (uint32_t)want;
-        before += share;
+        walk.reach[j] = (uint32_t)r;
+        walk.share[j] = (uint32_t)(base + (j < rem ? 1 : 0));
         if (r > r_max) r_max = r;
     }
+    walk.ctrl = ctrl;
+    walk.pos = by_rank;
+    walk.dom = dom;
 
     const uint32_t nfine = (uint32_t)((L + kSelFine - 1) / kSelFine);
     const size_t pool_lds = (size_t)kPoolWaves * 2 * (size_t)kSelFine * sizeof(float);
@@ -1409,11 +1623,8 @@ hipError_t launch_select_window(const float *scores, const SelectJob &job, int32
     // at most n_out + kSelSmall <= kCandCap seeds
     const uint32_t max_seeds = (uint32_t)n_out + (uint32_t)kSelSmall;
     hipLaunchKernelGGL(seed_rank, dim3((max_seeds + kSeedRankThreads / 16 - 1) / (kSeedRankThreads / 16)), dim3(kSeedRankThreads),
-                       (size_t)((max_seeds + 127u) & ~127u) * sizeof(uint64_t), s, scores, L, ctrl, cand, 2 * r_max, rank, dom_left, dom_right);
-    hipLaunchKernelGGL(seed_lists, dim3(n), dim3(kThreads), 2 * (size_t)kCandCap * sizeof(uint32_t), s, sp, L, ctrl, cand, rank,
-                       dom_left, dom_right, ctrl + 2, cand);
-    hipLaunchKernelGGL(allocate_ranked, dim3(1), dim3(kRankThreads), alloc_lds, s, ctrl + 2, cand + kCandCap, n, n_out, picked, picked_n);
-    hipLaunchKernelGGL(emit_sorted, emit_grid, dim3(kEmitThreads), 0, s, picked, picked_n, n_out, job.sink, out_idx, out_count);
+                       (size_t)((max_seeds + 127u) & ~127u) * sizeof(uint64_t), s, scores, L, ctrl, cand, 2 * r_max, by_rank, dom);
+    launch_walk<kWalkSeeds>(walk, job, n_out, ws, lay, out_idx, out_count, s);
     return hipGetLastError();
 }
 
@@ -1433,9 +1644,9 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
     uint64_t *cand = (uint64_t *)(ws + lay.cand);
     uint64_t *tie = (uint64_t *)(ws + lay.tie);
     float *cells = (float *)(ws + lay.cells);
-    const size_t alloc_lds = (size_t)kHashSlots * sizeof(uint32_t) + (size_t)ILRE_MAX_BUDGET * sizeof(uint32_t);
-    uint32_t *picked = (uint32_t *)(ws + lay.picked), *picked_n = picked + ILRE_MAX_BUDGET;
-    const dim3 emit_grid((unsigned)((n_out + kEmitPerBlock - 1) / kEmitPerBlock) + 1u);
+    WalkArgs walk{};
+    walk.ctrl = ctrl;
+    walk.cand = cand;
 
     hipError_t e = set_select_attributes();
     if (e != hipSuccess) return e;
@@ -1444,8 +1655,7 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
         fused = nullptr;
     }
     if (L == 0) {  // nothing but the sink part
-        hipLaunchKernelGGL(allocate_ranked, dim3(1), dim3(kRankThreads), alloc_lds, s, ctrl, cand, 0, 0, picked, picked_n);
-        hipLaunchKernelGGL(emit_sorted, emit_grid, dim3(kEmitThreads), 0, s, picked, picked_n, 0, job.sink, out_idx, out_count);
+        launch_walk<kWalkCells>(walk, job, 0, ws, lay, out_idx, out_count, s);
         return hipGetLastError();
     }
     if (job.mode == kSelWindowMax) return launch_select_window(scores, job, out_idx, out_count, ws, lay, s, fused);
@@ -1509,8 +1719,18 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
     hipLaunchKernelGGL(pool_hist<2>, dim3(hblocks, n), dim3(kPoolThreads), pool_lds, s, cells, n, ctrl, hist, done, ent);
     hipLaunchKernelGGL(collect, dim3(cblocks, n), dim3(kPoolThreads), pool_lds, s, cells, ctrl, cand, tie, ent);
     hipLaunchKernelGGL(refine, dim3(n), dim3(kThreads), (size_t)sort_n * sizeof(uint64_t), s, ctrl, cand, tie, sort_n);
-    hipLaunchKernelGGL(allocate_ranked, dim3(1), dim3(kRankThreads), alloc_lds, s, ctrl, cand, n, n_out, picked, picked_n);
-    hipLaunchKernelGGL(emit_sorted, emit_grid, dim3(kEmitThreads), 0, s, picked, picked_n, n_out, job.sink, out_idx, out_count);
+    walk.n = n;
+    bool word_cells = true;  // cells lie inside words of the set: sizes 1, 2, 4, 8, 16, 32
+    for (int j = 0; j < n; ++j) {
+        walk.share[j] = prm.share[j];
+        walk.reach[j] = prm.cell[j];
+        walk.cells[j] = prm.want[j];
+        word_cells = word_cells && 32 % prm.cell[j] == 0;
+    }
+    if (word_cells)
+        launch_walk<kWalkWordCells>(walk, job, n_out, ws, lay, out_idx, out_count, s);
+    else
+        launch_walk<kWalkCells>(walk, job, n_out, ws, lay, out_idx, out_count, s);
     return hipGetLastError();
 }
 

@@ -542,3 +542,31 @@ def test_select_randomised_against_oracle(seed):
             n_got = int(count.item())
             got = got.cpu().numpy()
             assert got[:n_got].tolist() == want.tolist() and (got[n_got:] == -1).all(), (seed, case, L, kind, budget, mk, ak, sink)
+
+
+# the walk's set of allocated tokens is a bitmap in LDS up to 1179648 tokens and a table of 32-token words beyond
+WALK_CASES = [
+    # L, sink, budget, window sizes (stride-1 form), max / average sizes (printed form)
+    (1179647, 0, 8192, (1, 63, 3), (1,), (1, 3)),          # last chunk of the bitmap one token short of full; 8 rounds a list
+    (1179648, 0, 4096, (1, 3, 7), (2, 5), (1, 2)),         # the bitmap exactly full
+    (1179652, 4, 4096, (2047, 1), (32, 33), (1, 4)),       # the body exactly full; intervals and cells over many words
+    (1179649, 0, 8192, (1, 1, 31), (1, 64), (2, 1)),       # one token more: the table
+    (8192, 0, 8191, (65, 129, 1), (3, 7), (1, 2, 5)),      # nearly every token kept: shares end inside intervals
+    (8224, 1, 1, (1,), (8,), (16,)),
+]
+
+
+@pytest.mark.parametrize("L,sink,budget,windows,mk,ak", WALK_CASES, ids=[f"L{c[0]}_B{c[2]}" for c in WALK_CASES])
+def test_walk_over_bitmap_and_word_table(L, sink, budget, windows, mk, ak):
+    """Both forms of the walk at the edges of its set representations, bit-exact with the oracle."""
+    _announce(f"walk L={L} sink={sink} budget={budget}")
+    rng = np.random.default_rng(L + budget)
+    s = _scores_for("needles", L, rng)
+    dev = torch.from_numpy(s).cuda()
+    got = il.ilre_select(dev, budget, windows, sink=sink)
+    got_p, count = il.ilre_select_max_avg(dev, budget, mk, ak, sink)
+    torch.cuda.synchronize()
+    assert got.cpu().numpy().tolist() == oracle.allocate(s, windows, budget, sink=sink).tolist()
+    n = int(count.item())
+    got_p = got_p.cpu().numpy()
+    assert got_p[:n].tolist() == oracle.allocate_max_avg(s, mk, ak, budget, sink=sink).tolist() and (got_p[n:] == -1).all()
