@@ -436,7 +436,10 @@ int run_scoring(const void *q, const void *k_cache, int64_t L, int32_t Lq, int32
     a.dump = (float *)(ws + lay.flag) + 16;
     e = ilre::launch_col_scores(p, a, opts->score_mode, out_scores, s, false, true);
     if (e != hipSuccess) return hip_fail(e, "column-score launch");
-    fused = ilre::FusedScores{a.partial, p.nunits, opts->score_mode == ILRE_SCORE_MAX ? 1 : 0, out_scores, L};
+    // every row's probabilities sum to one: the scores' mean is rows / L, that of their row maxima at least 1 / L
+    const bool rmax = opts->score_mode == ILRE_SCORE_MAX;
+    const float mean = (rmax ? 1.0f : (float)((int64_t)Hq * Lq)) / (float)L;
+    fused = ilre::FusedScores{a.partial, p.nunits, rmax ? 1 : 0, out_scores, L, mean};
     return ILRE_OK;
 }
 

@@ -124,8 +124,6 @@ struct SelectLayout {
 struct SelCtrl {
     uint32_t want;        // K_j: ranked elements that are candidates
     uint32_t share;       // B_j
-    uint32_t before;      // window: elements before and after the centre
-    uint32_t after;
     uint32_t bin1;        // level-1 bin (key bits 31..21) holding the K_j-th largest key
     uint32_t above1;      // keys in bins above it
     uint32_t need1;       // still needed from inside it
@@ -137,11 +135,11 @@ struct SelCtrl {
     uint32_t total_n;     // candidates (elements) after refine
     uint32_t len;         // elements in the source array
     uint32_t cell;        // tokens an element stands for (m; 1 in the window-max form)
-    uint32_t op;          // SelMode of the value function
-    uint64_t src_off;     // source array: floats from the base pointer the pooling kernels are given
     uint64_t tie_off;     // boundary lists: uint64 words from the base of the tie region
     uint32_t exact;       // 1: refine cuts the candidates to exactly `want`
-    uint32_t pad[3];
+    float edge;           // printed form: averages below it are not counted
+    uint32_t cut;         // printed form: 1 + the lowest bin of which elements are collected (0: all elements)
+    uint32_t pad;
 };
 
 // Workspace carving for a job (only mode, L, counts and the max kernels are read).
@@ -155,6 +153,7 @@ struct FusedScores {
     int rmax;              // 0 sum, 1 max over the units
     float *scores;         // L floats
     int64_t L;
+    float mean;            // the scores' scale: their mean (sum over the rows) or a lower bound of it (max)
 };
 
 // `scores` points at the body (the first token after the sink part).

@@ -9,22 +9,13 @@
 // whatever the earlier ones took; in the printed form K_m is given), so the candidate sets are built
 // for all combinations at once:
 //
-//   cell_max     printed form only: the strided max pooling, one cell array per max kernel
 //   sel_init     clears histograms and counters, writes each combination's control block
-//   pool_hist<1> wavefronts share out the 256-element "fine chunks" of the source array (the scores, or
-//                a cell array): elements + halo into the wavefront's own LDS buffers, pooled value
-//                (sliding maximum by doubling, or the average summed left to right), a 2048-bin LDS
-//                histogram of the top 11 bits of the value's order-preserving key, added to the
-//                combination's global histogram.  The last workgroup of a combination to finish
-//                locates the bin holding its K_j-th largest key.
-//   pool_hist<2> same pooling; histogram of the next 11 bits of the keys inside that bin; the last
-//                workgroup locates the 22-bit prefix of the K_j-th largest key.
-//   collect      keys above the prefix go to the combination's candidate list, keys that share it to
-//                a boundary list (a few dozen on real scores; everything on all-equal scores)
-//   refine       per combination: the boundary list is radix-selected down (8 bits a pass, survivors
-//                compacted) to what is needed -- in the window-max form only while it is longer than
-//                kSelSmall, extra candidates rank last and are harmless; in the printed form to
-//                exactly K_m elements -- and joins the candidates
+//   pool_averages<0>   the strided max pooling (one cell array per max kernel) and per combination a histogram of
+//                the averages; the last workgroup of a max kernel finds its combinations' cuts, the bin
+//                that holds the K_j-th best
+//   pool_averages<1>   the averages at or above the cut, into the combination's list
+//   refine       per combination: the list sorted, the first K_j elements kept; a list too long to sort (many equal
+//                averages) is radix-selected down first, 8 bits a pass, survivors compacted
 //   allocate_walk   one workgroup walks the combinations in order over their ranked cells: the allocated set is
 //                a bitmap in LDS, tokens that it holds are skipped, the first B_j others are taken; the ascending
 //                output is then read off the bitmap
@@ -37,9 +28,15 @@
 // so every candidate token has a seed inside its window, and a seed that B' others outrank owns no token
 // of any candidate prefix.  Hence:
 //
-//   sel_init, pool_hist<1>, pool_hist<2>, collect, refine    as above, for ONE combination with window 1:
-//                the B' best raw scores (plus, harmlessly, up to kSelSmall more that share the 22-bit
-//                prefix of the last one)
+//   sel_init     as above, for ONE combination
+//   pool_hist<1> wavefronts share out the 256-token "fine chunks" of the scores: a 2048-bin LDS histogram of
+//                the top 11 bits of the scores' order-preserving keys, added to the global one.  The last workgroup
+//                to finish locates the bin holding the B'-th largest key
+//   pool_hist<2> the next 11 bits of the keys inside that bin: the 22-bit prefix of the B'-th largest key
+//   collect      keys above the prefix go to the seed list, keys that share it to a boundary list (a few dozen on
+//                real scores; everything on all-equal scores)
+//   refine       the boundary list joins the seeds, radix-selected down first while it is longer than kSelSmall
+//                (extra seeds rank last and are harmless)
 //   seed_rank    per seed: its rank among the seeds (counting: a wavefront's lanes share out the staged keys
 //                and compare them with its four seeds) and the nearest seed that outranks it on either side
 //                (a scan of the raw scores around it, 16 lanes a seed: whatever outranks a seed is a seed)
@@ -61,6 +58,9 @@
 // the same key gives them once the element index is replaced by the token index.
 #include "ilre_internal.h"
 
+#include <string.h>
+
+#include <algorithm>
 #include <type_traits>
 
 namespace ilre {
@@ -71,21 +71,19 @@ constexpr int kPoolThreads = 256;                 // pooling passes: four wavefr
 constexpr int kPoolWaves = kPoolThreads / 64;
 constexpr int kPerThread = kSelFine / 64;         // 4 tokens per lane
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
+constexpr uint32_t kSortSmall = 4096;             // printed form: lists up to this long are sorted whole
 
 // Per-combination description, host -> sel_init (by value), which copies it into the control blocks.
 struct SelParams {
     int n;
-    uint32_t op, exact;
-    uint32_t before[ILRE_MAX_POOL_KERNELS], after[ILRE_MAX_POOL_KERNELS];
+    uint32_t exact;
     uint32_t share[ILRE_MAX_POOL_KERNELS], want[ILRE_MAX_POOL_KERNELS];
     uint32_t len[ILRE_MAX_POOL_KERNELS], cell[ILRE_MAX_POOL_KERNELS];
-    uint64_t src_off[ILRE_MAX_POOL_KERNELS], tie_off[ILRE_MAX_POOL_KERNELS];
-};
-
-struct CellParams {
-    int n;
-    uint32_t m[ILRE_MAX_POOL_KERNELS], len[ILRE_MAX_POOL_KERNELS];
-    uint64_t off[ILRE_MAX_POOL_KERNELS];
+    uint64_t tie_off[ILRE_MAX_POOL_KERNELS];
+    float edge[ILRE_MAX_POOL_KERNELS];     // where the bins start, if `sample` is null
+    const float *sample;                   // else: found from kBaseSamples of these sample_n scores
+    int64_t sample_n;
+    uint64_t deep;                         // bit j: combination j wants so many that its bins start below all samples
 };
 
 // Order-preserving map of a finite float onto uint32 (larger float -> larger key; the two zeros share one).
@@ -180,9 +178,41 @@ __device__ __forceinline__ uint32_t block_scan_inclusive(uint32_t x, uint32_t *w
     return x + before;
 }
 
+// Where the bins of scores of unknown scale start: at the median of a sample (the K_j-th best is above it), or below
+// its minimum for a combination that wants a large part of the elements.  Any edge gives the same result; one far off
+// puts everything into one bin.
+constexpr int kBaseSamples = 256;
+__device__ float sampled_edge(const float *scores, int64_t n, bool deep)
+{
+    __shared__ __align__(16) uint32_t key[kBaseSamples];
+    __shared__ uint32_t above[kBaseSamples];
+    __shared__ float edge;
+    const int t = threadIdx.x;
+    float x = 0.f;
+    if (t < kBaseSamples) {
+        x = scores[(int64_t)t * n / kBaseSamples];
+        key[t] = ordered_bits(x);
+        above[t] = 0;
+    }
+    __syncthreads();
+    constexpr int kShare = kThreads / kBaseSamples, kPart = kBaseSamples / kShare;  // threads a sample, samples a thread compares with
+    const int u = t % kBaseSamples, part = t / kBaseSamples;
+    uint32_t c = 0;
+    for (int k = 0; k < kPart; ++k) {
+        const int v = part * kPart + k;
+        c += key[v] > key[u] || (key[v] == key[u] && v < u) ? 1u : 0u;
+    }
+    atomicAdd(&above[u], c);
+    __syncthreads();
+    if (t < kBaseSamples && above[t] == (uint32_t)(deep ? kBaseSamples - 1 : kBaseSamples / 2)) edge = deep ? 0.25f * x : x;
+    __syncthreads();
+    return edge;
+}
+
 __global__ __launch_bounds__(kThreads) void sel_init(const SelParams prm, uint32_t *hist, SelCtrl *ctrl, uint32_t *done)
 {
     const int j = blockIdx.x;
+    const float edge = prm.sample ? sampled_edge(prm.sample, prm.sample_n, (prm.deep >> j) & 1u) : prm.edge[j];
     // hist holds [2][n][kSelBins]; block j clears its rows of both levels
     for (int i = threadIdx.x; i < kSelBins; i += kThreads) {
         hist[(size_t)j * kSelBins + i] = 0;
@@ -192,34 +222,16 @@ __global__ __launch_bounds__(kThreads) void sel_init(const SelParams prm, uint32
         SelCtrl c{};
         c.want = prm.want[j];
         c.share = prm.share[j];
-        c.before = prm.before[j];
-        c.after = prm.after[j];
         c.bin1 = kSelBins;
         c.bin2 = kSelBins;
         c.len = prm.len[j];
         c.cell = prm.cell[j];
-        c.op = prm.op;
-        c.src_off = prm.src_off[j];
         c.tie_off = prm.tie_off[j];
         c.exact = prm.exact;
+        c.edge = edge > 0x1p-90f && edge < 0x1p90f ? edge : 0x1p-90f;
         ctrl[j] = c;
         done[j] = 0;          // [2][n]: workgroups finished per histogram level and combination
         done[prm.n + j] = 0;
-    }
-}
-
-// MaxPooling of Algorithm 1 with size = stride = m: cell p = max(body[p*m .. p*m+m-1]) for the whole
-// cells; the tokens after the last whole cell belong to none.  grid = (workgroups, max kernels).
-__global__ __launch_bounds__(kPoolThreads) void cell_max(const float *body, const CellParams cp, float *cells)
-{
-    const int i = blockIdx.y;
-    const uint32_t m = cp.m[i], len = cp.len[i];
-    float *out = cells + cp.off[i];
-    for (uint32_t p = blockIdx.x * kPoolThreads + threadIdx.x; p < len; p += gridDim.x * kPoolThreads) {
-        const float *src = body + (size_t)p * m;
-        float v = src[0];
-        for (uint32_t u = 1; u < m; ++u) v = fmaxf(v, src[u]);
-        out[p] = v;
     }
 }
 
@@ -239,25 +251,11 @@ __device__ __forceinline__ uint32_t entry_chunk(const Entries &e, uint32_t i) { 
 // memory changed) is all the synchronisation a wavefront-private buffer needs.
 __device__ __forceinline__ void lds_wave_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
-// What a combination computes from its source array.
-struct Pooling {
-    const float *src;
-    int64_t len;        // elements in src
-    int before, after;  // window [e - before, e + after]
-    int op;             // SelMode
-};
-__device__ __forceinline__ Pooling pooling_of(const float *vals, const SelCtrl &c)
-{
-    return Pooling{vals + c.src_off, (int64_t)c.len, (int)c.before, (int)c.after, (int)c.op};
-}
-__device__ __forceinline__ size_t pool_lds_floats(int before, int after) { return (size_t)(kSelFine + before + after); }
-
-// Window 1 in the window-max form (the seed pass): the pooled value is the element.  kRawBatch fine chunks
-// (entries e0 .. e0 + kRawBatch - 1 of the visit list) are fetched at once; fcs[u] < 0 marks a missing entry.
+// kRawBatch fine chunks (entries e0 .. e0 + kRawBatch - 1 of the visit list) are fetched at once; fcs[u] < 0 marks a
+// missing entry.
 constexpr int kRawBatch = 4;
-__device__ __forceinline__ bool raw_window(const Pooling &pl) { return pl.op == kSelWindowMax && pl.before + pl.after == 0; }
-__device__ __forceinline__ void raw_fetch(const Pooling &pl, const Entries &ent, uint32_t e0, uint32_t nent, int64_t (&fcs)[kRawBatch],
-                                          float (&vals)[kRawBatch][kPerThread])
+__device__ __forceinline__ void raw_fetch(const float *src, int64_t len, const Entries &ent, uint32_t e0, uint32_t nent,
+                                          int64_t (&fcs)[kRawBatch], float (&vals)[kRawBatch][kPerThread])
 {
     const int lane = threadIdx.x & 63;
 #pragma unroll
@@ -267,92 +265,23 @@ __device__ __forceinline__ void raw_fetch(const Pooling &pl, const Entries &ent,
 #pragma unroll
         for (int k = 0; k < kPerThread; ++k) {
             const int64_t e = (fcs[u] < 0 ? 0 : fcs[u]) * kSelFine + lane + k * 64;
-            vals[u][k] = pl.src[e < pl.len ? e : pl.len - 1];  // lanes past the end are ignored by the callers
+            vals[u][k] = src[e < len ? e : len - 1];  // lanes past the end are ignored by the callers
         }
 }
 
-// Pooled values of this lane's kPerThread elements (lane + 64k) of fine chunk `fc`, computed by one
-// wavefront in its own LDS buffers b0/b1 (kSelFine + before + after floats each).
-//   kSelWindowMax: pooled[e] = max(src[u] : e - before <= u <= e + after, 0 <= u < len)  (MaxPooling at
-//     stride 1, window clipped to the context).  Sliding maximum by doubling: m_p[i] = max(src[i ..
-//     i+p-1]) for p = 1, 2, 4, ... <= w, then two overlapping windows of length p cover the window.
-//   kSelMaxAvg: pooled[e] = (src[e-before] + ... + src[e+after]) / w with zeros outside the array,
-//     summed left to right in fp32 and divided with round-to-nearest (AvgPooling at stride 1).
-__device__ __forceinline__ void pooled_wave(const Pooling &pl, int64_t fc, float *b0, float *b1, float (&out)[kPerThread])
-{
-    const int lane = threadIdx.x & 63;
-    const int len = kSelFine + pl.before + pl.after;
-    const int64_t first = fc * kSelFine - pl.before;
-    const float pad = pl.op == kSelMaxAvg ? 0.0f : -INFINITY;
-    lds_wave_sync();  // the previous chunk's reads of these buffers are done
-    // Loads are unconditional from a clamped address (padding is selected afterwards), so that a
-    // lane's loads are all in flight together instead of one memory latency after the other.
-    const int64_t last = pl.len - 1;
-    auto clamped = [&](int64_t e) { return pl.src[e < 0 ? 0 : (e > last ? last : e)]; };
-    {
-        float v[kPerThread];
-#pragma unroll
-        for (int k = 0; k < kPerThread; ++k) v[k] = clamped(first + lane + k * 64);
-        const int ih = kSelFine + lane;  // halo part: before + after <= 2 * 1023 elements
-        const float vh = clamped(first + ih);
-#pragma unroll
-        for (int k = 0; k < kPerThread; ++k) {
-            const int64_t e = first + lane + k * 64;
-            b0[lane + k * 64] = (e >= 0 && e <= last) ? v[k] : pad;
-        }
-        if (ih < len) b0[ih] = (first + ih >= 0 && first + ih <= last) ? vh : pad;
-        for (int i = ih + 64; i < len; i += 64) {
-            const int64_t e = first + i;
-            const float x = clamped(e);
-            b0[i] = (e >= 0 && e <= last) ? x : pad;
-        }
-    }
-    lds_wave_sync();
-    const int w = pl.before + pl.after + 1;
-    if (pl.op == kSelMaxAvg) {
-        float sum[kPerThread];
-#pragma unroll
-        for (int k = 0; k < kPerThread; ++k) sum[k] = 0.0f;
-        for (int u = 0; u < w; ++u) {
-#pragma unroll
-            for (int k = 0; k < kPerThread; ++k) sum[k] = sum[k] + b0[lane + k * 64 + u];
-        }
-        const float div = (float)w;
-#pragma unroll
-        for (int k = 0; k < kPerThread; ++k) out[k] = __fdiv_rn(sum[k], div);
-        return;
-    }
-    int p = 1;
-    float *src = b0, *dst = b1;
-    while (2 * p <= w) {
-        for (int i = lane; i < len; i += 64) dst[i] = (i + p < len) ? fmaxf(src[i], src[i + p]) : src[i];
-        lds_wave_sync();
-        float *t = src;
-        src = dst;
-        dst = t;
-        p *= 2;
-    }
-#pragma unroll
-    for (int k = 0; k < kPerThread; ++k) {
-        const int tl = lane + k * 64;
-        out[k] = fmaxf(src[tl], src[tl + w - p]);
-    }
-}
-
-// For combination j: the bin b with  count(bins > b) < need <= count(bins >= b), by one wavefront.
+// The bin b with  count(bins > b) < need <= count(bins >= b), by one wavefront.
 // Lane l sums 32 bins (descending order of bins); a scan over the lanes finds the lane whose segment
 // holds the crossing, and a second scan over that segment's 32 bins (one bin a lane) finds the bin.
 // LEVEL 1 reads `want`, LEVEL 2 the remainder left by level 1.
 template <int LEVEL>
-__device__ void find_bins(const uint32_t *hist, SelCtrl *ctrl, int j)
+__device__ void find_bins(const uint32_t *hj, SelCtrl *ctrl)
 {
     const int lane = threadIdx.x & 63;
     constexpr int BPL = kSelBins / 64;
     static_assert(BPL == 32, "the second scan maps one bin of a segment to each of 32 lanes");
     if (threadIdx.x < 64) {
-        const uint32_t need = LEVEL == 1 ? ctrl[j].want : ctrl[j].need1;
-        if (need == 0 || (LEVEL == 2 && ctrl[j].bin1 >= (uint32_t)kSelBins)) return;  // uniform in the wave
-        const uint32_t *hj = hist + (size_t)j * kSelBins;
+        const uint32_t need = LEVEL == 1 ? ctrl->want : ctrl->need1;
+        if (need == 0 || (LEVEL == 2 && ctrl->bin1 >= (uint32_t)kSelBins)) return;  // uniform in the wave
         uint32_t sum = 0;
 #pragma unroll 16
         for (int k = 0; k < BPL; ++k) sum += load_u32(&hj[kSelBins - 1 - (lane * BPL + k)]);
@@ -367,13 +296,13 @@ __device__ void find_bins(const uint32_t *hist, SelCtrl *ctrl, int j)
         const uint32_t above = seg_above + in2 - own;
         if (lane < 32 && above < need && need <= above + own) {  // exactly one lane
             if (LEVEL == 1) {
-                ctrl[j].bin1 = bin;
-                ctrl[j].above1 = above;
-                ctrl[j].need1 = need - above;
+                ctrl->bin1 = bin;
+                ctrl->above1 = above;
+                ctrl->need1 = need - above;
             } else {
-                ctrl[j].bin2 = bin;
-                ctrl[j].above2 = above;
-                ctrl[j].need2 = need - above;
+                ctrl->bin2 = bin;
+                ctrl->above2 = above;
+                ctrl->need2 = need - above;
             }
         }
     }
@@ -461,74 +390,60 @@ __device__ __forceinline__ void hist_account(uint32_t *lh, const float (&pooled)
     }
 }
 
-// The workgroup's LDS histogram goes to the combination's global one; the last workgroup of combination j to
-// get here sees it complete and locates the bin.  The bins are only ever touched by device-scope atomics (adds
-// here, atomic loads in find_bins), which are performed at the memory side, common to all eight L2s.  Each
-// thread waits until its adds have been performed (vmcnt counts them), then one thread counts the workgroup in
-// with another device-scope atomic: whoever reads the final count reads, with atomic loads issued after it, bins
-// that hold every add.  A device-scope release fence in their place would also write this L2's unrelated dirty
-// lines back, tens of microseconds per workgroup; the acquire side, one workgroup per combination, is cheap and
-// is there.  `counter` is the completion counter of this level and combination, `workgroups` how many count in.
-template <int LEVEL>
-__device__ __forceinline__ void hist_finish(uint32_t *lh, uint32_t *hist, SelCtrl *ctrl, int j, uint32_t *counter,
-                                            uint32_t workgroups, uint32_t *is_last)
+// Completion counting.  A workgroup's additions to the histograms are device-scope atomics, performed at the memory side,
+// common to all eight L2s.  Each thread waits until its own have been performed (vmcnt counts them), then one thread
+// counts the workgroup in with another: whoever reads the final count reads, with atomic loads issued after it, bins that
+// hold every addition.  A device-scope release fence in their place would also write this L2's unrelated dirty lines back,
+// tens of microseconds per workgroup; the acquire side, one workgroup per counter, is cheap and is there.
+__device__ __forceinline__ bool count_in(uint32_t *counter, uint32_t workgroups, uint32_t *is_last)
 {
-    __syncthreads();
-    for (int i = threadIdx.x; i < kSelBins; i += kPoolThreads) {
-        const uint32_t c = lh[i];
-        if (c) atomicAdd(&hist[(size_t)j * kSelBins + i], c);
-    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0)
         *is_last = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == workgroups - 1;
     __syncthreads();
-    if (*is_last) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        find_bins<LEVEL>(hist, ctrl, j);
-    }
+    if (!*is_last) return false;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    return true;
 }
 
-// LEVEL 1: histogram of key bits 31..21 over the visited elements.  LEVEL 2: of bits 20..10 over the
-// elements whose bits 31..21 equal the combination's level-1 bin.  grid = (workgroups, combinations);
-// the wavefronts of a grid row share out the entries.
+// The workgroup's LDS histogram goes to the global one; the last workgroup to count in locates the bin.
 template <int LEVEL>
-__global__ __launch_bounds__(kPoolThreads) void pool_hist(const float *vals, int n, SelCtrl *ctrl, uint32_t *hist_all,
-                                                          uint32_t *done, const Entries ent)
+__device__ __forceinline__ void hist_finish(uint32_t *lh, uint32_t *hist, SelCtrl *ctrl, uint32_t *counter, uint32_t workgroups, uint32_t *is_last)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
+    __syncthreads();
+    for (int i = threadIdx.x; i < kSelBins; i += kPoolThreads) {
+        const uint32_t c = lh[i];
+        if (c) atomicAdd(&hist[i], c);
+    }
+    if (count_in(counter, workgroups, is_last)) find_bins<LEVEL>(hist, ctrl);
+}
+
+// LEVEL 1: histogram of key bits 31..21 over the visited elements.  LEVEL 2: of bits 20..10 over the elements whose
+// bits 31..21 equal the level-1 bin.  A wavefront fetches kRawBatch fine chunks before it accounts for any, so
+// that their loads are in flight together.
+template <int LEVEL>
+__global__ __launch_bounds__(kPoolThreads) void pool_hist(const float *vals, SelCtrl *ctrl, uint32_t *hist_all, uint32_t *done,
+                                                          const Entries ent)
+{
     __shared__ uint32_t lh[kSelBins];
     __shared__ uint32_t is_last;
-    const int j = blockIdx.y;
-    const Pooling pl = pooling_of(vals, ctrl[j]);
     const int wave = threadIdx.x >> 6;
-    uint32_t *hist = hist_all + (size_t)(LEVEL - 1) * n * kSelBins;
-    float *b0 = (float *)smem + (size_t)wave * 2 * pool_lds_floats(pl.before, pl.after);
-    float *b1 = b0 + pool_lds_floats(pl.before, pl.after);
-    const uint32_t bin1 = LEVEL == 2 ? ctrl[j].bin1 : 0;
+    uint32_t *hist = hist_all + (size_t)(LEVEL - 1) * kSelBins;
+    const uint32_t bin1 = LEVEL == 2 ? ctrl->bin1 : 0;
+    const int64_t len = (int64_t)ctrl->len;
     for (int i = threadIdx.x; i < kSelBins; i += kPoolThreads) lh[i] = 0;
     __syncthreads();
-    const uint32_t nent = entry_count(ent, (uint32_t)pl.len);
-    if (raw_window(pl)) {
-        // window 1: the elements themselves; a wavefront fetches kRawBatch fine chunks before it accounts for
-        // any, so that their loads are in flight together
-        for (uint32_t e0 = (blockIdx.x * kPoolWaves + wave) * kRawBatch; e0 < nent; e0 += gridDim.x * kPoolWaves * kRawBatch) {
-            float vals_[kRawBatch][kPerThread];
-            int64_t fcs[kRawBatch];
-            raw_fetch(pl, ent, e0, nent, fcs, vals_);
+    const uint32_t nent = entry_count(ent, (uint32_t)len);
+    for (uint32_t e0 = (blockIdx.x * kPoolWaves + wave) * kRawBatch; e0 < nent; e0 += gridDim.x * kPoolWaves * kRawBatch) {
+        float vals_[kRawBatch][kPerThread];
+        int64_t fcs[kRawBatch];
+        raw_fetch(vals, len, ent, e0, nent, fcs, vals_);
 #pragma unroll
-            for (int u = 0; u < kRawBatch; ++u)
-                if (fcs[u] >= 0) hist_account<LEVEL>(lh, vals_[u], fcs[u] * kSelFine, pl.len, bin1);  // uniform
-        }
-    } else {
-        for (uint32_t e = blockIdx.x * kPoolWaves + wave; e < nent; e += gridDim.x * kPoolWaves) {
-            const int64_t fc = entry_chunk(ent, e);
-            float pooled[kPerThread];
-            pooled_wave(pl, fc, b0, b1, pooled);
-            hist_account<LEVEL>(lh, pooled, fc * kSelFine, pl.len, bin1);
-        }
+        for (int u = 0; u < kRawBatch; ++u)
+            if (fcs[u] >= 0) hist_account<LEVEL>(lh, vals_[u], fcs[u] * kSelFine, len, bin1);  // uniform
     }
-    hist_finish<LEVEL>(lh, hist, ctrl, j, &done[(LEVEL - 1) * n + j], gridDim.x, &is_last);
+    hist_finish<LEVEL>(lh, hist, ctrl, &done[LEVEL - 1], gridDim.x, &is_last);
 }
 
 // The whole path's first selection pass, fused with the last scoring step: score[t] = sum (or max) over the
@@ -595,58 +510,36 @@ __global__ __launch_bounds__(kPoolThreads) void reduce_hist1(const float *partia
             hist_account<1>(lh, v[c], (int64_t)(fc0 + c) * kSelFine - sink, L - sink, 0);
         }
     }
-    hist_finish<1>(lh, hist, ctrl, 0, &done[0], gridDim.x, &is_last);
+    hist_finish<1>(lh, hist, ctrl, &done[0], gridDim.x, &is_last);
 }
 
-__global__ __launch_bounds__(kPoolThreads) void collect(const float *vals, SelCtrl *ctrl, uint64_t *cand, uint64_t *tie,
-                                                        const Entries ent)
+__global__ __launch_bounds__(kPoolThreads) void collect(const float *vals, SelCtrl *ctrl, uint64_t *cand, uint64_t *tie, const Entries ent)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int j = blockIdx.y;
-    const Pooling pl = pooling_of(vals, ctrl[j]);
+    const int64_t len = (int64_t)ctrl->len;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t bin1 = ctrl[j].bin1, bin2 = ctrl[j].bin2;
-    if (bin1 >= (uint32_t)kSelBins || bin2 >= (uint32_t)kSelBins) return;  // nothing wanted from this combination
-    const uint32_t prefix = (bin1 << 11) | bin2;  // 22-bit prefix of the K_j-th largest key
-    float *b0 = (float *)smem + (size_t)wave * 2 * pool_lds_floats(pl.before, pl.after);
-    float *b1 = b0 + pool_lds_floats(pl.before, pl.after);
-    uint64_t *cand_j = cand + (size_t)j * kCandCap;
-    uint64_t *tie_j = tie + ctrl[j].tie_off;
-    const uint32_t nent = entry_count(ent, (uint32_t)pl.len);
+    const uint32_t bin1 = ctrl->bin1, bin2 = ctrl->bin2;
+    if (bin1 >= (uint32_t)kSelBins || bin2 >= (uint32_t)kSelBins) return;  // nothing wanted
+    const uint32_t prefix = (bin1 << 11) | bin2;  // 22-bit prefix of the K-th largest key
+    const uint32_t nent = entry_count(ent, (uint32_t)len);
     // keys above the prefix are candidates, keys that share it go to the boundary list
-    auto classify = [&](float pooled, int64_t fc, int k, bool &above, bool &same, uint64_t &key) {
-        const int64_t el = fc * kSelFine + lane + k * 64;
-        const bool valid = fc >= 0 && el < pl.len;
-        const uint32_t p22 = valid ? ordered_bits(pooled) >> 10 : 0;
-        key = make_key(pooled, (uint32_t)el);
-        above = valid && p22 > prefix;
-        same = valid && p22 == prefix;
-    };
-    if (raw_window(pl)) {
-        for (uint32_t e0 = (blockIdx.x * kPoolWaves + wave) * kRawBatch; e0 < nent; e0 += gridDim.x * kPoolWaves * kRawBatch) {
-            float vals_[kRawBatch][kPerThread];
-            int64_t fcs[kRawBatch];
-            raw_fetch(pl, ent, e0, nent, fcs, vals_);
-            bool above[kRawBatch * kPerThread], same[kRawBatch * kPerThread];
-            uint64_t key[kRawBatch * kPerThread];
+    for (uint32_t e0 = (blockIdx.x * kPoolWaves + wave) * kRawBatch; e0 < nent; e0 += gridDim.x * kPoolWaves * kRawBatch) {
+        float vals_[kRawBatch][kPerThread];
+        int64_t fcs[kRawBatch];
+        raw_fetch(vals, len, ent, e0, nent, fcs, vals_);
+        bool above[kRawBatch * kPerThread], same[kRawBatch * kPerThread];
+        uint64_t key[kRawBatch * kPerThread];
 #pragma unroll
-            for (int u = 0; u < kRawBatch; ++u)
+        for (int u = 0; u < kRawBatch; ++u)
 #pragma unroll
-                for (int k = 0; k < kPerThread; ++k)
-                    classify(vals_[u][k], fcs[u], k, above[u * kPerThread + k], same[u * kPerThread + k], key[u * kPerThread + k]);
-            wave_append2<kRawBatch * kPerThread>(above, same, key, cand_j, &ctrl[j].cand_n, tie_j, &ctrl[j].tie_n);
-        }
-    } else {
-        for (uint32_t e = blockIdx.x * kPoolWaves + wave; e < nent; e += gridDim.x * kPoolWaves) {
-            const int64_t fc = entry_chunk(ent, e);
-            float pooled[kPerThread];
-            pooled_wave(pl, fc, b0, b1, pooled);
-            bool above[kPerThread], same[kPerThread];
-            uint64_t key[kPerThread];
-#pragma unroll
-            for (int k = 0; k < kPerThread; ++k) classify(pooled[k], fc, k, above[k], same[k], key[k]);
-            wave_append2<kPerThread>(above, same, key, cand_j, &ctrl[j].cand_n, tie_j, &ctrl[j].tie_n);
-        }
+            for (int k = 0; k < kPerThread; ++k) {
+                const int64_t el = fcs[u] * kSelFine + lane + k * 64;
+                const bool valid = fcs[u] >= 0 && el < len;
+                const uint32_t p22 = valid ? ordered_bits(vals_[u][k]) >> 10 : 0;
+                key[u * kPerThread + k] = make_key(vals_[u][k], (uint32_t)el);
+                above[u * kPerThread + k] = valid && p22 > prefix;
+                same[u * kPerThread + k] = valid && p22 == prefix;
+            }
+        wave_append2<kRawBatch * kPerThread>(above, same, key, cand, &ctrl->cand_n, tie, &ctrl->tie_n);
     }
 }
 
@@ -732,6 +625,355 @@ __global__ __launch_bounds__(kPoolThreads) void mark_active(const float *cm, uin
         if ((hits >> i) & 1u) list[at++] = c0 + i;
 }
 
+// ---------------------------------------------------------------- printed form: averages, thresholds, candidates
+
+// x / n, correctly rounded, n a small integer and y = 1 / n rounded: a quotient refined with its exact remainder
+// twice.  (After one step it is within an ulp, and a quotient within an ulp refined with the rounded reciprocal is
+// the rounded quotient: Markstein, IBM J. R&D 34 (1990).)  The remainder must not underflow.
+__device__ __forceinline__ float divide_small(float x, float n, float y)
+{
+    float q = x * y;
+    q = fmaf(fmaf(-n, q, x), y, q);
+    q = fmaf(fmaf(-n, q, x), y, q);
+    const float ax = fabsf(x);
+    if (ax < 0x1p-90f || ax > 0x1p100f) q = __fdiv_rn(x, n);
+    return q;
+}
+
+constexpr int kAvgThreads = 512;
+constexpr int kAvgWaves = kAvgThreads / 64;
+constexpr int kAvgNarrow = 2, kAvgWide = 4;       // windows a lane sums
+constexpr int kAvgGroup = 16;                     // average kernels a workgroup handles
+constexpr int kAvgBins = 1024;                    // bins per average kernel
+constexpr int kAvgBinShift = 17;                  // float bits a bin spans: a 64th of a binade, 1024 of them 16 binades
+constexpr int kAvgList = 256;                     // any sizes: collected elements a workgroup holds per average kernel before it writes them
+constexpr uint16_t kNoAvg = 0xFFFF;
+static_assert(kAvgBins <= kSelBins, "a combination's row of the histogram holds its bins");
+// LDS of pool_averages: counts or collected elements, then a buffer of cells per wavefront (readable two past the last)
+constexpr size_t avg_shared(int pass, int per, bool small)
+{
+    return pass == 0 ? ((size_t)kAvgGroup * kAvgBins + 64) * sizeof(uint32_t)
+                     : (small ? (size_t)kAvgWaves * 64 * per : (size_t)kAvgList) * kAvgGroup * sizeof(uint64_t);
+}
+constexpr size_t avg_lds(int pass, int per, bool small, int n_top)
+{
+    return avg_shared(pass, per, small) + (size_t)kAvgWaves * (size_t)(64 * per + (small ? kAvgGroup : n_top) + 1) * sizeof(float);
+}
+
+struct AvgParams {
+    int n_avg, groups;                                    // average kernels, groups of kAvgGroup of them
+    uint32_t m[ILRE_MAX_POOL_KERNELS], len[ILRE_MAX_POOL_KERNELS];  // per max kernel: size, cells
+    uint64_t off[ILRE_MAX_POOL_KERNELS];                  // its cells
+    uint16_t avg[ILRE_MAX_POOL_KERNELS], at[ILRE_MAX_POOL_KERNELS];  // average kernels ascending, and their number in the order given
+    uint16_t at_of_size[kAvgGroup];                       // SMALL: number of the average kernel of size 1, 2, .. (kNoAvg: none)
+};
+
+// The cut of a combination: 1 + the highest bin b with at least `need` elements in the bins from b up (0: fewer than that
+// were counted, everything is wanted).  By one wavefront: lane l sums 16 bins in descending order of bins, a scan over the
+// lanes finds the lane whose segment holds the crossing.
+__device__ __forceinline__ uint32_t find_cut(const uint32_t *h, uint32_t need)
+{
+    const int lane = threadIdx.x & 63;
+    constexpr int BPL = kAvgBins / 64;
+    const uint64_t *h2 = (const uint64_t *)(h + kAvgBins - (lane + 1) * BPL);  // this lane's bins, lowest first
+    uint64_t two[BPL / 2];
+#pragma unroll
+    for (int k = 0; k < BPL / 2; ++k) two[k] = load_u64(&h2[k]);
+    uint32_t sum = 0;
+#pragma unroll
+    for (int k = 0; k < BPL / 2; ++k) sum += (uint32_t)two[k] + (uint32_t)(two[k] >> 32);
+    const uint32_t incl = wave_scan_add(sum);
+    // in the lane with the crossing: how many of its bins, from the top, are needed
+    uint32_t above = incl - sum, bins = 0;
+#pragma unroll
+    for (int k = BPL / 2 - 1; k >= 0; --k) {
+        bins += above < need ? 1u : 0u;
+        above += (uint32_t)(two[k] >> 32);
+        bins += above < need ? 1u : 0u;
+        above += (uint32_t)two[k];
+    }
+    const uint64_t hit = __ballot(incl - sum < need && need <= incl);
+    if (hit == 0) return 0;  // uniform
+    const int seg = __ffsll((unsigned long long)hit) - 1;
+    return (uint32_t)(kAvgBins - seg * BPL) - (uint32_t)__builtin_amdgcn_readlane((int)bins, seg) + 1u;
+}
+
+// Both passes over the averages of Algorithm 1.  PASS 0: the strided max pooling (each cell computed where its windows
+// are, and written out), and per combination a histogram, whose cut the last workgroup finds.  PASS 1: the elements
+// at or above the cut, into the combination's list.  grid = (workgroups, max kernels x groups).
+//
+// A window's sum for average kernel n is its sum for n - 1 plus one cell if both windows start at the same cell, which is
+// also the order the definition sums in: a lane takes windows by their first cell and gets all average kernels' sums from
+// n_max additions.  Counting and comparing go by the sum; the average itself (the quotient ranks, two sums may share
+// one) is computed for what is collected only, a full wavefront at a time.  For that the cut is lowered by 2^-21 of its
+// value: whatever lies below has a smaller quotient than everything at or above the cut.
+//
+// Bins follow the bits of the sum upward from the sum at ctrl.edge, 1.1 - 1.6 % wide, the last one open above: the bin of
+// the K_j-th best holds few others, and any scores whose edge is near their bulk are resolved, so one pass of counting
+// does (two passes of 11 key bits from the sign down took twice as long).  With PER = kAvgWide only the largest of
+// a lane's four sums, 64 windows apart, is counted: the K_j-th best of those is at most the K_j-th best of all, the few
+// elements more that reach it are sorted out later, and a quarter of the additions to LDS, of which 16 lanes' worth
+// takes about as long as all the rest of the loop, are left.  It needs K_j to be well below a quarter of the cells.
+//
+// SMALL: average kernels of sizes 1 .. 16, each once (the paper's set): straight-line code without branches.
+// Bound: instructions and LDS round trips of few workgroups on short contexts, additions to the global counts on long ones.
+// Measured (kernel trace), 48 combinations, budget 4096, before -> after (before: every combination pooled its own
+// windows, two histogram passes): counting 29.6 + 26 -> 13.6 us on 128K tokens, 40.6 + 34.0 -> 34.2 us on 1M; collecting
+// 8.1 -> 10.7 us and 23.6 -> 20.4 us; the separate max pooling, 4.7 and 10.1 us, is gone.
+template <int PASS, int PER, bool SMALL>
+__global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, float *cells, const AvgParams ap, SelCtrl *ctrl,
+                                                             uint32_t *hist, uint32_t *done, uint64_t *lists)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ uint32_t c_comb[kAvgGroup], c_count[kAvgGroup], c_base[kAvgGroup];
+    __shared__ float c_rcp[kAvgGroup];
+    __shared__ uint32_t is_last;
+    constexpr int CHUNK = 64 * PER;            // windows a wavefront sums at a time
+    constexpr int QUEUE = CHUNK * kAvgGroup;   // SMALL, PASS 1: elements a wavefront may collect from a chunk
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int i = blockIdx.y / ap.groups, g0 = (blockIdx.y % ap.groups) * kAvgGroup;
+    const int ng = min(kAvgGroup, ap.n_avg - g0), rows = SMALL ? kAvgGroup : ng;
+    const uint32_t m = ap.m[i], len = ap.len[i];
+    const int n_top = ap.avg[g0 + ng - 1], ahead = (n_top - 1) / 2;  // the first windows start before the first cell
+    const uint32_t pitch = CHUNK + (SMALL ? kAvgGroup : n_top) - 1;
+    uint32_t *lh = (uint32_t *)smem;      // PASS 0: [kAvgGroup][kAvgBins], then a word per lane
+    uint64_t *ll = (uint64_t *)smem;      // PASS 1: [kAvgGroup][kAvgList], sum above element; SMALL: [kAvgWaves][QUEUE]
+    float *buf = (float *)(smem + avg_shared(PASS, PER, SMALL)) + (size_t)wave * (pitch + 2);
+    float *out = cells + ap.off[i];
+    const uint32_t chunks = len ? (uint32_t)(((uint64_t)len + ahead + CHUNK - 1) / CHUNK) : 0u;
+
+    // a chunk's cells from clamped addresses (so that loads need no branch), zero outside the array
+    auto stage = [&](auto size_tag, int64_t cell) {
+        constexpr int M = decltype(size_tag)::value;  // 0: any
+        const uint32_t at = cell < 0 ? 0u : (cell < (int64_t)len ? (uint32_t)cell : len - 1);
+        float v;
+        if (PASS == 1) {
+            v = out[at];
+        } else if (M != 0) {
+            const float *src = body + (size_t)at * M;
+            v = src[0];
+#pragma unroll
+            for (int u = 1; u < M; ++u) v = fmaxf(v, src[u]);
+        } else {
+            const float *src = body + (size_t)at * m;
+            v = src[0];
+            for (uint32_t u = 1; u < m; ++u) v = fmaxf(v, src[u]);
+        }
+        return cell < 0 || cell >= (int64_t)len ? 0.0f : v;
+    };
+    auto fetch = [&](uint32_t c, float(&v)[PER + 1]) {
+        const int64_t first = (int64_t)c * CHUNK - ahead;
+        auto all = [&](auto size_tag) {
+#pragma unroll
+            for (int k = 0; k <= PER; ++k) v[k] = stage(size_tag, first + lane + 64 * k);
+        };
+        if (PASS == 1 || m == 1)
+            all(std::integral_constant<int, 1>{});
+        else if (m == 2)
+            all(std::integral_constant<int, 2>{});
+        else if (m == 4)
+            all(std::integral_constant<int, 4>{});
+        else if (m == 8)
+            all(std::integral_constant<int, 8>{});
+        else
+            all(std::integral_constant<int, 0>{});
+    };
+    float cell[PER + 1];
+    if (blockIdx.x * kAvgWaves < chunks) fetch(blockIdx.x * kAvgWaves + wave, cell);
+
+    // average kernel q's numbers are lane q's, in every wavefront (SMALL: the one of size n has number n - 1)
+    uint32_t l_size, l_want;
+    float l_edge;  // the sum from which on elements matter to this pass
+    {
+        uint32_t q, at;
+        if (SMALL) {
+            q = min(lane, kAvgGroup - 1);
+            at = ap.at_of_size[q];
+            l_size = q + 1;
+        } else {
+            q = min(lane, ng - 1);
+            at = ap.at[g0 + q];
+            l_size = ap.avg[g0 + q];
+        }
+        const bool used = !SMALL || at != kNoAvg;
+        const uint32_t j = (uint32_t)(i * ap.n_avg) + (used ? at : 0u), cut = ctrl[j].cut;
+        l_want = ctrl[j].want;
+        l_edge = ctrl[j].edge * (float)l_size;
+        if (PASS == 1) l_edge = cut ? __uint_as_float(__float_as_uint(l_edge) + ((cut - 1) << kAvgBinShift)) * (1.0f - 0x1p-21f) : -INFINITY;
+        if (!used) l_edge = INFINITY;
+        if ((int)threadIdx.x < rows) {
+            c_comb[threadIdx.x] = used ? j : 0xFFFFFFFFu;
+            c_count[threadIdx.x] = 0;
+            c_rcp[threadIdx.x] = __fdiv_rn(1.0f, (float)l_size);
+        }
+    }
+    auto of = [](uint32_t x, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)x, q); };
+    auto of_f = [](float x, int q) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), q)); };
+    if (PASS == 0)
+        for (int x = threadIdx.x * 4; x < rows * kAvgBins; x += kAvgThreads * 4) *(uint4 *)&lh[x] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+
+    for (uint32_t c0 = blockIdx.x * kAvgWaves; c0 < chunks; c0 += gridDim.x * kAvgWaves) {
+        const uint32_t c = c0 + wave;  // a chunk past the last one has no elements
+        const int64_t first = (int64_t)c * CHUNK - ahead;  // first cell of the chunk's first window
+        lds_wave_sync();  // the previous chunk's reads of the buffer are done
+#pragma unroll
+        for (int k = 0; k <= PER; ++k) {
+            const uint32_t x = lane + 64 * k;
+            if (x < pitch) buf[x] = cell[k];
+            if (PASS == 0 && g0 == 0 && k < PER && first + x >= 0 && first + x < (int64_t)len) out[first + x] = cell[k];
+        }
+        if (!SMALL)
+            for (uint32_t x = lane + 64 * (PER + 1); x < pitch; x += 64) buf[x] = stage(std::integral_constant<int, 0>{}, first + x);
+        lds_wave_sync();
+        if (c0 + gridDim.x * kAvgWaves < chunks) fetch(c + gridDim.x * kAvgWaves, cell);  // in flight while this chunk is summed
+
+        float sum[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) sum[k] = 0.0f;
+        const uint32_t el0 = (uint32_t)first + lane;  // modulo 2^32: an element before the array is one far behind it
+        if (SMALL) {
+            uint32_t queued = 0;        // uniform
+            uint32_t l_mine = 0;        // lane q: this wavefront's queued elements of size q + 1
+#pragma unroll
+            for (int u = 0; u < kAvgGroup; ++u) {
+                const float edge = of_f(l_edge, u);
+                const uint32_t before = queued;
+                float best = -INFINITY;
+#pragma unroll
+                for (int k = 0; k < PER; ++k) {
+                    sum[k] = sum[k] + buf[lane + 64 * k + u];
+                    const bool in = el0 + 64u * k + u / 2 < len;
+                    // (positive floats are ordered like their bits; what is not counted goes to a word of the lane's own)
+                    auto count = [&](float x, bool hit) {
+                        const uint32_t bin = min((__float_as_uint(x) - __float_as_uint(edge)) >> kAvgBinShift, (uint32_t)kAvgBins - 1u);
+                        atomicAdd(&lh[hit ? u * kAvgBins + bin : (uint32_t)(kAvgGroup * kAvgBins + lane)], 1u);
+                    };
+                    if (PASS == 0 && PER == kAvgWide) {
+                        best = fmaxf(best, in ? sum[k] : -INFINITY);
+                        if (k == PER - 1) count(best, best >= edge);
+                    } else if (PASS == 0) {
+                        count(sum[k], in & (sum[k] >= edge));
+                    } else {
+                        const bool hit = in & (sum[k] >= edge);
+                        const uint64_t mask = __ballot(hit);
+                        const uint32_t at = queued + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                        if (hit) ll[wave * QUEUE + at] = (uint64_t)__float_as_uint(sum[k]) << 32 | (uint32_t)(u << 8 | (lane + 64 * k));
+                        queued += (uint32_t)__popcll(mask);
+                    }
+                }
+                if (PASS == 1) l_mine = lane == u ? queued - before : l_mine;
+            }
+            if (PASS == 1) {
+                // one reservation per workgroup and size, then every wavefront writes its own
+                uint32_t l_off = 0;
+                if (lane < kAvgGroup && l_mine) l_off = atomicAdd(&c_count[lane], l_mine);
+                __syncthreads();
+                if ((int)threadIdx.x < kAvgGroup && c_count[threadIdx.x]) {
+                    c_base[threadIdx.x] = atomicAdd(&ctrl[c_comb[threadIdx.x]].tie_n, c_count[threadIdx.x]);
+                    c_count[threadIdx.x] = 0;
+                }
+                __syncthreads();
+                // where this wavefront's elements of a size start in the list, less where they start in its queue
+                const uint32_t l_to = (lane < kAvgGroup ? c_base[lane] : 0u) + l_off - (wave_scan_add(l_mine) - l_mine);
+                for (uint32_t x = lane; x < ((queued + 63u) & ~63u); x += 64) {
+                    const bool valid = x < queued;
+                    const uint64_t e = ll[wave * QUEUE + (valid ? x : 0)];
+                    const uint32_t u = valid ? (uint32_t)e >> 8 : 0u, w = (uint32_t)e & 255u;
+                    const uint32_t to = (uint32_t)__shfl((int)l_to, (int)u) + x;
+                    const float avg = divide_small(__uint_as_float((uint32_t)(e >> 32)), (float)(u + 1), c_rcp[u]);
+                    if (valid) lists[ctrl[c_comb[u]].tie_off + to] = make_key(avg, (uint32_t)first + w + u / 2);
+                }
+            }
+            continue;
+        }
+
+        // any sizes: a rolled loop, its LDS reads two steps ahead
+        float now[PER], next[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            now[k] = buf[lane + 64 * k];
+            next[k] = buf[lane + 64 * k + 1];
+        }
+        int q = 0;
+        for (uint32_t u = 0; q < ng; ++u) {
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+                sum[k] = sum[k] + now[k];
+                now[k] = next[k];
+                next[k] = buf[lane + 64 * k + u + 2];
+            }
+            for (; q < ng && of(l_size, q) == u + 1; ++q) {  // average kernel q's sums are complete
+                const float edge = of_f(l_edge, q);
+#pragma unroll
+                for (int k = 0; k < PER; ++k) {
+                    const uint32_t el = el0 + 64u * k + u / 2;
+                    const bool hit = sum[k] >= edge && el < len;
+                    if (PASS == 0) {
+                        const uint32_t bin = min((__float_as_uint(sum[k]) - __float_as_uint(edge)) >> kAvgBinShift, (uint32_t)kAvgBins - 1u);
+                        if (hit) atomicAdd(&lh[q * kAvgBins + bin], 1u);
+                    } else {
+                        const uint64_t mask = __ballot(hit);
+                        if (mask == 0) continue;
+                        uint32_t at = 0;
+                        if (lane == 0) at = atomicAdd(&c_count[q], (uint32_t)__popcll(mask));
+                        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+                        if (hit && at < (uint32_t)kAvgList) ll[q * kAvgList + at] = (uint64_t)__float_as_uint(sum[k]) << 32 | el;
+                        if (__any(hit && at >= (uint32_t)kAvgList)) {  // the workgroup's list is full
+                            SelCtrl *ct = &ctrl[c_comb[q]];
+                            const uint64_t key = make_key(__fdiv_rn(sum[k], (float)(u + 1)), el);
+                            wave_append(hit && at >= (uint32_t)kAvgList, key, lists + ct->tie_off, &ct->tie_n);
+                        }
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();
+    if (PASS == 0) {
+        constexpr int kBatch = 4;
+        for (int x0 = threadIdx.x * 4; x0 < rows * kAvgBins; x0 += kAvgThreads * 4 * kBatch) {
+            uint4 v[kBatch];
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b) {
+                const int x = x0 + b * kAvgThreads * 4;
+                v[b] = x < rows * kAvgBins ? *(const uint4 *)&lh[x] : make_uint4(0, 0, 0, 0);
+            }
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b) {
+                if ((v[b].x | v[b].y | v[b].z | v[b].w) == 0) continue;
+                const int x = x0 + b * kAvgThreads * 4;
+                uint32_t *h = hist + (size_t)c_comb[x / kAvgBins] * kSelBins + x % kAvgBins;
+                if (v[b].x) atomicAdd(&h[0], v[b].x);
+                if (v[b].y) atomicAdd(&h[1], v[b].y);
+                if (v[b].z) atomicAdd(&h[2], v[b].z);
+                if (v[b].w) atomicAdd(&h[3], v[b].w);
+            }
+        }
+        if (count_in(&done[blockIdx.y], gridDim.x, &is_last)) {
+            for (int q = wave; q < rows; q += kAvgWaves) {
+                if (c_comb[q] == 0xFFFFFFFFu) continue;
+                const uint32_t cut = find_cut(hist + (size_t)c_comb[q] * kSelBins, of(l_want, q));
+                if (lane == 0) ctrl[c_comb[q]].cut = cut;
+            }
+        }
+    } else if (!SMALL) {
+        for (int q = wave; q < ng; q += kAvgWaves) {
+            const uint32_t j = c_comb[q], n = min(c_count[q], (uint32_t)kAvgList);
+            if (n == 0) continue;
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&ctrl[j].tie_n, n);
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+            uint64_t *list = lists + ctrl[j].tie_off;
+            const float fn = (float)of(l_size, q), rcp = __fdiv_rn(1.0f, fn);
+            for (uint32_t x = lane; x < n; x += 64) {
+                const uint64_t e = ll[q * kAvgList + x];
+                list[at + x] = make_key(divide_small(__uint_as_float((uint32_t)(e >> 32)), fn, rcp), (uint32_t)e);
+            }
+        }
+    }
+}
+
 // Boundary list -> candidates.  Window-max form: short lists (the normal case) are appended whole,
 // candidates below the cut are harmless, they rank last; long ones are radix-selected down first.
 // Printed form: the list is always cut to what the K_m-cell cap leaves.
@@ -745,14 +987,16 @@ __global__ __launch_bounds__(kThreads) void refine(SelCtrl *ctrl, uint64_t *cand
     uint64_t *cand_j = cand + (size_t)j * kCandCap;
     uint64_t *A = tie + ctrl[j].tie_off;
     uint64_t *B = A + ctrl[j].len;
+    const bool exact = ctrl[j].exact != 0;
     uint32_t nA = ctrl[j].tie_n;
-    uint32_t need = ctrl[j].need2;
-    uint32_t candn = ctrl[j].cand_n;
-    const uint32_t keep_small = ctrl[j].exact ? 0u : (uint32_t)kSelSmall;
+    uint32_t need = exact ? ctrl[j].want : ctrl[j].need2;
+    uint32_t candn = exact ? 0u : ctrl[j].cand_n;
+    const uint32_t keep = exact ? sort_n : (uint32_t)kSelSmall;
     const int lane = threadIdx.x & 63;
 
-    // The list shares its top 22 key bits (key64 bits 63..42).  Peel 8 more bits a pass.
-    for (int shift = 40; shift >= 0 && nA > keep_small && need < nA; shift -= 8) {
+    // A list too long to be sorted (or to join the seeds) as it is: peel 8 key bits a pass.  In the window-max form the
+    // list shares its top 22 key bits (key64 bits 63..42).
+    for (int shift = exact ? 56 : 40; shift >= 0 && nA + (exact ? candn : 0u) > keep && need < nA; shift -= 8) {
         if (threadIdx.x < 256) h[threadIdx.x] = 0;
         if (threadIdx.x < 2) cnt[threadIdx.x] = 0;
         __syncthreads();
@@ -803,23 +1047,25 @@ __global__ __launch_bounds__(kThreads) void refine(SelCtrl *ctrl, uint64_t *cand
         A = B;
         B = t;
     }
-    for (uint32_t i = threadIdx.x; i < nA; i += kThreads) cand_j[candn + i] = load_u64(&A[i]);
     const uint32_t total = candn + nA;
-    if (threadIdx.x == 0) ctrl[j].total_n = total;
-    if (!ctrl[j].exact) return;  // uniform
+    if (!exact) {  // uniform
+        for (uint32_t i = threadIdx.x; i < nA; i += kThreads) cand_j[candn + i] = load_u64(&A[i]);
+        if (threadIdx.x == 0) ctrl[j].total_n = total;
+        return;
+    }
 
-    // Printed form: hand the candidates to the allocation walk in rank order.  Bitonic sort of the
+    // Printed form: the first `want` elements in rank order, for the allocation walk.  Bitonic sort of the
     // keys (descending; padding keys of 0 sink to the end) in LDS, one barrier per stage.
     extern __shared__ __align__(16) unsigned char smem[];
     uint64_t *srt = (uint64_t *)smem;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this workgroup's stores to cand_j have reached the L2
+    uint32_t padded = 2;
+    while (padded < total) padded *= 2;  // total <= sort_n, or exactly `want` <= sort_n after the peeling
+    for (uint32_t i = threadIdx.x; i < padded; i += kThreads)
+        srt[i] = i < candn ? load_u64(&cand_j[i]) : (i < total ? load_u64(&A[i - candn]) : 0ull);
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < sort_n; i += kThreads)
-        srt[i] = i < total ? load_u64(&cand_j[i]) : 0ull;
-    __syncthreads();
-    for (uint32_t k = 2; k <= sort_n; k <<= 1) {
+    for (uint32_t k = 2; k <= padded; k <<= 1) {
         for (uint32_t d = k >> 1; d > 0; d >>= 1) {
-            for (uint32_t i = threadIdx.x; i < sort_n / 2; i += kThreads) {
+            for (uint32_t i = threadIdx.x; i < padded / 2; i += kThreads) {
                 const uint32_t lo = ((i & ~(d - 1)) << 1) | (i & (d - 1)), hi = lo + d;
                 const uint64_t a = srt[lo], b = srt[hi];
                 const bool descending = (lo & k) == 0;
@@ -833,7 +1079,7 @@ __global__ __launch_bounds__(kThreads) void refine(SelCtrl *ctrl, uint64_t *cand
     }
     // The allocation walk wants the elements in rank order; the list (uint32) takes over the storage of the keys.
     uint32_t *ranked = (uint32_t *)cand_j;
-    for (uint32_t r = threadIdx.x; r < total; r += kThreads) ranked[r] = key_token(srt[r]);
+    for (uint32_t r = threadIdx.x; r < ctrl[j].want; r += kThreads) ranked[r] = key_token(srt[r]);
 }
 
 // Last step of the allocation: the sink indices, then the nsel allocated tokens in ascending order, then -1
@@ -1464,6 +1710,26 @@ SelectLayout make_select_layout(const SelectJob &job)
 
 namespace {
 
+template <int PASS, int PER, bool SMALL>
+hipError_t raise_avg_lds()
+{
+    return hipFuncSetAttribute((const void *)pool_averages<PASS, PER, SMALL>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)avg_lds(PASS, PER, SMALL, SMALL ? kAvgGroup : ILRE_MAX_AVG_KERNEL));
+}
+
+// One chunk of windows a wavefront where that is at most two workgroups a compute unit, more of them beyond: a
+// workgroup carries the clearing and flushing of its 64 KiB of counts.
+template <int PASS, int PER, bool SMALL>
+void launch_averages(const float *scores, float *cells, const AvgParams &ap, int n_max, int64_t len_max, int n_top, SelCtrl *ctrl, uint32_t *hist,
+                     uint32_t *done, uint64_t *lists, hipStream_t s)
+{
+    const uint32_t rows = (uint32_t)(n_max * ap.groups), per_wg = kAvgWaves * 64 * PER;
+    const uint32_t want = (uint32_t)((len_max + n_top + per_wg - 1) / per_wg), most = 2 * kNumCU / rows;
+    const uint32_t gx = want < most ? want : (most > 16 ? most : 16u);
+    hipLaunchKernelGGL((pool_averages<PASS, PER, SMALL>), dim3(gx, rows), dim3(kAvgThreads), avg_lds(PASS, PER, SMALL, n_top), s, scores, cells, ap,
+                       ctrl, hist, done, lists);
+}
+
 // Dynamic LDS ceilings of the selection kernels: the same constants on every call, set once per process
 // and device-independent.
 hipError_t set_select_attributes()
@@ -1471,7 +1737,6 @@ hipError_t set_select_attributes()
     static hipError_t status = [] {
         constexpr int kWalkLds = kBitmapTokens / 8 + kRingBytes;
         static_assert(kWalkLds >= 2 * kWordSlots * (int)sizeof(uint32_t) + kRingBytes, "the word table fits where the bitmap does");
-        constexpr int kPoolLdsMax = kPoolWaves * 2 * (kSelFine + 2 * (ILRE_MAX_AVG_KERNEL > ILRE_MAX_POOL_KERNEL ? ILRE_MAX_AVG_KERNEL : ILRE_MAX_POOL_KERNEL)) * (int)sizeof(float);
         constexpr int kSortLdsMax = 16384 * (int)sizeof(uint64_t);  // >= ILRE_MAX_BUDGET + 1 keys, padded to a power of two
         constexpr int kSeedRankLds = kCandCap * (int)sizeof(uint64_t);
         hipError_t e;
@@ -1479,9 +1744,10 @@ hipError_t set_select_attributes()
                                  (const void *)allocate_walk<kWalkWordCells, false>, (const void *)allocate_walk<kWalkWordCells, true>,
                                  (const void *)allocate_walk<kWalkCells, false>, (const void *)allocate_walk<kWalkCells, true>})
             if ((e = hipFuncSetAttribute(walk, hipFuncAttributeMaxDynamicSharedMemorySize, kWalkLds)) != hipSuccess) return e;
-        if ((e = hipFuncSetAttribute((const void *)pool_hist<1>, hipFuncAttributeMaxDynamicSharedMemorySize, kPoolLdsMax)) != hipSuccess) return e;
-        if ((e = hipFuncSetAttribute((const void *)pool_hist<2>, hipFuncAttributeMaxDynamicSharedMemorySize, kPoolLdsMax)) != hipSuccess) return e;
-        if ((e = hipFuncSetAttribute((const void *)collect, hipFuncAttributeMaxDynamicSharedMemorySize, kPoolLdsMax)) != hipSuccess) return e;
+        if ((e = raise_avg_lds<0, kAvgWide, true>()) != hipSuccess || (e = raise_avg_lds<0, kAvgNarrow, true>()) != hipSuccess ||
+            (e = raise_avg_lds<0, kAvgNarrow, false>()) != hipSuccess || (e = raise_avg_lds<1, kAvgNarrow, true>()) != hipSuccess ||
+            (e = raise_avg_lds<1, kAvgNarrow, false>()) != hipSuccess)
+            return e;
         if ((e = hipFuncSetAttribute((const void *)refine, hipFuncAttributeMaxDynamicSharedMemorySize, kSortLdsMax)) != hipSuccess) return e;
         if ((e = hipFuncSetAttribute((const void *)seed_rank, hipFuncAttributeMaxDynamicSharedMemorySize, kSeedRankLds)) != hipSuccess) return e;
         return hipSuccess;
@@ -1495,12 +1761,6 @@ uint32_t pool_blocks(uint32_t entries, uint32_t cap)
     return want < cap ? (want ? want : 1u) : cap;
 }
 uint32_t clamp_u32(uint32_t x, uint32_t lo, uint32_t hi) { return x < lo ? lo : (x > hi ? hi : x); }
-
-// Workgroups per combination in the pooling passes; beyond the cap the wavefronts loop over the entries.
-// A histogram workgroup carries fixed work (clearing and flushing 2048 bins, one atomic per hot bin on a
-// handful of addresses, about 13 ns each and serialised, the completion counter), so those passes aim at
-// about one resident round of workgroups over all combinations.
-constexpr uint32_t kHistGrid = 2560, kCollectGrid = 8192;
 
 // The walk and its ascending output: straight from the bitmap where it fits the LDS, else through the list of
 // allocated tokens, which emit_sorted puts in order.
@@ -1543,7 +1803,6 @@ hipError_t launch_select_window(const float *scores, const SelectJob &job, int32
     // the seed combination: window 1 on the scores, the n_out best wanted
     SelParams prm{};
     prm.n = 1;
-    prm.op = (uint32_t)kSelWindowMax;
     prm.exact = 0;
     prm.share[0] = (uint32_t)n_out;
     prm.want[0] = (uint32_t)n_out;
@@ -1565,7 +1824,6 @@ hipError_t launch_select_window(const float *scores, const SelectJob &job, int32
     walk.dom = dom;
 
     const uint32_t nfine = (uint32_t)((L + kSelFine - 1) / kSelFine);
-    const size_t pool_lds = (size_t)kPoolWaves * 2 * (size_t)kSelFine * sizeof(float);
     Entries ent{nullptr, nullptr};
     uint32_t entries = nfine;
     const bool pruned = (int64_t)nfine >= 4 * (int64_t)n_out && nfine >= 16384;
@@ -1592,8 +1850,8 @@ hipError_t launch_select_window(const float *scores, const SelectJob &job, int32
         hipLaunchKernelGGL(chunk_max, dim3(2048), dim3(kPoolThreads), 0, s, scores, L, nfine, cm);
         hipLaunchKernelGGL(sel_init, dim3(1), dim3(kThreads), 0, s, pp, phist, pctrl, pdone);
         const uint32_t pblocks = pool_blocks((nfine2 + kRawBatch - 1) / kRawBatch, 1024);
-        hipLaunchKernelGGL(pool_hist<1>, dim3(pblocks, 1), dim3(kPoolThreads), pool_lds, s, cm, 1, pctrl, phist, pdone, all);
-        hipLaunchKernelGGL(pool_hist<2>, dim3(pblocks, 1), dim3(kPoolThreads), pool_lds, s, cm, 1, pctrl, phist, pdone, all);
+        hipLaunchKernelGGL(pool_hist<1>, dim3(pblocks), dim3(kPoolThreads), 0, s, cm, pctrl, phist, pdone, all);
+        hipLaunchKernelGGL(pool_hist<2>, dim3(pblocks), dim3(kPoolThreads), 0, s, cm, pctrl, phist, pdone, all);
         hipLaunchKernelGGL(mark_active, dim3((nfine + kPoolThreads * kMarkPerThread - 1) / (kPoolThreads * kMarkPerThread)), dim3(kPoolThreads), 0, s, cm,
                            nfine, 0, pctrl, active);
         ent = Entries{active, &pctrl->cand_n};
@@ -1615,10 +1873,10 @@ hipError_t launch_select_window(const float *scores, const SelectJob &job, int32
             hipLaunchKernelGGL(reduce_hist1<0>, dim3(rblocks), dim3(kPoolThreads), 0, s, fused->partial, fused->nunits, fused->L,
                                job.sink, fused->scores, ctrl, hist, done);
     } else {
-        hipLaunchKernelGGL(pool_hist<1>, dim3(hblocks, 1), dim3(kPoolThreads), pool_lds, s, scores, 1, ctrl, hist, done, ent);
+        hipLaunchKernelGGL(pool_hist<1>, dim3(hblocks), dim3(kPoolThreads), 0, s, scores, ctrl, hist, done, ent);
     }
-    hipLaunchKernelGGL(pool_hist<2>, dim3(hblocks, 1), dim3(kPoolThreads), pool_lds, s, scores, 1, ctrl, hist, done, ent);
-    hipLaunchKernelGGL(collect, dim3(cblocks, 1), dim3(kPoolThreads), pool_lds, s, scores, ctrl, cand, tie, ent);
+    hipLaunchKernelGGL(pool_hist<2>, dim3(hblocks), dim3(kPoolThreads), 0, s, scores, ctrl, hist, done, ent);
+    hipLaunchKernelGGL(collect, dim3(cblocks), dim3(kPoolThreads), 0, s, scores, ctrl, cand, tie, ent);
     hipLaunchKernelGGL(refine, dim3(1), dim3(kThreads), 0, s, ctrl, cand, tie, 0u);
     // at most n_out + kSelSmall <= kCandCap seeds
     const uint32_t max_seeds = (uint32_t)n_out + (uint32_t)kSelSmall;
@@ -1633,6 +1891,7 @@ hipError_t launch_select_window(const float *scores, const SelectJob &job, int32
 hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out_idx, int32_t *out_count,
                          void *workspace, const SelectLayout &lay, hipStream_t s, const FusedScores *fused)
 {
+    const float mean_score = fused ? fused->mean : 0.f;
     const int64_t L = job.L;
     const int n = job.combos();
     const int budget = job.budget;
@@ -1662,14 +1921,13 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
 
     // The algorithm as printed.  B_c: floor(B / n), the first B mod n combinations one more; K_m = B / m + 1 cells.
     SelParams prm{};
-    CellParams cp{};
+    AvgParams ap{};
     prm.n = n;
-    prm.op = (uint32_t)job.mode;
     prm.exact = 1u;
     const int base = budget / n, rem = budget % n;
     int64_t before = 0, tie_off = 0, len_max = 0;
-    int halo_max = 0;
     uint64_t cell_off = 0;
+    bool coarse = true;  // windows can be counted kAvgWide at a time
     for (int j = 0; j < n; ++j) {
         const int share = base + (j < rem ? 1 : 0);
         int64_t len;
@@ -1680,11 +1938,11 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
         prm.cell[j] = (uint32_t)cell;
         prm.tie_off[j] = (uint64_t)tie_off;
         tie_off += 2 * len;
-        const int i = j / job.n_avg, na = job.avg_kernels[j % job.n_avg];
         if (j % job.n_avg == 0) {
-            cp.m[i] = (uint32_t)cell;
-            cp.len[i] = (uint32_t)len;
-            cp.off[i] = cell_off;
+            const int i = j / job.n_avg;
+            ap.m[i] = (uint32_t)cell;
+            ap.len[i] = (uint32_t)len;
+            ap.off[i] = cell_off;
             cell_off += (uint64_t)len;
         }
         // K_m = B / m + 1 cells are candidates; of those the walk can only reach the first
@@ -1694,30 +1952,49 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
         const int64_t reach = (before + share + cell - 1) / cell;
         if (reach < km) km = reach;
         prm.want[j] = (uint32_t)(km < len ? km : len);
-        prm.before[j] = (uint32_t)((na - 1) / 2);
-        prm.after[j] = (uint32_t)(na / 2);
-        prm.src_off[j] = cp.off[i];
         before += share;
-        if ((int)(prm.before[j] + prm.after[j]) > halo_max) halo_max = (int)(prm.before[j] + prm.after[j]);
         if (len > len_max) len_max = len;
+        // The bins start at half the mean score, or well below it where a large part of the cells is wanted.
+        const bool deep = 4 * (int64_t)prm.want[j] > len;
+        coarse = coarse && 2 * kAvgWide * (int64_t)prm.want[j] <= len;
+        if (deep) prm.deep |= 1ull << j;
+        prm.edge[j] = deep ? mean_score / 64 : mean_score / 2;
     }
-    cp.n = job.n_max;
-    uint32_t sort_n = 2;  // candidates are sorted in LDS, padded to a power of two
+    if (!(mean_score > 0.f)) {
+        prm.sample = scores;
+        prm.sample_n = L;
+    }
+    ap.n_avg = job.n_avg;
+    ap.groups = (job.n_avg + kAvgGroup - 1) / kAvgGroup;
+    int order[ILRE_MAX_POOL_KERNELS];
+    for (int k = 0; k < job.n_avg; ++k) order[k] = k;
+    std::stable_sort(order, order + job.n_avg, [&](int x, int y) { return job.avg_kernels[x] < job.avg_kernels[y]; });
+    for (int k = 0; k < job.n_avg; ++k) {
+        ap.at[k] = (uint16_t)order[k];
+        ap.avg[k] = (uint16_t)job.avg_kernels[order[k]];
+    }
+    const int n_top = ap.avg[job.n_avg - 1];
+    bool small = n_top <= kAvgGroup;  // every size once, 16 at most
+    for (int k = 0; k < kAvgGroup; ++k) ap.at_of_size[k] = kNoAvg;
+    for (int k = 0; k < job.n_avg && small; ++k) {
+        uint16_t &at = ap.at_of_size[ap.avg[k] - 1];
+        small = at == kNoAvg;
+        at = ap.at[k];
+    }
+    uint32_t sort_n = kSortSmall;  // elements are sorted in LDS, up to a power of two of them
     for (int j = 0; j < n; ++j)
         while (sort_n < prm.want[j]) sort_n *= 2;
-    const uint32_t nfine = (uint32_t)((len_max + kSelFine - 1) / kSelFine);
-    const size_t pool_lds = (size_t)kPoolWaves * 2 * (size_t)(kSelFine + halo_max) * sizeof(float);
-    const Entries ent{nullptr, nullptr};
-    uint32_t cb = (uint32_t)((len_max + kPoolThreads - 1) / kPoolThreads);
-    if (cb > 2048u) cb = 2048u;
-    if (cb) hipLaunchKernelGGL(cell_max, dim3(cb, job.n_max), dim3(kPoolThreads), 0, s, scores, cp, cells);
-    const uint32_t hcap = clamp_u32(kHistGrid / (uint32_t)n, 32u, 256u), ccap = clamp_u32(kCollectGrid / (uint32_t)n, 64u, 1024u);
-    const uint32_t hblocks = pool_blocks(nfine, hcap), cblocks = pool_blocks(nfine, ccap);
-
     hipLaunchKernelGGL(sel_init, dim3(n), dim3(kThreads), 0, s, prm, hist, ctrl, done);
-    hipLaunchKernelGGL(pool_hist<1>, dim3(hblocks, n), dim3(kPoolThreads), pool_lds, s, cells, n, ctrl, hist, done, ent);
-    hipLaunchKernelGGL(pool_hist<2>, dim3(hblocks, n), dim3(kPoolThreads), pool_lds, s, cells, n, ctrl, hist, done, ent);
-    hipLaunchKernelGGL(collect, dim3(cblocks, n), dim3(kPoolThreads), pool_lds, s, cells, ctrl, cand, tie, ent);
+    if (small && coarse)
+        launch_averages<0, kAvgWide, true>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
+    else if (small)
+        launch_averages<0, kAvgNarrow, true>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
+    else
+        launch_averages<0, kAvgNarrow, false>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
+    if (small)
+        launch_averages<1, kAvgNarrow, true>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
+    else
+        launch_averages<1, kAvgNarrow, false>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
     hipLaunchKernelGGL(refine, dim3(n), dim3(kThreads), (size_t)sort_n * sizeof(uint64_t), s, ctrl, cand, tie, sort_n);
     walk.n = n;
     bool word_cells = true;  // cells lie inside words of the set: sizes 1, 2, 4, 8, 16, 32

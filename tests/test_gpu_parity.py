@@ -570,3 +570,36 @@ def test_walk_over_bitmap_and_word_table(L, sink, budget, windows, mk, ak):
     n = int(count.item())
     got_p = got_p.cpu().numpy()
     assert got_p[:n].tolist() == oracle.allocate_max_avg(s, mk, ak, budget, sink=sink).tolist() and (got_p[n:] == -1).all()
+
+
+AVERAGE_CASES = [
+    # L, budget, max sizes, average sizes, kind: chunks of 128 / 256 windows and their remainders, the straight-line code for
+    # sizes 1..16 and the loop for others (over 16, repeated), shares that want little, much or all of the cells
+    (256, 20, (2,), (1, 16), "random"), (258, 20, (2,), (2, 15), "random"), (2047, 40, (8,), (3, 16, 7), "needles"),
+    (2056, 250, (8, 1), (1, 2), "random"), (4096, 60, (2, 16), (16,), "random"), (5000, 1200, (3,), (1, 5), "random"),
+    (5000, 1240, (1,), (16, 1), "random"), (20000, 100, (2, 4), (17, 1), "needles"), (20000, 100, (2, 4), (5, 5, 3), "needles"),
+    (70000, 300, (1,), (64, 1, 2), "needles"), (70000, 8000, (4, 2), tuple(range(1, 17)), "random"), (30000, 200, (2,), (1, 2, 3), "equal"),
+    (30000, 200, (2,), (17, 18), "equal"), (9000, 100, (1, 2), (3, 7), "tiny"), (9000, 100, (1, 2), (3, 7, 16), "negative"),
+    (9000, 100, (2, 3), (1, 6), "huge_range"),
+]
+
+
+@pytest.mark.parametrize("L,budget,mk,ak,kind", AVERAGE_CASES, ids=[f"L{c[0]}_{c[4]}_{len(c[3])}x{c[3][0]}" for c in AVERAGE_CASES])
+def test_averages_at_the_edges_of_their_chunks_and_bins(L, budget, mk, ak, kind):
+    _announce(f"averages L={L} budget={budget} max={mk} avg={ak} {kind}")
+    rng = np.random.default_rng(L + len(ak))
+    if kind == "tiny":            # quotients whose remainders underflow, denormals among them
+        s = (rng.random(L) * 2.0 ** -120).astype(np.float32)
+        s[::7] = np.float32(2.0 ** -140)
+    elif kind == "negative":
+        s = (-1.0 - rng.random(L)).astype(np.float32)
+    elif kind == "huge_range":    # far more than the bins span on either side
+        s = np.exp2(rng.uniform(-100, 100, size=L)).astype(np.float32)
+    else:
+        s = _scores_for(kind, L, rng)
+    want = oracle.allocate_max_avg(s, mk, ak, budget, sink=0)
+    got, count = il.ilre_select_max_avg(torch.from_numpy(s).cuda(), budget, mk, ak, 0)
+    torch.cuda.synchronize()
+    n = int(count.item())
+    got = got.cpu().numpy()
+    assert got[:n].tolist() == want.tolist() and (got[n:] == -1).all()
