@@ -758,11 +758,15 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv)
         p.waves = 4;
         p.nb = 1;
     } else {
-        p.nb = 2;
-        // 8 waves (512 rows) unless 4 waves (256 rows) leave fewer padded rows
+        // 8 waves (512 rows) unless 4 waves (256 rows) leave fewer padded rows.  Up to 128 rows take one 32-row block a
+        // wavefront: half the matrix work of a mostly padded 256, and what is left is the K stream (100003 tokens, 4 kv
+        // heads, 119 rows each: 31.0 -> 22.0 us a pass, 4.7 TB/s).  More rows do not: a K fragment then feeds one MFMA
+        // instead of two, about 1.2 times as much per row (50001 tokens, 8 kv heads, 384 rows each: three blocks of
+        // 128 rows 52.5 + 53.7 us and 16 more score vectors to add up, one padded block of 512 60.1 + 55.0 us).
         const int64_t pad8 = ((p.rows_per_group + 511) / 512) * 512;
         const int64_t pad4 = ((p.rows_per_group + 255) / 256) * 256;
         p.waves = pad4 < pad8 ? 4 : 8;
+        p.nb = p.rows_per_group <= 128 ? 1 : 2;
     }
     p.tile_tokens = dtype == ILRE_F32 ? Traits<ILRE_F32>::tile_tokens(p.waves) : Traits<ILRE_BF16>::tile_tokens(p.waves);
     p.rows_per_wg = p.waves * p.nb * 32;
@@ -800,6 +804,8 @@ hipError_t launch_row_stats(const ScorePlan &p, const ScoreArgs &a, float *row_m
     hipError_t e;
     if (p.dtype == ILRE_F32)
         e = launch_score(score_kernel<ILRE_F32, 1, 4, 0, 0>, p.grid, 256, lds, a, s);
+    else if (p.nb == 1)
+        e = launch_score(score_kernel<ILRE_BF16, 1, 4, 0, 0>, p.grid, 256, lds, a, s);
     else if (p.waves == 4)
         e = launch_score(score_kernel<ILRE_BF16, 2, 4, 0, 0>, p.grid, 256, lds, a, s);
     else
@@ -839,6 +845,9 @@ hipError_t launch_col_scores(const ScorePlan &p, const ScoreArgs &a, int score_m
     if (p.dtype == ILRE_F32)
         e = mx ? launch_score(score_kernel<ILRE_F32, 1, 4, 1, 1>, p.grid, 256, lds, a, s)
                : launch_score(score_kernel<ILRE_F32, 1, 4, 1, 0>, p.grid, 256, lds, a, s);
+    else if (p.nb == 1)
+        e = mx ? launch_score(score_kernel<ILRE_BF16, 1, 4, 1, 1>, p.grid, 256, lds, a, s)
+               : launch_score(score_kernel<ILRE_BF16, 1, 4, 1, 0>, p.grid, 256, lds, a, s);
     else if (p.waves == 4)
         e = mx ? launch_score(score_kernel<ILRE_BF16, 2, 4, 1, 1>, p.grid, 256, lds, a, s)
                : launch_score(score_kernel<ILRE_BF16, 2, 4, 1, 0>, p.grid, 256, lds, a, s);

@@ -74,6 +74,23 @@ def test_staged_scoring(name, L, Lq, Hq, Hkv, dtype, cs):
     assert bad == 0, f"max mode: {bad} scores out of tolerance, worst {worst:.2f}x"
 
 
+@pytest.mark.parametrize("Lq,Hq,Hkv,L", [(1, 2, 2, 64), (1, 2, 2, 40001), (17, 28, 4, 9000), (32, 4, 1, 64 * 515), (32, 8, 2, 65), (43, 3, 1, 9000)],
+                         ids=["1_row", "1_row_many_splits", "119_rows", "128_rows", "128_rows_ragged", "129_rows"])
+def test_scoring_narrow_query_block(Lq, Hq, Hkv, L):
+    """Up to 128 query rows a kv head go one 32-row block a wavefront, more go two: both sides of the line, tiles of 64
+    tokens, one and several of them a split.  Tolerance as everywhere: what fp32 sums of bf16 products allow."""
+    _announce(f"narrow query block Lq={Lq} Hq={Hq} Hkv={Hkv} L={L}")
+    inp = inputs.custom(L=L, Lq=Lq, Hq=Hq, Hkv=Hkv, d=128, dtype="bf16", n_spans=2 if L > 200 else 0, span_len=(8, 24),
+                        channel_scale=True, seed=Lq + L)
+    q, k = to_device(inp.q), to_device(inp.k)
+    for gpu_mode, mode in ((il.ILRE_SCORE_SUM, oracle.MODE_SUM), (il.ILRE_SCORE_MAX, oracle.MODE_MAX)):
+        want, _, _ = oracle.scores(inp.q, inp.k, mode=mode)
+        _, got = il.ilre_recall(q, k, 16, (3,), score_mode=gpu_mode)
+        torch.cuda.synchronize()
+        bad, worst = score_errors(got.cpu().numpy(), want)
+        assert bad == 0, f"{bad} scores out of tolerance, worst {worst:.2f}x"
+
+
 @pytest.mark.parametrize("seed", range(3))
 def test_scoring_randomised_shapes(seed):
     """Random shapes around the kernels' block sizes (32-row query blocks, 64/128-token tiles, 4- and 8-wave
