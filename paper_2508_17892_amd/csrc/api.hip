@@ -410,7 +410,8 @@ namespace {
 // Eq. 4 and Eq. 5 (the part the two forms of the whole path share).  The scores are left as per-unit partial
 // vectors, described by `fused`, for the selection to reduce into out_scores on its way.
 int run_scoring(const void *q, const void *k_cache, int64_t L, int32_t Lq, int32_t Hq, int32_t Hkv, int32_t d,
-                float *out_scores, const ilre_opts *opts, const ilre::ScorePlan &p, const Layout &lay, ilre::FusedScores &fused)
+                float *out_scores, const ilre_opts *opts, const ilre::ScorePlan &p, const Layout &lay, const ilre::ClearWords &clear,
+                ilre::FusedScores &fused)
 {
     int rc;
     ilre::ScoreArgs a{};
@@ -428,7 +429,7 @@ int run_scoring(const void *q, const void *k_cache, int64_t L, int32_t Lq, int32
         a.wg_time = (uint32_t *)(ws + lay.wg_time);
         a.split_table = (int32_t *)(ws + lay.split_table);
     }
-    hipError_t e = ilre::launch_row_stats(p, a, row_max, row_sumexp, s, true);
+    hipError_t e = ilre::launch_row_stats(p, a, row_max, row_sumexp, s, true, clear);
     if (e != hipSuccess) return hip_fail(e, "row-statistics launch");
     a.row_max = row_max;
     a.row_sumexp = row_sumexp;
@@ -528,11 +529,12 @@ int ilre_recall(const void *q, const void *k_cache, int64_t L, int32_t Lq, int32
     const Layout lay = make_layout(p, L, (int64_t)Hq * Lq, window_job(L, 0, budget, pool_kernels, opts->n_pool_kernels));
     if ((rc = check_workspace(opts, lay.total))) return rc;
     ilre::FusedScores fused{};
-    if ((rc = run_scoring(q, k_cache, L, Lq, Hq, Hkv, d, out_scores, opts, p, lay, fused))) return rc;
     unsigned char *ws = (unsigned char *)opts->workspace;
     const ilre::SelectJob job = window_job(L, opts->sink, budget, pool_kernels, opts->n_pool_kernels);
-    const hipError_t e = ilre::launch_select(out_scores + opts->sink, job, out_idx, nullptr, ws + lay.select,
-                                             ilre::make_select_layout(job), (hipStream_t)opts->stream, &fused);
+    const ilre::SelectLayout sel = ilre::make_select_layout(job);
+    const ilre::ClearWords clear = ilre::select_clear_words(job, sel, ws + lay.select);
+    if ((rc = run_scoring(q, k_cache, L, Lq, Hq, Hkv, d, out_scores, opts, p, lay, clear, fused))) return rc;
+    const hipError_t e = ilre::launch_select(out_scores + opts->sink, job, out_idx, nullptr, ws + lay.select, sel, (hipStream_t)opts->stream, &fused);
     if (e != hipSuccess) return hip_fail(e, "selection launch");
     return ILRE_OK;
 }
@@ -552,7 +554,7 @@ int ilre_recall_max_avg(const void *q, const void *k_cache, int64_t L, int32_t L
     const Layout lay = make_layout(p, L, (int64_t)Hq * Lq, job);
     if ((rc = check_workspace(opts, lay.total))) return rc;
     ilre::FusedScores fused{};
-    if ((rc = run_scoring(q, k_cache, L, Lq, Hq, Hkv, d, out_scores, opts, p, lay, fused))) return rc;
+    if ((rc = run_scoring(q, k_cache, L, Lq, Hq, Hkv, d, out_scores, opts, p, lay, ilre::ClearWords{}, fused))) return rc;
     unsigned char *ws = (unsigned char *)opts->workspace;
     const hipError_t e = ilre::launch_select(out_scores + sink, job, out_idx, out_count, ws + lay.select, lay.sel,
                                              (hipStream_t)opts->stream, &fused);

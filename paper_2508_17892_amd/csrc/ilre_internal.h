@@ -70,10 +70,16 @@ struct ScoreArgs {
 
 ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv);
 
+// Words a launch sets to zero on the side, for a kernel behind it.
+struct ClearWords {
+    uint32_t *at;  // 16-byte aligned (null: nothing to clear)
+    uint32_t n;    // a multiple of 4
+};
+
 // offsets = true also fills a.row_off, the table of pass 2's per-row exponent offsets, for a launch_col_scores
 // with have_offsets = true behind it (otherwise launch_col_scores derives the table from row_max / row_sumexp).
 hipError_t launch_row_stats(const ScorePlan &p, const ScoreArgs &a, float *row_max, float *row_sumexp,
-                            hipStream_t s, bool offsets = false);
+                            hipStream_t s, bool offsets = false, const ClearWords &clear = ClearWords{});
 // reduce = false leaves the per-unit partial score vectors in a.partial for launch_reduce_units (or for the
 // selection's first pass, which can do the reduction on its way).
 hipError_t launch_col_scores(const ScorePlan &p, const ScoreArgs &a, int score_mode, float *out_scores,
@@ -83,8 +89,9 @@ hipError_t launch_reduce_units(const float *partial, int nunits, int64_t L, int 
 // ---------------------------------------------------------------- selection (Algorithm 1)
 
 constexpr int kSelFine = 256;       // elements a wavefront pools at a time ("fine chunk")
-constexpr int kSelBins = 2048;      // histogram bins per level: 11 key bits
-constexpr int kSelSmall = 2048;     // boundary lists up to this long join the candidates unrefined
+constexpr int kSelBins = 2048;      // printed form: words a combination's row of the histogram may take
+constexpr int kSeedBins = 2048;     // window-max form: histogram bins
+constexpr int kSelSmall = 2048;     // seeds beyond the wanted ones that are not worth sorting out
 constexpr int kCandCap = 10240;     // candidate capacity in tokens (>= ILRE_MAX_BUDGET + kSelSmall)
 
 // Two forms of Algorithm 1 share the selection kernels.  A "combination" j ranks the elements of a
@@ -107,10 +114,32 @@ struct SelectJob {
     int combos() const { return n_max * n_avg; }
 };
 
+// Histogram bins of the window-max form: monotone in the key (ordered_bits of a score), fine where the cut is expected,
+// coarse on either side.  Bin 0 is what lies below k0 and is not counted.
+struct KeyBins {
+    uint32_t k0, k1, k2;  // keys where the three ranges start
+    uint32_t s0, s1, s2;  // keys a bin spans, as a shift
+    uint32_t pad[2];
+};
+
+// Device state of one seed search (window-max form); all zero when its first pass starts.
+struct SeedState {
+    KeyBins bins;         // left by seed_init where the scores' scale is not known to the host
+    uint32_t cut;         // bin that holds the K-th largest key
+    uint32_t need;        // of that bin's keys, how many are among the K largest
+    uint64_t lists_n;     // keys above the cut bin, collected in `cand` (low half), keys in it, collected in `tie` (high half)
+    uint32_t refined;     // not 0: the seeds are cand[0 .. refined), else both lists
+    uint32_t active_n;    // pre-pass: fine chunks left
+    uint32_t done[2];     // workgroups finished: counting, collecting
+    uint32_t pad[48];
+    uint32_t hist[kSeedBins];
+};
+
 struct SelectLayout {
-    size_t hist;      // uint32 [2][n][kSelBins]  (level 1, level 2), then [2][kSelBins] of the pre-pass
-    size_t ctrl;      // SelCtrl [n + 1]  (the last one belongs to the pre-pass)
-    size_t done;      // uint32 [2][n], then [2] of the pre-pass: workgroups finished per level and combination
+    size_t state;     // kSelWindowMax: SeedState [2]  (the seeds, the pruning pre-pass)
+    size_t hist;      // kSelMaxAvg: uint32 [n][kSelBins]
+    size_t ctrl;      // kSelMaxAvg: SelCtrl [n]
+    size_t done;      // kSelMaxAvg: uint32 [n]: workgroups finished per max kernel and group of average kernels
     size_t cmax;      // float [ceil(L / kSelFine)]: fine-chunk maxima (pruning pre-pass)
     size_t active;    // uint32 [ceil(L / kSelFine)]: fine chunks left after pruning
     size_t cells;     // float: the max-pooled cell arrays, one per max kernel (kSelMaxAvg)
@@ -121,25 +150,14 @@ struct SelectLayout {
     size_t total;
 };
 
+// Printed form: one combination's state.
 struct SelCtrl {
     uint32_t want;        // K_j: ranked elements that are candidates
-    uint32_t share;       // B_j
-    uint32_t bin1;        // level-1 bin (key bits 31..21) holding the K_j-th largest key
-    uint32_t above1;      // keys in bins above it
-    uint32_t need1;       // still needed from inside it
-    uint32_t bin2;        // level-2 bin (key bits 20..10) inside bin1
-    uint32_t above2;      // keys of bin1 in level-2 bins above bin2
-    uint32_t need2;       // still needed from inside (bin1, bin2)
-    uint32_t cand_n;      // filled length of cand[j] after collect
-    uint32_t tie_n;       // filled length of the first boundary list
-    uint32_t total_n;     // candidates (elements) after refine
+    uint32_t tie_n;       // elements collected
     uint32_t len;         // elements in the source array
-    uint32_t cell;        // tokens an element stands for (m; 1 in the window-max form)
-    uint64_t tie_off;     // boundary lists: uint64 words from the base of the tie region
-    uint32_t exact;       // 1: refine cuts the candidates to exactly `want`
-    float edge;           // printed form: averages below it are not counted
-    uint32_t cut;         // printed form: 1 + the lowest bin of which elements are collected (0: all elements)
-    uint32_t pad;
+    float edge;           // averages below it are not counted
+    uint32_t cut;         // 1 + the lowest bin of which elements are collected (0: all elements)
+    uint64_t tie_off;     // lists of elements: uint64 words from the base of the tie region
 };
 
 // Workspace carving for a job (only mode, L, counts and the max kernels are read).
@@ -155,6 +173,10 @@ struct FusedScores {
     int64_t L;
     float mean;            // the scores' scale: their mean (sum over the rows) or a lower bound of it (max)
 };
+
+// The words of a workspace's selection region (at `base`) that have to be zero before a window-max selection with
+// FusedScores starts.
+ClearWords select_clear_words(const SelectJob &job, const SelectLayout &lay, void *base);
 
 // `scores` points at the body (the first token after the sink part).
 hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out_idx, int32_t *out_count,

@@ -631,11 +631,16 @@ struct OffsetTable {
 };
 __global__ __launch_bounds__(256) void combine_row_stats(const float *part_m, const float *part_z, int nsplit, int64_t nrows,
                                                          float *row_max, float *row_sumexp, const OffsetTable tab,
-                                                         const BalanceArgs bal)
+                                                         const BalanceArgs bal, const ClearWords clear, unsigned stat_blocks)
 {
     constexpr int kBlock = 4;
-    if (bal.wg_time && blockIdx.x == gridDim.x - 1) {  // the launch's last workgroup is there for the table alone
-        make_split_table(bal);
+    if (blockIdx.x >= stat_blocks) {
+        if (bal.wg_time && blockIdx.x == stat_blocks) {  // one workgroup is there for the table alone
+            make_split_table(bal);
+            return;
+        }
+        // the last one clears what the selection counts in (a launch of its own took 4.7 us)
+        for (uint32_t i = threadIdx.x * 4; i < clear.n; i += blockDim.x * 4) *(uint4 *)&clear.at[i] = make_uint4(0, 0, 0, 0);
         return;
     }
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -795,7 +800,8 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv)
     return p;
 }
 
-hipError_t launch_row_stats(const ScorePlan &p, const ScoreArgs &a, float *row_max, float *row_sumexp, hipStream_t s, bool offsets)
+hipError_t launch_row_stats(const ScorePlan &p, const ScoreArgs &a, float *row_max, float *row_sumexp, hipStream_t s, bool offsets,
+                            const ClearWords &clear)
 {
     // One launch: a workgroup whose sums against frozen references leave the safe range walks its split a second
     // time in the always-safe form before it writes its partials.
@@ -816,8 +822,9 @@ hipError_t launch_row_stats(const ScorePlan &p, const ScoreArgs &a, float *row_m
     const int64_t groups = nrows + (offsets ? (int64_t)(tab.group_entries - tab.rows_per_group) * a.Hkv : 0);
     const bool balance = a.wg_time != nullptr && a.split_table != nullptr;
     const BalanceArgs bal{balance ? a.wg_time : nullptr, a.split_table, a.table_tag, p.grid, p.nqb, p.nsplit, a.Hkv, p.ntiles};
-    hipLaunchKernelGGL(combine_row_stats, dim3((unsigned)((groups * kCombineLanes + 255) / 256) + (balance ? 1u : 0u)), dim3(256), 0, s,
-                       a.part_m, a.part_z, a.nsplit, nrows, row_max, row_sumexp, tab, bal);
+    const unsigned stat_blocks = (unsigned)((groups * kCombineLanes + 255) / 256);
+    hipLaunchKernelGGL(combine_row_stats, dim3(stat_blocks + (balance ? 1u : 0u) + (clear.at ? 1u : 0u)), dim3(256), 0, s, a.part_m, a.part_z,
+                       a.nsplit, nrows, row_max, row_sumexp, tab, bal, clear, stat_blocks);
     return hipGetLastError();
 }
 

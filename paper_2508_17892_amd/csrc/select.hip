@@ -28,15 +28,15 @@
 // so every candidate token has a seed inside its window, and a seed that B' others outrank owns no token
 // of any candidate prefix.  Hence:
 //
-//   sel_init     as above, for ONE combination
-//   pool_hist<1> wavefronts share out the 256-token "fine chunks" of the scores: a 2048-bin LDS histogram of
-//                the top 11 bits of the scores' order-preserving keys, added to the global one.  The last workgroup
-//                to finish locates the bin holding the B'-th largest key
-//   pool_hist<2> the next 11 bits of the keys inside that bin: the 22-bit prefix of the B'-th largest key
-//   collect      keys above the prefix go to the seed list, keys that share it to a boundary list (a few dozen on
-//                real scores; everything on all-equal scores)
-//   refine       the boundary list joins the seeds, radix-selected down first while it is longer than kSelSmall
-//                (extra seeds rank last and are harmless)
+//   seed_init    (ilre_select alone) clears the state and places the histogram's bins by a sample of the scores; in the
+//                whole path the kernel between the scoring passes clears it and the bins follow the scores' mean
+//   count_scores a 2048-bin histogram of the scores' order-preserving keys, in LDS, added to the global one; the last
+//                workgroup to finish finds the bin that holds the B'-th largest (reduce_count: the same on the scores'
+//                way from per-unit partial vectors)
+//   collect      keys above the cut bin go to the seed list, keys in it to a boundary list (a few hundred on real
+//                scores; everything on all-equal scores).  Boundary keys are seeds too (extra seeds rank last and are
+//                harmless) unless that makes over kSelSmall too many: the last workgroup to finish then radix-selects
+//                them down first
 //   seed_rank    per seed: its rank among the seeds (counting: a wavefront's lanes share out the staged keys
 //                and compare them with its four seeds) and the nearest seed that outranks it on either side
 //                (a scan of the raw scores around it, 16 lanes a seed: whatever outranks a seed is a seed)
@@ -46,10 +46,9 @@
 //                intervals as they are, no list is written
 //
 // Long contexts in the window-max form (L >= 4M and >= 1024 tokens per budgeted token) start with a
-// pruning pre-pass: the maximum of every fine chunk (one streaming read of the scores), the 22-bit
-// prefix of the budget-th largest of those maxima (the same two histogram passes, run on the maxima),
-// and the list of fine chunks that can still hold an admitted token; the three pooling passes then
-// visit only that list.
+// pruning pre-pass: the maximum of every fine chunk (one streaming read of the scores), the bin that
+// holds the budget-th largest of those maxima (the same histogram, run on the maxima), and the list of
+// fine chunks that can still hold a seed; counting and collecting then visit only that list.
 //
 // Ranking is (pooled value descending, token index ascending): the 64-bit key is the ordered value
 // bits above the complemented element index, so all keys are distinct and every step is
@@ -66,8 +65,8 @@
 namespace ilre {
 namespace {
 
-constexpr int kThreads = 1024;                    // sel_init, refine: one large workgroup
-constexpr int kPoolThreads = 256;                 // pooling passes: four wavefronts, one fine chunk each
+constexpr int kThreads = 1024;                    // sel_init, seed_init, refine: one large workgroup
+constexpr int kPoolThreads = 256;                 // passes over the scores: four wavefronts
 constexpr int kPoolWaves = kPoolThreads / 64;
 constexpr int kPerThread = kSelFine / 64;         // 4 tokens per lane
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
@@ -76,7 +75,6 @@ constexpr uint32_t kSortSmall = 4096;             // printed form: lists up to t
 // Per-combination description, host -> sel_init (by value), which copies it into the control blocks.
 struct SelParams {
     int n;
-    uint32_t exact;
     uint32_t share[ILRE_MAX_POOL_KERNELS], want[ILRE_MAX_POOL_KERNELS];
     uint32_t len[ILRE_MAX_POOL_KERNELS], cell[ILRE_MAX_POOL_KERNELS];
     uint64_t tie_off[ILRE_MAX_POOL_KERNELS];
@@ -108,6 +106,11 @@ __device__ __forceinline__ uint32_t load_u32(const uint32_t *p)
 __device__ __forceinline__ uint64_t load_u64(const uint64_t *p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void store_u64(uint64_t *p, uint64_t x)
+{
+    __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Wavefront scans and reductions with DPP row shifts and row broadcasts: six plain vector instructions,
@@ -213,25 +216,79 @@ __global__ __launch_bounds__(kThreads) void sel_init(const SelParams prm, uint32
 {
     const int j = blockIdx.x;
     const float edge = prm.sample ? sampled_edge(prm.sample, prm.sample_n, (prm.deep >> j) & 1u) : prm.edge[j];
-    // hist holds [2][n][kSelBins]; block j clears its rows of both levels
-    for (int i = threadIdx.x; i < kSelBins; i += kThreads) {
-        hist[(size_t)j * kSelBins + i] = 0;
-        hist[((size_t)prm.n + j) * kSelBins + i] = 0;
-    }
+    for (int i = threadIdx.x; i < kSelBins; i += kThreads) hist[(size_t)j * kSelBins + i] = 0;
     if (threadIdx.x == 0) {
         SelCtrl c{};
         c.want = prm.want[j];
-        c.share = prm.share[j];
-        c.bin1 = kSelBins;
-        c.bin2 = kSelBins;
         c.len = prm.len[j];
-        c.cell = prm.cell[j];
         c.tie_off = prm.tie_off[j];
-        c.exact = prm.exact;
         c.edge = edge > 0x1p-90f && edge < 0x1p90f ? edge : 0x1p-90f;
         ctrl[j] = c;
-        done[j] = 0;          // [2][n]: workgroups finished per histogram level and combination
-        done[prm.n + j] = 0;
+        done[j] = 0;
+    }
+}
+
+// A histogram's bins for scores of known scale, as an attention's scores are (in the sum form their mean is exact): 256
+// bins a binade from half the mean to four times it, where many scores of a flat distribution lie side by side, 32 a
+// binade from 2^-17 up to 2^25 of the mean.  By Markov's inequality few are above; what is below is not counted.
+KeyBins bins_of_mean(float mean)
+{
+    uint32_t bits;
+    memcpy(&bits, &mean, sizeof bits);
+    const uint32_t key = bits | 0x80000000u;  // ordered_bits of a positive float
+    KeyBins b{};
+    b.k0 = key - (17u << 23), b.s0 = 18;
+    b.k1 = key - (1u << 23), b.s1 = 15;
+    b.k2 = key + (2u << 23), b.s2 = 18;
+    return b;
+}
+
+__device__ __forceinline__ uint32_t bin_of(const KeyBins &b, uint32_t key)
+{
+    const uint32_t low = min(max(key, b.k0), b.k1) - b.k0, mid = min(max(key, b.k1), b.k2) - b.k1, high = max(key, b.k2) - b.k2;
+    const uint32_t bin = min(1u + (low >> b.s0) + (mid >> b.s1) + (high >> b.s2), (uint32_t)kSeedBins - 1u);
+    return key < b.k0 ? 0u : bin;
+}
+
+// Clears the states of a seed search on scores of unknown scale and places the bins by a sample of what is counted first:
+// the scores, or the maxima of fine chunks.  `lo` and `hi` are the sample's ranks (0: the largest) that enclose the K-th
+// largest with four standard deviations of a sample's count; between those two keys lie half of the bins, the others
+// cover all keys below (two binades each) and above.  Whatever the sample is, the result is the same.
+struct SeedInit {
+    const float *vals;
+    int64_t n;
+    uint32_t lo, hi;
+};
+__global__ __launch_bounds__(kThreads) void seed_init(const SeedInit p, SeedState *st)
+{
+    __shared__ __align__(16) uint32_t key[kBaseSamples];
+    __shared__ uint32_t bound[2];
+    static_assert(kThreads == 4 * kBaseSamples, "four threads a sample");
+    constexpr int kWords = sizeof(SeedState) / 16, kKept = sizeof(KeyBins) / 16;  // (the bins are written below)
+    for (int i = threadIdx.x; i < 2 * kWords; i += kThreads)
+        if (i % kWords >= kKept) ((uint4 *)st)[i] = make_uint4(0, 0, 0, 0);
+    const uint32_t u = threadIdx.x >> 2, part = threadIdx.x & 3;
+    const uint32_t k = ordered_bits(p.vals[(int64_t)u * p.n / kBaseSamples]);
+    if (part == 0) key[u] = k;
+    __syncthreads();
+    uint32_t c = 0;
+#pragma unroll 8
+    for (uint32_t v = part; v < (uint32_t)kBaseSamples; v += 4) c += key[v] > k || (key[v] == k && v < u) ? 1u : 0u;
+    c += (uint32_t)__shfl_xor((int)c, 1);
+    c += (uint32_t)__shfl_xor((int)c, 2);
+    if (part == 0 && c == p.lo) bound[0] = k;
+    if (part == 0 && c == p.hi) bound[1] = k;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        constexpr uint32_t kLow = 256, kMid = 1023, kHigh = kSeedBins - 1 - kLow - kMid;
+        KeyBins b{};
+        b.k0 = 0, b.s0 = 24;
+        b.k1 = bound[0];
+        b.k2 = max(bound[1], min(bound[1] + 1u, 0xFFFFFFFFu - 1u));
+        b.s1 = b.s2 = 0;
+        while ((b.k2 - b.k1) >> b.s1 >= kMid) ++b.s1;
+        while ((0xFFFFFFFFu - b.k2) >> b.s2 >= kHigh) ++b.s2;
+        st[0].bins = st[1].bins = b;
     }
 }
 
@@ -251,61 +308,23 @@ __device__ __forceinline__ uint32_t entry_chunk(const Entries &e, uint32_t i) { 
 // memory changed) is all the synchronisation a wavefront-private buffer needs.
 __device__ __forceinline__ void lds_wave_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
-// kRawBatch fine chunks (entries e0 .. e0 + kRawBatch - 1 of the visit list) are fetched at once; fcs[u] < 0 marks a
+// BATCH fine chunks (entries e0 .. e0 + BATCH - 1 of the visit list) are fetched at once; fcs[u] < 0 marks a
 // missing entry.
 constexpr int kRawBatch = 4;
+template <int BATCH>
 __device__ __forceinline__ void raw_fetch(const float *src, int64_t len, const Entries &ent, uint32_t e0, uint32_t nent,
-                                          int64_t (&fcs)[kRawBatch], float (&vals)[kRawBatch][kPerThread])
+                                          int64_t (&fcs)[BATCH], float (&vals)[BATCH][kPerThread])
 {
     const int lane = threadIdx.x & 63;
 #pragma unroll
-    for (int u = 0; u < kRawBatch; ++u) fcs[u] = e0 + u < nent ? (int64_t)entry_chunk(ent, e0 + u) : -1;
+    for (int u = 0; u < BATCH; ++u) fcs[u] = e0 + u < nent ? (int64_t)entry_chunk(ent, e0 + u) : -1;
 #pragma unroll
-    for (int u = 0; u < kRawBatch; ++u)
+    for (int u = 0; u < BATCH; ++u)
 #pragma unroll
         for (int k = 0; k < kPerThread; ++k) {
             const int64_t e = (fcs[u] < 0 ? 0 : fcs[u]) * kSelFine + lane + k * 64;
             vals[u][k] = src[e < len ? e : len - 1];  // lanes past the end are ignored by the callers
         }
-}
-
-// The bin b with  count(bins > b) < need <= count(bins >= b), by one wavefront.
-// Lane l sums 32 bins (descending order of bins); a scan over the lanes finds the lane whose segment
-// holds the crossing, and a second scan over that segment's 32 bins (one bin a lane) finds the bin.
-// LEVEL 1 reads `want`, LEVEL 2 the remainder left by level 1.
-template <int LEVEL>
-__device__ void find_bins(const uint32_t *hj, SelCtrl *ctrl)
-{
-    const int lane = threadIdx.x & 63;
-    constexpr int BPL = kSelBins / 64;
-    static_assert(BPL == 32, "the second scan maps one bin of a segment to each of 32 lanes");
-    if (threadIdx.x < 64) {
-        const uint32_t need = LEVEL == 1 ? ctrl->want : ctrl->need1;
-        if (need == 0 || (LEVEL == 2 && ctrl->bin1 >= (uint32_t)kSelBins)) return;  // uniform in the wave
-        uint32_t sum = 0;
-#pragma unroll 16
-        for (int k = 0; k < BPL; ++k) sum += load_u32(&hj[kSelBins - 1 - (lane * BPL + k)]);
-        const uint32_t incl = wave_scan_add(sum);
-        const uint64_t hit = __ballot(incl - sum < need && need <= incl);
-        if (hit == 0) return;  // fewer than `need` keys in all (never: need <= number of elements)
-        const int seg = __ffsll((unsigned long long)hit) - 1;
-        const uint32_t seg_above = (uint32_t)__builtin_amdgcn_readlane((int)(incl - sum), seg);
-        const uint32_t bin = kSelBins - 1 - (seg * BPL + (lane & 31));
-        const uint32_t own = lane < 32 ? load_u32(&hj[bin]) : 0u;
-        const uint32_t in2 = wave_scan_add(own);  // lanes 32.. hold zeros and are not looked at
-        const uint32_t above = seg_above + in2 - own;
-        if (lane < 32 && above < need && need <= above + own) {  // exactly one lane
-            if (LEVEL == 1) {
-                ctrl->bin1 = bin;
-                ctrl->above1 = above;
-                ctrl->need1 = need - above;
-            } else {
-                ctrl->bin2 = bin;
-                ctrl->above2 = above;
-                ctrl->need2 = need - above;
-            }
-        }
-    }
 }
 
 // Append the selected items of a wavefront to a list: one slot reservation per wavefront.
@@ -348,45 +367,10 @@ __device__ __forceinline__ void wave_append2(const bool (&pa)[N], const bool (&p
 #pragma unroll
     for (int g = 0; g < N; ++g) {
         const uint64_t ma = __ballot(pa[g]), mb = __ballot(pb[g]);
-        if (pa[g]) la[base_a + (uint32_t)__popcll(ma & below)] = item[g];
-        if (pb[g]) lb[base_b + (uint32_t)__popcll(mb & below)] = item[g];
+        if (pa[g]) store_u64(&la[base_a + (uint32_t)__popcll(ma & below)], item[g]);
+        if (pb[g]) store_u64(&lb[base_b + (uint32_t)__popcll(mb & below)], item[g]);
         base_a += (uint32_t)__popcll(ma);
         base_b += (uint32_t)__popcll(mb);
-    }
-}
-
-// Histogram accounting of a wavefront's kPerThread values per lane (element `first + lane + 64k`, valid while
-// below `len`) into the workgroup's LDS histogram.  LEVEL 1: key bits 31..21.  LEVEL 2: bits 20..10 of the
-// keys whose bits 31..21 equal bin1.
-template <int LEVEL>
-__device__ __forceinline__ void hist_account(uint32_t *lh, const float (&pooled)[kPerThread], int64_t first, int64_t len,
-                                             uint32_t bin1)
-{
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int k = 0; k < kPerThread; ++k) {
-        const int64_t el = first + lane + k * 64;
-        const uint32_t key = ordered_bits(pooled[k]);
-        if (LEVEL == 1) {
-            // Real score distributions put most of a wavefront's 64 keys into one or two bins, and
-            // same-address LDS atomics serialise: the two most common bins are counted with ballots
-            // and added once, whatever is left goes one by one.
-            const uint32_t bin = key >> 21;
-            bool todo = el >= 0 && el < len;
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const uint64_t open = __ballot(todo);
-                if (open == 0) break;  // uniform
-                const int leader = __ffsll((unsigned long long)open) - 1;
-                const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)bin, leader);
-                const uint64_t same = __ballot(todo && bin == b0);
-                if (lane == leader) atomicAdd(&lh[b0], (uint32_t)__popcll(same));
-                todo = todo && bin != b0;
-            }
-            if (todo) atomicAdd(&lh[bin], 1u);
-        } else if (el >= 0 && el < len && (key >> 21) == bin1) {
-            atomicAdd(&lh[(key >> 10) & (kSelBins - 1)], 1u);
-        }
     }
 }
 
@@ -407,140 +391,129 @@ __device__ __forceinline__ bool count_in(uint32_t *counter, uint32_t workgroups,
     return true;
 }
 
-// The workgroup's LDS histogram goes to the global one; the last workgroup to count in locates the bin.
-template <int LEVEL>
-__device__ __forceinline__ void hist_finish(uint32_t *lh, uint32_t *hist, SelCtrl *ctrl, uint32_t *counter, uint32_t workgroups, uint32_t *is_last)
+// The workgroup's LDS histogram goes to the global one; the last workgroup to count in finds the cut: the bin b with
+// count(bins > b) < want <= count(bins >= b), bin 0 (everything not counted) if fewer than `want` were.
+__device__ __forceinline__ void count_finish(uint32_t *lh, SeedState *st, uint32_t want)
 {
+    __shared__ uint32_t is_last, wsum[kPoolWaves];
     __syncthreads();
-    for (int i = threadIdx.x; i < kSelBins; i += kPoolThreads) {
-        const uint32_t c = lh[i];
-        if (c) atomicAdd(&hist[i], c);
+    constexpr int kPer = kSeedBins / kPoolThreads;
+    // neighbouring lanes, neighbouring bins: an atomic request is a cache line
+    uint32_t c[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) c[k] = lh[k * kPoolThreads + threadIdx.x];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k)
+        if (c[k]) atomicAdd(&st->hist[k * kPoolThreads + threadIdx.x], c[k]);
+    if (!count_in(&st->done[0], gridDim.x, &is_last)) return;
+    // thread t: bins top - kPer + 1 .. top
+    const int top = kSeedBins - 1 - (int)threadIdx.x * kPer;
+    const uint64_t *h2 = (const uint64_t *)&st->hist[top - kPer + 1];
+    uint64_t two[kPer / 2];
+#pragma unroll
+    for (int k = 0; k < kPer / 2; ++k) two[k] = load_u64(&h2[k]);
+    uint32_t sum = 0;
+#pragma unroll
+    for (int k = 0; k < kPer / 2; ++k) sum += (uint32_t)two[k] + (uint32_t)(two[k] >> 32);
+    uint32_t total;
+    uint32_t above = block_scan_inclusive<kPoolThreads>(sum, wsum, total) - sum;
+    if (total < want) {
+        if (threadIdx.x == 0) st->cut = 0, st->need = want - total;
+    } else if (above < want && want <= above + sum) {  // one thread
+#pragma unroll
+        for (int k = kPer - 1; k >= 0; --k) {
+            const uint32_t n = (uint32_t)(two[k / 2] >> (k & 1 ? 32 : 0));
+            if (above < want && want <= above + n) st->cut = (uint32_t)(top - kPer + 1 + k), st->need = want - above;
+            above += n;
+        }
     }
-    if (count_in(counter, workgroups, is_last)) find_bins<LEVEL>(hist, ctrl);
 }
 
-// LEVEL 1: histogram of key bits 31..21 over the visited elements.  LEVEL 2: of bits 20..10 over the elements whose
-// bits 31..21 equal the level-1 bin.  A wavefront fetches kRawBatch fine chunks before it accounts for any, so
-// that their loads are in flight together.
-template <int LEVEL>
-__global__ __launch_bounds__(kPoolThreads) void pool_hist(const float *vals, SelCtrl *ctrl, uint32_t *hist_all, uint32_t *done,
-                                                          const Entries ent)
+__device__ __forceinline__ void count_clear(uint32_t *lh)
 {
-    __shared__ uint32_t lh[kSelBins];
-    __shared__ uint32_t is_last;
-    const int wave = threadIdx.x >> 6;
-    uint32_t *hist = hist_all + (size_t)(LEVEL - 1) * kSelBins;
-    const uint32_t bin1 = LEVEL == 2 ? ctrl->bin1 : 0;
-    const int64_t len = (int64_t)ctrl->len;
-    for (int i = threadIdx.x; i < kSelBins; i += kPoolThreads) lh[i] = 0;
+    for (int i = threadIdx.x * 4; i < kSeedBins; i += kPoolThreads * 4) *(uint4 *)&lh[i] = make_uint4(0, 0, 0, 0);
     __syncthreads();
+}
+__device__ __forceinline__ void count_one(uint32_t *lh, const KeyBins &bins, float x, bool valid)
+{
+    const uint32_t bin = bin_of(bins, ordered_bits(x));
+    if (valid && bin) atomicAdd(&lh[bin], 1u);
+}
+
+// Histogram of the visited scores (or chunk maxima), bins from the state.  A wavefront fetches kRawBatch fine chunks
+// before it counts any, so that their loads are in flight together.
+__global__ __launch_bounds__(kPoolThreads) void count_scores(const float *vals, int64_t len, uint32_t want, SeedState *st, const Entries ent)
+{
+    __shared__ __align__(16) uint32_t lh[kSeedBins];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const KeyBins bins = st->bins;
+    count_clear(lh);
     const uint32_t nent = entry_count(ent, (uint32_t)len);
     for (uint32_t e0 = (blockIdx.x * kPoolWaves + wave) * kRawBatch; e0 < nent; e0 += gridDim.x * kPoolWaves * kRawBatch) {
-        float vals_[kRawBatch][kPerThread];
+        float v[kRawBatch][kPerThread];
         int64_t fcs[kRawBatch];
-        raw_fetch(vals, len, ent, e0, nent, fcs, vals_);
+        raw_fetch(vals, len, ent, e0, nent, fcs, v);
 #pragma unroll
-        for (int u = 0; u < kRawBatch; ++u)
-            if (fcs[u] >= 0) hist_account<LEVEL>(lh, vals_[u], fcs[u] * kSelFine, len, bin1);  // uniform
+        for (int u = 0; u < kRawBatch; ++u) {
+            if (fcs[u] < 0) break;  // uniform
+#pragma unroll
+            for (int k = 0; k < kPerThread; ++k) count_one(lh, bins, v[u][k], fcs[u] * kSelFine + lane + k * 64 < len);
+        }
     }
-    hist_finish<LEVEL>(lh, hist, ctrl, &done[LEVEL - 1], gridDim.x, &is_last);
+    count_finish(lh, st, want);
 }
 
 // The whole path's first selection pass, fused with the last scoring step: score[t] = sum (or max) over the
-// (kv head, query block) units of their partial column results, written out for every token, and the level-1
-// histogram of the body's scores (tokens sink .. L-1) for the single seed combination, in one pass over the
-// partial vectors.  The sum runs in unit order, as in the stand-alone reduction.
-template <int RMAX>
-__global__ __launch_bounds__(kPoolThreads) void reduce_hist1(const float *partial, int nunits, int64_t L, int sink, float *score,
-                                                             SelCtrl *ctrl, uint32_t *hist, uint32_t *done)
+// (kv head, query block) units of their partial column results, written out for every token, and the
+// histogram of the body's scores (tokens sink .. L-1), in one pass over the partial vectors.  The sum runs in unit
+// order, as in the stand-alone reduction.  Bound: the partial vectors are 64 MiB at 1M tokens, this pass is their one
+// reader; on short contexts the chain clear - load - count - add - find.  PER tokens a lane: one, so that the loads are
+// spread over the chip; four from 32K tokens on, because every workgroup adds its counts to the global ones and it is the
+// number of those additions that counts (128K tokens: 512 workgroups, and bins four times finer, 42 us).  Measured
+// (kernel trace), before (two histogram passes of 11 key bits, two chunks of 256 tokens a wavefront, a kernel to clear)
+// -> after: 32K tokens 4.7 + 10.5 + 6.9 -> 7.3 us, 128K 4.7 + 11.3 + 7.4 -> 8.7 us.
+template <int RMAX, int PER>
+__global__ __launch_bounds__(kPoolThreads) void reduce_count(const float *partial, int nunits, int64_t L, int sink, float *score,
+                                                             const KeyBins bins, uint32_t want, SeedState *st)
 {
-    __shared__ uint32_t lh[kSelBins];
-    __shared__ uint32_t is_last;
+    __shared__ __align__(16) uint32_t lh[kSeedBins];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int i = threadIdx.x; i < kSelBins; i += kPoolThreads) lh[i] = 0;
-    __syncthreads();
-    const uint32_t nfine = (uint32_t)((L + kSelFine - 1) / kSelFine);
-    // A wavefront takes kChunks fine chunks a round and the units eight at a time: 64 independent loads per lane
-    // are in flight before the first sum (the partial vectors are 64 MiB at 1M tokens; this pass is their one
-    // reader and must run at memory speed).
-    constexpr int kChunks = 2, kUnits = 8;
-    for (uint32_t fc0 = (blockIdx.x * kPoolWaves + wave) * kChunks; fc0 < nfine; fc0 += gridDim.x * kPoolWaves * kChunks) {
-        float v[kChunks][kPerThread];
-        int64_t tok[kChunks][kPerThread];
+    count_clear(lh);
+    constexpr int kUnits = PER == 1 ? 16 : 8;  // units whose loads are in flight together
+    constexpr int kTokens = 64 * PER;          // of a wavefront at a time
+    for (int64_t t0 = (int64_t)(blockIdx.x * kPoolWaves + wave) * kTokens; t0 < L; t0 += (int64_t)gridDim.x * kPoolWaves * kTokens) {
+        float v[PER];
+        int64_t tok[PER];
 #pragma unroll
-        for (int c = 0; c < kChunks; ++c)
-#pragma unroll
-            for (int k = 0; k < kPerThread; ++k) {
-                const int64_t t = (int64_t)(fc0 + c) * kSelFine + lane + k * 64;
-                tok[c][k] = t < L ? t : L - 1;
-            }
+        for (int k = 0; k < PER; ++k) tok[k] = t0 + lane + k * 64 < L ? t0 + lane + k * 64 : L - 1;
         for (int u0 = 0; u0 < nunits; u0 += kUnits) {
-            float x[kUnits][kChunks][kPerThread];
+            float x[kUnits][PER];
 #pragma unroll
             for (int uu = 0; uu < kUnits; ++uu) {
                 const int64_t u = u0 + uu < nunits ? u0 + uu : nunits - 1;
 #pragma unroll
-                for (int c = 0; c < kChunks; ++c)
-#pragma unroll
-                    for (int k = 0; k < kPerThread; ++k) x[uu][c][k] = partial[u * L + tok[c][k]];
+                for (int k = 0; k < PER; ++k) x[uu][k] = partial[u * L + tok[k]];
             }
 #pragma unroll
             for (int uu = 0; uu < kUnits; ++uu) {
                 if (u0 + uu >= nunits) break;  // uniform
 #pragma unroll
-                for (int c = 0; c < kChunks; ++c)
-#pragma unroll
-                    for (int k = 0; k < kPerThread; ++k) {
-                        if (u0 + uu == 0)
-                            v[c][k] = x[uu][c][k];
-                        else
-                            v[c][k] = RMAX ? fmaxf(v[c][k], x[uu][c][k]) : v[c][k] + x[uu][c][k];
-                    }
+                for (int k = 0; k < PER; ++k) {
+                    if (u0 + uu == 0)
+                        v[k] = x[uu][k];
+                    else
+                        v[k] = RMAX ? fmaxf(v[k], x[uu][k]) : v[k] + x[uu][k];
+                }
             }
         }
 #pragma unroll
-        for (int c = 0; c < kChunks; ++c) {
-            if (fc0 + c >= nfine) break;  // uniform
-#pragma unroll
-            for (int k = 0; k < kPerThread; ++k) {
-                const int64_t t = (int64_t)(fc0 + c) * kSelFine + lane + k * 64;
-                if (t < L) score[t] = v[c][k];
-            }
-            // body element of token t is t - sink; the sink tokens (negative elements) are not counted
-            hist_account<1>(lh, v[c], (int64_t)(fc0 + c) * kSelFine - sink, L - sink, 0);
+        for (int k = 0; k < PER; ++k) {
+            const int64_t t = t0 + lane + k * 64;
+            if (t < L) score[t] = v[k];
+            count_one(lh, bins, v[k], t >= sink && t < L);
         }
     }
-    hist_finish<1>(lh, hist, ctrl, &done[0], gridDim.x, &is_last);
-}
-
-__global__ __launch_bounds__(kPoolThreads) void collect(const float *vals, SelCtrl *ctrl, uint64_t *cand, uint64_t *tie, const Entries ent)
-{
-    const int64_t len = (int64_t)ctrl->len;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t bin1 = ctrl->bin1, bin2 = ctrl->bin2;
-    if (bin1 >= (uint32_t)kSelBins || bin2 >= (uint32_t)kSelBins) return;  // nothing wanted
-    const uint32_t prefix = (bin1 << 11) | bin2;  // 22-bit prefix of the K-th largest key
-    const uint32_t nent = entry_count(ent, (uint32_t)len);
-    // keys above the prefix are candidates, keys that share it go to the boundary list
-    for (uint32_t e0 = (blockIdx.x * kPoolWaves + wave) * kRawBatch; e0 < nent; e0 += gridDim.x * kPoolWaves * kRawBatch) {
-        float vals_[kRawBatch][kPerThread];
-        int64_t fcs[kRawBatch];
-        raw_fetch(vals, len, ent, e0, nent, fcs, vals_);
-        bool above[kRawBatch * kPerThread], same[kRawBatch * kPerThread];
-        uint64_t key[kRawBatch * kPerThread];
-#pragma unroll
-        for (int u = 0; u < kRawBatch; ++u)
-#pragma unroll
-            for (int k = 0; k < kPerThread; ++k) {
-                const int64_t el = fcs[u] * kSelFine + lane + k * 64;
-                const bool valid = fcs[u] >= 0 && el < len;
-                const uint32_t p22 = valid ? ordered_bits(vals_[u][k]) >> 10 : 0;
-                key[u * kPerThread + k] = make_key(vals_[u][k], (uint32_t)el);
-                above[u * kPerThread + k] = valid && p22 > prefix;
-                same[u * kPerThread + k] = valid && p22 == prefix;
-            }
-        wave_append2<kRawBatch * kPerThread>(above, same, key, cand, &ctrl->cand_n, tie, &ctrl->tie_n);
-    }
+    count_finish(lh, st, want);
 }
 
 // Pruning pre-pass for long contexts, step 1: cm[c] = max of the scores of fine chunk c.  Pure
@@ -585,39 +558,28 @@ __global__ __launch_bounds__(kPoolThreads) void chunk_max(const float *scores, i
     }
 }
 
-// Pruning pre-pass, step 3 (step 2 is the two-level histogram run on cm for the `budget`-th largest
-// chunk maximum): at least `budget` tokens score at or above the lower edge of that maximum's 22-bit
-// prefix, so no kernel admits a token whose pooled score is below it; a fine chunk can only hold such
-// a token if a chunk maximum within `reach` chunks of it reaches the prefix.
+// Pruning pre-pass, step 3 (step 2 is the histogram run on cm for the `budget`-th largest chunk maximum): at least
+// `budget` scores, one a chunk, are in that maximum's bin or above it, so no seed is in a bin below; a fine chunk can
+// only hold a seed if its maximum reaches the bin.
 // One slot reservation per workgroup (same-address atomics serialise at about 13 ns each, and a few thousand
 // scattered hits would otherwise mean a few thousand of them): a thread looks at kMarkPerThread consecutive chunks.
 constexpr int kMarkPerThread = 16;
-__global__ __launch_bounds__(kPoolThreads) void mark_active(const float *cm, uint32_t nfine, int reach, SelCtrl *pctrl,
-                                                            uint32_t *list)
+__global__ __launch_bounds__(kPoolThreads) void mark_active(const float *cm, uint32_t nfine, SeedState *pre, uint32_t *list)
 {
     __shared__ uint32_t wsum[kPoolWaves];
     __shared__ uint32_t base_slot;
     const uint32_t c0 = (blockIdx.x * kPoolThreads + threadIdx.x) * kMarkPerThread;
-    const uint32_t bin1 = pctrl->bin1, bin2 = pctrl->bin2;
-    const uint32_t prefix = (bin1 >= (uint32_t)kSelBins || bin2 >= (uint32_t)kSelBins) ? 0u : (bin1 << 11) | bin2;
+    const KeyBins bins = pre->bins;
+    const uint32_t cut = pre->cut;
     uint32_t hits = 0;  // bit i: chunk c0 + i is active
 #pragma unroll
-    for (int i = 0; i < kMarkPerThread; ++i) {
-        const uint32_t c = c0 + i;
-        if (c < nfine) {
-            float m = cm[c];
-            for (int d = 1; d <= reach; ++d) {
-                if (c >= (uint32_t)d) m = fmaxf(m, cm[c - d]);
-                if (c + d < nfine) m = fmaxf(m, cm[c + d]);
-            }
-            if ((ordered_bits(m) >> 10) >= prefix) hits |= 1u << i;
-        }
-    }
+    for (int i = 0; i < kMarkPerThread; ++i)
+        if (c0 + i < nfine && bin_of(bins, ordered_bits(cm[c0 + i])) >= cut) hits |= 1u << i;
     uint32_t total;
     const uint32_t mine = (uint32_t)__popc(hits);
     uint32_t at = block_scan_inclusive<kPoolThreads>(mine, wsum, total) - mine;
     if (total == 0) return;  // uniform
-    if (threadIdx.x == 0) base_slot = atomicAdd(&pctrl->cand_n, total);
+    if (threadIdx.x == 0) base_slot = atomicAdd(&pre->active_n, total);
     __syncthreads();
     at += base_slot;
 #pragma unroll
@@ -974,33 +936,30 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
     }
 }
 
-// Boundary list -> candidates.  Window-max form: short lists (the normal case) are appended whole,
-// candidates below the cut are harmless, they rank last; long ones are radix-selected down first.
-// Printed form: the list is always cut to what the K_m-cell cap leaves.
-__global__ __launch_bounds__(kThreads) void refine(SelCtrl *ctrl, uint64_t *cand, uint64_t *tie, uint32_t sort_n)
+// Of the `need` largest of A's nA distinct keys those that a radix selection finds on its way are appended to
+// cand[candn ..]; the rest is among the remaining list, which shrinks by 8 key bits a pass, from A into B and back.
+// Stops when what there is fits `keep`, or is exactly what is needed.  By one workgroup.
+template <int THREADS>
+__device__ void peel(uint64_t *&A, uint64_t *&B, uint32_t &nA, uint32_t &need, uint64_t *cand, uint32_t &candn, uint32_t keep)
 {
     __shared__ uint32_t h[256];
     __shared__ uint32_t cnt[2];
     __shared__ uint32_t pick[3];  // digit, count above it, count in it
-
-    const int j = blockIdx.x;
-    uint64_t *cand_j = cand + (size_t)j * kCandCap;
-    uint64_t *A = tie + ctrl[j].tie_off;
-    uint64_t *B = A + ctrl[j].len;
-    const bool exact = ctrl[j].exact != 0;
-    uint32_t nA = ctrl[j].tie_n;
-    uint32_t need = exact ? ctrl[j].want : ctrl[j].need2;
-    uint32_t candn = exact ? 0u : ctrl[j].cand_n;
-    const uint32_t keep = exact ? sort_n : (uint32_t)kSelSmall;
+    constexpr int kBatch = 8;     // keys a thread has in flight
     const int lane = threadIdx.x & 63;
-
-    // A list too long to be sorted (or to join the seeds) as it is: peel 8 key bits a pass.  In the window-max form the
-    // list shares its top 22 key bits (key64 bits 63..42).
-    for (int shift = exact ? 56 : 40; shift >= 0 && nA + (exact ? candn : 0u) > keep && need < nA; shift -= 8) {
+    for (int shift = 56; shift >= 0 && nA + candn > keep && need < nA; shift -= 8) {
+        __syncthreads();
         if (threadIdx.x < 256) h[threadIdx.x] = 0;
         if (threadIdx.x < 2) cnt[threadIdx.x] = 0;
         __syncthreads();
-        for (uint32_t i = threadIdx.x; i < nA; i += kThreads) atomicAdd(&h[(load_u64(&A[i]) >> shift) & 255u], 1u);
+        for (uint32_t i0 = threadIdx.x; i0 < nA; i0 += THREADS * kBatch) {
+            uint64_t key[kBatch];
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b) key[b] = load_u64(&A[min(i0 + b * THREADS, nA - 1)]);
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b)
+                if (i0 + b * THREADS < nA) atomicAdd(&h[(key[b] >> shift) & 255u], 1u);
+        }
         __syncthreads();
         if (threadIdx.x < 64) {
             // lane l owns digits 255-4l .. 252-4l (descending); find the digit holding the need-th key
@@ -1026,14 +985,20 @@ __global__ __launch_bounds__(kThreads) void refine(SelCtrl *ctrl, uint64_t *cand
         }
         __syncthreads();
         const uint32_t digit = pick[0], above = pick[1], inside = pick[2];
-        const uint32_t rounds = (nA + kThreads - 1) / kThreads;
-        for (uint32_t it = 0; it < rounds; ++it) {
-            const uint32_t i = it * kThreads + threadIdx.x;
-            const bool valid = i < nA;
-            const uint64_t key = valid ? load_u64(&A[i]) : 0;
-            const uint32_t d = (uint32_t)(key >> shift) & 255u;
-            wave_append(valid && d > digit, key, cand_j + candn, &cnt[0]);
-            wave_append(valid && d == digit, key, B, &cnt[1]);
+        if (inside == nA) continue;  // all share the digit
+        for (uint32_t first = 0; first < nA; first += THREADS * kBatch) {  // uniform
+            uint64_t key[kBatch];
+            bool more[kBatch], same[kBatch];
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b) key[b] = load_u64(&A[min(first + b * THREADS + threadIdx.x, nA - 1)]);
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b) {
+                const bool valid = first + b * THREADS + threadIdx.x < nA;
+                const uint32_t d = (uint32_t)(key[b] >> shift) & 255u;
+                more[b] = valid && d > digit;
+                same[b] = valid && d == digit;
+            }
+            wave_append2<kBatch>(more, same, key, cand + candn, &cnt[0], B, &cnt[1]);
         }
         // The survivors go through global memory to the next pass of this same workgroup: wait until
         // the stores have reached the L2 and read them back past the L1 (load_u64).  A fence would do
@@ -1047,14 +1012,90 @@ __global__ __launch_bounds__(kThreads) void refine(SelCtrl *ctrl, uint64_t *cand
         A = B;
         B = t;
     }
-    const uint32_t total = candn + nA;
-    if (!exact) {  // uniform
-        for (uint32_t i = threadIdx.x; i < nA; i += kThreads) cand_j[candn + i] = load_u64(&A[i]);
-        if (threadIdx.x == 0) ctrl[j].total_n = total;
-        return;
-    }
+}
 
-    // Printed form: the first `want` elements in rank order, for the allocation walk.  Bitonic sort of the
+// Window-max form: keys above the cut bin are seeds, keys in it go to the boundary list.  A workgroup reserves its slots
+// in both lists with one atomic on the two counters (they are one word for it): a returning atomic on an address that
+// everybody wants takes its turn at about 13 ns (128K tokens: one per wavefront and list 21 us, this 6.2 us).  Both lists are
+// written with device-scope stores, so that the last workgroup (on whichever XCD) may read the boundary list if it is
+// one of the long ones (a kernel of its own for that took 2 - 4.7 us to find nothing to do).
+template <int BATCH>
+__global__ __launch_bounds__(kPoolThreads) void collect(const float *vals, int64_t len, uint32_t want, const KeyBins known, bool sampled,
+                                                        SeedState *st, uint64_t *cand, uint64_t *tie, const Entries ent)
+{
+    __shared__ uint32_t is_last;
+    __shared__ uint64_t wave_n[kPoolWaves], base;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const KeyBins bins = sampled ? st->bins : known;
+    const uint32_t cut = st->cut;
+    const uint32_t nent = entry_count(ent, (uint32_t)len);
+    for (uint32_t e0 = blockIdx.x * kPoolWaves * BATCH; e0 < nent; e0 += gridDim.x * kPoolWaves * BATCH) {  // uniform
+        float v[BATCH][kPerThread];
+        int64_t fcs[BATCH];
+        raw_fetch(vals, len, ent, e0 + wave * BATCH, nent, fcs, v);
+        bool above[BATCH * kPerThread], same[BATCH * kPerThread];
+        uint32_t na = 0, ns = 0;
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u)
+#pragma unroll
+            for (int k = 0; k < kPerThread; ++k) {
+                const int g = u * kPerThread + k;
+                const bool valid = fcs[u] >= 0 && fcs[u] * kSelFine + lane + k * 64 < len;
+                const uint32_t bin = bin_of(bins, ordered_bits(v[u][k]));
+                above[g] = valid && bin > cut;
+                same[g] = valid && bin == cut;
+                na += (uint32_t)__popcll(__ballot(above[g]));
+                ns += (uint32_t)__popcll(__ballot(same[g]));
+            }
+        const uint64_t mine = (uint64_t)ns << 32 | na;
+        if (lane == 0) wave_n[wave] = mine;
+        __syncthreads();
+        uint64_t before = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < kPoolWaves; ++w) {
+            before += w < wave ? wave_n[w] : 0;
+            all += wave_n[w];
+        }
+        if (threadIdx.x == 0 && all) base = atomicAdd((unsigned long long *)&st->lists_n, all);
+        __syncthreads();
+        if (mine) {  // uniform in the wavefront
+            const uint64_t at = base + before;
+            uint32_t at_a = (uint32_t)at, at_s = (uint32_t)(at >> 32);
+            const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+            for (int g = 0; g < BATCH * kPerThread; ++g) {
+                const uint64_t ma = __ballot(above[g]), ms = __ballot(same[g]);
+                if ((ma | ms) == 0) continue;  // uniform
+                const uint64_t key = make_key(v[g / kPerThread][g % kPerThread], (uint32_t)(fcs[g / kPerThread] * kSelFine + lane + g % kPerThread * 64));
+                if (above[g]) store_u64(&cand[at_a + (uint32_t)__popcll(ma & below)], key);
+                if (same[g]) store_u64(&tie[at_s + (uint32_t)__popcll(ms & below)], key);
+                at_a += (uint32_t)__popcll(ma);
+                at_s += (uint32_t)__popcll(ms);
+            }
+        }
+    }
+    if (!count_in(&st->done[1], gridDim.x, &is_last)) return;
+    const uint64_t lists_n = load_u64(&st->lists_n);
+    uint32_t candn = (uint32_t)lists_n, nA = (uint32_t)(lists_n >> 32), need = want - candn;
+    if (candn + nA <= want + (uint32_t)kSelSmall) return;  // uniform
+    uint64_t *A = tie, *B = tie + len;
+    peel<kPoolThreads>(A, B, nA, need, cand, candn, want + (uint32_t)kSelSmall);
+    for (uint32_t i = threadIdx.x; i < nA; i += kPoolThreads) cand[candn + i] = load_u64(&A[i]);
+    if (threadIdx.x == 0) st->refined = candn + nA;
+}
+
+// Printed form: the list of a combination, sorted and cut to the K_j elements in rank order.  A list too long to sort (many
+// equal averages) is radix-selected down first.
+__global__ __launch_bounds__(kThreads) void refine(const SelCtrl *ctrl, uint64_t *cand, uint64_t *tie, uint32_t sort_n)
+{
+    const int j = blockIdx.x;
+    uint64_t *cand_j = cand + (size_t)j * kCandCap;
+    uint64_t *A = tie + ctrl[j].tie_off;
+    uint64_t *B = A + ctrl[j].len;
+    uint32_t nA = ctrl[j].tie_n, need = ctrl[j].want, candn = 0;
+    peel<kThreads>(A, B, nA, need, cand_j, candn, sort_n);
+    const uint32_t total = candn + nA;
+    // The first `want` elements in rank order, for the allocation walk.  Bitonic sort of the
     // keys (descending; padding keys of 0 sink to the end) in LDS, one barrier per stage.
     extern __shared__ __align__(16) unsigned char smem[];
     uint64_t *srt = (uint64_t *)smem;
@@ -1209,6 +1250,8 @@ constexpr int kRingBytes = kWalkAhead * kWalkSpan * (int)sizeof(uint32_t);    //
 static_assert(kRingBytes >= ILRE_MAX_BUDGET * (int)sizeof(uint16_t) && (kWalkAhead & (kWalkAhead - 1)) == 0, "the ring's memory is used again");
 static_assert(kBitmapTokens / 32 < 65536 && ILRE_MAX_BUDGET < 65536, "16-bit word numbers and places");
 
+__device__ __forceinline__ uint32_t seed_count(const SeedState &s) { return s.refined ? s.refined : (uint32_t)s.lists_n + (uint32_t)(s.lists_n >> 32); }
+
 // What the intervals of a list are.
 enum WalkItems {
     kWalkSeeds,      // tokens owned by a seed: found from its position, its outranking neighbours and the window radius
@@ -1222,7 +1265,7 @@ struct WalkArgs {
     uint32_t share[ILRE_MAX_POOL_KERNELS];    // B_j
     uint32_t reach[ILRE_MAX_POOL_KERNELS];    // window radius, or tokens per cell
     uint32_t cells[ILRE_MAX_POOL_KERNELS];    // cells: length of the list (>= 1)
-    const SelCtrl *ctrl;                      // seeds: their number
+    const SeedState *seeds;                   // seeds: their number
     const uint32_t *pos, *dom;                // seeds, by rank: token, and the distances to its outranking neighbours
     const uint64_t *cand;                     // cells: per combination the ranked cells, uint32
     uint32_t *picked, *picked_n;              // HASHED: the allocated tokens in the order they are taken
@@ -1275,7 +1318,7 @@ __global__ __launch_bounds__(kWalkThreads) void allocate_walk(const WalkArgs a)
     uint32_t seed[SEEDS ? kWalkPasses : 1][kWalkPer], dom[SEEDS ? kWalkPasses : 1][kWalkPer];
     uint32_t nseeds = 0;
     if (SEEDS) {
-        nseeds = a.ctrl[0].total_n;
+        nseeds = seed_count(*a.seeds);
 #pragma unroll
         for (int p = 0; p < kWalkPasses; ++p) {
             const int r2 = p * kWalkThreads + tid;
@@ -1574,15 +1617,16 @@ __global__ __launch_bounds__(kWalkThreads) void allocate_walk(const WalkArgs a)
 constexpr int kSeedRankThreads = 512;  // 32 seeds a workgroup
 constexpr uint32_t kNoDom = 0x7FFF;    // farther than two radii: binds no kernel size
 static_assert(kNoDom > ILRE_MAX_POOL_KERNEL, "reach is twice the largest radius");
-__global__ __launch_bounds__(kSeedRankThreads) void seed_rank(const float *scores, int64_t L, const SelCtrl *sc, const uint64_t *seeds,
-                                                              int reach, uint32_t *by_rank, uint32_t *dom)
+__global__ __launch_bounds__(kSeedRankThreads) void seed_rank(const float *scores, int64_t L, const SeedState *st, const uint64_t *cand,
+                                                              const uint64_t *tie, int reach, uint32_t *by_rank, uint32_t *dom)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     uint64_t *all = (uint64_t *)smem;  // every seed's key, staged once per workgroup (kCandCap at most)
-    const uint32_t ns = sc->total_n;
+    const uint32_t ns = seed_count(*st), nc = st->refined ? ns : (uint32_t)st->lists_n;
     if (blockIdx.x * (kSeedRankThreads / 16) >= ns) return;  // uniform
     // (the seeds were written by earlier kernels: plain loads, all in flight together)
-    stage_to_lds<uint64_t, kSeedRankThreads>(all, seeds, ns);
+    stage_to_lds<uint64_t, kSeedRankThreads>(all, cand, nc);
+    if (nc < ns) stage_to_lds<uint64_t, kSeedRankThreads>(all + nc, tie, ns - nc);
     const uint32_t padded = (ns + 127u) & ~127u;  // whole rounds of 64 lanes x 2 keys; the padding outranks nothing
     if (threadIdx.x < 128 && ns + threadIdx.x < padded) all[ns + threadIdx.x] = 0ull;
     __syncthreads();
@@ -1672,17 +1716,17 @@ SelectLayout make_select_layout(const SelectJob &job)
     SelectLayout lay{};
     const int n = job.combos() > 0 ? job.combos() : 1;
     const bool window = job.mode == kSelWindowMax;
-    // histogram passes run per combination in the printed form, for the single seed combination in the
-    // window-max form; one more set belongs to the pruning pre-pass
     const int nh = window ? 1 : n;
     const size_t nfine = (size_t)((job.L + kSelFine - 1) / kSelFine);
     size_t off = 0;
+    lay.state = off;
+    off = up(off + (window ? 2 * sizeof(SeedState) : 0));
     lay.hist = off;
-    off = up(off + 2 * (size_t)(nh + 1) * kSelBins * sizeof(uint32_t));
+    off = up(off + (window ? 0 : (size_t)n * kSelBins * sizeof(uint32_t)));
     lay.ctrl = off;
-    off = up(off + (size_t)(nh + 1) * sizeof(SelCtrl));
+    off = up(off + (window ? 0 : (size_t)n * sizeof(SelCtrl)));
     lay.done = off;
-    off = up(off + 2 * (size_t)(nh + 1) * sizeof(uint32_t));
+    off = up(off + (window ? 0 : (size_t)n * sizeof(uint32_t)));
     lay.cmax = off;
     off = up(off + nfine * sizeof(float));
     lay.active = off;
@@ -1760,7 +1804,6 @@ uint32_t pool_blocks(uint32_t entries, uint32_t cap)
     const uint32_t want = (entries + kPoolWaves - 1) / kPoolWaves;
     return want < cap ? (want ? want : 1u) : cap;
 }
-uint32_t clamp_u32(uint32_t x, uint32_t lo, uint32_t hi) { return x < lo ? lo : (x > hi ? hi : x); }
 
 // The walk and its ascending output: straight from the bitmap where it fits the LDS, else through the list of
 // allocated tokens, which emit_sorted puts in order.
@@ -1786,6 +1829,13 @@ void launch_walk(WalkArgs &w, const SelectJob &job, int n_out, unsigned char *ws
     }
 }
 
+// Whether a window-max selection starts with the pruning pre-pass.
+bool prunes(int64_t L, int n_out)
+{
+    const int64_t nfine = (L + kSelFine - 1) / kSelFine;
+    return nfine >= 4 * (int64_t)n_out && nfine >= 16384;
+}
+
 // Window-max form: the seeds (best raw scores), their ranks and neighbours, the walk.
 hipError_t launch_select_window(const float *scores, const SelectJob &job, int32_t *out_idx, int32_t *out_count,
                                 unsigned char *ws, const SelectLayout &lay, hipStream_t s, const FusedScores *fused)
@@ -1793,21 +1843,12 @@ hipError_t launch_select_window(const float *scores, const SelectJob &job, int32
     const int64_t L = job.L;
     const int n = job.combos();
     const int n_out = (int)(job.budget < L ? job.budget : L);
-    uint32_t *hist = (uint32_t *)(ws + lay.hist);
-    SelCtrl *ctrl = (SelCtrl *)(ws + lay.ctrl);  // [0] the seed combination, [1] the pruning pre-pass
-    uint32_t *done = (uint32_t *)(ws + lay.done);
-    uint64_t *cand = (uint64_t *)(ws + lay.cand);  // the seeds' keys
+    SeedState *st = (SeedState *)(ws + lay.state);  // [0] the seeds, [1] the pruning pre-pass
+    uint64_t *cand = (uint64_t *)(ws + lay.cand);
     uint64_t *tie = (uint64_t *)(ws + lay.tie);
     uint32_t *by_rank = (uint32_t *)(ws + lay.seed), *dom = by_rank + kCandCap;
+    const uint32_t want = (uint32_t)n_out;  // the best raw scores that are seeds
 
-    // the seed combination: window 1 on the scores, the n_out best wanted
-    SelParams prm{};
-    prm.n = 1;
-    prm.exact = 0;
-    prm.share[0] = (uint32_t)n_out;
-    prm.want[0] = (uint32_t)n_out;
-    prm.len[0] = (uint32_t)L;
-    prm.cell[0] = 1;
     // B_c: floor(B / n), the first B mod n kernel sizes one more
     WalkArgs walk{};
     walk.n = n;
@@ -1819,74 +1860,77 @@ hipError_t launch_select_window(const float *scores, const SelectJob &job, int32
         walk.share[j] = (uint32_t)(base + (j < rem ? 1 : 0));
         if (r > r_max) r_max = r;
     }
-    walk.ctrl = ctrl;
+    walk.seeds = st;
     walk.pos = by_rank;
     walk.dom = dom;
 
     const uint32_t nfine = (uint32_t)((L + kSelFine - 1) / kSelFine);
     Entries ent{nullptr, nullptr};
     uint32_t entries = nfine;
-    const bool pruned = (int64_t)nfine >= 4 * (int64_t)n_out && nfine >= 16384;
+    const bool pruned = prunes(L, n_out);
     if (fused && pruned) {  // the pre-pass wants the finished scores
         const hipError_t e = launch_reduce_units(fused->partial, fused->nunits, fused->L, fused->rmax, fused->scores, s);
         if (e != hipSuccess) return e;
         fused = nullptr;
     }
+    auto start_search = [&](const float *vals, int64_t len) {
+        const double rank = (double)kBaseSamples * want / (double)len, spread = 4 * sqrt(rank) + 4;
+        const SeedInit init{vals, len, (uint32_t)std::min(rank + spread, kBaseSamples - 1.0), (uint32_t)std::max(rank - spread, 0.0)};
+        hipLaunchKernelGGL(seed_init, dim3(1), dim3(kThreads), 0, s, init, st);
+    };
+    if (!fused && !pruned) start_search(scores, L);
     if (pruned) {
         // Long contexts: only fine chunks whose maximum reaches the n_out-th largest chunk maximum (up to its
-        // 22-bit prefix) can hold one of the n_out best scores; visit only those.
+        // bin) can hold one of the n_out best scores; visit only those.
         float *cm = (float *)(ws + lay.cmax);
         uint32_t *active = (uint32_t *)(ws + lay.active);
-        uint32_t *phist = hist + 2 * (size_t)kSelBins;
-        SelCtrl *pctrl = ctrl + 1;
-        uint32_t *pdone = done + 2;
-        SelParams pp{};
-        pp.n = 1;
-        pp.len[0] = nfine;
-        pp.cell[0] = 1;
-        pp.want[0] = (uint32_t)n_out;
         const uint32_t nfine2 = (nfine + kSelFine - 1) / kSelFine;
         const Entries all{nullptr, nullptr};
         hipLaunchKernelGGL(chunk_max, dim3(2048), dim3(kPoolThreads), 0, s, scores, L, nfine, cm);
-        hipLaunchKernelGGL(sel_init, dim3(1), dim3(kThreads), 0, s, pp, phist, pctrl, pdone);
-        const uint32_t pblocks = pool_blocks((nfine2 + kRawBatch - 1) / kRawBatch, 1024);
-        hipLaunchKernelGGL(pool_hist<1>, dim3(pblocks), dim3(kPoolThreads), 0, s, cm, pctrl, phist, pdone, all);
-        hipLaunchKernelGGL(pool_hist<2>, dim3(pblocks), dim3(kPoolThreads), 0, s, cm, pctrl, phist, pdone, all);
+        start_search(cm, nfine);
+        hipLaunchKernelGGL(count_scores, dim3(pool_blocks((nfine2 + kRawBatch - 1) / kRawBatch, 256u)), dim3(kPoolThreads), 0, s, cm, (int64_t)nfine,
+                           want, st + 1, all);
         hipLaunchKernelGGL(mark_active, dim3((nfine + kPoolThreads * kMarkPerThread - 1) / (kPoolThreads * kMarkPerThread)), dim3(kPoolThreads), 0, s, cm,
-                           nfine, 0, pctrl, active);
-        ent = Entries{active, &pctrl->cand_n};
+                           nfine, st + 1, active);
+        ent = Entries{active, &st[1].active_n};
         // with a list the entry count is only known on the device: size the grid for the worst case the
         // pruning rule is meant for (a few times the budget) and let the wavefronts loop
         entries = 4u * (uint32_t)n_out + 1024u;
     }
-    // window 1: a wavefront takes kRawBatch fine chunks per round
-    const uint32_t batches = (entries + kRawBatch - 1) / kRawBatch;
-    const uint32_t hblocks = pool_blocks(batches, 256u), cblocks = pool_blocks(batches, 1024u);
-    hipLaunchKernelGGL(sel_init, dim3(1), dim3(kThreads), 0, s, prm, hist, ctrl, done);
+    KeyBins bins{};
     if (fused) {
-        // the last step of the scoring (sum of the partial score vectors) and the level-1 histogram in one pass
-        const uint32_t rblocks = pool_blocks((uint32_t)((fused->L + kSelFine - 1) / kSelFine + 1) / 2, 512u);
-        if (fused->rmax)
-            hipLaunchKernelGGL(reduce_hist1<1>, dim3(rblocks), dim3(kPoolThreads), 0, s, fused->partial, fused->nunits, fused->L,
-                               job.sink, fused->scores, ctrl, hist, done);
-        else
-            hipLaunchKernelGGL(reduce_hist1<0>, dim3(rblocks), dim3(kPoolThreads), 0, s, fused->partial, fused->nunits, fused->L,
-                               job.sink, fused->scores, ctrl, hist, done);
+        // the last step of the scoring (sum of the partial score vectors) and the histogram in one pass
+        bins = bins_of_mean(fused->mean);
+        const uint32_t groups = (uint32_t)((fused->L + 63) / 64);  // of 64 tokens
+        const bool wide = groups > 128u * kPoolWaves;
+        auto kernel = fused->rmax ? (wide ? reduce_count<1, 4> : reduce_count<1, 1>) : (wide ? reduce_count<0, 4> : reduce_count<0, 1>);
+        hipLaunchKernelGGL(kernel, dim3(pool_blocks(wide ? (groups + 3) / 4 : groups, 512u)), dim3(kPoolThreads), 0, s, fused->partial, fused->nunits,
+                           fused->L, job.sink, fused->scores, bins, want, st);
     } else {
-        hipLaunchKernelGGL(pool_hist<1>, dim3(hblocks), dim3(kPoolThreads), 0, s, scores, ctrl, hist, done, ent);
+        hipLaunchKernelGGL(count_scores, dim3(pool_blocks((entries + kRawBatch - 1) / kRawBatch, 256u)), dim3(kPoolThreads), 0, s, scores, L, want, st, ent);
     }
-    hipLaunchKernelGGL(pool_hist<2>, dim3(hblocks), dim3(kPoolThreads), 0, s, scores, ctrl, hist, done, ent);
-    hipLaunchKernelGGL(collect, dim3(cblocks), dim3(kPoolThreads), 0, s, scores, ctrl, cand, tie, ent);
-    hipLaunchKernelGGL(refine, dim3(1), dim3(kThreads), 0, s, ctrl, cand, tie, 0u);
+    // a fine chunk a wavefront while that is one workgroup a compute unit
+    if (entries <= (uint32_t)(kNumCU * kPoolWaves))
+        hipLaunchKernelGGL(collect<1>, dim3(pool_blocks(entries, kNumCU)), dim3(kPoolThreads), 0, s, scores, L, want, bins, !fused, st, cand, tie, ent);
+    else
+        hipLaunchKernelGGL(collect<kRawBatch>, dim3(pool_blocks((entries + kRawBatch - 1) / kRawBatch, 512u)), dim3(kPoolThreads), 0, s, scores, L, want,
+                           bins, !fused, st, cand, tie, ent);
     // at most n_out + kSelSmall <= kCandCap seeds
     const uint32_t max_seeds = (uint32_t)n_out + (uint32_t)kSelSmall;
     hipLaunchKernelGGL(seed_rank, dim3((max_seeds + kSeedRankThreads / 16 - 1) / (kSeedRankThreads / 16)), dim3(kSeedRankThreads),
-                       (size_t)((max_seeds + 127u) & ~127u) * sizeof(uint64_t), s, scores, L, ctrl, cand, 2 * r_max, by_rank, dom);
+                       (size_t)((max_seeds + 127u) & ~127u) * sizeof(uint64_t), s, scores, L, st, cand, tie, 2 * r_max, by_rank, dom);
     launch_walk<kWalkSeeds>(walk, job, n_out, ws, lay, out_idx, out_count, s);
     return hipGetLastError();
 }
 
 }  // namespace
+
+ClearWords select_clear_words(const SelectJob &job, const SelectLayout &lay, void *base)
+{
+    const int n_out = (int)(job.budget < job.L ? job.budget : job.L);
+    if (job.mode != kSelWindowMax || job.L == 0 || prunes(job.L, n_out)) return ClearWords{};
+    return ClearWords{(uint32_t *)((unsigned char *)base + lay.state), (uint32_t)(sizeof(SeedState) / sizeof(uint32_t))};
+}
 
 hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out_idx, int32_t *out_count,
                          void *workspace, const SelectLayout &lay, hipStream_t s, const FusedScores *fused)
@@ -1904,7 +1948,6 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
     uint64_t *tie = (uint64_t *)(ws + lay.tie);
     float *cells = (float *)(ws + lay.cells);
     WalkArgs walk{};
-    walk.ctrl = ctrl;
     walk.cand = cand;
 
     hipError_t e = set_select_attributes();
@@ -1923,7 +1966,6 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
     SelParams prm{};
     AvgParams ap{};
     prm.n = n;
-    prm.exact = 1u;
     const int base = budget / n, rem = budget % n;
     int64_t before = 0, tie_off = 0, len_max = 0;
     uint64_t cell_off = 0;

@@ -620,3 +620,55 @@ def test_averages_at_the_edges_of_their_chunks_and_bins(L, budget, mk, ak, kind)
     n = int(count.item())
     got = got.cpu().numpy()
     assert got[:n].tolist() == want.tolist() and (got[n:] == -1).all()
+
+
+SEED_CASES = [
+    # L, budget, sink, kind: where the K-th best lies among the histogram's bins -- inside the fine ones, in the coarse ones
+    # on either side, all in one bin (the boundary list is then radix-selected), below everything that is counted
+    (1, 1, 0, "random"), (255, 255, 0, "random"), (3000, 2999, 1, "random"), (9000, 8192, 0, "needles"), (20000, 60, 3, "negative"),
+    (300001, 3000, 0, "sign_mixed"), (300001, 500, 0, "flat"), (262144, 4096, 0, "one_bin"), (262145, 2000, 2, "huge_range"),
+    (262145, 8192, 0, "mostly_zero"), (4200001, 900, 1, "flat"), (4200001, 900, 0, "clustered"), (4200000, 64, 0, "negative"),
+]
+
+
+@pytest.mark.parametrize("L,budget,sink,kind", SEED_CASES, ids=[f"L{c[0]}_B{c[1]}_{c[3]}" for c in SEED_CASES])
+def test_seeds_of_any_distribution(L, budget, sink, kind):
+    _announce(f"seeds L={L} budget={budget} sink={sink} {kind}")
+    rng = np.random.default_rng(L + budget)
+    if kind == "negative":
+        s = (-1.0 - rng.random(L)).astype(np.float32)
+    elif kind == "sign_mixed":
+        s = rng.standard_normal(L).astype(np.float32)
+    elif kind == "flat":
+        s = (1.0 + 1e-6 * rng.standard_normal(L)).astype(np.float32)
+    elif kind == "one_bin":       # a sample never sees the two ends: the bulk, and the cut in it, are one coarse bin
+        s = np.where(np.arange(L) % 1024 == 0, np.where(np.arange(L) % 2048 == 0, 1e30, 1e-30), 1.5 + 0.4 * rng.random(L)).astype(np.float32)
+    elif kind == "huge_range":
+        s = np.exp2(rng.uniform(-140, 120, size=L)).astype(np.float32) * np.where(rng.random(L) < 0.5, -1, 1).astype(np.float32)
+    elif kind == "mostly_zero":
+        s = np.where(rng.random(L) < 0.01, rng.random(L), 0.0).astype(np.float32)
+    elif kind == "clustered":     # many seeds in few chunks: their maxima are far below the cut
+        s = (0.01 + 0.001 * rng.random(L)).astype(np.float32)
+        s[1000:9000] = 4 + 4 * rng.random(8000)
+    else:
+        s = _scores_for(kind, L, rng) if L > 300 else rng.random(L).astype(np.float32)
+    got = il.ilre_select(torch.from_numpy(s).cuda(), budget, (1, 3, 7), sink=sink)
+    torch.cuda.synchronize()
+    assert got.cpu().numpy().tolist() == oracle.allocate(s, (1, 3, 7), budget, sink=sink).tolist()
+
+
+@pytest.mark.parametrize("L,scale,qfactor,sink", [(70000, 0.0, 0.0, 0), (70000, 0.0, 1e-3, 1), (140001, 40.0, 1.0, 0), (9000, 40.0, 1.0, 2), (63, 0.0, 1.0, 0)],
+                         ids=["all_equal", "flat", "spiky", "spiky_short", "one_wavefront"])
+def test_recall_where_the_mean_says_little(L, scale, qfactor, sink):
+    """In the whole path the bins follow the scores' mean: scores all equal to it, nearly so, and nearly all far below it
+    (a few keys take everything); the selection is the oracle's on the GPU's own scores, and on the selection alone."""
+    _announce(f"recall L={L} scale={scale} q*{qfactor}")
+    inp = inputs.custom(L=L, Lq=16, Hq=8, Hkv=2, d=128, dtype="f32", n_spans=2 if L > 200 else 0, span_len=(8, 24), channel_scale=True, seed=5)
+    q, k = to_device(inp.q) * qfactor, to_device(inp.k)
+    budget = min(3000, L // 2)
+    for mode in (il.ILRE_SCORE_SUM, il.ILRE_SCORE_MAX):
+        idx, scores = il.ilre_recall(q, k, budget, (3, 7), score_mode=mode, sink=sink, scale=scale)
+        alone = il.ilre_select(scores, budget, (3, 7), sink=sink)
+        torch.cuda.synchronize()
+        want = oracle.allocate(scores.cpu().numpy(), (3, 7), budget, sink=sink).tolist()
+        assert idx.cpu().numpy().tolist() == want and alone.cpu().numpy().tolist() == want
