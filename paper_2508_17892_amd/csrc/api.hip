@@ -32,7 +32,7 @@ int fail(int status, const char *fmt, ...)
 size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
-    size_t part_m, part_z, flag, row_max, row_sumexp, row_off, wg_time, split_table, partial, select, total;
+    size_t part_m, part_z, flag, row_max, row_sumexp, wg_time, split_table, partial, select, total;
     ilre::SelectLayout sel;
 };
 
@@ -78,8 +78,6 @@ Layout make_layout(const ilre::ScorePlan &p, int64_t L, int64_t nrows, const ilr
     off = up256(off + (size_t)nrows * sizeof(float));
     l.row_sumexp = off;
     off = up256(off + (size_t)nrows * sizeof(float));
-    l.row_off = off;
-    off = up256(off + (size_t)p.nunits * p.rows_per_wg * sizeof(float));
     l.wg_time = off;
     off = up256(off + (size_t)p.grid * sizeof(uint32_t));
     l.split_table = off;
@@ -357,7 +355,6 @@ int ilre_col_scores(const void *q, const void *k_cache, int64_t L, int32_t Lq, i
     unsigned char *ws = (unsigned char *)opts->workspace;
     a.row_max = row_max;
     a.row_sumexp = row_sumexp;
-    a.row_off = (float *)(ws + lay.row_off);
     if (p.balanced) a.split_table = (int32_t *)(ws + lay.split_table);  // taken only if an ilre_row_stats of this shape left it there
     a.partial = (float *)(ws + lay.partial);
     a.dump = (float *)(ws + lay.flag) + 16;
@@ -424,18 +421,19 @@ int run_scoring(const void *q, const void *k_cache, int64_t L, int32_t Lq, int32
     a.part_z = (float *)(ws + lay.part_z);
     float *row_max = (float *)(ws + lay.row_max);
     float *row_sumexp = (float *)(ws + lay.row_sumexp);
-    a.row_off = (float *)(ws + lay.row_off);
+    a.merge = p.merge_in_cols;
     if (p.balanced) {
         a.wg_time = (uint32_t *)(ws + lay.wg_time);
         a.split_table = (int32_t *)(ws + lay.split_table);
     }
-    hipError_t e = ilre::launch_row_stats(p, a, row_max, row_sumexp, s, true, clear);
+    hipError_t e = ilre::launch_row_stats(p, a, row_max, row_sumexp, s);
     if (e != hipSuccess) return hip_fail(e, "row-statistics launch");
     a.row_max = row_max;
     a.row_sumexp = row_sumexp;
+    a.clear = clear;
     a.partial = (float *)(ws + lay.partial);
     a.dump = (float *)(ws + lay.flag) + 16;
-    e = ilre::launch_col_scores(p, a, opts->score_mode, out_scores, s, false, true);
+    e = ilre::launch_col_scores(p, a, opts->score_mode, out_scores, s, false);
     if (e != hipSuccess) return hip_fail(e, "column-score launch");
     // every row's probabilities sum to one: the scores' mean is rows / L, that of their row maxima at least 1 / L
     const bool rmax = opts->score_mode == ILRE_SCORE_MAX;

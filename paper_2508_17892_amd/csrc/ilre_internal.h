@@ -41,9 +41,16 @@ struct ScorePlan {
     int64_t tiles_per_split;
     int nunits;           // Hkv * nqb  (partial score vectors of pass 2)
     int grid;             // workgroups launched (a few may be idle padding for the XCD mapping)
+    bool merge_in_cols;   // whole path: pass 2 merges the partial row statistics (no launch in between)
     bool balanced;        // pass 2's token ranges are sized by the XCDs' speed in pass 1
     uint64_t table_tag;   // header of a range table made for this plan
     size_t lds_bytes_stats, lds_bytes_cols;
+};
+
+// Words a launch sets to zero on the side, for a kernel behind it.
+struct ClearWords {
+    uint32_t *at;  // 16-byte aligned (n = 0: nothing to clear)
+    uint32_t n;    // a multiple of 4
 };
 
 struct ScoreArgs {
@@ -63,27 +70,20 @@ struct ScoreArgs {
     uint64_t table_tag;
     // pass 2 (column scores)
     const float *row_max, *row_sumexp;  // [Hq*Lq]
-    float *row_off;                     // [nunits][rows_per_wg]: pass 2's exponent offsets in workgroup order
+    bool merge;                         // whole path: no row statistics, pass 2 merges the partials itself
+    ClearWords clear;                   // what pass 2 sets to zero on the side
     float *partial;                     // [nunits][L]
     float *dump;                        // 16 floats nobody reads: target of stores that have nothing to store
 };
 
 ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv);
 
-// Words a launch sets to zero on the side, for a kernel behind it.
-struct ClearWords {
-    uint32_t *at;  // 16-byte aligned (null: nothing to clear)
-    uint32_t n;    // a multiple of 4
-};
-
-// offsets = true also fills a.row_off, the table of pass 2's per-row exponent offsets, for a launch_col_scores
-// with have_offsets = true behind it (otherwise launch_col_scores derives the table from row_max / row_sumexp).
-hipError_t launch_row_stats(const ScorePlan &p, const ScoreArgs &a, float *row_max, float *row_sumexp,
-                            hipStream_t s, bool offsets = false, const ClearWords &clear = ClearWords{});
+// With a.merge the partials are all that is left behind.
+hipError_t launch_row_stats(const ScorePlan &p, const ScoreArgs &a, float *row_max, float *row_sumexp, hipStream_t s);
 // reduce = false leaves the per-unit partial score vectors in a.partial for launch_reduce_units (or for the
 // selection's first pass, which can do the reduction on its way).
 hipError_t launch_col_scores(const ScorePlan &p, const ScoreArgs &a, int score_mode, float *out_scores,
-                             hipStream_t s, bool reduce = true, bool have_offsets = false);
+                             hipStream_t s, bool reduce = true);
 hipError_t launch_reduce_units(const float *partial, int nunits, int64_t L, int rmax, float *out_scores, hipStream_t s);
 
 // ---------------------------------------------------------------- selection (Algorithm 1)

@@ -125,6 +125,53 @@ __device__ __forceinline__ void row_accumulate(const f32x16 &acc, float c, float
     for (int v = 0; v < 16; ++v) z[v & 3] += fast_exp2(fmaf(acc[v], c, nm));
 }
 
+// A row's exponent offset in pass 2 from its statistics in the natural-log units of Eq. 4.
+__device__ __forceinline__ float row_offset(float row_max, float row_sumexp) { return -(row_max * kLog2e + __log2f(row_sumexp)); }
+
+// The same straight from the per-split partials m[s*pitch], z[s*pitch], added up in the order of combine_row_stats: the
+// splits are dealt to kCombineLanes sums, which a tree of neighbours reduces.  SHARERS threads (1, or 2 neighbouring
+// lanes) share a row, each with its kCombineLanes / SHARERS sums.  All loads are in flight together, next to those of
+// the first K tiles.  It saves a launch of 3.8 - 5 us; on the other hand every workgroup of a kv head reads all of the
+// head's partials.  Measured, merge kernel -> this, whole recall: 16 splits (1000 tokens) 33.1 -> 29.1 us, 32 splits
+// (40000 tokens, 32/8 heads, 128 queries) 115.4 -> 113.9 us; 64 splits (20000 tokens fp32) 132.4 -> 134.2 us,
+// 256 splits (100000 tokens, 8/2 heads, 64 queries) 72.2 -> 86.9 us: two splits a sum is where it stops to pay.
+constexpr int kCombineLanes = 16;
+constexpr int kMergeSplits = 2 * kCombineLanes;
+template <int SHARERS>
+__device__ __forceinline__ float merged_offset(const float *pm, const float *pz, int nsplit, int64_t pitch, int part)
+{
+    constexpr int OWN = kCombineLanes / SHARERS, ROUNDS = kMergeSplits / kCombineLanes;
+    float m[ROUNDS][OWN], z[ROUNDS][OWN];
+#pragma unroll
+    for (int k = 0; k < ROUNDS; ++k)
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) {
+            const int s = k * kCombineLanes + part * OWN + i;
+            const int64_t at = (int64_t)(s < nsplit ? s : nsplit - 1) * pitch;
+            m[k][i] = pm[at];
+            z[k][i] = pz[at];
+        }
+    float mm = kNegBig, sum[OWN];
+#pragma unroll
+    for (int k = 0; k < ROUNDS; ++k)
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) mm = fmaxf(mm, m[k][i]);
+    if (SHARERS == 2) mm = fmaxf(mm, quad_swap1(mm));
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) sum[i] = 0.f;
+#pragma unroll
+    for (int k = 0; k < ROUNDS; ++k)
+#pragma unroll
+        for (int i = 0; i < OWN; ++i)
+            if (k * kCombineLanes + part * OWN + i < nsplit) sum[i] += z[k][i] * fast_exp2(m[k][i] - mm);
+#pragma unroll
+    for (int o = 1; o < OWN; o <<= 1)
+#pragma unroll
+        for (int i = 0; i < OWN; i += 2 * o) sum[i] += sum[i + o];
+    if (SHARERS == 2) sum[0] += quad_swap1(sum[0]);
+    return row_offset(mm * kLn2, sum[0]);
+}
+
 // MODE 0: row statistics.  MODE 1: column scores (RMAX = 0 sum over rows, 1 max over rows).
 template <int DT, int NB, int WAVES, int MODE, int RMAX>
 __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
@@ -163,6 +210,9 @@ __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
     const bool timed = MODE == 0 && a.wg_time != nullptr && threadIdx.x == 0;
     const unsigned long long t_begin = timed ? wall_clock64() : 0ull;
     if (timed) a.wg_time[blockIdx.x] = 0u;
+    // what the selection counts in is cleared on the side (a launch of its own took 4.7 us)
+    if (MODE == 1 && blockIdx.x == 0)
+        for (uint32_t i = threadIdx.x * 4; i < a.clear.n; i += WAVES * 64 * 4) *(uint4 *)&a.clear.at[i] = make_uint4(0, 0, 0, 0);
     if (pair >= (int64_t)a.Hkv * a.nsplit) return;
     const int g = (int)(pair / a.nsplit);
     const int split = (int)(pair % a.nsplit);
@@ -252,6 +302,12 @@ __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
     // relative to the tile buffer being read; advanced from buffer to buffer in place
     unsigned frag_addr[STEPS];
 
+    // the first two tiles go to buffers 0 and 1
+    auto issue_first = [&]() {
+        issue_tile(tile0, 0);
+        if (tile0 + 1 < tile1) issue_tile(tile0 + 1, 1);
+    };
+
     // pass-1 state: one (max, sum) per owned query row, in base-2 exponent units
     float m[NB], z[NB][4];
     // pass-2 state: per accumulator register the row's exponent offset -(max*log2e + log2 sum)
@@ -267,21 +323,33 @@ __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
             for (int k = 0; k < 4; ++k) z[b][k] = 0.f;
         }
     } else {
-        // the workgroup's slice of the offset table (filled before this launch: one entry per query row in the
-        // order the workgroups own them, -inf for padded rows, whose q = 0: exp2(0*c - inf) = 0); accumulator
-        // registers 4j .. 4j+3 of a lane are four consecutive rows
-        const float4 *off4 = (const float4 *)(a.row_off + (int64_t)unit * (WAVES * NB * 32) + wave * (NB * 32));
+        // The exponent offsets of the workgroup's rows, one row a thread (NB = 1: a pair of threads), handed out through
+        // LDS (a kernel that wrote them to a table before took 4.7 us of a staged call: 50001 tokens 149.9 -> 146.9 us): accumulator registers 4j .. 4j+3 of a lane are four consecutive rows.  Rows past the group's last one,
+        // whose q = 0, get -inf: exp2(0*c - inf) = 0.
+        issue_first();  // K and Q are on their way meanwhile
+        constexpr int ROWS = WAVES * NB * 32, SHARERS = WAVES * 64 / ROWS;
+        const int local = tid / SHARERS, rl = qb * ROWS + local;
+        const bool real = rl < a.rows_per_group;
+        const int64_t r = (int64_t)g * a.rows_per_group + (real ? rl : a.rows_per_group - 1);
+        float off;
+        if (a.merge)
+            off = merged_offset<SHARERS>(a.part_m + r, a.part_z + r, a.nsplit, nrows, tid % SHARERS);
+        else
+            off = row_offset(a.row_max[r], a.row_sumexp[r]);
+        if (tid % SHARERS == 0) red[local] = real ? off : -INFINITY;
+        __syncthreads();
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const float4 x = off4[(b * 32 + 8 * j + 4 * half) / 4];
+                const float4 x = *(const float4 *)&red[wave * (NB * 32) + b * 32 + 8 * j + 4 * half];
                 noff[b][4 * j + 0] = x.x;
                 noff[b][4 * j + 1] = x.y;
                 noff[b][4 * j + 2] = x.z;
                 noff[b][4 * j + 3] = x.w;
             }
         }
+        // (the buffers are written again only behind the barrier in front of the first tile)
     }
 
     // Pass 2: combine the NPART partial column results of a finished tile in a fixed order.  Wave w
@@ -358,9 +426,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
     auto start_split = [&]() {
 #pragma unroll
         for (int st = 0; st < STEPS; ++st) frag_addr[st] = lds0 + l32 * ROWB + (((2 * st + half) ^ (l32 & 15)) * 16);
-        // Prologue: the first two tiles go to buffers 0 and 1.
-        issue_tile(tile0, 0);
-        if (tile0 + 1 < tile1) issue_tile(tile0 + 1, 1);
+        if (MODE == 0) issue_first();
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
 
@@ -515,33 +581,11 @@ __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
     }
 }
 
-// Pass 2's per-row exponent offsets, -(max*log2e + log2 sum), laid out in the order the workgroups own the rows:
-// entry (unit, local) is row `qb*rows_per_wg + local` of kv head g's group, unit = g*nqb + qb; rows past the
-// group's last one (padding of the last query block) get -inf.  Done once here rather than by every lane of
-// every workgroup of the column-score kernel, whose row indices cost two integer divisions each.
-__global__ __launch_bounds__(256) void row_offsets_kernel(const float *row_max, const float *row_sumexp, float *row_off, int entries,
-                                                          int rows_per_wg, int nqb, int rows_per_group, int G, int Lq)
-{
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= entries) return;
-    const int unit = e / rows_per_wg, local = e % rows_per_wg;
-    const int g = unit / nqb, qb = unit % nqb;
-    const int rl = qb * rows_per_wg + local;
-    float off = -INFINITY;
-    if (rl < rows_per_group) {
-        const int64_t r = (int64_t)(g * G + rl / Lq) * Lq + rl % Lq;
-        off = -(row_max[r] * kLog2e + __log2f(row_sumexp[r]));
-    }
-    row_off[e] = off;
-}
-
 // Merge the per-split partial statistics of each row (fixed order) and convert to the natural-log units of
 // Eq. 4: row_max = a reference <= max_t logit, row_sumexp = sum_t exp(logit - row_max).
 // Sixteen lanes share a row and the splits among them, so that all of a row's partials are fetched in one
 // round of loads (a thread a row would fetch them in a chain of memory latencies: this kernel sits between
 // the two scoring passes and is all latency).
-constexpr int kCombineLanes = 16;
-// Where the offset of row rl of kv head g's group sits in pass 2's table (see row_offsets_kernel).
 // Pass 2's token ranges from pass 1's workgroup times.  The 8 XCDs of the chip do not run at one speed (their
 // workgroups finish up to 6 % apart, the same dies ahead in every launch), and a launch lasts as long as its
 // slowest XCD.  Split s of every kv head runs on the same XCD when the splits per head are a multiple of 8, so
@@ -624,29 +668,19 @@ __device__ void make_split_table(const BalanceArgs &b)
     }
 }
 
-struct OffsetTable {
-    float *row_off;  // null: not wanted
-    int group_entries;  // nqb * rows_per_wg: entries per kv head, of which the first rows_per_group are rows
-    int rows_per_group, G, Lq, Hkv;
-};
 __global__ __launch_bounds__(256) void combine_row_stats(const float *part_m, const float *part_z, int nsplit, int64_t nrows,
-                                                         float *row_max, float *row_sumexp, const OffsetTable tab,
-                                                         const BalanceArgs bal, const ClearWords clear, unsigned stat_blocks)
+                                                         float *row_max, float *row_sumexp, const BalanceArgs bal,
+                                                         unsigned stat_blocks)
 {
     constexpr int kBlock = 4;
-    if (blockIdx.x >= stat_blocks) {
-        if (bal.wg_time && blockIdx.x == stat_blocks) {  // one workgroup is there for the table alone
-            make_split_table(bal);
-            return;
-        }
-        // the last one clears what the selection counts in (a launch of its own took 4.7 us)
-        for (uint32_t i = threadIdx.x * 4; i < clear.n; i += blockDim.x * 4) *(uint4 *)&clear.at[i] = make_uint4(0, 0, 0, 0);
+    if (blockIdx.x >= stat_blocks) {  // one workgroup is there for the table alone
+        make_split_table(bal);
         return;
     }
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t r = gid / kCombineLanes;
     const int sub = (int)(gid % kCombineLanes);
-    const int64_t rr = r < nrows ? r : nrows - 1;  // surplus groups redo the last row and store no statistics
+    const int64_t rr = r < nrows ? r : nrows - 1;  // surplus groups redo the last row and store nothing
     float mm = kNegBig;
     for (int s0 = sub; s0 < nsplit; s0 += kCombineLanes * kBlock) {
         float m[kBlock];
@@ -676,23 +710,9 @@ __global__ __launch_bounds__(256) void combine_row_stats(const float *part_m, co
     }
 #pragma unroll
     for (int o = 1; o < kCombineLanes; o <<= 1) zz += __shfl_xor(zz, o);
-    if (sub != 0) return;
-    if (r < nrows) {
-        row_max[r] = mm * kLn2;
-        row_sumexp[r] = zz;
-        if (tab.row_off) {
-            // the same value row_offsets_kernel derives from the two outputs just written
-            const int h = (int)(r / tab.Lq), i = (int)(r % tab.Lq);
-            const int rl = (h % tab.G) * tab.Lq + i;
-            tab.row_off[(int64_t)(h / tab.G) * tab.group_entries + rl] = -((mm * kLn2) * kLog2e + __log2f(zz));
-        }
-    } else if (tab.row_off) {
-        // surplus groups fill the table's padding (rows past a group's last one)
-        const int pad_per_group = tab.group_entries - tab.rows_per_group;
-        const int64_t p = r - nrows;
-        if (p < (int64_t)pad_per_group * tab.Hkv)
-            tab.row_off[(p / pad_per_group) * tab.group_entries + tab.rows_per_group + p % pad_per_group] = -INFINITY;
-    }
+    if (sub != 0 || r >= nrows) return;
+    row_max[r] = mm * kLn2;
+    row_sumexp[r] = zz;
 }
 
 // score[t] = sum (or max) over the (kv head, query block) units of their partial column results.
@@ -790,6 +810,7 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv)
     const size_t tiles = dtype == ILRE_F32 ? tile_lds_bytes<ILRE_F32>(p.waves) : tile_lds_bytes<ILRE_BF16>(p.waves);
     // pass 2's ranges follow the XCDs' speed where a range is long enough for that to matter
     p.balanced = p.tiles_per_split >= 64 && p.nsplit >= kNumXCD && p.nsplit <= kMaxBalancedSplits;
+    p.merge_in_cols = !p.balanced && p.nsplit <= kMergeSplits;
     uint64_t tag = 0x494c52652d584344ull;  // what a table has to have been made for
     for (uint64_t v : {(uint64_t)L, (uint64_t)p.ntiles, (uint64_t)p.nsplit, (uint64_t)p.nqb, (uint64_t)Hkv, (uint64_t)p.tile_tokens,
                        (uint64_t)p.grid})
@@ -800,8 +821,7 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv)
     return p;
 }
 
-hipError_t launch_row_stats(const ScorePlan &p, const ScoreArgs &a, float *row_max, float *row_sumexp, hipStream_t s, bool offsets,
-                            const ClearWords &clear)
+hipError_t launch_row_stats(const ScorePlan &p, const ScoreArgs &a, float *row_max, float *row_sumexp, hipStream_t s)
 {
     // One launch: a workgroup whose sums against frozen references leave the safe range walks its split a second
     // time in the always-safe form before it writes its partials.
@@ -817,14 +837,12 @@ hipError_t launch_row_stats(const ScorePlan &p, const ScoreArgs &a, float *row_m
     else
         e = launch_score(score_kernel<ILRE_BF16, 2, 8, 0, 0>, p.grid, 512, lds, a, s);
     if (e != hipSuccess) return e;
-    const OffsetTable tab{offsets ? a.row_off : nullptr, p.nqb * p.rows_per_wg, p.rows_per_group, a.G, a.Lq, a.Hkv};
-    // one 16-lane group per row, and with the table one more per padded table entry
-    const int64_t groups = nrows + (offsets ? (int64_t)(tab.group_entries - tab.rows_per_group) * a.Hkv : 0);
+    if (a.merge) return hipSuccess;  // pass 2 takes the partials
     const bool balance = a.wg_time != nullptr && a.split_table != nullptr;
     const BalanceArgs bal{balance ? a.wg_time : nullptr, a.split_table, a.table_tag, p.grid, p.nqb, p.nsplit, a.Hkv, p.ntiles};
-    const unsigned stat_blocks = (unsigned)((groups * kCombineLanes + 255) / 256);
-    hipLaunchKernelGGL(combine_row_stats, dim3(stat_blocks + (balance ? 1u : 0u) + (clear.at ? 1u : 0u)), dim3(256), 0, s, a.part_m, a.part_z,
-                       a.nsplit, nrows, row_max, row_sumexp, tab, bal, clear, stat_blocks);
+    const unsigned stat_blocks = (unsigned)((nrows * kCombineLanes + 255) / 256);
+    hipLaunchKernelGGL(combine_row_stats, dim3(stat_blocks + (balance ? 1u : 0u)), dim3(256), 0, s, a.part_m, a.part_z, a.nsplit, nrows,
+                       row_max, row_sumexp, bal, stat_blocks);
     return hipGetLastError();
 }
 
@@ -838,17 +856,11 @@ hipError_t launch_reduce_units(const float *partial, int nunits, int64_t L, int 
     return hipGetLastError();
 }
 
-hipError_t launch_col_scores(const ScorePlan &p, const ScoreArgs &a, int score_mode, float *out_scores, hipStream_t s, bool reduce,
-                             bool have_offsets)
+hipError_t launch_col_scores(const ScorePlan &p, const ScoreArgs &a, int score_mode, float *out_scores, hipStream_t s, bool reduce)
 {
     hipError_t e;
     const size_t lds = p.lds_bytes_cols;
     const bool mx = score_mode == ILRE_SCORE_MAX;
-    if (!have_offsets) {
-        const int entries = p.nunits * p.rows_per_wg;
-        hipLaunchKernelGGL(row_offsets_kernel, dim3((unsigned)((entries + 255) / 256)), dim3(256), 0, s, a.row_max, a.row_sumexp,
-                           a.row_off, entries, p.rows_per_wg, p.nqb, p.rows_per_group, a.G, a.Lq);
-    }
     if (p.dtype == ILRE_F32)
         e = mx ? launch_score(score_kernel<ILRE_F32, 1, 4, 1, 1>, p.grid, 256, lds, a, s)
                : launch_score(score_kernel<ILRE_F32, 1, 4, 1, 0>, p.grid, 256, lds, a, s);
