@@ -648,6 +648,39 @@ def test_averages_at_the_edges_of_their_chunks_and_bins(L, budget, mk, ak, kind)
     assert got[:n].tolist() == want.tolist() and (got[n:] == -1).all()
 
 
+RANK_CASES = [
+    # L, budget, copies of a value, kind: lists of one element up to the 4096 that the counting sort takes and one more, bins
+    # of up to 128 equal elements (ranked inside the bin) and one more (the network), ranges of one value and of all
+    (1, 1, 1, "random"), (64, 64, 1, "random"), (1025, 1025, 1, "random"), (4096, 4096, 1, "random"), (4097, 4097, 1, "random"),
+    (4096, 4000, 127, "copies"), (4096, 4000, 128, "copies"), (4096, 4000, 129, "copies"), (4096, 4096, 4096, "copies"),
+    (4000, 4000, 1, "two_ends"), (128, 128, 128, "copies"), (4096, 4096, 2, "signs"), (9000, 2000, 3, "signs"),
+]
+
+
+@pytest.mark.parametrize("L,budget,copies,kind", RANK_CASES, ids=[f"L{c[0]}_B{c[1]}_{c[2]}x_{c[3]}" for c in RANK_CASES])
+def test_rank_order_of_a_combinations_list(L, budget, copies, kind):
+    """One cell a token, no averaging: the list is ranked scores, bit-exact with the oracle.  A second combination takes
+    what the first one's rank order left, so an exchange inside a list shows in what is allocated."""
+    _announce(f"rank order L={L} budget={budget} copies={copies} {kind}")
+    rng = np.random.default_rng(L + budget + copies)
+    s = np.repeat((1 + rng.permutation((L + copies - 1) // copies)).astype(np.float32), copies)[:L]
+    if kind == "two_ends":        # two bins hold everything
+        s = np.where(rng.random(L) < 0.5, 1e30, 1e-30).astype(np.float32) * (1 + 0.01 * rng.random(L)).astype(np.float32)
+    elif kind == "signs":
+        s *= np.where(rng.random(L) < 0.5, -1, 1).astype(np.float32)
+    elif kind == "random":
+        s = rng.random(L).astype(np.float32)
+    s = s[rng.permutation(L)]
+    for mk, ak in (((1,), (1,)), ((1,), (1, 2, 3)), ((2, 1), (1, 3))):
+        for b in sorted({budget, max(1, budget // 2), max(1, budget // 7)}):
+            want = oracle.allocate_max_avg(s, mk, ak, b, sink=0)
+            got, count = il.ilre_select_max_avg(torch.from_numpy(s).cuda(), b, mk, ak, 0)
+            torch.cuda.synchronize()
+            n = int(count.item())
+            got = got.cpu().numpy()
+            assert got[:n].tolist() == want.tolist() and (got[n:] == -1).all(), (mk, ak, b)
+
+
 SEED_CASES = [
     # L, budget, sink, kind: where the K-th best lies among the histogram's bins -- inside the fine ones, in the coarse ones
     # on either side, all in one bin (the boundary list is then radix-selected), below everything that is counted
