@@ -745,7 +745,8 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
 
     // average kernel q's numbers are lane q's, in every wavefront (SMALL: the one of size n has number n - 1)
     uint32_t l_size, l_want;
-    float l_edge;  // the sum from which on elements matter to this pass
+    uint32_t l_len;  // SMALL: elements of that size: none of a size that was not asked for (an edge alone would let sums of +inf pass)
+    float l_edge;    // the sum from which on elements matter to this pass
     {
         uint32_t q, at;
         if (SMALL) {
@@ -762,7 +763,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
         l_want = ctrl[j].want;
         l_edge = ctrl[j].edge * (float)l_size;
         if (PASS == 1) l_edge = cut ? __uint_as_float(__float_as_uint(l_edge) + ((cut - 1) << kAvgBinShift)) * (1.0f - 0x1p-21f) : -INFINITY;
-        if (!used) l_edge = INFINITY;
+        l_len = used ? len : 0u;
         if ((int)threadIdx.x < rows) {
             c_comb[threadIdx.x] = used ? j : 0xFFFFFFFFu;
             c_count[threadIdx.x] = 0;
@@ -800,12 +801,12 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
 #pragma unroll
             for (int u = 0; u < kAvgGroup; ++u) {
                 const float edge = of_f(l_edge, u);
-                const uint32_t before = queued;
+                const uint32_t before = queued, els = of(l_len, u);
                 float best = -INFINITY;
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
                     sum[k] = sum[k] + buf[lane + 64 * k + u];
-                    const bool in = el0 + 64u * k + u / 2 < len;
+                    const bool in = el0 + 64u * k + u / 2 < els;
                     // (positive floats are ordered like their bits; what is not counted goes to a word of the lane's own)
                     auto count = [&](float x, bool hit) {
                         const uint32_t bin = min((__float_as_uint(x) - __float_as_uint(edge)) >> kAvgBinShift, (uint32_t)kAvgBins - 1u);

@@ -648,6 +648,29 @@ def test_averages_at_the_edges_of_their_chunks_and_bins(L, budget, mk, ak, kind)
     assert got[:n].tolist() == want.tolist() and (got[n:] == -1).all()
 
 
+@pytest.mark.parametrize("ak", [tuple(range(1, 10)), (5,), (2, 7, 16), tuple(range(1, 17))], ids=["1_to_9", "5_alone", "2_7_16", "1_to_16"])
+@pytest.mark.parametrize("top", [3e37, 3.2e38, -3e37], ids=["9_cells_finite", "2_cells_infinite", "negative"])
+def test_averages_of_scores_near_the_largest_float(top, ak):
+    """Finite scores whose window sums pass the largest float: of sizes up to 16 a window sum is formed whether the size was
+    asked for or not, and a sum of +inf must not count for one that was not.  Both ways of counting (a share of a small and
+    of a large part of the cells), a span inside and one at the end of the body."""
+    _announce(f"averages near the largest float: {top} {ak}")
+    rng = np.random.default_rng(7)
+    L = 9001
+    s = rng.random(L).astype(np.float32)
+    s[3000:3040] = np.float32(top) * (0.9 + 0.1 * rng.random(40)).astype(np.float32)
+    s[-20:] = np.float32(top)
+    for mk in ((2, 4), (1,), (3,)):
+        for budget in (100, 5000):
+            with np.errstate(over="ignore"):
+                want = oracle.allocate_max_avg(s, mk, ak, budget, sink=1)
+            got, count = il.ilre_select_max_avg(torch.from_numpy(s).cuda(), budget, mk, ak, 1)
+            torch.cuda.synchronize()
+            n = int(count.item())
+            got = got.cpu().numpy()
+            assert got[:n].tolist() == want.tolist() and (got[n:] == -1).all(), (mk, budget)
+
+
 RANK_CASES = [
     # L, budget, copies of a value, kind: lists of one element up to the 4096 that the counting sort takes and one more, bins
     # of up to 128 equal elements (ranked inside the bin) and one more (the network), ranges of one value and of all
