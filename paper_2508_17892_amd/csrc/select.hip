@@ -181,10 +181,22 @@ __device__ __forceinline__ uint32_t block_scan_inclusive(uint32_t x, uint32_t *w
     return x + before;
 }
 
+// Samples of n elements: one at a hashed place in each of kBaseSamples equal parts, because scores have a structure
+// (the first token of every chunk, the sink at the very front) that a regular grid can fall in with.
+constexpr int kBaseSamples = 256;
+__device__ __forceinline__ int64_t sample_at(uint32_t t, int64_t n)
+{
+    const int64_t begin = (int64_t)t * n / kBaseSamples, end = (int64_t)(t + 1) * n / kBaseSamples;
+    uint32_t h = (t + 1) * 0x9E3779B1u;
+    h = (h ^ (h >> 15)) * 0x85EBCA77u;
+    h = (h ^ (h >> 13)) * 0xC2B2AE3Du;
+    h ^= h >> 16;
+    return begin + (int64_t)(((uint64_t)h * (uint64_t)(end - begin)) >> 32);
+}
+
 // Where the bins of scores of unknown scale start: at the median of a sample (the K_j-th best is above it), or below
 // its minimum for a combination that wants a large part of the elements.  Any edge gives the same result; one far off
 // puts everything into one bin.
-constexpr int kBaseSamples = 256;
 __device__ float sampled_edge(const float *scores, int64_t n, bool deep)
 {
     __shared__ __align__(16) uint32_t key[kBaseSamples];
@@ -193,7 +205,7 @@ __device__ float sampled_edge(const float *scores, int64_t n, bool deep)
     const int t = threadIdx.x;
     float x = 0.f;
     if (t < kBaseSamples) {
-        x = scores[(int64_t)t * n / kBaseSamples];
+        x = scores[sample_at(t, n)];
         key[t] = ordered_bits(x);
         above[t] = 0;
     }
@@ -251,9 +263,11 @@ __device__ __forceinline__ uint32_t bin_of(const KeyBins &b, uint32_t key)
 }
 
 // Clears the states of a seed search on scores of unknown scale and places the bins by a sample of what is counted first:
-// the scores, or the maxima of fine chunks.  `lo` and `hi` are the sample's ranks (0: the largest) that enclose the K-th
-// largest with four standard deviations of a sample's count; between those two keys lie half of the bins, the others
-// cover all keys below (two binades each) and above.  Whatever the sample is, the result is the same.
+// the scores, or the maxima of fine chunks.  `lo` and `hi` are the sample's ranks (0: the largest) four standard deviations
+// of a sample's count to either side of the K-th largest, `hi` at least 2: one or two samples may be far above everything
+// else.  Where few elements are wanted the K-th largest then lies above `hi` more often than not (up to a few hundredths
+// of all elements do), so the middle half of the bins reaches as far above it as from `lo` to it.  The others cover all
+// keys below (two binades each) and above.  Whatever the sample is, the result is the same.
 struct SeedInit {
     const float *vals;
     int64_t n;
@@ -268,7 +282,7 @@ __global__ __launch_bounds__(kThreads) void seed_init(const SeedInit p, SeedStat
     for (int i = threadIdx.x; i < 2 * kWords; i += kThreads)
         if (i % kWords >= kKept) ((uint4 *)st)[i] = make_uint4(0, 0, 0, 0);
     const uint32_t u = threadIdx.x >> 2, part = threadIdx.x & 3;
-    const uint32_t k = ordered_bits(p.vals[(int64_t)u * p.n / kBaseSamples]);
+    const uint32_t k = ordered_bits(p.vals[sample_at(u, p.n)]);
     if (part == 0) key[u] = k;
     __syncthreads();
     uint32_t c = 0;
@@ -284,7 +298,7 @@ __global__ __launch_bounds__(kThreads) void seed_init(const SeedInit p, SeedStat
         KeyBins b{};
         b.k0 = 0, b.s0 = 24;
         b.k1 = bound[0];
-        b.k2 = max(bound[1], min(bound[1] + 1u, 0xFFFFFFFFu - 1u));
+        b.k2 = bound[1] + min(max(bound[1] - bound[0], 1u), 0xFFFFFFFEu - bound[1]);
         b.s1 = b.s2 = 0;
         while ((b.k2 - b.k1) >> b.s1 >= kMid) ++b.s1;
         while ((0xFFFFFFFFu - b.k2) >> b.s2 >= kHigh) ++b.s2;
@@ -1979,7 +1993,7 @@ hipError_t launch_select_window(const float *scores, const SelectJob &job, int32
     }
     auto start_search = [&](const float *vals, int64_t len) {
         const double rank = (double)kBaseSamples * want / (double)len, spread = 4 * sqrt(rank) + 4;
-        const SeedInit init{vals, len, (uint32_t)std::min(rank + spread, kBaseSamples - 1.0), (uint32_t)std::max(rank - spread, 0.0)};
+        const SeedInit init{vals, len, (uint32_t)std::min(rank + spread, kBaseSamples - 1.0), (uint32_t)std::max(rank - spread, 2.0)};
         hipLaunchKernelGGL(seed_init, dim3(1), dim3(kThreads), 0, s, init, st);
     };
     if (!fused && !pruned) start_search(scores, L);

@@ -754,3 +754,52 @@ def test_recall_where_the_mean_says_little(L, scale, qfactor, sink):
         torch.cuda.synchronize()
         want = oracle.allocate(scores.cpu().numpy(), (3, 7), budget, sink=sink).tolist()
         assert idx.cpu().numpy().tolist() == want and alone.cpu().numpy().tolist() == want
+
+
+def _device_us(call, rounds=5, reps=4):
+    """Time of one call in a row of them, the best of a few rounds."""
+    call()
+    best = float("inf")
+    for _ in range(rounds):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        for _ in range(reps):
+            call()
+        end.record()
+        end.synchronize()
+        best = min(best, begin.elapsed_time(end) * 1000 / reps)
+    return best
+
+
+def _raised(L, seed, every=0, first=0.0):
+    """A dense background, every so many tokens three times as high, the first token on its own."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    s = torch.randn(L, device="cuda", generator=g).mul_(0.0024).add_(0.008).clamp_(min=1e-4)
+    if every:
+        s[::every] *= 3
+    if first:
+        s[0] = first
+    return s
+
+
+@pytest.mark.parametrize("L,every,first", [(1 << 20, 1024, 0.0), (1 << 17, 1024, 0.0), (5 << 20, 0, 1e6)],
+                         ids=["chunk_starts_1M", "chunk_starts_128K", "sink_5M"])
+def test_time_of_a_selection_does_not_follow_the_places_of_its_scores(L, every, first):
+    """The histogram's bins are placed by a sample.  High scores on a regular grid, or at the very front, are as quickly
+    sorted out as the same scores in random places (when the sample fell in with the grid: 10 times as long on 1M tokens).
+    Three times as long is far from what two runs differ by."""
+    _announce(f"time of a selection, L={L} every {every} first {first}")
+    s = _raised(L, 3, every, first)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4)
+    mixed = s[torch.randperm(L, device="cuda", generator=g)].contiguous()
+    ws = il.alloc_workspace(L, 1, 1, 1, 128, 3, il.ILRE_F32)
+    out = il.ilre_select(s, 4096, (1, 3, 7), workspace=ws)
+    torch.cuda.synchronize()
+    if L <= 1 << 20:
+        assert out.cpu().numpy().tolist() == oracle.allocate(s.cpu().numpy(), (1, 3, 7), 4096).tolist()
+    as_it_is = _device_us(lambda: il.ilre_select(s, 4096, (1, 3, 7), workspace=ws))
+    at_random = _device_us(lambda: il.ilre_select(mixed, 4096, (1, 3, 7), workspace=ws))
+    print(f"{as_it_is:.1f} us, in random places {at_random:.1f} us", flush=True)
+    assert as_it_is < 3 * at_random + 10
