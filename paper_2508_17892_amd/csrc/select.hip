@@ -953,28 +953,46 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
 
 // Of the `need` largest of A's nA distinct keys those that a radix selection finds on its way are appended to
 // cand[candn ..]; the rest is among the remaining list, which shrinks by 8 key bits a pass, from A into B and back.
-// Stops when what there is fits `keep`, or is exactly what is needed.  By one workgroup.
+// Stops when what there is fits `keep`, or is exactly what is needed.  By one workgroup.  Keys that share all of a
+// digit (equal values do in all of theirs) cost one pass, which also says where they differ first; lanes that share
+// one count with a single addition.
 template <int THREADS>
 __device__ void peel(uint64_t *&A, uint64_t *&B, uint32_t &nA, uint32_t &need, uint64_t *cand, uint32_t &candn, uint32_t keep)
 {
     __shared__ uint32_t h[256];
     __shared__ uint32_t cnt[2];
     __shared__ uint32_t pick[3];  // digit, count above it, count in it
-    constexpr int kBatch = 8;     // keys a thread has in flight
+    __shared__ unsigned long long differ;  // bits in which keys differ
+    constexpr int kBatch = 8;  // keys a thread has in flight
     const int lane = threadIdx.x & 63;
-    for (int shift = 56; shift >= 0 && nA + candn > keep && need < nA; shift -= 8) {
+    int shift = 56;
+    while (nA + candn > keep && need < nA) {
         __syncthreads();
         if (threadIdx.x < 256) h[threadIdx.x] = 0;
         if (threadIdx.x < 2) cnt[threadIdx.x] = 0;
+        if (threadIdx.x == 0) differ = 0;
         __syncthreads();
-        for (uint32_t i0 = threadIdx.x; i0 < nA; i0 += THREADS * kBatch) {
+        const uint64_t any = load_u64(&A[0]);
+        uint64_t bits = 0;
+        for (uint32_t first = 0; first < nA; first += THREADS * kBatch) {  // uniform
             uint64_t key[kBatch];
 #pragma unroll
-            for (int b = 0; b < kBatch; ++b) key[b] = load_u64(&A[min(i0 + b * THREADS, nA - 1)]);
+            for (int b = 0; b < kBatch; ++b) key[b] = load_u64(&A[min(first + b * THREADS + threadIdx.x, nA - 1)]);
 #pragma unroll
-            for (int b = 0; b < kBatch; ++b)
-                if (i0 + b * THREADS < nA) atomicAdd(&h[(key[b] >> shift) & 255u], 1u);
+            for (int b = 0; b < kBatch; ++b) {
+                const uint32_t i = first + b * THREADS + threadIdx.x, d = (uint32_t)(key[b] >> shift) & 255u;
+                const uint64_t there = __ballot(i < nA);
+                bits |= key[b] ^ any;
+                if (__ballot(d == (uint32_t)__builtin_amdgcn_readfirstlane((int)d)) == ~0ull) {
+                    if (lane == 0 && there) atomicAdd(&h[d], (uint32_t)__popcll(there));
+                } else if (i < nA) {
+                    atomicAdd(&h[d], 1u);
+                }
+            }
         }
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) bits |= (uint64_t)__shfl_xor((unsigned long long)bits, o);
+        if (lane == 0) atomicOr(&differ, (unsigned long long)bits);
         __syncthreads();
         if (threadIdx.x < 64) {
             // lane l owns digits 255-4l .. 252-4l (descending); find the digit holding the need-th key
@@ -1000,7 +1018,11 @@ __device__ void peel(uint64_t *&A, uint64_t *&B, uint32_t &nA, uint32_t &need, u
         }
         __syncthreads();
         const uint32_t digit = pick[0], above = pick[1], inside = pick[2];
-        if (inside == nA) continue;  // all share the digit
+        if (inside == nA) {  // all share the digit, and those above it
+            if (differ == 0) break;  // (never: keys are distinct)
+            shift = max(63 - __clzll((long long)differ) - 7, 0);
+            continue;
+        }
         for (uint32_t first = 0; first < nA; first += THREADS * kBatch) {  // uniform
             uint64_t key[kBatch];
             bool more[kBatch], same[kBatch];
@@ -1023,6 +1045,7 @@ __device__ void peel(uint64_t *&A, uint64_t *&B, uint32_t &nA, uint32_t &need, u
         candn += above;
         need -= above;
         nA = inside;
+        shift = max(shift - 8, 0);
         uint64_t *t = A;
         A = B;
         B = t;
@@ -1033,18 +1056,20 @@ __device__ void peel(uint64_t *&A, uint64_t *&B, uint32_t &nA, uint32_t &need, u
 // in both lists with one atomic on the two counters (they are one word for it): a returning atomic on an address that
 // everybody wants takes its turn at about 13 ns (128K tokens: one per wavefront and list 21 us, this 6.2 us).  Both lists are
 // written with device-scope stores, so that the last workgroup (on whichever XCD) may read the boundary list if it is
-// one of the long ones (a kernel of its own for that took 2 - 4.7 us to find nothing to do).
-template <int BATCH>
-__global__ __launch_bounds__(kPoolThreads) void collect(const float *vals, int64_t len, uint32_t want, const KeyBins known, bool sampled,
-                                                        SeedState *st, uint64_t *cand, uint64_t *tie, const Entries ent)
+// one of the long ones (a kernel of its own for that took 2 - 4.7 us to find nothing to do).  All keys equal, that workgroup
+// is most of the whole call: 32K tokens 86 us with four wavefronts, 128K 135 us with eight (203 with four), 1M 833 us (1483).
+template <int BATCH, int THREADS>
+__global__ __launch_bounds__(THREADS) void collect(const float *vals, int64_t len, uint32_t want, const KeyBins known, bool sampled,
+                                                   SeedState *st, uint64_t *cand, uint64_t *tie, const Entries ent)
 {
+    constexpr int WAVES = THREADS / 64;
     __shared__ uint32_t is_last;
-    __shared__ uint64_t wave_n[kPoolWaves], base;
+    __shared__ uint64_t wave_n[WAVES], base;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const KeyBins bins = sampled ? st->bins : known;
     const uint32_t cut = st->cut;
     const uint32_t nent = entry_count(ent, (uint32_t)len);
-    for (uint32_t e0 = blockIdx.x * kPoolWaves * BATCH; e0 < nent; e0 += gridDim.x * kPoolWaves * BATCH) {  // uniform
+    for (uint32_t e0 = blockIdx.x * WAVES * BATCH; e0 < nent; e0 += gridDim.x * WAVES * BATCH) {  // uniform
         float v[BATCH][kPerThread];
         int64_t fcs[BATCH];
         raw_fetch(vals, len, ent, e0 + wave * BATCH, nent, fcs, v);
@@ -1067,7 +1092,7 @@ __global__ __launch_bounds__(kPoolThreads) void collect(const float *vals, int64
         __syncthreads();
         uint64_t before = 0, all = 0;
 #pragma unroll
-        for (int w = 0; w < kPoolWaves; ++w) {
+        for (int w = 0; w < WAVES; ++w) {
             before += w < wave ? wave_n[w] : 0;
             all += wave_n[w];
         }
@@ -1094,8 +1119,8 @@ __global__ __launch_bounds__(kPoolThreads) void collect(const float *vals, int64
     uint32_t candn = (uint32_t)lists_n, nA = (uint32_t)(lists_n >> 32), need = want - candn;
     if (candn + nA <= want + (uint32_t)kSelSmall) return;  // uniform
     uint64_t *A = tie, *B = tie + len;
-    peel<kPoolThreads>(A, B, nA, need, cand, candn, want + (uint32_t)kSelSmall);
-    for (uint32_t i = threadIdx.x; i < nA; i += kPoolThreads) cand[candn + i] = load_u64(&A[i]);
+    peel<THREADS>(A, B, nA, need, cand, candn, want + (uint32_t)kSelSmall);
+    for (uint32_t i = threadIdx.x; i < nA; i += THREADS) cand[candn + i] = load_u64(&A[i]);
     if (threadIdx.x == 0) st->refined = candn + nA;
 }
 
@@ -2027,12 +2052,19 @@ hipError_t launch_select_window(const float *scores, const SelectJob &job, int32
     } else {
         hipLaunchKernelGGL(count_scores, dim3(pool_blocks((entries + kRawBatch - 1) / kRawBatch, 256u)), dim3(kPoolThreads), 0, s, scores, L, want, st, ent);
     }
-    // a fine chunk a wavefront while that is one workgroup a compute unit
-    if (entries <= (uint32_t)(kNumCU * kPoolWaves))
-        hipLaunchKernelGGL(collect<1>, dim3(pool_blocks(entries, kNumCU)), dim3(kPoolThreads), 0, s, scores, L, want, bins, !fused, st, cand, tie, ent);
+    // Workgroups of eight wavefronts, a fine chunk a wavefront while that is one workgroup a compute unit; of four up to 64K
+    // tokens, where the smaller one is done sooner (1000 tokens 27.2 us against 27.7 for the whole call, 32K 35.1 against 35.6;
+    // 128K 37.4 against 36.9, 1M 50.4 against 48.5).
+    auto collect_with = [&](auto kernel, int threads, uint32_t per_wave) {
+        const uint32_t per_wg = (uint32_t)threads / 64 * per_wave, want_wg = (entries + per_wg - 1) / per_wg;
+        hipLaunchKernelGGL(kernel, dim3(std::min(want_wg, (uint32_t)kNumCU)), dim3(threads), 0, s, scores, L, want, bins, !fused, st, cand, tie, ent);
+    };
+    if (entries <= 256)
+        collect_with(collect<1, 256>, 256, 1);
+    else if (entries <= (uint32_t)kNumCU * 8)
+        collect_with(collect<1, 512>, 512, 1);
     else
-        hipLaunchKernelGGL(collect<kRawBatch>, dim3(pool_blocks((entries + kRawBatch - 1) / kRawBatch, 512u)), dim3(kPoolThreads), 0, s, scores, L, want,
-                           bins, !fused, st, cand, tie, ent);
+        collect_with(collect<kRawBatch, 512>, 512, kRawBatch);
     // at most n_out + kSelSmall <= kCandCap seeds
     const uint32_t max_seeds = (uint32_t)n_out + (uint32_t)kSelSmall;
     hipLaunchKernelGGL(seed_rank, dim3((max_seeds + kSeedRankThreads / 16 - 1) / (kSeedRankThreads / 16)), dim3(kSeedRankThreads),

@@ -803,3 +803,22 @@ def test_time_of_a_selection_does_not_follow_the_places_of_its_scores(L, every, 
     at_random = _device_us(lambda: il.ilre_select(mixed, 4096, (1, 3, 7), workspace=ws))
     print(f"{as_it_is:.1f} us, in random places {at_random:.1f} us", flush=True)
     assert as_it_is < 3 * at_random + 10
+
+
+@pytest.mark.parametrize("L,kind", [(1 << 17, "equal"), (1 << 17, "mostly_zero"), (100001, "two_values")])
+def test_time_of_a_selection_among_equal_scores(L, kind):
+    """Where more scores are equal than are wanted, one workgroup sorts them out by their places.  That takes about four
+    times as long as scores that differ (a pass and an addition per key for each digit they share: 23 times)."""
+    _announce(f"time of a selection among equal scores, L={L} {kind}")
+    rng = np.random.default_rng(5)
+    s = {"equal": np.full(L, 0.25), "mostly_zero": np.where(rng.random(L) < 0.01, rng.random(L), 0.0),
+         "two_values": np.where(rng.random(L) < 0.02, 0.5, 0.25)}[kind].astype(np.float32)
+    dev, ws = torch.from_numpy(s).cuda(), il.alloc_workspace(L, 1, 1, 1, 128, 3, il.ILRE_F32)
+    got = il.ilre_select(dev, 4096, (1, 3, 7), workspace=ws)
+    torch.cuda.synchronize()
+    assert got.cpu().numpy().tolist() == oracle.allocate(s, (1, 3, 7), 4096).tolist()
+    other = torch.from_numpy(rng.random(L).astype(np.float32)).cuda()
+    equal = _device_us(lambda: il.ilre_select(dev, 4096, (1, 3, 7), workspace=ws))
+    differ = _device_us(lambda: il.ilre_select(other, 4096, (1, 3, 7), workspace=ws))
+    print(f"{equal:.1f} us, scores that differ {differ:.1f} us", flush=True)
+    assert equal < 10 * differ
