@@ -115,25 +115,26 @@ struct SelectJob {
 };
 
 // Histogram bins of the window-max form: monotone in the key (ordered_bits of a score), fine where the cut is expected,
-// coarse on either side.  Bin 0 is what lies below k0 and is not counted.
+// coarse on either side.  Bin 0 is what lies below the first range and is not counted.
+constexpr int kBinRanges = 5;
 struct KeyBins {
-    uint32_t k0, k1, k2;  // keys where the three ranges start
-    uint32_t s0, s1, s2;  // keys a bin spans, as a shift
+    uint32_t start[kBinRanges];  // keys where the ranges start (a range may be empty)
+    uint32_t shift[kBinRanges];  // keys a bin spans, as a shift
     uint32_t pad[2];
 };
 
 // Device state of one seed search (window-max form); all zero when its first pass starts.
 struct SeedState {
     KeyBins bins;         // left by seed_init where the scores' scale is not known to the host
-    uint32_t cut;         // bin that holds the K-th largest key
-    uint32_t need;        // of that bin's keys, how many are among the K largest
     uint64_t lists_n;     // keys above the cut bin, collected in `cand` (low half), keys in it, collected in `tie` (high half)
-    uint32_t refined;     // not 0: the seeds are cand[0 .. refined), else both lists
+    uint32_t cut;         // bin that holds the K-th largest key
+    uint32_t refined;     // not 0: the seeds are the first `refined` of `cand`, else both lists
     uint32_t active_n;    // pre-pass: fine chunks left
     uint32_t done[2];     // workgroups finished: counting, collecting
-    uint32_t pad[48];
+    uint32_t pad[45];
     uint32_t hist[kSeedBins];
 };
+static_assert(sizeof(SeedState) % 16 == 0 && sizeof(KeyBins) % 16 == 0 && offsetof(SeedState, hist) % 16 == 0, "cleared in 16-byte words");
 
 struct SelectLayout {
     size_t state;     // kSelWindowMax: SeedState [2]  (the seeds, the pruning pre-pass)

@@ -240,26 +240,36 @@ __global__ __launch_bounds__(kThreads) void sel_init(const SelParams prm, uint32
     }
 }
 
-// A histogram's bins for scores of known scale, as an attention's scores are (in the sum form their mean is exact): 256
-// bins a binade from half the mean to four times it, where many scores of a flat distribution lie side by side, 32 a
-// binade from 2^-17 up to 2^25 of the mean.  By Markov's inequality few are above; what is below is not counted.
+// A histogram's bins for scores whose scale is known to the host, as an attention's is.  In the sum form their mean is
+// exact, and 256 bins a binade lie from half the mean to four times it, where many scores of a flat distribution lie side
+// by side; the 3 % around the mean, where all scores of an attention lie that hardly tells its keys apart, have 16 bins
+// for each of those (one bin held most of 128K such scores: 482 us where other scores take 290).  Down to 2^-17 of the
+// mean, where scores lie if a sink has most of the mass, there are 16 bins a binade, up to 2^18 of it 32; by Markov's
+// inequality one score in 2^18 is above, and what is below is not counted.  In the max form `mean` is only a lower bound of
+// the mean (a flat attention's is not far above it): the cut then lies in the range above more often.
 KeyBins bins_of_mean(float mean)
 {
     uint32_t bits;
     memcpy(&bits, &mean, sizeof bits);
     const uint32_t key = bits | 0x80000000u;  // ordered_bits of a positive float
     KeyBins b{};
-    b.k0 = key - (17u << 23), b.s0 = 18;
-    b.k1 = key - (1u << 23), b.s1 = 15;
-    b.k2 = key + (2u << 23), b.s2 = 18;
+    b.start[0] = key - (17u << 23), b.shift[0] = 19;
+    b.start[1] = key - (1u << 23), b.shift[1] = 15;
+    b.start[2] = key - (1u << 17), b.shift[2] = 9;
+    b.start[3] = key + (1u << 17), b.shift[3] = 15;
+    b.start[4] = key + (2u << 23), b.shift[4] = 18;
     return b;
 }
 
 __device__ __forceinline__ uint32_t bin_of(const KeyBins &b, uint32_t key)
 {
-    const uint32_t low = min(max(key, b.k0), b.k1) - b.k0, mid = min(max(key, b.k1), b.k2) - b.k1, high = max(key, b.k2) - b.k2;
-    const uint32_t bin = min(1u + (low >> b.s0) + (mid >> b.s1) + (high >> b.s2), (uint32_t)kSeedBins - 1u);
-    return key < b.k0 ? 0u : bin;
+    uint32_t bin = 1;
+#pragma unroll
+    for (int i = 0; i < kBinRanges; ++i) {
+        const uint32_t at = i + 1 < kBinRanges ? min(max(key, b.start[i]), b.start[i + 1]) : max(key, b.start[i]);
+        bin += (at - b.start[i]) >> b.shift[i];
+    }
+    return key < b.start[0] ? 0u : min(bin, (uint32_t)kSeedBins - 1u);
 }
 
 // Clears the states of a seed search on scores of unknown scale and places the bins by a sample of what is counted first:
@@ -295,13 +305,11 @@ __global__ __launch_bounds__(kThreads) void seed_init(const SeedInit p, SeedStat
     __syncthreads();
     if (threadIdx.x == 0) {
         constexpr uint32_t kLow = 256, kMid = 1023, kHigh = kSeedBins - 1 - kLow - kMid;
-        KeyBins b{};
-        b.k0 = 0, b.s0 = 24;
-        b.k1 = bound[0];
-        b.k2 = bound[1] + min(max(bound[1] - bound[0], 1u), 0xFFFFFFFEu - bound[1]);
-        b.s1 = b.s2 = 0;
-        while ((b.k2 - b.k1) >> b.s1 >= kMid) ++b.s1;
-        while ((0xFFFFFFFFu - b.k2) >> b.s2 >= kHigh) ++b.s2;
+        const uint32_t top = bound[1] + min(max(bound[1] - bound[0], 1u), 0xFFFFFFFEu - bound[1]);
+        uint32_t mid = 0, high = 0;
+        while ((top - bound[0]) >> mid >= kMid) ++mid;
+        while ((0xFFFFFFFFu - top) >> high >= kHigh) ++high;
+        const KeyBins b{{0, bound[0], top, top, top}, {24, mid, 0, 0, high}, {}};
         st[0].bins = st[1].bins = b;
     }
 }
@@ -432,12 +440,12 @@ __device__ __forceinline__ void count_finish(uint32_t *lh, SeedState *st, uint32
     uint32_t total;
     uint32_t above = block_scan_inclusive<kPoolThreads>(sum, wsum, total) - sum;
     if (total < want) {
-        if (threadIdx.x == 0) st->cut = 0, st->need = want - total;
+        if (threadIdx.x == 0) st->cut = 0;
     } else if (above < want && want <= above + sum) {  // one thread
 #pragma unroll
         for (int k = kPer - 1; k >= 0; --k) {
             const uint32_t n = (uint32_t)(two[k / 2] >> (k & 1 ? 32 : 0));
-            if (above < want && want <= above + n) st->cut = (uint32_t)(top - kPer + 1 + k), st->need = want - above;
+            if (above < want && want <= above + n) st->cut = (uint32_t)(top - kPer + 1 + k);
             above += n;
         }
     }

@@ -783,9 +783,9 @@ def _raised(L, seed, every=0, first=0.0):
     return s
 
 
-@pytest.mark.parametrize("L,every,first", [(1 << 20, 1024, 0.0), (1 << 17, 1024, 0.0), (5 << 20, 0, 1e6)],
-                         ids=["chunk_starts_1M", "chunk_starts_128K", "sink_5M"])
-def test_time_of_a_selection_does_not_follow_the_places_of_its_scores(L, every, first):
+@pytest.mark.parametrize("L,budget,every,first", [(1 << 20, 4096, 1024, 0.0), (1 << 17, 4096, 1024, 0.0), (16 << 20, 256, 0, 1e20)],
+                         ids=["chunk_starts_1M", "chunk_starts_128K", "sink_16M"])
+def test_time_of_a_selection_does_not_follow_the_places_of_its_scores(L, budget, every, first):
     """The histogram's bins are placed by a sample.  High scores on a regular grid, or at the very front, are as quickly
     sorted out as the same scores in random places (when the sample fell in with the grid: 10 times as long on 1M tokens).
     Three times as long is far from what two runs differ by."""
@@ -795,12 +795,12 @@ def test_time_of_a_selection_does_not_follow_the_places_of_its_scores(L, every, 
     g.manual_seed(4)
     mixed = s[torch.randperm(L, device="cuda", generator=g)].contiguous()
     ws = il.alloc_workspace(L, 1, 1, 1, 128, 3, il.ILRE_F32)
-    out = il.ilre_select(s, 4096, (1, 3, 7), workspace=ws)
+    out = il.ilre_select(s, budget, (1, 3, 7), workspace=ws)
     torch.cuda.synchronize()
     if L <= 1 << 20:
         assert out.cpu().numpy().tolist() == oracle.allocate(s.cpu().numpy(), (1, 3, 7), 4096).tolist()
-    as_it_is = _device_us(lambda: il.ilre_select(s, 4096, (1, 3, 7), workspace=ws))
-    at_random = _device_us(lambda: il.ilre_select(mixed, 4096, (1, 3, 7), workspace=ws))
+    as_it_is = _device_us(lambda: il.ilre_select(s, budget, (1, 3, 7), workspace=ws))
+    at_random = _device_us(lambda: il.ilre_select(mixed, budget, (1, 3, 7), workspace=ws))
     print(f"{as_it_is:.1f} us, in random places {at_random:.1f} us", flush=True)
     assert as_it_is < 3 * at_random + 10
 
@@ -822,3 +822,27 @@ def test_time_of_a_selection_among_equal_scores(L, kind):
     differ = _device_us(lambda: il.ilre_select(other, 4096, (1, 3, 7), workspace=ws))
     print(f"{equal:.1f} us, scores that differ {differ:.1f} us", flush=True)
     assert equal < 10 * differ
+
+
+@pytest.mark.parametrize("mode,factor", [(il.ILRE_SCORE_SUM, 0.05), (il.ILRE_SCORE_MAX, 5e-4)], ids=["sum", "max"])
+def test_time_of_a_recall_of_a_flat_attention(mode, factor):
+    """Query states that hardly tell the keys apart: scores that differ by a thousandth and less, within a hundredth of their mean.
+    The bins there are fine enough to find the cut, where one bin held most of the scores before, and the indices are the
+    oracle's on the GPU's own scores."""
+    _announce(f"time of a recall of a flat attention, mode {mode}")
+    L, Lq, Hq, Hkv = 131072, 64, 32, 8
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    q = torch.randn(Hq, Lq, 128, device="cuda", generator=g)
+    k = torch.randn(Hkv, L, 128, device="cuda", generator=g).bfloat16()
+    flat, other = (factor * q).bfloat16(), q.bfloat16()
+    ws = il.alloc_workspace(L, Lq, Hq, Hkv, 128, 3, il.ILRE_BF16)
+    idx, scores = il.ilre_recall(flat, k, 4096, (1, 3, 7), score_mode=mode, sink=4, workspace=ws)
+    torch.cuda.synchronize()
+    spread = float(scores.std() / scores.mean())
+    assert 5e-5 < spread < 3e-3 and abs(float(scores.mean()) * L / (Hq * Lq if mode == il.ILRE_SCORE_SUM else 1) - 1) < 0.015
+    assert idx.cpu().numpy().tolist() == oracle.allocate(scores.cpu().numpy(), (1, 3, 7), 4096, sink=4).tolist()
+    t_flat = _device_us(lambda: il.ilre_recall(flat, k, 4096, (1, 3, 7), score_mode=mode, sink=4, workspace=ws))
+    t_other = _device_us(lambda: il.ilre_recall(other, k, 4096, (1, 3, 7), score_mode=mode, sink=4, workspace=ws))
+    print(f"{t_flat:.1f} us, other states {t_other:.1f} us", flush=True)
+    assert t_flat < 1.35 * t_other
