@@ -89,7 +89,7 @@ hipError_t launch_reduce_units(const float *partial, int nunits, int64_t L, int 
 // ---------------------------------------------------------------- selection (Algorithm 1)
 
 constexpr int kSelFine = 256;       // elements a wavefront pools at a time ("fine chunk")
-constexpr int kSelBins = 2048;      // printed form: words a combination's row of the histogram may take
+constexpr int kAvgBins = 256;       // printed form: histogram bins per combination
 constexpr int kSeedBins = 2048;     // window-max form: histogram bins
 constexpr int kSelSmall = 2048;     // seeds beyond the wanted ones that are not worth sorting out
 constexpr int kCandCap = 10240;     // candidate capacity in tokens (>= ILRE_MAX_BUDGET + kSelSmall)
@@ -138,7 +138,7 @@ static_assert(sizeof(SeedState) % 16 == 0 && sizeof(KeyBins) % 16 == 0 && offset
 
 struct SelectLayout {
     size_t state;     // kSelWindowMax: SeedState [2]  (the seeds, the pruning pre-pass)
-    size_t hist;      // kSelMaxAvg: uint32 [n][kSelBins]
+    size_t hist;      // kSelMaxAvg: uint32 [n][kAvgBins]
     size_t ctrl;      // kSelMaxAvg: SelCtrl [n]
     size_t done;      // kSelMaxAvg: uint32 [n]: workgroups finished per max kernel and group of average kernels
     size_t cmax;      // float [ceil(L / kSelFine)]: fine-chunk maxima (pruning pre-pass)
@@ -156,7 +156,9 @@ struct SelCtrl {
     uint32_t want;        // K_j: ranked elements that are candidates
     uint32_t tie_n;       // elements collected
     uint32_t len;         // elements in the source array
-    float edge;           // averages below it are not counted
+    float edge;           // window sums below it are not counted: the bins start here
+    uint32_t span;        // keys (of float bits) the fine bins cover
+    uint32_t fine, coarse;  // keys a bin spans up to there and beyond, as shifts
     uint32_t cut;         // 1 + the lowest bin of which elements are collected (0: all elements)
     uint64_t tie_off;     // lists of elements: uint64 words from the base of the tie region
 };

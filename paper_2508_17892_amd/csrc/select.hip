@@ -57,6 +57,7 @@
 // the same key gives them once the element index is replaced by the token index.
 #include "ilre_internal.h"
 
+#include <float.h>
 #include <string.h>
 
 #include <algorithm>
@@ -72,16 +73,13 @@ constexpr int kPerThread = kSelFine / 64;         // 4 tokens per lane
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
 constexpr uint32_t kSortSmall = 4096;             // printed form: lists up to this long are sorted whole
 
-// Per-combination description, host -> sel_init (by value), which copies it into the control blocks.
+// Per-combination description, host -> sel_init (by value).
 struct SelParams {
-    int n;
-    uint32_t share[ILRE_MAX_POOL_KERNELS], want[ILRE_MAX_POOL_KERNELS];
-    uint32_t len[ILRE_MAX_POOL_KERNELS], cell[ILRE_MAX_POOL_KERNELS];
+    const float *body;
+    uint32_t want[ILRE_MAX_POOL_KERNELS], len[ILRE_MAX_POOL_KERNELS];
     uint64_t tie_off[ILRE_MAX_POOL_KERNELS];
-    float edge[ILRE_MAX_POOL_KERNELS];     // where the bins start, if `sample` is null
-    const float *sample;                   // else: found from kBaseSamples of these sample_n scores
-    int64_t sample_n;
-    uint64_t deep;                         // bit j: combination j wants so many that its bins start below all samples
+    uint16_t m[ILRE_MAX_POOL_KERNELS], avg[ILRE_MAX_POOL_KERNELS];
+    uint8_t lo[ILRE_MAX_POOL_KERNELS], hi[ILRE_MAX_POOL_KERNELS];  // ranks in the sample that place the bins
 };
 
 // Order-preserving map of a finite float onto uint32 (larger float -> larger key; the two zeros share one).
@@ -95,6 +93,8 @@ __device__ __forceinline__ uint64_t make_key(float pooled, uint32_t token)
 {
     return ((uint64_t)ordered_bits(pooled) << 32) | (uint64_t)(0xFFFFFFFFu - token);
 }
+
+__device__ __forceinline__ float float_of_key(uint32_t key) { return __uint_as_float(key ^ (key >> 31 ? 0x80000000u : 0xFFFFFFFFu)); }
 
 __device__ __forceinline__ uint32_t key_token(uint64_t key) { return 0xFFFFFFFFu - (uint32_t)key; }
 
@@ -194,47 +194,105 @@ __device__ __forceinline__ int64_t sample_at(uint32_t t, int64_t n)
     return begin + (int64_t)(((uint64_t)h * (uint64_t)(end - begin)) >> 32);
 }
 
-// Where the bins of scores of unknown scale start: at the median of a sample (the K_j-th best is above it), or below
-// its minimum for a combination that wants a large part of the elements.  Any edge gives the same result; one far off
-// puts everything into one bin.
-__device__ float sampled_edge(const float *scores, int64_t n, bool deep)
+// The sample's keys of the ranks lo, hi and 0 (the largest) into `bound`: a wavefront each finds one bit by bit, with the
+// whole sample in its registers.  (Comparing each sample with all others took the workgroup 3 us.)
+__device__ __forceinline__ void sampled_bounds(const uint32_t (&key)[kBaseSamples], uint32_t lo, uint32_t hi, uint32_t (&bound)[3])
 {
-    __shared__ __align__(16) uint32_t key[kBaseSamples];
-    __shared__ uint32_t above[kBaseSamples];
-    __shared__ float edge;
-    const int t = threadIdx.x;
-    float x = 0.f;
-    if (t < kBaseSamples) {
-        x = scores[sample_at(t, n)];
-        key[t] = ordered_bits(x);
-        above[t] = 0;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    __syncthreads();
+    if (wave < 3) {
+        constexpr int kOwn = kBaseSamples / 64;
+        uint32_t k[kOwn], at = 0;
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) k[i] = key[64 * i + lane];
+        const int want = (int)(wave == 0 ? lo : wave == 1 ? hi : 0u) + 1;
+        for (uint32_t bit = 0x80000000u; bit; bit >>= 1) {
+            int n = 0;
+#pragma unroll
+            for (int i = 0; i < kOwn; ++i) n += __popcll(__ballot(k[i] >= (at | bit)));
+            at |= n >= want ? bit : 0u;
+        }
+        if (lane == 0) bound[wave] = at;
     }
     __syncthreads();
-    constexpr int kShare = kThreads / kBaseSamples, kPart = kBaseSamples / kShare;  // threads a sample, samples a thread compares with
-    const int u = t % kBaseSamples, part = t / kBaseSamples;
-    uint32_t c = 0;
-    for (int k = 0; k < kPart; ++k) {
-        const int v = part * kPart + k;
-        c += key[v] > key[u] || (key[v] == key[u] && v < u) ? 1u : 0u;
-    }
-    atomicAdd(&above[u], c);
-    __syncthreads();
-    if (t < kBaseSamples && above[t] == (uint32_t)(deep ? kBaseSamples - 1 : kBaseSamples / 2)) edge = deep ? 0.25f * x : x;
-    __syncthreads();
-    return edge;
 }
 
+// The ranks of `samples` elements out of `len` that enclose the `want`-th largest element with four standard deviations of
+// a sample's count; the upper one has two samples above it, which may be far above everything else.
+struct SampleRanks {
+    uint32_t lo, hi;
+};
+SampleRanks sample_ranks(double want_lo, double want_hi, double len)
+{
+    const double lo = kBaseSamples * want_lo / len, hi = kBaseSamples * want_hi / len;
+    return {(uint32_t)std::min(lo + 4 * sqrt(lo) + 4, kBaseSamples - 1.0), (uint32_t)std::min(std::max(hi - 4 * sqrt(hi) - 4, 2.0), kBaseSamples - 1.0)};
+}
+
+// Clears the counters and places each combination's bins by a sample of its own window sums: half of them between the
+// sample's keys of the ranks lo and hi, a quarter from there to its largest, and the rest beyond.  At most a few hundredths
+// of the elements more than are wanted reach the lowest bin, whatever the scores look like, and few are in one bin.
+// (Bins of a fixed width, 64 a binade, upward from the scores' median: 1M scores that differ by a thousandth 1170 us,
+// their logarithms 831, raised at every 1024th token 847, where others take 100.  More bins than these do not pay: every
+// workgroup adds its counts to the global ones, a request per cache line; with 1024 bins counting took 50 us on 1M tokens.)
 __global__ __launch_bounds__(kThreads) void sel_init(const SelParams prm, uint32_t *hist, SelCtrl *ctrl, uint32_t *done)
 {
+    __shared__ __align__(16) uint32_t key[kBaseSamples];
+    __shared__ uint32_t bound[3];
     const int j = blockIdx.x;
-    const float edge = prm.sample ? sampled_edge(prm.sample, prm.sample_n, (prm.deep >> j) & 1u) : prm.edge[j];
-    for (int i = threadIdx.x; i < kSelBins; i += kThreads) hist[(size_t)j * kSelBins + i] = 0;
+    static_assert(kThreads == 4 * kBaseSamples, "four threads a sample");
+    static_assert(kAvgBins <= kThreads, "a word a thread");
+    if (threadIdx.x < (unsigned)kAvgBins) hist[(size_t)j * kAvgBins + threadIdx.x] = 0;
+    const uint32_t len = prm.len[j];
+    SelCtrl c{};
+    if (len) {  // uniform
+        // a window's cells are tokens side by side: the sample's four threads take every fourth cell
+        const int part = threadIdx.x & 3, n = prm.avg[j];
+        const int64_t m = prm.m[j], first = sample_at(threadIdx.x >> 2, len) - (n - 1) / 2;
+        auto sum_of = [&](auto size_tag) {
+            constexpr int M = decltype(size_tag)::value;  // 0: any
+            float sum = 0.0f;
+#pragma unroll 4
+            for (int c = part; c < n; c += 4) {
+                const int64_t at = first + c;
+                const bool in = at >= 0 && at < (int64_t)len;
+                const float *src = prm.body + (in ? at : 0) * (M ? M : m);
+                float v = src[0];
+                if (M != 0) {
+#pragma unroll
+                    for (int u = 1; u < M; ++u) v = fmaxf(v, src[u]);
+                } else {
+                    for (int u = 1; u < (int)m; ++u) v = fmaxf(v, src[u]);
+                }
+                sum += in ? v : 0.0f;
+            }
+            return sum;
+        };
+        float sum;
+        if (m == 1)
+            sum = sum_of(std::integral_constant<int, 1>{});
+        else if (m == 2)
+            sum = sum_of(std::integral_constant<int, 2>{});
+        else if (m == 4)
+            sum = sum_of(std::integral_constant<int, 4>{});
+        else if (m == 8)
+            sum = sum_of(std::integral_constant<int, 8>{});
+        else
+            sum = sum_of(std::integral_constant<int, 0>{});
+        sum += __shfl_xor(sum, 1);
+        sum += __shfl_xor(sum, 2);
+        if (part == 0) key[threadIdx.x >> 2] = ordered_bits(sum);
+        sampled_bounds(key, prm.lo[j], prm.hi[j], bound);
+        auto shift_for = [](uint32_t keys, int bits) { return keys >> bits ? (uint32_t)(32 - bits - __clz((int)keys)) : 0u; };
+        static_assert(kAvgBins == 256, "2^7 bins up to the second key, 2^6 to the third");
+        c.span = bound[1] - bound[0];
+        c.fine = shift_for(c.span, 7);
+        c.coarse = bound[2] > bound[1] ? shift_for(bound[2] - bound[1], 6) : 21;  // four bins a binade where the sample says nothing
+        c.edge = float_of_key(bound[0]);
+    }
     if (threadIdx.x == 0) {
-        SelCtrl c{};
         c.want = prm.want[j];
-        c.len = prm.len[j];
+        c.len = len;
         c.tie_off = prm.tie_off[j];
-        c.edge = edge > 0x1p-90f && edge < 0x1p90f ? edge : 0x1p-90f;
         ctrl[j] = c;
         done[j] = 0;
     }
@@ -273,36 +331,23 @@ __device__ __forceinline__ uint32_t bin_of(const KeyBins &b, uint32_t key)
 }
 
 // Clears the states of a seed search on scores of unknown scale and places the bins by a sample of what is counted first:
-// the scores, or the maxima of fine chunks.  `lo` and `hi` are the sample's ranks (0: the largest) four standard deviations
-// of a sample's count to either side of the K-th largest, `hi` at least 2: one or two samples may be far above everything
-// else.  Where few elements are wanted the K-th largest then lies above `hi` more often than not (up to a few hundredths
-// of all elements do), so the middle half of the bins reaches as far above it as from `lo` to it.  The others cover all
-// keys below (two binades each) and above.  Whatever the sample is, the result is the same.
+// the scores, or the maxima of fine chunks.  Half of the bins lie between the sample's two keys and as far above the upper
+// one, above which the K-th largest lies more often than not where few are wanted.  The others cover all keys below (two
+// binades each) and above.  Whatever the sample is, the result is the same.
 struct SeedInit {
     const float *vals;
     int64_t n;
-    uint32_t lo, hi;
+    SampleRanks ranks;
 };
 __global__ __launch_bounds__(kThreads) void seed_init(const SeedInit p, SeedState *st)
 {
     __shared__ __align__(16) uint32_t key[kBaseSamples];
-    __shared__ uint32_t bound[2];
-    static_assert(kThreads == 4 * kBaseSamples, "four threads a sample");
+    __shared__ uint32_t bound[3];
     constexpr int kWords = sizeof(SeedState) / 16, kKept = sizeof(KeyBins) / 16;  // (the bins are written below)
     for (int i = threadIdx.x; i < 2 * kWords; i += kThreads)
         if (i % kWords >= kKept) ((uint4 *)st)[i] = make_uint4(0, 0, 0, 0);
-    const uint32_t u = threadIdx.x >> 2, part = threadIdx.x & 3;
-    const uint32_t k = ordered_bits(p.vals[sample_at(u, p.n)]);
-    if (part == 0) key[u] = k;
-    __syncthreads();
-    uint32_t c = 0;
-#pragma unroll 8
-    for (uint32_t v = part; v < (uint32_t)kBaseSamples; v += 4) c += key[v] > k || (key[v] == k && v < u) ? 1u : 0u;
-    c += (uint32_t)__shfl_xor((int)c, 1);
-    c += (uint32_t)__shfl_xor((int)c, 2);
-    if (part == 0 && c == p.lo) bound[0] = k;
-    if (part == 0 && c == p.hi) bound[1] = k;
-    __syncthreads();
+    if (threadIdx.x < kBaseSamples) key[threadIdx.x] = ordered_bits(p.vals[sample_at(threadIdx.x, p.n)]);
+    sampled_bounds(key, p.ranks.lo, p.ranks.hi, bound);
     if (threadIdx.x == 0) {
         constexpr uint32_t kLow = 256, kMid = 1023, kHigh = kSeedBins - 1 - kLow - kMid;
         const uint32_t top = bound[1] + min(max(bound[1] - bound[0], 1u), 0xFFFFFFFEu - bound[1]);
@@ -628,11 +673,8 @@ constexpr int kAvgThreads = 512;
 constexpr int kAvgWaves = kAvgThreads / 64;
 constexpr int kAvgNarrow = 2, kAvgWide = 4;       // windows a lane sums
 constexpr int kAvgGroup = 16;                     // average kernels a workgroup handles
-constexpr int kAvgBins = 1024;                    // bins per average kernel
-constexpr int kAvgBinShift = 17;                  // float bits a bin spans: a 64th of a binade, 1024 of them 16 binades
 constexpr int kAvgList = 256;                     // any sizes: collected elements a workgroup holds per average kernel before it writes them
 constexpr uint16_t kNoAvg = 0xFFFF;
-static_assert(kAvgBins <= kSelBins, "a combination's row of the histogram holds its bins");
 // LDS of pool_averages: counts or collected elements, then a buffer of cells per wavefront (readable two past the last)
 constexpr size_t avg_shared(int pass, int per, bool small)
 {
@@ -690,11 +732,12 @@ __device__ __forceinline__ uint32_t find_cut(const uint32_t *h, uint32_t need)
 // also the order the definition sums in: a lane takes windows by their first cell and gets all average kernels' sums from
 // n_max additions.  Counting and comparing go by the sum; the average itself (the quotient ranks, two sums may share
 // one) is computed for what is collected only, a full wavefront at a time.  For that the cut is lowered by 2^-21 of its
-// value: whatever lies below has a smaller quotient than everything at or above the cut.
+// value (and by two of the smallest floats a cell): whatever lies below has a smaller quotient than everything at or above
+// the cut.
 //
-// Bins follow the bits of the sum upward from the sum at ctrl.edge, 1.1 - 1.6 % wide, the last one open above: the bin of
-// the K_j-th best holds few others, and any scores whose edge is near their bulk are resolved, so one pass of counting
-// does (two passes of 11 key bits from the sign down took twice as long).  With PER = kAvgWide only the largest of
+// Bins follow the bits of the sum upward from ctrl.edge, the last one open above; they are placed by a sample (sel_init), so
+// that the bin of the K_j-th best holds few others and one pass of counting does (two passes of 11 key bits from the
+// sign down took twice as long).  With PER = kAvgWide only the largest of
 // a lane's four sums, 64 windows apart, is counted: the K_j-th best of those is at most the K_j-th best of all, the few
 // elements more that reach it are sorted out later, and a quarter of the additions to LDS, of which 16 lanes' worth
 // takes about as long as all the rest of the loop, are left.  It needs K_j to be well below a quarter of the cells.
@@ -766,7 +809,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
     if (blockIdx.x * kAvgWaves < chunks) fetch(blockIdx.x * kAvgWaves + wave, cell);
 
     // average kernel q's numbers are lane q's, in every wavefront (SMALL: the one of size n has number n - 1)
-    uint32_t l_size, l_want;
+    uint32_t l_size, l_want, l_span, l_shift;  // l_shift: fine, and coarse above it
     uint32_t l_len;  // SMALL: elements of that size: none of a size that was not asked for (an edge alone would let sums of +inf pass)
     float l_edge;    // the sum from which on elements matter to this pass
     {
@@ -783,8 +826,18 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
         const bool used = !SMALL || at != kNoAvg;
         const uint32_t j = (uint32_t)(i * ap.n_avg) + (used ? at : 0u), cut = ctrl[j].cut;
         l_want = ctrl[j].want;
-        l_edge = ctrl[j].edge * (float)l_size;
-        if (PASS == 1) l_edge = cut ? __uint_as_float(__float_as_uint(l_edge) + ((cut - 1) << kAvgBinShift)) * (1.0f - 0x1p-21f) : -INFINITY;
+        const uint32_t fine = ctrl[j].fine, coarse = ctrl[j].coarse;
+        l_span = ctrl[j].span;
+        l_shift = fine | coarse << 8;
+        l_edge = ctrl[j].edge;
+        if (PASS == 1) {
+            const uint32_t bin = cut - 1, n_fine = l_span >> fine;
+            const uint32_t at = bin <= n_fine ? bin << fine : l_span + ((bin - n_fine) << coarse);
+            // (a bin that holds something starts at a float's key, +inf at most)
+            const float low = fminf(float_of_key(ordered_bits(l_edge) + at), FLT_MAX);
+            l_edge = cut ? low - (fabsf(low) * 0x1p-21f + (float)l_size * 0x1p-148f) : -INFINITY;
+        }
+        if (!used) l_edge = INFINITY;
         l_len = used ? len : 0u;
         if ((int)threadIdx.x < rows) {
             c_comb[threadIdx.x] = used ? j : 0xFFFFFFFFu;
@@ -793,6 +846,12 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
         }
     }
     auto of = [](uint32_t x, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)x, q); };
+    // bin of a sum that is not below the edge (differences of float bits in signed order, modulo 2^32)
+    auto bin_from = [](float x, float edge, uint32_t span, uint32_t shift) {
+        auto bits = [](float f) { return __float_as_uint(f) ^ ((uint32_t)(__float_as_int(f) >> 31) >> 1); };
+        const uint32_t d = bits(x) - bits(edge);
+        return min((min(d, span) >> (shift & 31u)) + ((max(d, span) - span) >> (shift >> 8)), (uint32_t)kAvgBins - 1u);
+    };
     auto of_f = [](float x, int q) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), q)); };
     if (PASS == 0)
         for (int x = threadIdx.x * 4; x < rows * kAvgBins; x += kAvgThreads * 4) *(uint4 *)&lh[x] = make_uint4(0, 0, 0, 0);
@@ -823,24 +882,24 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
 #pragma unroll
             for (int u = 0; u < kAvgGroup; ++u) {
                 const float edge = of_f(l_edge, u);
-                const uint32_t before = queued, els = of(l_len, u);
+                const uint32_t before = queued, els = of(l_len, u), span = of(l_span, u), shift = of(l_shift, u);
                 float best = -INFINITY;
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
                     sum[k] = sum[k] + buf[lane + 64 * k + u];
                     const bool in = el0 + 64u * k + u / 2 < els;
-                    // (positive floats are ordered like their bits; what is not counted goes to a word of the lane's own)
+                    // (what is not counted goes to a word of the lane's own)
                     auto count = [&](float x, bool hit) {
-                        const uint32_t bin = min((__float_as_uint(x) - __float_as_uint(edge)) >> kAvgBinShift, (uint32_t)kAvgBins - 1u);
+                        const uint32_t bin = bin_from(x, edge, span, shift);
                         atomicAdd(&lh[hit ? u * kAvgBins + bin : (uint32_t)(kAvgGroup * kAvgBins + lane)], 1u);
                     };
                     if (PASS == 0 && PER == kAvgWide) {
                         best = fmaxf(best, in ? sum[k] : -INFINITY);
                         if (k == PER - 1) count(best, best >= edge);
                     } else if (PASS == 0) {
-                        count(sum[k], in & (sum[k] >= edge));
+                        count(sum[k], in & !(sum[k] < edge));
                     } else {
-                        const bool hit = in & (sum[k] >= edge);
+                        const bool hit = in & !(sum[k] < edge);
                         const uint64_t mask = __ballot(hit);
                         const uint32_t at = queued + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
                         if (hit) ll[wave * QUEUE + at] = (uint64_t)__float_as_uint(sum[k]) << 32 | (uint32_t)(u << 8 | (lane + 64 * k));
@@ -893,10 +952,9 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
                     const uint32_t el = el0 + 64u * k + u / 2;
-                    const bool hit = sum[k] >= edge && el < len;
+                    const bool hit = !(sum[k] < edge) && el < len;
                     if (PASS == 0) {
-                        const uint32_t bin = min((__float_as_uint(sum[k]) - __float_as_uint(edge)) >> kAvgBinShift, (uint32_t)kAvgBins - 1u);
-                        if (hit) atomicAdd(&lh[q * kAvgBins + bin], 1u);
+                        if (hit) atomicAdd(&lh[q * kAvgBins + bin_from(sum[k], edge, of(l_span, q), of(l_shift, q))], 1u);
                     } else {
                         const uint64_t mask = __ballot(hit);
                         if (mask == 0) continue;
@@ -928,7 +986,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
             for (int b = 0; b < kBatch; ++b) {
                 if ((v[b].x | v[b].y | v[b].z | v[b].w) == 0) continue;
                 const int x = x0 + b * kAvgThreads * 4;
-                uint32_t *h = hist + (size_t)c_comb[x / kAvgBins] * kSelBins + x % kAvgBins;
+                uint32_t *h = hist + (size_t)c_comb[x / kAvgBins] * kAvgBins + x % kAvgBins;
                 if (v[b].x) atomicAdd(&h[0], v[b].x);
                 if (v[b].y) atomicAdd(&h[1], v[b].y);
                 if (v[b].z) atomicAdd(&h[2], v[b].z);
@@ -938,7 +996,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
         if (count_in(&done[blockIdx.y], gridDim.x, &is_last)) {
             for (int q = wave; q < rows; q += kAvgWaves) {
                 if (c_comb[q] == 0xFFFFFFFFu) continue;
-                const uint32_t cut = find_cut(hist + (size_t)c_comb[q] * kSelBins, of(l_want, q));
+                const uint32_t cut = find_cut(hist + (size_t)c_comb[q] * kAvgBins, of(l_want, q));
                 if (lane == 0) ctrl[c_comb[q]].cut = cut;
             }
         }
@@ -1873,7 +1931,7 @@ SelectLayout make_select_layout(const SelectJob &job)
     lay.state = off;
     off = up(off + (window ? 2 * sizeof(SeedState) : 0));
     lay.hist = off;
-    off = up(off + (window ? 0 : (size_t)n * kSelBins * sizeof(uint32_t)));
+    off = up(off + (window ? 0 : (size_t)n * kAvgBins * sizeof(uint32_t)));
     lay.ctrl = off;
     off = up(off + (window ? 0 : (size_t)n * sizeof(SelCtrl)));
     lay.done = off;
@@ -2025,8 +2083,7 @@ hipError_t launch_select_window(const float *scores, const SelectJob &job, int32
         fused = nullptr;
     }
     auto start_search = [&](const float *vals, int64_t len) {
-        const double rank = (double)kBaseSamples * want / (double)len, spread = 4 * sqrt(rank) + 4;
-        const SeedInit init{vals, len, (uint32_t)std::min(rank + spread, kBaseSamples - 1.0), (uint32_t)std::max(rank - spread, 2.0)};
+        const SeedInit init{vals, len, sample_ranks(want, want, (double)len)};
         hipLaunchKernelGGL(seed_init, dim3(1), dim3(kThreads), 0, s, init, st);
     };
     if (!fused && !pruned) start_search(scores, L);
@@ -2093,7 +2150,6 @@ ClearWords select_clear_words(const SelectJob &job, const SelectLayout &lay, voi
 hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out_idx, int32_t *out_count,
                          void *workspace, const SelectLayout &lay, hipStream_t s, const FusedScores *fused)
 {
-    const float mean_score = fused ? fused->mean : 0.f;
     const int64_t L = job.L;
     const int n = job.combos();
     const int budget = job.budget;
@@ -2123,19 +2179,21 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
     // The algorithm as printed.  B_c: floor(B / n), the first B mod n combinations one more; K_m = B / m + 1 cells.
     SelParams prm{};
     AvgParams ap{};
-    prm.n = n;
     const int base = budget / n, rem = budget % n;
     int64_t before = 0, tie_off = 0, len_max = 0;
     uint64_t cell_off = 0;
     bool coarse = true;  // windows can be counted kAvgWide at a time
+    int share_of[ILRE_MAX_POOL_KERNELS], cell_of[ILRE_MAX_POOL_KERNELS];
     for (int j = 0; j < n; ++j) {
         const int share = base + (j < rem ? 1 : 0);
         int64_t len;
         int cell;
         combo_shape(job, j, len, cell);
-        prm.share[j] = (uint32_t)share;
+        share_of[j] = share;
+        cell_of[j] = cell;
         prm.len[j] = (uint32_t)len;
-        prm.cell[j] = (uint32_t)cell;
+        prm.m[j] = (uint16_t)cell;
+        prm.avg[j] = (uint16_t)job.avg_kernels[j % job.n_avg];
         prm.tie_off[j] = (uint64_t)tie_off;
         tie_off += 2 * len;
         if (j % job.n_avg == 0) {
@@ -2154,15 +2212,7 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
         prm.want[j] = (uint32_t)(km < len ? km : len);
         before += share;
         if (len > len_max) len_max = len;
-        // The bins start at half the mean score, or well below it where a large part of the cells is wanted.
-        const bool deep = 4 * (int64_t)prm.want[j] > len;
         coarse = coarse && 2 * kAvgWide * (int64_t)prm.want[j] <= len;
-        if (deep) prm.deep |= 1ull << j;
-        prm.edge[j] = deep ? mean_score / 64 : mean_score / 2;
-    }
-    if (!(mean_score > 0.f)) {
-        prm.sample = scores;
-        prm.sample_n = L;
     }
     ap.n_avg = job.n_avg;
     ap.groups = (job.n_avg + kAvgGroup - 1) / kAvgGroup;
@@ -2181,11 +2231,19 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
         small = at == kNoAvg;
         at = ap.at[k];
     }
+    const bool wide = small && coarse;
+    prm.body = scores;
+    for (int j = 0; j < n; ++j) {
+        // counted kAvgWide at a time, the K_j best ones may be as few as a quarter as many, next to each other
+        const SampleRanks r = sample_ranks((wide ? kAvgWide : 1.0) * prm.want[j], prm.want[j], std::max(1.0, (double)prm.len[j]));
+        prm.lo[j] = (uint8_t)r.lo;
+        prm.hi[j] = (uint8_t)std::min(r.hi, r.lo);
+    }
     uint32_t sort_n = kSortSmall;  // elements are sorted in LDS, up to a power of two of them
     for (int j = 0; j < n; ++j)
         while (sort_n < prm.want[j]) sort_n *= 2;
     hipLaunchKernelGGL(sel_init, dim3(n), dim3(kThreads), 0, s, prm, hist, ctrl, done);
-    if (small && coarse)
+    if (wide)
         launch_averages<0, kAvgWide, true>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
     else if (small)
         launch_averages<0, kAvgNarrow, true>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
@@ -2199,10 +2257,10 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
     walk.n = n;
     bool word_cells = true;  // cells lie inside words of the set: sizes 1, 2, 4, 8, 16, 32
     for (int j = 0; j < n; ++j) {
-        walk.share[j] = prm.share[j];
-        walk.reach[j] = prm.cell[j];
+        walk.share[j] = (uint32_t)share_of[j];
+        walk.reach[j] = (uint32_t)cell_of[j];
         walk.cells[j] = prm.want[j];
-        word_cells = word_cells && 32 % prm.cell[j] == 0;
+        word_cells = word_cells && 32 % cell_of[j] == 0;
     }
     if (word_cells)
         launch_walk<kWalkWordCells>(walk, job, n_out, ws, lay, out_idx, out_count, s);

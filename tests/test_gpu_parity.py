@@ -846,3 +846,78 @@ def test_time_of_a_recall_of_a_flat_attention(mode, factor):
     t_other = _device_us(lambda: il.ilre_recall(other, k, 4096, (1, 3, 7), score_mode=mode, sink=4, workspace=ws))
     print(f"{t_flat:.1f} us, other states {t_other:.1f} us", flush=True)
     assert t_flat < 1.35 * t_other
+
+
+def _any_scores(kind, L, rng):
+    if kind == "signed":
+        return rng.standard_normal(L).astype(np.float32)
+    if kind == "logarithms":
+        return np.log(0.008 * (1 + 0.3 * rng.standard_normal(L)).clip(0.01)).astype(np.float32)
+    if kind == "half_zero":
+        return np.where(rng.random(L) < 0.5, rng.random(L), 0.0).astype(np.float32)
+    if kind == "flat":
+        return (0.008 * (1 + 1e-3 * rng.standard_normal(L))).astype(np.float32)
+    if kind == "outliers":        # a few dozen of either sign, the sums in between within a thousandth
+        s = (1 + 1e-3 * rng.random(L)).astype(np.float32)
+        s[rng.integers(0, L, 30)] = 1e30
+        s[rng.integers(0, L, 30)] = -1e30
+        return s
+    if kind == "denormal":
+        return (rng.integers(-3, 4, size=L) * 2.0 ** -149).astype(np.float32)
+    if kind == "chunk_starts":
+        s = (0.008 * (1 + 0.3 * rng.standard_normal(L))).clip(1e-4).astype(np.float32)
+        s[::1024] *= 3
+        return s
+    return (0.008 * (1 + 0.3 * rng.standard_normal(L))).clip(1e-4).astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["signed", "logarithms", "half_zero", "flat", "outliers", "denormal"])
+def test_averages_of_any_sign_and_scale(kind):
+    """The bins of the averages start at a sampled sum of any sign: both ways of counting, a body of few cells (all of the
+    sample is one of them) and of many, the straight-line sizes and others; bit-exact with the oracle."""
+    for L, budget, mk, ak in ((60, 20, (4, 64), (1, 3)), (9001, 100, (2, 8), tuple(range(1, 17))), (9001, 6000, (1, 3), (2, 16)),
+                              (70001, 2000, (2,), (5, 17, 33)), (262144, 4096, (2, 4, 8), (1, 2, 7, 16))):
+        _announce(f"averages of any sign and scale: {kind} L={L} budget={budget} max={mk} avg={ak}")
+        s = _any_scores(kind, L, np.random.default_rng(L + budget))
+        want = oracle.allocate_max_avg(s, mk, ak, budget, sink=1)
+        got, count = il.ilre_select_max_avg(torch.from_numpy(s).cuda(), budget, mk, ak, 1)
+        torch.cuda.synchronize()
+        n = int(count.item())
+        got = got.cpu().numpy()
+        assert got[:n].tolist() == want.tolist() and (got[n:] == -1).all(), (L, budget, mk, ak)
+
+
+@pytest.mark.parametrize("kind,sink", [("chunk_starts", 0), ("flat", 4), ("logarithms", 4), ("half_zero", 0), ("half_zero", 4)])
+def test_time_of_a_printed_selection_does_not_follow_its_scores(kind, sink):
+    """A sample of each combination's own sums places its bins: scores that are raised on a grid, hardly differ, are negative
+    or half of them zero take about as long as others (two to eleven times with bins of one width upward from the
+    scores' median)."""
+    _announce(f"time of a printed selection: {kind} sink {sink}")
+    L, mk, ak = 1 << 20, (2, 4, 8), tuple(range(1, 17))
+    rng = np.random.default_rng(2)
+    ws = il.alloc_workspace_max_avg(L, 1, 1, 1, 128, sink, mk, len(ak), il.ILRE_F32)
+    us = []
+    for k in (kind, "dense"):
+        dev = torch.from_numpy(_any_scores(k, L, rng)).cuda()
+        us.append(_device_us(lambda: il.ilre_select_max_avg(dev, 4096, mk, ak, sink, workspace=ws)))
+    print(f"{us[0]:.1f} us, other scores {us[1]:.1f} us", flush=True)
+    assert us[0] < 1.7 * us[1]
+
+
+@pytest.mark.parametrize("n_nan", [1, 500, 5000])
+def test_scores_that_are_not_numbers_leave_a_valid_index_list(n_nan):
+    """Scores are finite by contract.  What a NaN among them does to the ranking is open, but the indices stay valid ones:
+    ascending, unique, as many as asked for."""
+    _announce(f"{n_nan} scores of NaN")
+    rng = np.random.default_rng(n_nan)
+    s = rng.random(9000).astype(np.float32)
+    s[rng.permutation(9000)[:n_nan]] = np.nan
+    dev = torch.from_numpy(s).cuda()
+    for mk, ak, budget in (((1,), (1,), 8000), ((2, 4), (1, 2, 3), 600), ((1, 2), (5, 17), 6000)):
+        got, count = il.ilre_select_max_avg(dev, budget, mk, ak, 0)
+        torch.cuda.synchronize()
+        n = int(count.item())
+        got = got.cpu().numpy()
+        assert 0 < n <= budget and (np.diff(got[:n]) > 0).all() and got[0] >= 0 and got[n - 1] < 9000 and (got[n:] == -1).all()
+    got = il.ilre_select(dev, 600, (3, 7)).cpu().numpy()
+    assert (np.diff(got) > 0).all() and got[0] >= 0 and got[-1] < 9000
