@@ -75,7 +75,8 @@ constexpr uint32_t kSortSmall = 4096;             // printed form: lists up to t
 
 // Per-combination description, host -> sel_init (by value).
 struct SelParams {
-    const float *body;
+    const float *src;                             // the body, or the cells
+    uint64_t off[ILRE_MAX_POOL_KERNELS];
     uint32_t want[ILRE_MAX_POOL_KERNELS], len[ILRE_MAX_POOL_KERNELS];
     uint64_t tie_off[ILRE_MAX_POOL_KERNELS];
     uint16_t m[ILRE_MAX_POOL_KERNELS], avg[ILRE_MAX_POOL_KERNELS];
@@ -251,11 +252,11 @@ __global__ __launch_bounds__(kThreads) void sel_init(const SelParams prm, uint32
         auto sum_of = [&](auto size_tag) {
             constexpr int M = decltype(size_tag)::value;  // 0: any
             float sum = 0.0f;
-#pragma unroll 4
+#pragma unroll(M == 1 ? 16 : 4)
             for (int c = part; c < n; c += 4) {
                 const int64_t at = first + c;
                 const bool in = at >= 0 && at < (int64_t)len;
-                const float *src = prm.body + (in ? at : 0) * (M ? M : m);
+                const float *src = prm.src + prm.off[j] + (in ? at : 0) * (M ? M : m);
                 float v = src[0];
                 if (M != 0) {
 #pragma unroll
@@ -675,24 +676,59 @@ constexpr int kAvgNarrow = 2, kAvgWide = 4;       // windows a lane sums
 constexpr int kAvgGroup = 16;                     // average kernels a workgroup handles
 constexpr int kAvgList = 256;                     // any sizes: collected elements a workgroup holds per average kernel before it writes them
 constexpr uint16_t kNoAvg = 0xFFFF;
-// LDS of pool_averages: counts or collected elements, then a buffer of cells per wavefront (readable two past the last)
-constexpr size_t avg_shared(int pass, int per, bool small)
+// LDS of pool_averages: counts or collected elements, then a buffer of cells per wavefront (readable kAvgAhead past the last)
+constexpr int kAvgAhead = 8;
+constexpr size_t avg_shared(int pass, int per, bool small, int rows)
 {
-    return pass == 0 ? ((size_t)kAvgGroup * kAvgBins + 64) * sizeof(uint32_t)
-                     : (small ? (size_t)kAvgWaves * 64 * per : (size_t)kAvgList) * kAvgGroup * sizeof(uint64_t);
+    return pass == 0 ? ((size_t)rows * kAvgBins + 64) * sizeof(uint32_t)
+                     : (small ? (size_t)kAvgWaves * 64 * per : (size_t)kAvgList) * rows * sizeof(uint64_t);
 }
-constexpr size_t avg_lds(int pass, int per, bool small, int n_top)
+constexpr size_t avg_lds(int pass, int per, bool small, int rows, int n_top)
 {
-    return avg_shared(pass, per, small) + (size_t)kAvgWaves * (size_t)(64 * per + (small ? kAvgGroup : n_top) + 1) * sizeof(float);
+    return avg_shared(pass, per, small, rows) + (size_t)kAvgWaves * (size_t)(64 * per + (small ? kAvgGroup : n_top) + kAvgAhead) * sizeof(float);
 }
 
 struct AvgParams {
-    int n_avg, groups;                                    // average kernels, groups of kAvgGroup of them
+    int n_avg, groups, rows;                              // average kernels, groups of kAvgGroup of them, kernels in the first group
+    bool pooled;                                          // the cells are there already (pool_cells)
     uint32_t m[ILRE_MAX_POOL_KERNELS], len[ILRE_MAX_POOL_KERNELS];  // per max kernel: size, cells
     uint64_t off[ILRE_MAX_POOL_KERNELS];                  // its cells
     uint16_t avg[ILRE_MAX_POOL_KERNELS], at[ILRE_MAX_POOL_KERNELS];  // average kernels ascending, and their number in the order given
     uint16_t at_of_size[kAvgGroup];                       // SMALL: number of the average kernel of size 1, 2, .. (kNoAvg: none)
 };
+
+// The strided max pooling on its own, where cells are large or windows reach over so many of them that each would be pooled
+// several times: 4, 16 or 64 neighbouring lanes read a cell's tokens side by side, kCellBatch cells of each in flight.
+// grid = (workgroups, max kernels).
+constexpr int kCellBatch = 4;
+__global__ __launch_bounds__(kPoolThreads) void pool_cells(const float *body, const AvgParams ap, float *cells)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t m = ap.m[blockIdx.y], len = ap.len[blockIdx.y];
+    float *out = cells + ap.off[blockIdx.y];
+    const uint32_t lanes = m < 16 ? 4u : m < 64 ? 16u : 64u, side = 64u / lanes, sub = lane & (lanes - 1);
+    const uint32_t step = side * kCellBatch;
+    for (uint64_t p0 = (uint64_t)(blockIdx.x * kPoolWaves + wave) * step; p0 < len; p0 += (uint64_t)gridDim.x * kPoolWaves * step) {
+        float v[kCellBatch];
+        const float *src[kCellBatch];
+        uint32_t p[kCellBatch];
+#pragma unroll
+        for (int b = 0; b < kCellBatch; ++b) {
+            p[b] = (uint32_t)p0 + b * side + lane / lanes;
+            src[b] = body + (size_t)min(p[b], len - 1) * m;
+            v[b] = src[b][0];
+        }
+        for (uint32_t u = sub; u < m; u += lanes)
+#pragma unroll
+            for (int b = 0; b < kCellBatch; ++b) v[b] = fmaxf(v[b], src[b][u]);
+        for (uint32_t o = 1; o < lanes; o <<= 1)
+#pragma unroll
+            for (int b = 0; b < kCellBatch; ++b) v[b] = fmaxf(v[b], __shfl_xor(v[b], (int)o));
+#pragma unroll
+        for (int b = 0; b < kCellBatch; ++b)
+            if (sub == 0 && p[b] < len) out[p[b]] = v[b];
+    }
+}
 
 // The cut of a combination: 1 + the highest bin b with at least `need` elements in the bins from b up (0: fewer than that
 // were counted, everything is wanted).  By one wavefront: lane l sums 16 bins in descending order of bins, a scan over the
@@ -765,7 +801,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
     const uint32_t pitch = CHUNK + (SMALL ? kAvgGroup : n_top) - 1;
     uint32_t *lh = (uint32_t *)smem;      // PASS 0: [kAvgGroup][kAvgBins], then a word per lane
     uint64_t *ll = (uint64_t *)smem;      // PASS 1: [kAvgGroup][kAvgList], sum above element; SMALL: [kAvgWaves][QUEUE]
-    float *buf = (float *)(smem + avg_shared(PASS, PER, SMALL)) + (size_t)wave * (pitch + 2);
+    float *buf = (float *)(smem + avg_shared(PASS, PER, SMALL, SMALL ? kAvgGroup : ap.rows)) + (size_t)wave * (pitch + kAvgAhead);
     float *out = cells + ap.off[i];
     const uint32_t chunks = len ? (uint32_t)(((uint64_t)len + ahead + CHUNK - 1) / CHUNK) : 0u;
 
@@ -774,7 +810,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
         constexpr int M = decltype(size_tag)::value;  // 0: any
         const uint32_t at = cell < 0 ? 0u : (cell < (int64_t)len ? (uint32_t)cell : len - 1);
         float v;
-        if (PASS == 1) {
+        if (PASS == 1 || (M == 1 && ap.pooled)) {
             v = out[at];
         } else if (M != 0) {
             const float *src = body + (size_t)at * M;
@@ -794,7 +830,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
 #pragma unroll
             for (int k = 0; k <= PER; ++k) v[k] = stage(size_tag, first + lane + 64 * k);
         };
-        if (PASS == 1 || m == 1)
+        if (PASS == 1 || ap.pooled || m == 1)
             all(std::integral_constant<int, 1>{});
         else if (m == 2)
             all(std::integral_constant<int, 2>{});
@@ -865,10 +901,20 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
         for (int k = 0; k <= PER; ++k) {
             const uint32_t x = lane + 64 * k;
             if (x < pitch) buf[x] = cell[k];
-            if (PASS == 0 && g0 == 0 && k < PER && first + x >= 0 && first + x < (int64_t)len) out[first + x] = cell[k];
+            if (PASS == 0 && !ap.pooled && g0 == 0 && k < PER && first + x >= 0 && first + x < (int64_t)len) out[first + x] = cell[k];
         }
-        if (!SMALL)
-            for (uint32_t x = lane + 64 * (PER + 1); x < pitch; x += 64) buf[x] = stage(std::integral_constant<int, 0>{}, first + x);
+        if (!SMALL) {
+            constexpr int kBatch = 8;
+            for (uint32_t x0 = lane + 64 * (PER + 1); x0 < pitch + lane; x0 += 64 * kBatch) {  // uniform
+                float more[kBatch];
+#pragma unroll
+                for (int b = 0; b < kBatch; ++b)
+                    more[b] = ap.pooled ? stage(std::integral_constant<int, 1>{}, first + x0 + 64 * b) : stage(std::integral_constant<int, 0>{}, first + x0 + 64 * b);
+#pragma unroll
+                for (int b = 0; b < kBatch; ++b)
+                    if (x0 + 64 * b < pitch) buf[x0 + 64 * b] = more[b];
+            }
+        }
         lds_wave_sync();
         if (c0 + gridDim.x * kAvgWaves < chunks) fetch(c + gridDim.x * kAvgWaves, cell);  // in flight while this chunk is summed
 
@@ -932,26 +978,34 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
             continue;
         }
 
-        // any sizes: a rolled loop, its LDS reads two steps ahead
-        float now[PER], next[PER];
+        // any sizes: a rolled loop, kAvgAhead cells a window read ahead of their additions (one by one with two in flight, a
+        // window of 1024 cells took 3 - 5 times as long as the whole selection otherwise does)
+        for (int q = 0, from = 0; q < ng;) {
+            const int to = (int)of(l_size, q);
+            for (int u = from; u < to; u += kAvgAhead) {
+                float x[PER][kAvgAhead];
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            now[k] = buf[lane + 64 * k];
-            next[k] = buf[lane + 64 * k + 1];
-        }
-        int q = 0;
-        for (uint32_t u = 0; q < ng; ++u) {
+                for (int i = 0; i < kAvgAhead; ++i)
 #pragma unroll
-            for (int k = 0; k < PER; ++k) {
-                sum[k] = sum[k] + now[k];
-                now[k] = next[k];
-                next[k] = buf[lane + 64 * k + u + 2];
+                    for (int k = 0; k < PER; ++k) x[k][i] = buf[lane + 64 * k + u + i];
+                if (u + kAvgAhead <= to) {
+#pragma unroll
+                    for (int i = 0; i < kAvgAhead; ++i)
+#pragma unroll
+                        for (int k = 0; k < PER; ++k) sum[k] = sum[k] + x[k][i];
+                } else {
+#pragma unroll
+                    for (int i = 0; i < kAvgAhead; ++i)
+#pragma unroll
+                        for (int k = 0; k < PER; ++k) sum[k] = u + i < to ? sum[k] + x[k][i] : sum[k];
+                }
             }
-            for (; q < ng && of(l_size, q) == u + 1; ++q) {  // average kernel q's sums are complete
+            from = to;
+            for (; q < ng && (int)of(l_size, q) == to; ++q) {  // average kernel q's sums are complete
                 const float edge = of_f(l_edge, q);
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
-                    const uint32_t el = el0 + 64u * k + u / 2;
+                    const uint32_t el = el0 + 64u * k + (uint32_t)(to - 1) / 2;
                     const bool hit = !(sum[k] < edge) && el < len;
                     if (PASS == 0) {
                         if (hit) atomicAdd(&lh[q * kAvgBins + bin_from(sum[k], edge, of(l_span, q), of(l_shift, q))], 1u);
@@ -964,7 +1018,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
                         if (hit && at < (uint32_t)kAvgList) ll[q * kAvgList + at] = (uint64_t)__float_as_uint(sum[k]) << 32 | el;
                         if (__any(hit && at >= (uint32_t)kAvgList)) {  // the workgroup's list is full
                             SelCtrl *ct = &ctrl[c_comb[q]];
-                            const uint64_t key = make_key(__fdiv_rn(sum[k], (float)(u + 1)), el);
+                            const uint64_t key = make_key(__fdiv_rn(sum[k], (float)to), el);
                             wave_append(hit && at >= (uint32_t)kAvgList, key, lists + ct->tie_off, &ct->tie_n);
                         }
                     }
@@ -1967,7 +2021,7 @@ template <int PASS, int PER, bool SMALL>
 hipError_t raise_avg_lds()
 {
     return hipFuncSetAttribute((const void *)pool_averages<PASS, PER, SMALL>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)avg_lds(PASS, PER, SMALL, SMALL ? kAvgGroup : ILRE_MAX_AVG_KERNEL));
+                               (int)avg_lds(PASS, PER, SMALL, kAvgGroup, SMALL ? kAvgGroup : ILRE_MAX_AVG_KERNEL));
 }
 
 // One chunk of windows a wavefront where that is at most two workgroups a compute unit, more of them beyond: a
@@ -1979,7 +2033,7 @@ void launch_averages(const float *scores, float *cells, const AvgParams &ap, int
     const uint32_t rows = (uint32_t)(n_max * ap.groups), per_wg = kAvgWaves * 64 * PER;
     const uint32_t want = (uint32_t)((len_max + n_top + per_wg - 1) / per_wg), most = 2 * kNumCU / rows;
     const uint32_t gx = want < most ? want : (most > 16 ? most : 16u);
-    hipLaunchKernelGGL((pool_averages<PASS, PER, SMALL>), dim3(gx, rows), dim3(kAvgThreads), avg_lds(PASS, PER, SMALL, n_top), s, scores, cells, ap,
+    hipLaunchKernelGGL((pool_averages<PASS, PER, SMALL>), dim3(gx, rows), dim3(kAvgThreads), avg_lds(PASS, PER, SMALL, SMALL ? kAvgGroup : ap.rows, n_top), s, scores, cells, ap,
                        ctrl, hist, done, lists);
 }
 
@@ -2216,6 +2270,7 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
     }
     ap.n_avg = job.n_avg;
     ap.groups = (job.n_avg + kAvgGroup - 1) / kAvgGroup;
+    ap.rows = std::min(job.n_avg, kAvgGroup);
     int order[ILRE_MAX_POOL_KERNELS];
     for (int k = 0; k < job.n_avg; ++k) order[k] = k;
     std::stable_sort(order, order + job.n_avg, [&](int x, int y) { return job.avg_kernels[x] < job.avg_kernels[y]; });
@@ -2232,8 +2287,15 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
         at = ap.at[k];
     }
     const bool wide = small && coarse;
-    prm.body = scores;
+    int m_top = 1;
+    for (int i = 0; i < job.n_max; ++i) m_top = std::max(m_top, job.max_kernels[i]);
+    ap.pooled = m_top > 8 || n_top > 64;
+    prm.src = ap.pooled ? cells : scores;
     for (int j = 0; j < n; ++j) {
+        if (ap.pooled) {
+            prm.off[j] = ap.off[j / job.n_avg];
+            prm.m[j] = 1;
+        }
         // counted kAvgWide at a time, the K_j best ones may be as few as a quarter as many, next to each other
         const SampleRanks r = sample_ranks((wide ? kAvgWide : 1.0) * prm.want[j], prm.want[j], std::max(1.0, (double)prm.len[j]));
         prm.lo[j] = (uint8_t)r.lo;
@@ -2242,6 +2304,8 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
     uint32_t sort_n = kSortSmall;  // elements are sorted in LDS, up to a power of two of them
     for (int j = 0; j < n; ++j)
         while (sort_n < prm.want[j]) sort_n *= 2;
+    if (ap.pooled)
+        hipLaunchKernelGGL(pool_cells, dim3((unsigned)std::min<int64_t>((L + 4095) / 4096, 1024), job.n_max), dim3(kPoolThreads), 0, s, scores, ap, cells);
     hipLaunchKernelGGL(sel_init, dim3(n), dim3(kThreads), 0, s, prm, hist, ctrl, done);
     if (wide)
         launch_averages<0, kAvgWide, true>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);

@@ -921,3 +921,37 @@ def test_scores_that_are_not_numbers_leave_a_valid_index_list(n_nan):
         assert 0 < n <= budget and (np.diff(got[:n]) > 0).all() and got[0] >= 0 and got[n - 1] < 9000 and (got[n:] == -1).all()
     got = il.ilre_select(dev, 600, (3, 7)).cpu().numpy()
     assert (np.diff(got) > 0).all() and got[0] >= 0 and got[-1] < 9000
+
+
+@pytest.mark.parametrize("L,mk", [(9000, (9, 15)), (9001, (16, 17, 1)), (40000, (63, 64)), (70001, (65, 2)), (70000, (1024, 1023)), (1000, (1024, 8)), (1025, (1024,))],
+                         ids=lambda x: str(x).replace(" ", ""))
+def test_large_cells_and_long_windows(L, mk):
+    """Cells of more than 8 tokens, or windows of more than 64 cells, are pooled by a kernel of their own: sizes around its 4,
+    16 and 64 lanes a cell, bodies that end inside a cell or are shorter than one, windows around the eight cells that are
+    read together; bit-exact with the oracle."""
+    for ak in ((1, 16), (7, 8, 9), (64, 65), (1024, 3), (5, 5, 1000)):
+        for budget in (50, min(3000, L - 1)):
+            _announce(f"large cells and long windows L={L} max={mk} avg={ak} budget={budget}")
+            s = _any_scores("signed" if ak[0] == 7 else "dense", L, np.random.default_rng(L + budget))
+            want = oracle.allocate_max_avg(s, mk, ak, budget, sink=1)
+            got, count = il.ilre_select_max_avg(torch.from_numpy(s).cuda(), budget, mk, ak, 1)
+            torch.cuda.synchronize()
+            n = int(count.item())
+            got = got.cpu().numpy()
+            assert got[:n].tolist() == want.tolist() and (got[n:] == -1).all(), (ak, budget)
+
+
+@pytest.mark.parametrize("mk,ak,most", [((64,), tuple(range(1, 17)), 2.5), ((1024,), (5,), 2.5), ((2,), (1024,), 5.0), ((1024,), (1024,), 5.0)],
+                         ids=["cells_of_64", "cells_of_1024", "windows_of_1024", "both"])
+def test_time_of_a_printed_selection_with_large_sizes(mk, ak, most):
+    """Against cells of 8 tokens and windows of up to 16 of them.  (A lane that reads a cell's tokens one after the other,
+    each cell for every window that reaches over it, and adds a window's cells one by one: 7 to 50 times as long.)"""
+    _announce(f"time of a printed selection: max {mk} avg {ak}")
+    L = 1 << 20
+    dev = torch.from_numpy(_any_scores("dense", L, np.random.default_rng(2))).cuda()
+    us = []
+    for m, a in ((mk, ak), ((8,), tuple(range(1, 17)))):
+        ws = il.alloc_workspace_max_avg(L, 1, 1, 1, 128, 0, m, len(a), il.ILRE_F32)
+        us.append(_device_us(lambda: il.ilre_select_max_avg(dev, 4096, m, a, 0, workspace=ws)))
+    print(f"{us[0]:.1f} us, ordinary sizes {us[1]:.1f} us", flush=True)
+    assert us[0] < most * us[1]
