@@ -246,14 +246,15 @@ __global__ __launch_bounds__(kThreads) void sel_init(const SelParams prm, uint32
     const uint32_t len = prm.len[j];
     SelCtrl c{};
     if (len) {  // uniform
-        // a window's cells are tokens side by side: the sample's four threads take every fourth cell
-        const int part = threadIdx.x & 3, n = prm.avg[j];
-        const int64_t m = prm.m[j], first = sample_at(threadIdx.x >> 2, len) - (n - 1) / 2;
+        // a window's cells are tokens side by side: four threads share a window, or sixteen a long one, a quarter as many
+        // of them (all samples of 1024 cells: 35 us of loads for one compute unit), each four times in the sample
+        const int n = prm.avg[j], lanes = n > 64 ? 16 : 4, part = threadIdx.x & (lanes - 1);
+        const int64_t m = prm.m[j], first = sample_at((threadIdx.x - part) >> 2, len) - (n - 1) / 2;
         auto sum_of = [&](auto size_tag) {
             constexpr int M = decltype(size_tag)::value;  // 0: any
             float sum = 0.0f;
 #pragma unroll(M == 1 ? 16 : 4)
-            for (int c = part; c < n; c += 4) {
+            for (int c = part; c < n; c += lanes) {
                 const int64_t at = first + c;
                 const bool in = at >= 0 && at < (int64_t)len;
                 const float *src = prm.src + prm.off[j] + (in ? at : 0) * (M ? M : m);
@@ -281,7 +282,11 @@ __global__ __launch_bounds__(kThreads) void sel_init(const SelParams prm, uint32
             sum = sum_of(std::integral_constant<int, 0>{});
         sum += __shfl_xor(sum, 1);
         sum += __shfl_xor(sum, 2);
-        if (part == 0) key[threadIdx.x >> 2] = ordered_bits(sum);
+        if (lanes == 16) {
+            sum += __shfl_xor(sum, 4);
+            sum += __shfl_xor(sum, 8);
+        }
+        if ((threadIdx.x & 3) == 0) key[threadIdx.x >> 2] = ordered_bits(sum);
         sampled_bounds(key, prm.lo[j], prm.hi[j], bound);
         auto shift_for = [](uint32_t keys, int bits) { return keys >> bits ? (uint32_t)(32 - bits - __clz((int)keys)) : 0u; };
         static_assert(kAvgBins == 256, "2^7 bins up to the second key, 2^6 to the third");
@@ -698,15 +703,16 @@ struct AvgParams {
 };
 
 // The strided max pooling on its own, where cells are large or windows reach over so many of them that each would be pooled
-// several times: 4, 16 or 64 neighbouring lanes read a cell's tokens side by side, kCellBatch cells of each in flight.
+// several times: 1, 4, 16 or 64 neighbouring lanes read a cell's tokens side by side, kCellBatch cells of each in flight.
 // grid = (workgroups, max kernels).
 constexpr int kCellBatch = 4;
+__host__ __device__ constexpr uint32_t cell_lanes(uint32_t m) { return m < 4 ? 1u : m < 16 ? 4u : m < 64 ? 16u : 64u; }
 __global__ __launch_bounds__(kPoolThreads) void pool_cells(const float *body, const AvgParams ap, float *cells)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t m = ap.m[blockIdx.y], len = ap.len[blockIdx.y];
     float *out = cells + ap.off[blockIdx.y];
-    const uint32_t lanes = m < 16 ? 4u : m < 64 ? 16u : 64u, side = 64u / lanes, sub = lane & (lanes - 1);
+    const uint32_t lanes = cell_lanes(m), side = 64u / lanes, sub = lane & (lanes - 1);
     const uint32_t step = side * kCellBatch;
     for (uint64_t p0 = (uint64_t)(blockIdx.x * kPoolWaves + wave) * step; p0 < len; p0 += (uint64_t)gridDim.x * kPoolWaves * step) {
         float v[kCellBatch];
@@ -2304,8 +2310,14 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
     uint32_t sort_n = kSortSmall;  // elements are sorted in LDS, up to a power of two of them
     for (int j = 0; j < n; ++j)
         while (sort_n < prm.want[j]) sort_n *= 2;
-    if (ap.pooled)
-        hipLaunchKernelGGL(pool_cells, dim3((unsigned)std::min<int64_t>((L + 4095) / 4096, 1024), job.n_max), dim3(kPoolThreads), 0, s, scores, ap, cells);
+    if (ap.pooled) {
+        uint32_t wgs = 1;
+        for (int i = 0; i < job.n_max; ++i) {
+            const uint32_t per_wg = 64u / cell_lanes(ap.m[i]) * kCellBatch * kPoolWaves;
+            wgs = std::max(wgs, std::min((ap.len[i] + per_wg - 1) / per_wg, 4u * kNumCU));
+        }
+        hipLaunchKernelGGL(pool_cells, dim3(wgs, job.n_max), dim3(kPoolThreads), 0, s, scores, ap, cells);
+    }
     hipLaunchKernelGGL(sel_init, dim3(n), dim3(kThreads), 0, s, prm, hist, ctrl, done);
     if (wide)
         launch_averages<0, kAvgWide, true>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
