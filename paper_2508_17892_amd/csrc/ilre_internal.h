@@ -157,8 +157,8 @@ struct SelCtrl {
     uint32_t tie_n;       // elements collected
     uint32_t len;         // elements in the source array
     float edge;           // window sums below it are not counted: the bins start here
-    uint32_t span;        // keys (of float bits) the fine bins cover
-    uint32_t fine, coarse;  // keys a bin spans up to there and beyond, as shifts
+    uint32_t span[2];     // keys (of float bits) from there on that the first range of bins covers, the first two cover
+    uint32_t shifts;      // keys a bin of the three ranges spans, as shifts, a byte each
     uint32_t cut;         // 1 + the lowest bin of which elements are collected (0: all elements)
     uint64_t tie_off;     // lists of elements: uint64 words from the base of the tie region
 };

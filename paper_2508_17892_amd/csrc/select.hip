@@ -79,8 +79,8 @@ struct SelParams {
     uint64_t off[ILRE_MAX_POOL_KERNELS];
     uint32_t want[ILRE_MAX_POOL_KERNELS], len[ILRE_MAX_POOL_KERNELS];
     uint64_t tie_off[ILRE_MAX_POOL_KERNELS];
-    uint16_t m[ILRE_MAX_POOL_KERNELS], avg[ILRE_MAX_POOL_KERNELS];
-    uint8_t lo[ILRE_MAX_POOL_KERNELS], hi[ILRE_MAX_POOL_KERNELS];  // ranks in the sample that place the bins
+    uint32_t m[ILRE_MAX_POOL_KERNELS], avg[ILRE_MAX_POOL_KERNELS];
+    uint32_t ranks[ILRE_MAX_POOL_KERNELS];        // in the sample: lo, mid, hi and 0, a byte each
 };
 
 // Order-preserving map of a finite float onto uint32 (larger float -> larger key; the two zeros share one).
@@ -195,18 +195,19 @@ __device__ __forceinline__ int64_t sample_at(uint32_t t, int64_t n)
     return begin + (int64_t)(((uint64_t)h * (uint64_t)(end - begin)) >> 32);
 }
 
-// The sample's keys of the ranks lo, hi and 0 (the largest) into `bound`: a wavefront each finds one bit by bit, with the
-// whole sample in its registers.  (Comparing each sample with all others took the workgroup 3 us.)
-__device__ __forceinline__ void sampled_bounds(const uint32_t (&key)[kBaseSamples], uint32_t lo, uint32_t hi, uint32_t (&bound)[3])
+// The sample's keys of N <= 4 ranks (0: the largest; a byte of `ranks` each) into `bound`: a wavefront each finds one bit by
+// bit, with the whole sample in its registers.  (Comparing each sample with all others took the workgroup 3 us.)
+template <int N>
+__device__ __forceinline__ void sampled_bounds(const uint32_t (&key)[kBaseSamples], uint32_t ranks, uint32_t (&bound)[N])
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     __syncthreads();
-    if (wave < 3) {
+    if (wave < N) {
         constexpr int kOwn = kBaseSamples / 64;
         uint32_t k[kOwn], at = 0;
 #pragma unroll
         for (int i = 0; i < kOwn; ++i) k[i] = key[64 * i + lane];
-        const int want = (int)(wave == 0 ? lo : wave == 1 ? hi : 0u) + 1;
+        const int want = (int)(ranks >> (8 * wave) & 255u) + 1;
         for (uint32_t bit = 0x80000000u; bit; bit >>= 1) {
             int n = 0;
 #pragma unroll
@@ -229,16 +230,16 @@ SampleRanks sample_ranks(double want_lo, double want_hi, double len)
     return {(uint32_t)std::min(lo + 4 * sqrt(lo) + 4, kBaseSamples - 1.0), (uint32_t)std::min(std::max(hi - 4 * sqrt(hi) - 4, 2.0), kBaseSamples - 1.0)};
 }
 
-// Clears the counters and places each combination's bins by a sample of its own window sums: half of them between the
-// sample's keys of the ranks lo and hi, a quarter from there to its largest, and the rest beyond.  At most a few hundredths
-// of the elements more than are wanted reach the lowest bin, whatever the scores look like, and few are in one bin.
+// Clears the counters and places each combination's bins by a sample of its own window sums: a quarter of them between its
+// keys of the ranks lo and mid, of mid (where the cut is expected) and hi, of hi and 0, and the rest beyond.  At most a few
+// hundredths of the elements more than are wanted reach the lowest bin, whatever the scores look like, and few are in one.
 // (Bins of a fixed width, 64 a binade, upward from the scores' median: 1M scores that differ by a thousandth 1170 us,
 // their logarithms 831, raised at every 1024th token 847, where others take 100.  More bins than these do not pay: every
 // workgroup adds its counts to the global ones, a request per cache line; with 1024 bins counting took 50 us on 1M tokens.)
 __global__ __launch_bounds__(kThreads) void sel_init(const SelParams prm, uint32_t *hist, SelCtrl *ctrl, uint32_t *done)
 {
     __shared__ __align__(16) uint32_t key[kBaseSamples];
-    __shared__ uint32_t bound[3];
+    __shared__ uint32_t bound[4];
     const int j = blockIdx.x;
     static_assert(kThreads == 4 * kBaseSamples, "four threads a sample");
     static_assert(kAvgBins <= kThreads, "a word a thread");
@@ -248,38 +249,47 @@ __global__ __launch_bounds__(kThreads) void sel_init(const SelParams prm, uint32
     if (len) {  // uniform
         // a window's cells are tokens side by side: four threads share a window, or sixteen a long one, a quarter as many
         // of them (all samples of 1024 cells: 35 us of loads for one compute unit), each four times in the sample
-        const int n = prm.avg[j], lanes = n > 64 ? 16 : 4, part = threadIdx.x & (lanes - 1);
+        const int n = (int)prm.avg[j], lanes = n > 64 ? 16 : 4, part = threadIdx.x & (lanes - 1);
         const int64_t m = prm.m[j], first = sample_at((threadIdx.x - part) >> 2, len) - (n - 1) / 2;
-        auto sum_of = [&](auto size_tag) {
+        auto sum_of = [&](auto size_tag, auto batch_tag) {
             constexpr int M = decltype(size_tag)::value;  // 0: any
+            constexpr int kBatch = decltype(batch_tag)::value;
             float sum = 0.0f;
-#pragma unroll(M == 1 ? 16 : 4)
-            for (int c = part; c < n; c += lanes) {
-                const int64_t at = first + c;
-                const bool in = at >= 0 && at < (int64_t)len;
-                const float *src = prm.src + prm.off[j] + (in ? at : 0) * (M ? M : m);
-                float v = src[0];
-                if (M != 0) {
+            for (int c0 = part; c0 < n; c0 += lanes * kBatch) {
+                float v[kBatch];
 #pragma unroll
-                    for (int u = 1; u < M; ++u) v = fmaxf(v, src[u]);
-                } else {
-                    for (int u = 1; u < (int)m; ++u) v = fmaxf(v, src[u]);
+                for (int b = 0; b < kBatch; ++b) {
+                    const int64_t at = first + c0 + lanes * b;
+                    const bool in = c0 + lanes * b < n && at >= 0 && at < (int64_t)len;
+                    const float *src = prm.src + prm.off[j] + (in ? at : 0) * (M ? M : m);
+                    float x = src[0];
+                    if (M != 0) {
+#pragma unroll
+                        for (int u = 1; u < M; ++u) x = fmaxf(x, src[u]);
+                    } else {
+                        for (int u = 1; u < (int)m; ++u) x = fmaxf(x, src[u]);
+                    }
+                    v[b] = in ? x : 0.0f;
                 }
-                sum += in ? v : 0.0f;
+#pragma unroll
+                for (int b = 0; b < kBatch; ++b) sum += v[b];
             }
             return sum;
         };
+        using std::integral_constant;
         float sum;
-        if (m == 1)
-            sum = sum_of(std::integral_constant<int, 1>{});
+        if (m == 1 && lanes == 16)
+            sum = sum_of(integral_constant<int, 1>{}, integral_constant<int, 16>{});
+        else if (m == 1)
+            sum = sum_of(integral_constant<int, 1>{}, integral_constant<int, 4>{});
         else if (m == 2)
-            sum = sum_of(std::integral_constant<int, 2>{});
+            sum = sum_of(integral_constant<int, 2>{}, integral_constant<int, 4>{});
         else if (m == 4)
-            sum = sum_of(std::integral_constant<int, 4>{});
+            sum = sum_of(integral_constant<int, 4>{}, integral_constant<int, 4>{});
         else if (m == 8)
-            sum = sum_of(std::integral_constant<int, 8>{});
+            sum = sum_of(integral_constant<int, 8>{}, integral_constant<int, 4>{});
         else
-            sum = sum_of(std::integral_constant<int, 0>{});
+            sum = sum_of(integral_constant<int, 0>{}, integral_constant<int, 4>{});
         sum += __shfl_xor(sum, 1);
         sum += __shfl_xor(sum, 2);
         if (lanes == 16) {
@@ -287,12 +297,14 @@ __global__ __launch_bounds__(kThreads) void sel_init(const SelParams prm, uint32
             sum += __shfl_xor(sum, 8);
         }
         if ((threadIdx.x & 3) == 0) key[threadIdx.x >> 2] = ordered_bits(sum);
-        sampled_bounds(key, prm.lo[j], prm.hi[j], bound);
-        auto shift_for = [](uint32_t keys, int bits) { return keys >> bits ? (uint32_t)(32 - bits - __clz((int)keys)) : 0u; };
-        static_assert(kAvgBins == 256, "2^7 bins up to the second key, 2^6 to the third");
-        c.span = bound[1] - bound[0];
-        c.fine = shift_for(c.span, 7);
-        c.coarse = bound[2] > bound[1] ? shift_for(bound[2] - bound[1], 6) : 21;  // four bins a binade where the sample says nothing
+        sampled_bounds(key, prm.ranks[j], bound);
+        constexpr int kBits = 6;
+        static_assert(kAvgBins == 4 << kBits, "a quarter of the bins from key to key");
+        auto shift_for = [](uint32_t keys) { return keys >> kBits ? (uint32_t)(32 - kBits - __clz((int)keys)) : 0u; };
+        c.span[0] = bound[1] - bound[0];
+        c.span[1] = bound[2] - bound[0];
+        c.shifts = shift_for(bound[1] - bound[0]) | shift_for(bound[2] - bound[1]) << 8;
+        c.shifts |= (bound[3] > bound[2] ? shift_for(bound[3] - bound[2]) : 21u) << 16;  // four a binade where the sample says nothing
         c.edge = float_of_key(bound[0]);
     }
     if (threadIdx.x == 0) {
@@ -348,12 +360,12 @@ struct SeedInit {
 __global__ __launch_bounds__(kThreads) void seed_init(const SeedInit p, SeedState *st)
 {
     __shared__ __align__(16) uint32_t key[kBaseSamples];
-    __shared__ uint32_t bound[3];
+    __shared__ uint32_t bound[2];
     constexpr int kWords = sizeof(SeedState) / 16, kKept = sizeof(KeyBins) / 16;  // (the bins are written below)
     for (int i = threadIdx.x; i < 2 * kWords; i += kThreads)
         if (i % kWords >= kKept) ((uint4 *)st)[i] = make_uint4(0, 0, 0, 0);
     if (threadIdx.x < kBaseSamples) key[threadIdx.x] = ordered_bits(p.vals[sample_at(threadIdx.x, p.n)]);
-    sampled_bounds(key, p.ranks.lo, p.ranks.hi, bound);
+    sampled_bounds(key, p.ranks.lo | p.ranks.hi << 8, bound);
     if (threadIdx.x == 0) {
         constexpr uint32_t kLow = 256, kMid = 1023, kHigh = kSeedBins - 1 - kLow - kMid;
         const uint32_t top = bound[1] + min(max(bound[1] - bound[0], 1u), 0xFFFFFFFEu - bound[1]);
@@ -851,7 +863,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
     if (blockIdx.x * kAvgWaves < chunks) fetch(blockIdx.x * kAvgWaves + wave, cell);
 
     // average kernel q's numbers are lane q's, in every wavefront (SMALL: the one of size n has number n - 1)
-    uint32_t l_size, l_want, l_span, l_shift;  // l_shift: fine, and coarse above it
+    uint32_t l_size, l_want, l_span0, l_span1, l_shift;
     uint32_t l_len;  // SMALL: elements of that size: none of a size that was not asked for (an edge alone would let sums of +inf pass)
     float l_edge;    // the sum from which on elements matter to this pass
     {
@@ -868,13 +880,13 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
         const bool used = !SMALL || at != kNoAvg;
         const uint32_t j = (uint32_t)(i * ap.n_avg) + (used ? at : 0u), cut = ctrl[j].cut;
         l_want = ctrl[j].want;
-        const uint32_t fine = ctrl[j].fine, coarse = ctrl[j].coarse;
-        l_span = ctrl[j].span;
-        l_shift = fine | coarse << 8;
+        l_span0 = ctrl[j].span[0];
+        l_span1 = ctrl[j].span[1];
+        l_shift = ctrl[j].shifts;
         l_edge = ctrl[j].edge;
         if (PASS == 1) {
-            const uint32_t bin = cut - 1, n_fine = l_span >> fine;
-            const uint32_t at = bin <= n_fine ? bin << fine : l_span + ((bin - n_fine) << coarse);
+            const uint32_t s0 = l_shift & 31u, s1 = l_shift >> 8 & 31u, s2 = l_shift >> 16, n0 = l_span0 >> s0, n1 = n0 + ((l_span1 - l_span0) >> s1);
+            const uint32_t bin = cut - 1, at = bin <= n0 ? bin << s0 : bin <= n1 ? l_span0 + ((bin - n0) << s1) : l_span1 + ((bin - n1) << s2);
             // (a bin that holds something starts at a float's key, +inf at most)
             const float low = fminf(float_of_key(ordered_bits(l_edge) + at), FLT_MAX);
             l_edge = cut ? low - (fabsf(low) * 0x1p-21f + (float)l_size * 0x1p-148f) : -INFINITY;
@@ -889,10 +901,11 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
     }
     auto of = [](uint32_t x, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)x, q); };
     // bin of a sum that is not below the edge (differences of float bits in signed order, modulo 2^32)
-    auto bin_from = [](float x, float edge, uint32_t span, uint32_t shift) {
+    auto bin_from = [](float x, float edge, uint32_t span0, uint32_t span1, uint32_t shifts) {
         auto bits = [](float f) { return __float_as_uint(f) ^ ((uint32_t)(__float_as_int(f) >> 31) >> 1); };
         const uint32_t d = bits(x) - bits(edge);
-        return min((min(d, span) >> (shift & 31u)) + ((max(d, span) - span) >> (shift >> 8)), (uint32_t)kAvgBins - 1u);
+        const uint32_t bin = (min(d, span0) >> (shifts & 31u)) + ((min(max(d, span0), span1) - span0) >> (shifts >> 8 & 31u)) + ((max(d, span1) - span1) >> (shifts >> 16));
+        return min(bin, (uint32_t)kAvgBins - 1u);
     };
     auto of_f = [](float x, int q) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), q)); };
     if (PASS == 0)
@@ -934,7 +947,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
 #pragma unroll
             for (int u = 0; u < kAvgGroup; ++u) {
                 const float edge = of_f(l_edge, u);
-                const uint32_t before = queued, els = of(l_len, u), span = of(l_span, u), shift = of(l_shift, u);
+                const uint32_t before = queued, els = of(l_len, u), span0 = of(l_span0, u), span1 = of(l_span1, u), shifts = of(l_shift, u);
                 float best = -INFINITY;
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
@@ -942,7 +955,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
                     const bool in = el0 + 64u * k + u / 2 < els;
                     // (what is not counted goes to a word of the lane's own)
                     auto count = [&](float x, bool hit) {
-                        const uint32_t bin = bin_from(x, edge, span, shift);
+                        const uint32_t bin = bin_from(x, edge, span0, span1, shifts);
                         atomicAdd(&lh[hit ? u * kAvgBins + bin : (uint32_t)(kAvgGroup * kAvgBins + lane)], 1u);
                     };
                     if (PASS == 0 && PER == kAvgWide) {
@@ -1014,7 +1027,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
                     const uint32_t el = el0 + 64u * k + (uint32_t)(to - 1) / 2;
                     const bool hit = !(sum[k] < edge) && el < len;
                     if (PASS == 0) {
-                        if (hit) atomicAdd(&lh[q * kAvgBins + bin_from(sum[k], edge, of(l_span, q), of(l_shift, q))], 1u);
+                        if (hit) atomicAdd(&lh[q * kAvgBins + bin_from(sum[k], edge, of(l_span0, q), of(l_span1, q), of(l_shift, q))], 1u);
                     } else {
                         const uint64_t mask = __ballot(hit);
                         if (mask == 0) continue;
@@ -1034,23 +1047,20 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
     }
     __syncthreads();
     if (PASS == 0) {
-        constexpr int kBatch = 4;
-        for (int x0 = threadIdx.x * 4; x0 < rows * kAvgBins; x0 += kAvgThreads * 4 * kBatch) {
-            uint4 v[kBatch];
+        // neighbouring lanes, neighbouring bins: an atomic request is a cache line, and all workgroups want the same few (four
+        // bins a lane, 1M tokens, one combination: 46 us for this pass)
+        constexpr int kBatch = 8;
+        for (int x0 = threadIdx.x; x0 < rows * kAvgBins; x0 += kAvgThreads * kBatch) {
+            uint32_t v[kBatch];
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
-                const int x = x0 + b * kAvgThreads * 4;
-                v[b] = x < rows * kAvgBins ? *(const uint4 *)&lh[x] : make_uint4(0, 0, 0, 0);
+                const int x = x0 + b * kAvgThreads;
+                v[b] = x < rows * kAvgBins ? lh[x] : 0u;
             }
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
-                if ((v[b].x | v[b].y | v[b].z | v[b].w) == 0) continue;
-                const int x = x0 + b * kAvgThreads * 4;
-                uint32_t *h = hist + (size_t)c_comb[x / kAvgBins] * kAvgBins + x % kAvgBins;
-                if (v[b].x) atomicAdd(&h[0], v[b].x);
-                if (v[b].y) atomicAdd(&h[1], v[b].y);
-                if (v[b].z) atomicAdd(&h[2], v[b].z);
-                if (v[b].w) atomicAdd(&h[3], v[b].w);
+                const int x = x0 + b * kAvgThreads;
+                if (v[b]) atomicAdd(&hist[(size_t)c_comb[x / kAvgBins] * kAvgBins + x % kAvgBins], v[b]);
             }
         }
         if (count_in(&done[blockIdx.y], gridDim.x, &is_last)) {
@@ -1256,7 +1266,7 @@ __global__ __launch_bounds__(THREADS) void collect(const float *vals, int64_t le
 // the elements of the first `want` go out in order.  False where one of the bins they are in holds more than kRankDeep:
 // the keys then lie in srt[0 .. total) in some order, for the network.
 constexpr int kRankBins = 2048;
-constexpr uint32_t kRankDeep = 128;
+constexpr uint32_t kRankDeep = 512;
 struct RankShared {
     uint32_t bin_n[kRankBins];
     uint32_t wmax[kThreads / 64], wmin[kThreads / 64], wsum[kThreads / 64];
@@ -1308,21 +1318,19 @@ __device__ bool rank_keys(RankShared &sh, uint64_t *srt, const uint64_t (&key)[P
     const bool deep = __syncthreads_or((n2.x > kRankDeep && before < want) || (n2.y > kRankDeep && before + n2.x < want));
 #pragma unroll
     for (int k = 0; k < PER; ++k)
-        if (have >> k & 1u) {
-            bin[k] = sh.bin_n[bin[k]];
-            srt[(bin[k] >> 14) + place[k]] = key[k];
-        }
+        if (have >> k & 1u) srt[(sh.bin_n[bin[k]] >> 14) + place[k]] = key[k];
     __syncthreads();
     if (deep) return false;
-#pragma unroll
-    for (int k = 0; k < PER; ++k)
-        if (have >> k & 1u) {
-            const uint32_t first = bin[k] >> 14, n = bin[k] & 16383u;
-            uint32_t rank = first;
-            if (first >= want) continue;
-            for (uint32_t i = 0; i < n; ++i) rank += srt[first + i] > key[k] ? 1u : 0u;
-            if (rank < want) ranked[rank] = key_token(key[k]);
-        }
+    // neighbouring threads, neighbouring places: a deep bin is the work of the few wavefronts that hold it, from one address
+    for (uint32_t x = threadIdx.x; x < all; x += kThreads) {
+        const uint64_t mine = srt[x];
+        const uint32_t at = sh.bin_n[(top - (uint32_t)(mine >> 32)) >> shift], first = at >> 14, n = at & 16383u;
+        if (first >= want) break;  // (so are those behind it)
+        uint32_t rank = first;
+#pragma unroll 8
+        for (uint32_t i = 0; i < n; ++i) rank += srt[first + i] > mine ? 1u : 0u;
+        if (rank < want) ranked[rank] = key_token(mine);
+    }
     return true;
 }
 
@@ -2252,8 +2260,8 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
         share_of[j] = share;
         cell_of[j] = cell;
         prm.len[j] = (uint32_t)len;
-        prm.m[j] = (uint16_t)cell;
-        prm.avg[j] = (uint16_t)job.avg_kernels[j % job.n_avg];
+        prm.m[j] = (uint32_t)cell;
+        prm.avg[j] = (uint32_t)job.avg_kernels[j % job.n_avg];
         prm.tie_off[j] = (uint64_t)tie_off;
         tie_off += 2 * len;
         if (j % job.n_avg == 0) {
@@ -2304,8 +2312,9 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
         }
         // counted kAvgWide at a time, the K_j best ones may be as few as a quarter as many, next to each other
         const SampleRanks r = sample_ranks((wide ? kAvgWide : 1.0) * prm.want[j], prm.want[j], std::max(1.0, (double)prm.len[j]));
-        prm.lo[j] = (uint8_t)r.lo;
-        prm.hi[j] = (uint8_t)std::min(r.hi, r.lo);
+        const uint32_t hi = std::min(r.hi, r.lo);
+        const double mid = 1.25 * kBaseSamples * prm.want[j] / std::max(1.0, (double)prm.len[j]) + 1;
+        prm.ranks[j] = r.lo | std::min(std::max((uint32_t)mid, hi), r.lo) << 8 | hi << 16;
     }
     uint32_t sort_n = kSortSmall;  // elements are sorted in LDS, up to a power of two of them
     for (int j = 0; j < n; ++j)
