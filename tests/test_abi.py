@@ -157,3 +157,15 @@ def test_row_stats_static_rejects_shapes_beyond_its_buffer():
     assert rc == il.ILRE_EUNSUPPORTED and "static buffer" in il.ilre_last_error()
     assert lib.ilre_row_stats_static(fake, fake, 1000, 8, 8, 2, 128, None, fake, ctypes.byref(o)) == il.ILRE_EINVAL
     assert lib.ilre_row_stats_static(fake, fake, 1000, 8, 8, 2, 64, fake, fake, ctypes.byref(o)) == il.ILRE_EUNSUPPORTED
+
+
+def test_walk_cases_sit_at_the_edge_of_the_bitmap():
+    """The GPU cases of the walk name the number of tokens up to which its set is a bitmap; it is the library's."""
+    import test_gpu_parity as parity_tests
+
+    with open(os.path.join(ROOT, "paper_2508_17892_amd", "csrc", "select.hip")) as f:
+        text = f.read()
+    chunk, chunks = (int(re.search(rf"constexpr int {name} = (\d+);", text).group(1)) for name in ("kBitmapChunk", "kBitmapChunks"))
+    assert parity_tests.BITMAP_TOKENS == chunks * chunk * 32
+    bodies = {c[0] - c[1] - parity_tests.BITMAP_TOKENS for c in parity_tests.WALK_CASES}
+    assert {-1, 0, 1} <= bodies

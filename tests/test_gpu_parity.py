@@ -587,24 +587,28 @@ def test_select_randomised_against_oracle(seed):
             assert got[:n_got].tolist() == want.tolist() and (got[n_got:] == -1).all(), (seed, case, L, kind, budget, mk, ak, sink)
 
 
-# the walk's set of allocated tokens is a bitmap in LDS up to 1179648 tokens and a table of 32-token words beyond
+# the walk's set of allocated tokens is a bitmap in LDS up to so many tokens and a table of 32-token words beyond
+BITMAP_TOKENS = 136 * 256 * 32
 WALK_CASES = [
     # L, sink, budget, window sizes (stride-1 form), max / average sizes (printed form)
-    (1179647, 0, 8192, (1, 63, 3), (1,), (1, 3)),          # last chunk of the bitmap one token short of full; 8 rounds a list
-    (1179648, 0, 4096, (1, 3, 7), (2, 5), (1, 2)),         # the bitmap exactly full
-    (1179652, 4, 4096, (2047, 1), (32, 33), (1, 4)),       # the body exactly full; intervals and cells over many words
-    (1179649, 0, 8192, (1, 1, 31), (1, 64), (2, 1)),       # one token more: the table
-    (8192, 0, 8191, (65, 129, 1), (3, 7), (1, 2, 5)),      # nearly every token kept: shares end inside intervals
+    (BITMAP_TOKENS - 1, 0, 8192, (1, 63, 3), (1,), (1, 3)),      # the bitmap one token short of full; 8 rounds a list
+    (BITMAP_TOKENS, 0, 4096, (1, 3, 7), (2, 5), (1, 2)),         # exactly full
+    (BITMAP_TOKENS + 4, 4, 4096, (2047, 1), (32, 33), (1, 4)),   # the body exactly full; intervals and cells over many words
+    (BITMAP_TOKENS + 1, 0, 8192, (1, 1, 31), (1, 64), (2, 1)),   # one token more: the table
+    (1179648, 0, 4096, (1, 3, 7), (2, 5), (1, 2)),
+    (8192, 0, 8191, (65, 129, 1), (3, 7), (1, 2, 5)),            # nearly every token kept: shares end inside intervals
     (8224, 1, 1, (1,), (8,), (16,)),
 ]
 
 
 @pytest.mark.parametrize("L,sink,budget,windows,mk,ak", WALK_CASES, ids=[f"L{c[0]}_B{c[2]}" for c in WALK_CASES])
 def test_walk_over_bitmap_and_word_table(L, sink, budget, windows, mk, ak):
-    """Both forms of the walk at the edges of its set representations, bit-exact with the oracle."""
+    """Both forms of the walk at the edges of its set representations, bit-exact with the oracle.  The last tokens are among
+    the best ones, so that the bitmap's last chunk is read off."""
     _announce(f"walk L={L} sink={sink} budget={budget}")
     rng = np.random.default_rng(L + budget)
     s = _scores_for("needles", L, rng)
+    s[-3:] = (9.0, 8.5, 9.5)
     dev = torch.from_numpy(s).cuda()
     got = il.ilre_select(dev, budget, windows, sink=sink)
     got_p, count = il.ilre_select_max_avg(dev, budget, mk, ak, sink)
@@ -673,9 +677,10 @@ def test_averages_of_scores_near_the_largest_float(top, ak):
 
 RANK_CASES = [
     # L, budget, copies of a value, kind: lists of one element up to the 4096 that the counting sort takes and one more, bins
-    # of up to 128 equal elements (ranked inside the bin) and one more (the network), ranges of one value and of all
+    # of up to 512 equal elements (ranked inside the bin) and one more (the network), ranges of one value and of all
     (1, 1, 1, "random"), (64, 64, 1, "random"), (1025, 1025, 1, "random"), (4096, 4096, 1, "random"), (4097, 4097, 1, "random"),
     (4096, 4000, 127, "copies"), (4096, 4000, 128, "copies"), (4096, 4000, 129, "copies"), (4096, 4096, 4096, "copies"),
+    (4096, 4000, 511, "copies"), (4096, 4096, 512, "copies"), (4096, 4000, 513, "copies"), (3000, 2900, 513, "copies"),
     (4000, 4000, 1, "two_ends"), (128, 128, 128, "copies"), (4096, 4096, 2, "signs"), (9000, 2000, 3, "signs"),
 ]
 
