@@ -1265,8 +1265,9 @@ __global__ __launch_bounds__(THREADS) void collect(const float *vals, int64_t le
 // Thread t holds PER keys, of which the ones in `have` exist (`total` in all; `top` and `low` enclose their value bits);
 // the elements of the first `want` go out in order.  False where one of the bins they are in holds more than kRankDeep:
 // the keys then lie in srt[0 .. total) in some order, for the network.
+// (A list of 4096 elements all in bins of 128: the whole call 50 us, of 256: 67, of 512: 100; by the network 68.)
 constexpr int kRankBins = 2048;
-constexpr uint32_t kRankDeep = 512;
+constexpr uint32_t kRankDeep = 256;
 struct RankShared {
     uint32_t bin_n[kRankBins];
     uint32_t wmax[kThreads / 64], wmin[kThreads / 64], wsum[kThreads / 64];

@@ -677,10 +677,10 @@ def test_averages_of_scores_near_the_largest_float(top, ak):
 
 RANK_CASES = [
     # L, budget, copies of a value, kind: lists of one element up to the 4096 that the counting sort takes and one more, bins
-    # of up to 512 equal elements (ranked inside the bin) and one more (the network), ranges of one value and of all
+    # of up to 256 equal elements (ranked inside the bin) and one more (the network), ranges of one value and of all
     (1, 1, 1, "random"), (64, 64, 1, "random"), (1025, 1025, 1, "random"), (4096, 4096, 1, "random"), (4097, 4097, 1, "random"),
     (4096, 4000, 127, "copies"), (4096, 4000, 128, "copies"), (4096, 4000, 129, "copies"), (4096, 4096, 4096, "copies"),
-    (4096, 4000, 511, "copies"), (4096, 4096, 512, "copies"), (4096, 4000, 513, "copies"), (3000, 2900, 513, "copies"),
+    (4096, 4000, 255, "copies"), (4096, 4096, 256, "copies"), (4096, 4000, 257, "copies"), (3000, 2900, 257, "copies"),
     (4000, 4000, 1, "two_ends"), (128, 128, 128, "copies"), (4096, 4096, 2, "signs"), (9000, 2000, 3, "signs"),
 ]
 
