@@ -141,8 +141,8 @@ struct SelectLayout {
     size_t hist;      // kSelMaxAvg: uint32 [n][kAvgBins]
     size_t ctrl;      // kSelMaxAvg: SelCtrl [n]
     size_t done;      // kSelMaxAvg: uint32 [n]: workgroups finished per max kernel and group of average kernels
-    size_t cmax;      // float [ceil(L / kSelFine)]: fine-chunk maxima (pruning pre-pass)
-    size_t active;    // uint32 [ceil(L / kSelFine)]: fine chunks left after pruning
+    size_t cmax;      // kSelWindowMax: float [ceil(L / kSelFine)]: fine-chunk maxima (pruning pre-pass)
+    size_t active;    // kSelWindowMax: uint32 [ceil(L / kSelFine)]: fine chunks left after pruning
     size_t cells;     // float: the max-pooled cell arrays, one per max kernel (kSelMaxAvg)
     size_t picked;    // uint32 [ILRE_MAX_BUDGET] the allocated tokens in the order they were taken, then their count
     size_t seed;      // kSelWindowMax, by rank: uint32 token[kCandCap], uint32 distances to the outranking neighbours[kCandCap]
@@ -174,7 +174,7 @@ struct FusedScores {
     int rmax;              // 0 sum, 1 max over the units
     float *scores;         // L floats
     int64_t L;
-    float mean;            // the scores' scale: their mean (sum over the rows) or a lower bound of it (max)
+    float mean;            // the scores' scale (window-max form): their mean (sum over the rows) or a lower bound of it (max)
 };
 
 // The words of a workspace's selection region (at `base`) that have to be zero before a window-max selection with

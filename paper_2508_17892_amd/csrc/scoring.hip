@@ -324,8 +324,9 @@ __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
         }
     } else {
         // The exponent offsets of the workgroup's rows, one row a thread (NB = 1: a pair of threads), handed out through
-        // LDS (a kernel that wrote them to a table before took 4.7 us of a staged call: 50001 tokens 149.9 -> 146.9 us): accumulator registers 4j .. 4j+3 of a lane are four consecutive rows.  Rows past the group's last one,
-        // whose q = 0, get -inf: exp2(0*c - inf) = 0.
+        // LDS (a kernel that wrote them to a table before took 4.7 us of a staged call: 50001 tokens 149.9 -> 146.9 us):
+        // accumulator registers 4j .. 4j+3 of a lane are four consecutive rows.  Rows past the group's last one, whose q = 0,
+        // get -inf: exp2(0*c - inf) = 0.
         issue_first();  // K and Q are on their way meanwhile
         constexpr int ROWS = WAVES * NB * 32, SHARERS = WAVES * 64 / ROWS;
         const int local = tid / SHARERS, rl = qb * ROWS + local;
@@ -581,11 +582,6 @@ __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
     }
 }
 
-// Merge the per-split partial statistics of each row (fixed order) and convert to the natural-log units of
-// Eq. 4: row_max = a reference <= max_t logit, row_sumexp = sum_t exp(logit - row_max).
-// Sixteen lanes share a row and the splits among them, so that all of a row's partials are fetched in one
-// round of loads (a thread a row would fetch them in a chain of memory latencies: this kernel sits between
-// the two scoring passes and is all latency).
 // Pass 2's token ranges from pass 1's workgroup times.  The 8 XCDs of the chip do not run at one speed (their
 // workgroups finish up to 6 % apart, the same dies ahead in every launch), and a launch lasts as long as its
 // slowest XCD.  Split s of every kv head runs on the same XCD when the splits per head are a multiple of 8, so
@@ -668,6 +664,11 @@ __device__ void make_split_table(const BalanceArgs &b)
     }
 }
 
+// Merge the per-split partial statistics of each row (fixed order) and convert to the natural-log units of
+// Eq. 4: row_max = a reference <= max_t logit, row_sumexp = sum_t exp(logit - row_max).
+// Sixteen lanes share a row and the splits among them, so that all of a row's partials are fetched in one
+// round of loads (a thread a row would fetch them in a chain of memory latencies: this kernel sits between
+// the two scoring passes and is all latency).
 __global__ __launch_bounds__(256) void combine_row_stats(const float *part_m, const float *part_z, int nsplit, int64_t nrows,
                                                          float *row_max, float *row_sumexp, const BalanceArgs bal,
                                                          unsigned stat_blocks)

@@ -9,12 +9,13 @@
 // whatever the earlier ones took; in the printed form K_m is given), so the candidate sets are built
 // for all combinations at once:
 //
-//   sel_init     clears histograms and counters, writes each combination's control block
-//   pool_averages<0>   the strided max pooling (one cell array per max kernel) and per combination a histogram of
-//                the averages; the last workgroup of a max kernel finds its combinations' cuts, the bin
-//                that holds the K_j-th best
+//   pool_cells   (cells of more than 8 tokens, or windows of more than 64 cells) the strided max pooling, one cell array
+//                per max kernel
+//   sel_init     clears histograms and counters, and per combination places the histogram's bins by a sample of its averages
+//   pool_averages<0>   the strided max pooling, if not there yet, and per combination a histogram of the averages;
+//                the last workgroup of a max kernel finds its combinations' cuts, the bin that holds the K_j-th best
 //   pool_averages<1>   the averages at or above the cut, into the combination's list
-//   refine       per combination: the list sorted, the first K_j elements kept; a list too long to sort (many equal
+//   refine       per combination: the list ranked, the first K_j elements kept; a list too long to sort (many equal
 //                averages) is radix-selected down first, 8 bits a pass, survivors compacted
 //   allocate_walk   one workgroup walks the combinations in order over their ranked cells: the allocated set is
 //                a bitmap in LDS, tokens that it holds are skipped, the first B_j others are taken; the ascending
@@ -29,7 +30,7 @@
 // of any candidate prefix.  Hence:
 //
 //   seed_init    (ilre_select alone) clears the state and places the histogram's bins by a sample of the scores; in the
-//                whole path the kernel between the scoring passes clears it and the bins follow the scores' mean
+//                whole path the second scoring pass clears it on the side and the bins follow the scores' mean
 //   count_scores a 2048-bin histogram of the scores' order-preserving keys, in LDS, added to the global one; the last
 //                workgroup to finish finds the bin that holds the B'-th largest (reduce_count: the same on the scores'
 //                way from per-unit partial vectors)
@@ -227,7 +228,8 @@ struct SampleRanks {
 SampleRanks sample_ranks(double want_lo, double want_hi, double len)
 {
     const double lo = kBaseSamples * want_lo / len, hi = kBaseSamples * want_hi / len;
-    return {(uint32_t)std::min(lo + 4 * sqrt(lo) + 4, kBaseSamples - 1.0), (uint32_t)std::min(std::max(hi - 4 * sqrt(hi) - 4, 2.0), kBaseSamples - 1.0)};
+    const double last = kBaseSamples - 1.0;
+    return {(uint32_t)std::min(lo + 4 * sqrt(lo) + 4, last), (uint32_t)std::min(std::max(hi - 4 * sqrt(hi) - 4, 2.0), last)};
 }
 
 // Clears the counters and places each combination's bins by a sample of its own window sums: a quarter of them between its
@@ -791,16 +793,16 @@ __device__ __forceinline__ uint32_t find_cut(const uint32_t *h, uint32_t need)
 //
 // Bins follow the bits of the sum upward from ctrl.edge, the last one open above; they are placed by a sample (sel_init), so
 // that the bin of the K_j-th best holds few others and one pass of counting does (two passes of 11 key bits from the
-// sign down took twice as long).  With PER = kAvgWide only the largest of
-// a lane's four sums, 64 windows apart, is counted: the K_j-th best of those is at most the K_j-th best of all, the few
-// elements more that reach it are sorted out later, and a quarter of the additions to LDS, of which 16 lanes' worth
-// takes about as long as all the rest of the loop, are left.  It needs K_j to be well below a quarter of the cells.
+// sign down took twice as long).  With PER = kAvgWide only the largest of a lane's four sums, 64 windows apart, is counted:
+// the K_j-th best of those is at most the K_j-th best of all, the few elements more that reach it are sorted out later,
+// and a quarter of the additions to LDS, of which 16 lanes' worth takes about as long as all the rest of the loop, are
+// left.  It needs K_j to be well below a quarter of the cells.
 //
 // SMALL: average kernels of sizes 1 .. 16, each once (the paper's set): straight-line code without branches.
 // Bound: instructions and LDS round trips of few workgroups on short contexts, additions to the global counts on long ones.
 // Measured (kernel trace), 48 combinations, budget 4096, before -> after (before: every combination pooled its own
-// windows, two histogram passes): counting 29.6 + 26 -> 13.6 us on 128K tokens, 40.6 + 34.0 -> 34.2 us on 1M; collecting
-// 8.1 -> 10.7 us and 23.6 -> 20.4 us; the separate max pooling, 4.7 and 10.1 us, is gone.
+// windows, two histogram passes): counting 29.6 + 26 -> 10.1 us on 128K tokens, 40.6 + 34.0 -> 15.9 us on 1M; collecting
+// 8.1 -> 10.5 us and 23.6 -> 21.1 us; the separate max pooling, 4.7 and 10.1 us, is gone.
 template <int PASS, int PER, bool SMALL>
 __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, float *cells, const AvgParams ap, SelCtrl *ctrl,
                                                              uint32_t *hist, uint32_t *done, uint64_t *lists)
@@ -904,8 +906,8 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
     auto bin_from = [](float x, float edge, uint32_t span0, uint32_t span1, uint32_t shifts) {
         auto bits = [](float f) { return __float_as_uint(f) ^ ((uint32_t)(__float_as_int(f) >> 31) >> 1); };
         const uint32_t d = bits(x) - bits(edge);
-        const uint32_t bin = (min(d, span0) >> (shifts & 31u)) + ((min(max(d, span0), span1) - span0) >> (shifts >> 8 & 31u)) + ((max(d, span1) - span1) >> (shifts >> 16));
-        return min(bin, (uint32_t)kAvgBins - 1u);
+        const uint32_t d0 = min(d, span0), d1 = min(max(d, span0), span1) - span0, d2 = max(d, span1) - span1;
+        return min((d0 >> (shifts & 31u)) + (d1 >> (shifts >> 8 & 31u)) + (d2 >> (shifts >> 16)), (uint32_t)kAvgBins - 1u);
     };
     auto of_f = [](float x, int q) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), q)); };
     if (PASS == 0)
@@ -927,8 +929,10 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
             for (uint32_t x0 = lane + 64 * (PER + 1); x0 < pitch + lane; x0 += 64 * kBatch) {  // uniform
                 float more[kBatch];
 #pragma unroll
-                for (int b = 0; b < kBatch; ++b)
-                    more[b] = ap.pooled ? stage(std::integral_constant<int, 1>{}, first + x0 + 64 * b) : stage(std::integral_constant<int, 0>{}, first + x0 + 64 * b);
+                for (int b = 0; b < kBatch; ++b) {
+                    const int64_t at = first + x0 + 64 * b;
+                    more[b] = ap.pooled ? stage(std::integral_constant<int, 1>{}, at) : stage(std::integral_constant<int, 0>{}, at);
+                }
 #pragma unroll
                 for (int b = 0; b < kBatch; ++b)
                     if (x0 + 64 * b < pitch) buf[x0 + 64 * b] = more[b];
@@ -1364,7 +1368,8 @@ __device__ void rank_network(uint64_t *srt, uint32_t total, uint32_t want, uint3
 // equal averages) is radix-selected down first.  Up to kSortSmall elements go by the counting sort: bound by the latency
 // of its few rounds through LDS on one workgroup a combination, where the network takes a round and a barrier for each of
 // 55 - 78 stages.  Measured (kernel trace): 9001 tokens 8.7 -> 4.8 us, 128K 15.6 -> 5.8 us, 1M
-// 14.4 -> 4.8 us.  Where a bin is deep (equal averages in number) or the list is longer, the network is the faster one still.
+// 14.4 -> 4.8 us; values in two clusters (spans just as many as are wanted, and the background's top) 47 -> 19 us.  Where a bin
+// is deep (equal averages in number) or the list is longer, the network is the faster one still.
 __global__ __launch_bounds__(kThreads) void refine(const SelCtrl *ctrl, uint64_t *cand, uint64_t *tie, uint32_t sort_n)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1995,7 +2000,7 @@ SelectLayout make_select_layout(const SelectJob &job)
     const int n = job.combos() > 0 ? job.combos() : 1;
     const bool window = job.mode == kSelWindowMax;
     const int nh = window ? 1 : n;
-    const size_t nfine = (size_t)((job.L + kSelFine - 1) / kSelFine);
+    const size_t nfine = window ? (size_t)((job.L + kSelFine - 1) / kSelFine) : 0;
     size_t off = 0;
     lay.state = off;
     off = up(off + (window ? 2 * sizeof(SeedState) : 0));
@@ -2040,7 +2045,7 @@ hipError_t raise_avg_lds()
 }
 
 // One chunk of windows a wavefront where that is at most two workgroups a compute unit, more of them beyond: a
-// workgroup carries the clearing and flushing of its 64 KiB of counts.
+// workgroup carries the clearing and flushing of its 16 KiB of counts.
 template <int PASS, int PER, bool SMALL>
 void launch_averages(const float *scores, float *cells, const AvgParams &ap, int n_max, int64_t len_max, int n_top, SelCtrl *ctrl, uint32_t *hist,
                      uint32_t *done, uint64_t *lists, hipStream_t s)
@@ -2048,8 +2053,8 @@ void launch_averages(const float *scores, float *cells, const AvgParams &ap, int
     const uint32_t rows = (uint32_t)(n_max * ap.groups), per_wg = kAvgWaves * 64 * PER;
     const uint32_t want = (uint32_t)((len_max + n_top + per_wg - 1) / per_wg), most = 2 * kNumCU / rows;
     const uint32_t gx = want < most ? want : (most > 16 ? most : 16u);
-    hipLaunchKernelGGL((pool_averages<PASS, PER, SMALL>), dim3(gx, rows), dim3(kAvgThreads), avg_lds(PASS, PER, SMALL, SMALL ? kAvgGroup : ap.rows, n_top), s, scores, cells, ap,
-                       ctrl, hist, done, lists);
+    const size_t lds = avg_lds(PASS, PER, SMALL, SMALL ? kAvgGroup : ap.rows, n_top);
+    hipLaunchKernelGGL((pool_averages<PASS, PER, SMALL>), dim3(gx, rows), dim3(kAvgThreads), lds, s, scores, cells, ap, ctrl, hist, done, lists);
 }
 
 // Dynamic LDS ceilings of the selection kernels: the same constants on every call, set once per process
