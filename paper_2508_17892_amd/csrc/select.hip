@@ -693,18 +693,21 @@ constexpr int kAvgThreads = 512;
 constexpr int kAvgWaves = kAvgThreads / 64;
 constexpr int kAvgNarrow = 2, kAvgWide = 4;       // windows a lane sums
 constexpr int kAvgGroup = 16;                     // average kernels a workgroup handles
-constexpr int kAvgList = 256;                     // any sizes: collected elements a workgroup holds per average kernel before it writes them
+// Collected elements a wavefront holds before it writes them.  64 KiB for a workgroup: with twice as much, and one workgroup a
+// compute unit, the wavefront that meets a span of high scores writes once instead of four times, but 16M tokens take 275
+// us to collect instead of 188.
+constexpr int kAvgQueue = 1024;
 constexpr uint16_t kNoAvg = 0xFFFF;
 // LDS of pool_averages: counts or collected elements, then a buffer of cells per wavefront (readable kAvgAhead past the last)
 constexpr int kAvgAhead = 8;
-constexpr size_t avg_shared(int pass, int per, bool small, int rows)
+constexpr size_t avg_shared(int pass, int rows)
 {
     return pass == 0 ? ((size_t)rows * kAvgBins + 64) * sizeof(uint32_t)
-                     : (small ? (size_t)kAvgWaves * 64 * per : (size_t)kAvgList) * rows * sizeof(uint64_t);
+                     : (size_t)kAvgWaves * kAvgQueue * sizeof(uint64_t);
 }
 constexpr size_t avg_lds(int pass, int per, bool small, int rows, int n_top)
 {
-    return avg_shared(pass, per, small, rows) + (size_t)kAvgWaves * (size_t)(64 * per + (small ? kAvgGroup : n_top) + kAvgAhead) * sizeof(float);
+    return avg_shared(pass, rows) + (size_t)kAvgWaves * (size_t)(64 * per + (small ? kAvgGroup : n_top) + kAvgAhead) * sizeof(float);
 }
 
 struct AvgParams {
@@ -809,10 +812,10 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t c_comb[kAvgGroup], c_count[kAvgGroup], c_base[kAvgGroup];
+    __shared__ uint64_t c_list[kAvgGroup];
     __shared__ float c_rcp[kAvgGroup];
     __shared__ uint32_t is_last;
     constexpr int CHUNK = 64 * PER;            // windows a wavefront sums at a time
-    constexpr int QUEUE = CHUNK * kAvgGroup;   // SMALL, PASS 1: elements a wavefront may collect from a chunk
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int i = blockIdx.y / ap.groups, g0 = (blockIdx.y % ap.groups) * kAvgGroup;
     const int ng = min(kAvgGroup, ap.n_avg - g0), rows = SMALL ? kAvgGroup : ng;
@@ -820,8 +823,8 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
     const int n_top = ap.avg[g0 + ng - 1], ahead = (n_top - 1) / 2;  // the first windows start before the first cell
     const uint32_t pitch = CHUNK + (SMALL ? kAvgGroup : n_top) - 1;
     uint32_t *lh = (uint32_t *)smem;      // PASS 0: [kAvgGroup][kAvgBins], then a word per lane
-    uint64_t *ll = (uint64_t *)smem;      // PASS 1: [kAvgGroup][kAvgList], sum above element; SMALL: [kAvgWaves][QUEUE]
-    float *buf = (float *)(smem + avg_shared(PASS, PER, SMALL, SMALL ? kAvgGroup : ap.rows)) + (size_t)wave * (pitch + kAvgAhead);
+    uint64_t *queue = (uint64_t *)smem + wave * kAvgQueue;  // PASS 1: sum above average kernel, chunk and window
+    float *buf = (float *)(smem + avg_shared(PASS, SMALL ? kAvgGroup : ap.rows)) + (size_t)wave * (pitch + kAvgAhead);
     float *out = cells + ap.off[i];
     const uint32_t chunks = len ? (uint32_t)(((uint64_t)len + ahead + CHUNK - 1) / CHUNK) : 0u;
 
@@ -899,6 +902,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
             c_comb[threadIdx.x] = used ? j : 0xFFFFFFFFu;
             c_count[threadIdx.x] = 0;
             c_rcp[threadIdx.x] = __fdiv_rn(1.0f, (float)l_size);
+            c_list[threadIdx.x] = ctrl[j].tie_off;
         }
     }
     auto of = [](uint32_t x, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)x, q); };
@@ -914,7 +918,44 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
         for (int x = threadIdx.x * 4; x < rows * kAvgBins; x += kAvgThreads * 4) *(uint4 *)&lh[x] = make_uint4(0, 0, 0, 0);
     __syncthreads();
 
-    for (uint32_t c0 = blockIdx.x * kAvgWaves; c0 < chunks; c0 += gridDim.x * kAvgWaves) {
+    // PASS 1: a wavefront's elements wait in its queue until the workgroup is done: one reservation per workgroup and list
+    // then, and no barrier before (one per chunk: 45 - 77 us of a call for the best 64 of 3M tokens, 3.7 ms at 64 max
+    // kernels on 16M).  A queue that fills up is written by its wavefront alone.  The word beside a sum names the average
+    // kernel, the element's place among the queue's of that kernel, and its chunk and window.
+    constexpr uint32_t kWindowBits = 7, kRoundBits = 10, kPlaceBits = 11, kPlaceAt = kWindowBits + kRoundBits, kKernelAt = kPlaceAt + kPlaceBits;
+    static_assert(kAvgNarrow * 64 == 1 << kWindowBits && kKernelAt + 4 == 32 && kAvgGroup == 16 && kAvgQueue <= 1 << kPlaceBits, "32 bits");
+    uint32_t queued = 0, l_mine = 0;  // uniform; lane q: queued elements of average kernel q
+    uint32_t round = 0, first_round = 0;  // chunks done; when the queue was empty
+    auto write_queue = [&](uint32_t l_to) {  // l_to: lane q's place in average kernel q's list
+        for (uint32_t x = lane; x < ((queued + 63u) & ~63u); x += 64) {
+            const bool valid = x < queued;
+            const uint64_t e = queue[valid ? x : 0];
+            const uint32_t name = (uint32_t)e, q = name >> kKernelAt;
+            const uint32_t to = (uint32_t)__shfl((int)l_to, (int)q) + (name >> kPlaceAt & ((1u << kPlaceBits) - 1u));
+            const uint32_t size = SMALL ? q + 1 : (uint32_t)__shfl((int)l_size, (int)q);
+            const uint32_t chunk = blockIdx.x * kAvgWaves + wave + (first_round + (name >> kWindowBits & ((1u << kRoundBits) - 1u))) * (gridDim.x * kAvgWaves);
+            const uint32_t el = chunk * (uint32_t)CHUNK - (uint32_t)ahead + (name & ((1u << kWindowBits) - 1u)) + (size - 1) / 2;
+            const float avg = divide_small(__uint_as_float((uint32_t)(e >> 32)), (float)size, c_rcp[q]);
+            if (valid) lists[c_list[q] + to] = make_key(avg, el);
+        }
+        queued = 0;
+        l_mine = 0;
+        first_round = round;
+    };
+    auto spill = [&](uint32_t room) {  // for so many more
+        if (queued + room <= (uint32_t)kAvgQueue && round - first_round < 1u << kRoundBits) return;
+        uint32_t l_to = 0;
+        if (l_mine) l_to = atomicAdd(&ctrl[c_comb[lane]].tie_n, l_mine);
+        write_queue(l_to);
+    };
+    auto enqueue = [&](float x, bool hit, int q, int k, uint32_t place) {  // place: of the queue's next element, less its index
+        const uint64_t mask = __ballot(hit);
+        const uint32_t at = queued + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+        const uint32_t where = (uint32_t)q << kKernelAt | (round - first_round) << kWindowBits | (uint32_t)(lane + 64 * k);
+        if (hit) queue[at] = (uint64_t)__float_as_uint(x) << 32 | (where + ((at + place) << kPlaceAt));
+        queued += (uint32_t)__popcll(mask);
+    };
+    for (uint32_t c0 = blockIdx.x * kAvgWaves; c0 < chunks; c0 += gridDim.x * kAvgWaves, ++round) {
         const uint32_t c = c0 + wave;  // a chunk past the last one has no elements
         const int64_t first = (int64_t)c * CHUNK - ahead;  // first cell of the chunk's first window
         lds_wave_sync();  // the previous chunk's reads of the buffer are done
@@ -946,16 +987,13 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
         for (int k = 0; k < PER; ++k) sum[k] = 0.0f;
         const uint32_t el0 = (uint32_t)first + lane;  // modulo 2^32: an element before the array is one far behind it
         if (SMALL) {
-            uint32_t queued = 0;        // uniform
-            uint32_t l_mine = 0;        // lane q: this wavefront's queued elements of size q + 1
-#pragma unroll
-            for (int u = 0; u < kAvgGroup; ++u) {
+            auto size = [&](int u, const float(&x)[PER]) {
                 const float edge = of_f(l_edge, u);
                 const uint32_t before = queued, els = of(l_len, u), span0 = of(l_span0, u), span1 = of(l_span1, u), shifts = of(l_shift, u);
                 float best = -INFINITY;
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
-                    sum[k] = sum[k] + buf[lane + 64 * k + u];
+                    sum[k] = sum[k] + x[k];
                     const bool in = el0 + 64u * k + u / 2 < els;
                     // (what is not counted goes to a word of the lane's own)
                     auto count = [&](float x, bool hit) {
@@ -968,34 +1006,40 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
                     } else if (PASS == 0) {
                         count(sum[k], in & !(sum[k] < edge));
                     } else {
-                        const bool hit = in & !(sum[k] < edge);
-                        const uint64_t mask = __ballot(hit);
-                        const uint32_t at = queued + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                        if (hit) ll[wave * QUEUE + at] = (uint64_t)__float_as_uint(sum[k]) << 32 | (uint32_t)(u << 8 | (lane + 64 * k));
-                        queued += (uint32_t)__popcll(mask);
+                        enqueue(sum[k], in & !(sum[k] < edge), u, k, of(l_mine, u) - before);
                     }
                 }
-                if (PASS == 1) l_mine = lane == u ? queued - before : l_mine;
-            }
-            if (PASS == 1) {
-                // one reservation per workgroup and size, then every wavefront writes its own
-                uint32_t l_off = 0;
-                if (lane < kAvgGroup && l_mine) l_off = atomicAdd(&c_count[lane], l_mine);
-                __syncthreads();
-                if ((int)threadIdx.x < kAvgGroup && c_count[threadIdx.x]) {
-                    c_base[threadIdx.x] = atomicAdd(&ctrl[c_comb[threadIdx.x]].tie_n, c_count[threadIdx.x]);
-                    c_count[threadIdx.x] = 0;
+                if (PASS == 1) l_mine += lane == u ? queued - before : 0u;
+            };
+            // (up to the next multiple of four of the largest size that was asked for)
+            if (PASS == 0) {
+#pragma unroll
+                for (int u = 0; u < kAvgGroup; ++u) {
+                    if (u % 4 == 0 && u >= n_top) break;
+                    float x[PER];
+#pragma unroll
+                    for (int k = 0; k < PER; ++k) x[k] = buf[lane + 64 * k + u];
+                    size(u, x);
                 }
-                __syncthreads();
-                // where this wavefront's elements of a size start in the list, less where they start in its queue
-                const uint32_t l_to = (lane < kAvgGroup ? c_base[lane] : 0u) + l_off - (wave_scan_add(l_mine) - l_mine);
-                for (uint32_t x = lane; x < ((queued + 63u) & ~63u); x += 64) {
-                    const bool valid = x < queued;
-                    const uint64_t e = ll[wave * QUEUE + (valid ? x : 0)];
-                    const uint32_t u = valid ? (uint32_t)e >> 8 : 0u, w = (uint32_t)e & 255u;
-                    const uint32_t to = (uint32_t)__shfl((int)l_to, (int)u) + x;
-                    const float avg = divide_small(__uint_as_float((uint32_t)(e >> 32)), (float)(u + 1), c_rcp[u]);
-                    if (valid) lists[ctrl[c_comb[u]].tie_off + to] = make_key(avg, (uint32_t)first + w + u / 2);
+            } else {
+                float x[4][PER], next[4][PER];
+                auto read = [&](int u0, float(&v)[4][PER]) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int k = 0; k < PER; ++k) v[i][k] = buf[lane + 64 * k + u0 + i];
+                };
+                read(0, x);
+#pragma unroll 1
+                for (int u0 = 0; u0 < n_top; u0 += 4) {
+                    spill(4 * CHUNK);
+                    read(u0 + 4, next);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) size(u0 + i, x[i]);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int k = 0; k < PER; ++k) x[i][k] = next[i][k];
                 }
             }
             continue;
@@ -1025,27 +1069,18 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
             }
             from = to;
             for (; q < ng && (int)of(l_size, q) == to; ++q) {  // average kernel q's sums are complete
+                if (PASS == 1) spill(CHUNK);
                 const float edge = of_f(l_edge, q);
+                const uint32_t before = queued;
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
-                    const uint32_t el = el0 + 64u * k + (uint32_t)(to - 1) / 2;
-                    const bool hit = !(sum[k] < edge) && el < len;
-                    if (PASS == 0) {
-                        if (hit) atomicAdd(&lh[q * kAvgBins + bin_from(sum[k], edge, of(l_span0, q), of(l_span1, q), of(l_shift, q))], 1u);
-                    } else {
-                        const uint64_t mask = __ballot(hit);
-                        if (mask == 0) continue;
-                        uint32_t at = 0;
-                        if (lane == 0) at = atomicAdd(&c_count[q], (uint32_t)__popcll(mask));
-                        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
-                        if (hit && at < (uint32_t)kAvgList) ll[q * kAvgList + at] = (uint64_t)__float_as_uint(sum[k]) << 32 | el;
-                        if (__any(hit && at >= (uint32_t)kAvgList)) {  // the workgroup's list is full
-                            SelCtrl *ct = &ctrl[c_comb[q]];
-                            const uint64_t key = make_key(__fdiv_rn(sum[k], (float)to), el);
-                            wave_append(hit && at >= (uint32_t)kAvgList, key, lists + ct->tie_off, &ct->tie_n);
-                        }
-                    }
+                    const bool hit = !(sum[k] < edge) && el0 + 64u * k + (uint32_t)(to - 1) / 2 < len;
+                    if (PASS == 1)
+                        enqueue(sum[k], hit, q, k, of(l_mine, q) - before);
+                    else if (hit)
+                        atomicAdd(&lh[q * kAvgBins + bin_from(sum[k], edge, of(l_span0, q), of(l_span1, q), of(l_shift, q))], 1u);
                 }
+                if (PASS == 1) l_mine += lane == q ? queued - before : 0u;
             }
         }
     }
@@ -1074,20 +1109,13 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
                 if (lane == 0) ctrl[c_comb[q]].cut = cut;
             }
         }
-    } else if (!SMALL) {
-        for (int q = wave; q < ng; q += kAvgWaves) {
-            const uint32_t j = c_comb[q], n = min(c_count[q], (uint32_t)kAvgList);
-            if (n == 0) continue;
-            uint32_t at = 0;
-            if (lane == 0) at = atomicAdd(&ctrl[j].tie_n, n);
-            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-            uint64_t *list = lists + ctrl[j].tie_off;
-            const float fn = (float)of(l_size, q), rcp = __fdiv_rn(1.0f, fn);
-            for (uint32_t x = lane; x < n; x += 64) {
-                const uint64_t e = ll[q * kAvgList + x];
-                list[at + x] = make_key(divide_small(__uint_as_float((uint32_t)(e >> 32)), fn, rcp), (uint32_t)e);
-            }
-        }
+    } else {
+        uint32_t l_off = 0;
+        if (l_mine) l_off = atomicAdd(&c_count[lane], l_mine);
+        __syncthreads();
+        if ((int)threadIdx.x < rows && c_count[threadIdx.x]) c_base[threadIdx.x] = atomicAdd(&ctrl[c_comb[threadIdx.x]].tie_n, c_count[threadIdx.x]);
+        __syncthreads();
+        write_queue((lane < rows ? c_base[lane] : 0u) + l_off);
     }
 }
 
