@@ -233,8 +233,9 @@ SampleRanks sample_ranks(double want_lo, double want_hi, double len)
 }
 
 // Clears the counters and places each combination's bins by a sample of its own window sums: a quarter of them between its
-// keys of the ranks lo and mid, of mid (where the cut is expected) and hi, of hi and 0, and the rest beyond.  At most a few
-// hundredths of the elements more than are wanted reach the lowest bin, whatever the scores look like, and few are in one.
+// keys of the ranks lo and mid, a quarter of mid (where the cut is expected) and hi, an eighth of hi and 0, and the rest
+// beyond, three times as far again (of many elements the few best lie far above the best sample).  At most a few hundredths of
+// the elements more than are wanted reach the lowest bin, whatever the scores look like, and few are in one.
 // (Bins of a fixed width, 64 a binade, upward from the scores' median: 1M scores that differ by a thousandth 1170 us,
 // their logarithms 831, raised at every 1024th token 847, where others take 100.  More bins than these do not pay: every
 // workgroup adds its counts to the global ones, a request per cache line; with 1024 bins counting took 50 us on 1M tokens.)
@@ -300,13 +301,12 @@ __global__ __launch_bounds__(kThreads) void sel_init(const SelParams prm, uint32
         }
         if ((threadIdx.x & 3) == 0) key[threadIdx.x >> 2] = ordered_bits(sum);
         sampled_bounds(key, prm.ranks[j], bound);
-        constexpr int kBits = 6;
-        static_assert(kAvgBins == 4 << kBits, "a quarter of the bins from key to key");
-        auto shift_for = [](uint32_t keys) { return keys >> kBits ? (uint32_t)(32 - kBits - __clz((int)keys)) : 0u; };
+        static_assert(kAvgBins == 4 << 6, "a quarter of the bins, an eighth");
+        auto shift_for = [](uint32_t keys, int bits) { return keys >> bits ? (uint32_t)(32 - bits - __clz((int)keys)) : 0u; };
         c.span[0] = bound[1] - bound[0];
         c.span[1] = bound[2] - bound[0];
-        c.shifts = shift_for(bound[1] - bound[0]) | shift_for(bound[2] - bound[1]) << 8;
-        c.shifts |= (bound[3] > bound[2] ? shift_for(bound[3] - bound[2]) : 21u) << 16;  // four a binade where the sample says nothing
+        c.shifts = shift_for(bound[1] - bound[0], 6) | shift_for(bound[2] - bound[1], 6) << 8;
+        c.shifts |= (bound[3] > bound[2] ? shift_for(bound[3] - bound[2], 5) : 21u) << 16;  // four a binade where the sample says nothing
         c.edge = float_of_key(bound[0]);
     }
     if (threadIdx.x == 0) {
