@@ -1613,7 +1613,7 @@ template <int ITEMS, bool HASHED>
 __global__ __launch_bounds__(kWalkThreads) void allocate_walk(const WalkArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ uint32_t wsum[2][kWalkWaves];
+    __shared__ uint32_t wsum[2][kWalkWaves], wlen[kWalkWaves];
     __shared__ uint32_t chunk_n[kBitmapChunks];
     constexpr bool SEEDS = ITEMS == kWalkSeeds;
     const TokenSet<HASHED> set{(uint32_t *)smem, (uint32_t *)smem + (HASHED ? kWordSlots : 0)};
@@ -1723,6 +1723,20 @@ __global__ __launch_bounds__(kWalkThreads) void allocate_walk(const WalkArgs a)
                 mask1[i] = some && last[i] >> 5 > first[i] >> 5 ? interval_bits((first[i] >> 5) + 1, first[i], last[i]) : 0u;
             }
             mask0[i] = some ? mask0[i] : 0u;
+        }
+        if (wide) {  // uniform
+            // Of intervals this long few fill a share, and each would cost a round trip per word: those behind as many tokens
+            // as the share and the tokens allocated so far are together cannot matter.  (A window of 2047 on 3M tokens, the
+            // whole call 308 -> 120 us.)
+            const uint32_t len0 = mask0[0] ? last[0] - first[0] + 1 : 0u, len1 = mask0[1] ? last[1] - first[1] + 1 : 0u;
+            const uint32_t upto = wave_scan_add(len0 + len1);
+            if (lane == 63) wlen[wave] = upto;
+            lds_barrier();
+            uint32_t ahead = upto - len0 - len1;
+#pragma unroll
+            for (int w = 0; w < kWalkWaves; ++w) ahead += w < wave ? wlen[w] : 0u;
+            if (ahead >= share + nsel) mask0[0] = mask1[0] = 0u;
+            if (ahead + len0 >= share + nsel) mask0[1] = mask1[1] = 0u;
         }
 #pragma unroll
         for (int i = 0; i < kWalkPer; ++i) {
