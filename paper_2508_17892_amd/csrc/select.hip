@@ -351,9 +351,10 @@ __device__ __forceinline__ uint32_t bin_of(const KeyBins &b, uint32_t key)
 }
 
 // Clears the states of a seed search on scores of unknown scale and places the bins by a sample of what is counted first:
-// the scores, or the maxima of fine chunks.  Half of the bins lie between the sample's two keys and as far above the upper
-// one, above which the K-th largest lies more often than not where few are wanted.  The others cover all keys below (two
-// binades each) and above.  Whatever the sample is, the result is the same.
+// the scores, or the maxima of fine chunks.  A quarter of the bins lies between the sample's two keys, a quarter from there to
+// 16 times as far as the sample's largest: of many scores the few best lie well above that one.  The others cover all keys
+// below (four binades each) and above.  Whatever the sample is, the result is the same.  (With the upper quarter ending as
+// far above the upper key as the lower one is below it, the cut of the best 64 of 3M tokens had 2000 others in its bin.)
 struct SeedInit {
     const float *vals;
     int64_t n;
@@ -362,19 +363,22 @@ struct SeedInit {
 __global__ __launch_bounds__(kThreads) void seed_init(const SeedInit p, SeedState *st)
 {
     __shared__ __align__(16) uint32_t key[kBaseSamples];
-    __shared__ uint32_t bound[2];
+    __shared__ uint32_t bound[3];
     constexpr int kWords = sizeof(SeedState) / 16, kKept = sizeof(KeyBins) / 16;  // (the bins are written below)
     for (int i = threadIdx.x; i < 2 * kWords; i += kThreads)
         if (i % kWords >= kKept) ((uint4 *)st)[i] = make_uint4(0, 0, 0, 0);
     if (threadIdx.x < kBaseSamples) key[threadIdx.x] = ordered_bits(p.vals[sample_at(threadIdx.x, p.n)]);
-    sampled_bounds(key, p.ranks.lo | p.ranks.hi << 8, bound);
+    sampled_bounds(key, p.ranks.lo | p.ranks.hi << 8, bound);  // and rank 0
     if (threadIdx.x == 0) {
-        constexpr uint32_t kLow = 256, kMid = 1023, kHigh = kSeedBins - 1 - kLow - kMid;
-        const uint32_t top = bound[1] + min(max(bound[1] - bound[0], 1u), 0xFFFFFFFEu - bound[1]);
-        uint32_t mid = 0, high = 0;
-        while ((top - bound[0]) >> mid >= kMid) ++mid;
-        while ((0xFFFFFFFFu - top) >> high >= kHigh) ++high;
-        const KeyBins b{{0, bound[0], top, top, top}, {24, mid, 0, 0, high}, {}};
+        // sizes of bins for which a number of keys takes fewer than 2^bits of them
+        auto shift_for = [](uint32_t keys, int bits) { return keys >> bits ? (uint32_t)(32 - bits - __clz((int)keys)) : 0u; };
+        const uint32_t low = bound[0], mid = bound[1], top = bound[2];
+        const uint32_t tail = top > mid ? shift_for(top - mid, 5) : 17u;  // 64 bins a binade where the sample says nothing
+        const uint32_t end = mid + min(512u << tail, 0xFFFFFFFEu - mid);
+        uint32_t far = 0;
+        constexpr uint32_t kFar = kSeedBins - 1 - 128 - 512 - 512 - 4;  // (a range may end inside a bin)
+        while ((0xFFFFFFFFu - end) >> far >= kFar) ++far;
+        const KeyBins b{{0, low, mid, end, end}, {25, shift_for(mid - low, 9), tail, 0, far}, {}};
         st[0].bins = st[1].bins = b;
     }
 }
@@ -1131,10 +1135,28 @@ __device__ void peel(uint64_t *&A, uint64_t *&B, uint32_t &nA, uint32_t &need, u
     __shared__ uint32_t cnt[2];
     __shared__ uint32_t pick[3];  // digit, count above it, count in it
     __shared__ unsigned long long differ;  // bits in which keys differ
+    constexpr int kFew = 256;
+    __shared__ __align__(16) uint64_t few[kFew];
     constexpr int kBatch = 8;  // keys a thread has in flight
     const int lane = threadIdx.x & 63;
     int shift = 56;
     while (nA + candn > keep && need < nA) {
+        if (nA <= (uint32_t)kFew) {  // uniform: each counts those ahead of it
+            if (threadIdx.x < (uint32_t)kFew) few[threadIdx.x] = threadIdx.x < nA ? load_u64(&A[threadIdx.x]) : 0ull;
+            __syncthreads();
+            if (threadIdx.x < nA) {
+                const uint64_t mine = few[threadIdx.x];
+                uint32_t rank = 0;
+#pragma unroll 8
+                for (uint32_t i = 0; i < (uint32_t)kFew; ++i) rank += few[i] > mine ? 1u : 0u;
+                if (rank < need) store_u64(&cand[candn + rank], mine);
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            candn += need;
+            need = nA = 0;
+            break;
+        }
         __syncthreads();
         if (threadIdx.x < 256) h[threadIdx.x] = 0;
         if (threadIdx.x < 2) cnt[threadIdx.x] = 0;
