@@ -1712,11 +1712,13 @@ __global__ __launch_bounds__(kWalkThreads) void allocate_walk(const WalkArgs a)
 
     uint32_t nsel = 0, taken = 0, share = 0, reach = 0;
     bool wide = false;  // an interval may touch more than two words
+    bool huge = false;  // HASHED: .. more than sixteen
     int gen = 0;
     auto start = [&](int j) {
         share = min(of(l_share, j), (uint32_t)a.n_out - nsel);
         reach = of(l_reach, j);
         wide = ITEMS != kWalkWordCells && (SEEDS ? 2 * reach + 1 : reach) > 33;
+        huge = HASHED && wide && (SEEDS ? 2 * reach + 1 : reach) > 512;
         taken = 0;
     };
     // one pass: this thread's two neighbouring intervals, of which the ones from `cn` on (cells) do not exist
@@ -1746,10 +1748,9 @@ __global__ __launch_bounds__(kWalkThreads) void allocate_walk(const WalkArgs a)
             }
             mask0[i] = some ? mask0[i] : 0u;
         }
-        if (wide) {  // uniform
-            // Of intervals this long few fill a share, and each would cost a round trip per word: those behind as many tokens
-            // as the share and the tokens allocated so far are together cannot matter.  (A window of 2047 on 3M tokens, the
-            // whole call 308 -> 120 us.)
+        if (HASHED && wide) {  // uniform
+            // Of intervals this long few fill a share, and each costs a probe per word: those behind as many tokens as the share
+            // and the tokens allocated so far are together cannot matter.
             const uint32_t len0 = mask0[0] ? last[0] - first[0] + 1 : 0u, len1 = mask0[1] ? last[1] - first[1] + 1 : 0u;
             const uint32_t upto = wave_scan_add(len0 + len1);
             if (lane == 63) wlen[wave] = upto;
@@ -1774,11 +1775,28 @@ __global__ __launch_bounds__(kWalkThreads) void allocate_walk(const WalkArgs a)
                 nfree[i] += __popc(free1[i]);
             }
         }
+        // Words beyond the second.  A lane goes through its interval's, but in the table, where each is a probe, a mark and up to 32
+        // notes, the wavefront takes huge intervals one at a time, a word a lane (at most 2047 tokens: 63 words).  One window of
+        // 2047 on 3M tokens, the whole call: 300 us a lane alone, 108 so; 64 windows of up to 127: 325 and 1000 us.
+        auto long_ones = [&](int i, bool some, auto each) {
+            for (uint64_t todo = __ballot(some && last[i] >> 5 > (first[i] >> 5) + 1); todo; todo &= todo - 1) {
+                const int of_lane = __ffsll((unsigned long long)todo) - 1;
+                const uint32_t f = of(first[i], of_lane), l = of(last[i], of_lane), w = (f >> 5) + 2 + lane;
+                each(of_lane, w, w <= l >> 5 ? ~set.get(w) & interval_bits(w, f, l) : 0u);
+            }
+        };
+        static_assert(ILRE_MAX_POOL_KERNEL <= 2047 && ILRE_MAX_MAX_KERNEL <= 2047, "an interval's words beyond the second are no more than lanes");
         if (wide) {  // uniform
 #pragma unroll
-            for (int i = 0; i < kWalkPer; ++i)
-                if (mask0[i])
+            for (int i = 0; i < kWalkPer; ++i) {
+                if (huge)
+                    long_ones(i, mask0[i] != 0, [&](int of_lane, uint32_t, uint32_t bits) {
+                        const uint32_t n = wave_total(wave_scan_add((uint32_t)__popc(bits)));
+                        nfree[i] += lane == of_lane ? n : 0u;
+                    });
+                else if (mask0[i])
                     for (uint32_t w = (first[i] >> 5) + 2; w <= last[i] >> 5; ++w) nfree[i] += __popc(~set.get(w) & interval_bits(w, first[i], last[i]));
+            }
         }
         const uint32_t mine = nfree[0] + nfree[1];
         static_assert(kWalkPer == 2, "two intervals a thread");
@@ -1812,15 +1830,25 @@ __global__ __launch_bounds__(kWalkThreads) void allocate_walk(const WalkArgs a)
             if (ITEMS != kWalkWordCells) {
                 if (free1[i]) set.set(w0 + 1, free1[i]);
                 if (HASHED) note(w0 + 1, free1[i], at);
-                if (wide && mask0[i]) {
-                    uint32_t more = min(quota, nfree[i]) - __popc(free0[i]) - __popc(free1[i]);
-                    for (uint32_t w = w0 + 2; more; ++w) {
-                        uint32_t bits = ~set.get(w) & interval_bits(w, first[i], last[i]);
-                        if ((uint32_t)__popc(bits) > more) bits = lowest_bits(bits, more);
-                        more -= __popc(bits);
-                        if (bits) set.set(w, bits);
-                        if (HASHED) note(w, bits, at);
-                    }
+                if (wide) {  // uniform
+                    uint32_t more = mask0[i] ? min(quota, nfree[i]) - __popc(free0[i]) - __popc(free1[i]) : 0u;
+                    if (huge)
+                        long_ones(i, more != 0, [&](int of_lane, uint32_t w, uint32_t bits) {
+                            const uint32_t n = __popc(bits), ahead = wave_scan_add(n) - n, want = of(more, of_lane);
+                            const uint32_t take = want > ahead ? min(n, want - ahead) : 0u;
+                            if (take < n) bits = lowest_bits(bits, take);
+                            if (bits) set.set(w, bits);
+                            uint32_t place = of(at, of_lane) + ahead;
+                            note(w, bits, place);
+                        });
+                    else
+                        for (uint32_t w = w0 + 2; more; ++w) {
+                            uint32_t bits = ~set.get(w) & interval_bits(w, first[i], last[i]);
+                            if ((uint32_t)__popc(bits) > more) bits = lowest_bits(bits, more);
+                            more -= __popc(bits);
+                            if (bits) set.set(w, bits);
+                            if (HASHED) note(w, bits, at);
+                        }
                 }
             }
             before += nfree[i];
