@@ -596,6 +596,11 @@ WALK_CASES = [
     (BITMAP_TOKENS + 4, 4, 4096, (2047, 1), (32, 33), (1, 4)),   # the body exactly full; intervals and cells over many words
     (BITMAP_TOKENS + 1, 0, 8192, (1, 1, 31), (1, 64), (2, 1)),   # one token more: the table
     (1179648, 0, 4096, (1, 3, 7), (2, 5), (1, 2)),
+    # the table with intervals of more and fewer than 512 tokens, shares that end inside them, many and few of them
+    (1200001, 3, 8192, (2047, 513, 511, 35), (1024, 600), (1, 2)),
+    (1200000, 0, 700, (2047, 65, 2047), (513, 512), (3,)),
+    (1300000, 1, 8191, (2047,), (1000, 33, 1), (1,)),
+    (1300033, 0, 4096, tuple(range(1, 1023, 64)), (64, 700), (1, 3)),
     (8192, 0, 8191, (65, 129, 1), (3, 7), (1, 2, 5)),            # nearly every token kept: shares end inside intervals
     (8224, 1, 1, (1,), (8,), (16,)),
 ]
@@ -609,6 +614,8 @@ def test_walk_over_bitmap_and_word_table(L, sink, budget, windows, mk, ak):
     rng = np.random.default_rng(L + budget)
     s = _scores_for("needles", L, rng)
     s[-3:] = (9.0, 8.5, 9.5)
+    if L >= 1300000:  # a background whose best tokens lie side by side: short intervals among long ones
+        s[L // 2:L // 2 + 6000] = (20 + rng.random(6000)).astype(np.float32)
     dev = torch.from_numpy(s).cuda()
     got = il.ilre_select(dev, budget, windows, sink=sink)
     got_p, count = il.ilre_select_max_avg(dev, budget, mk, ak, sink)
@@ -960,3 +967,20 @@ def test_time_of_a_printed_selection_with_large_sizes(mk, ak, most):
         us.append(_device_us(lambda: il.ilre_select_max_avg(dev, 4096, m, a, 0, workspace=ws)))
     print(f"{us[0]:.1f} us, ordinary sizes {us[1]:.1f} us", flush=True)
     assert us[0] < most * us[1]
+
+
+def test_time_of_long_contexts_with_few_or_huge_takings():
+    """3M tokens, where the walk's set is the table.  Windows of 2047 tokens take about twice as long as small ones (six times
+    when a lane marked an interval by itself), the best 64 of the printed form about as long as those of the window form
+    (twice when every chunk of windows reserved its places)."""
+    _announce("time of long contexts with few or huge takings")
+    L = 3 << 20
+    dev = torch.from_numpy(_scores_for("needles", L, np.random.default_rng(9))).cuda()
+    ws = il.alloc_workspace(L, 1, 1, 1, 128, 1, il.ILRE_F32)
+    ws_p = il.alloc_workspace_max_avg(L, 1, 1, 1, 128, 0, (1,), 1, il.ILRE_F32)
+    huge = _device_us(lambda: il.ilre_select(dev, 4096, (2047,), workspace=ws))
+    small = _device_us(lambda: il.ilre_select(dev, 4096, (31,), workspace=ws))
+    few = _device_us(lambda: il.ilre_select_max_avg(dev, 64, (1,), (7,), 0, workspace=ws_p))
+    few_window = _device_us(lambda: il.ilre_select(dev, 64, (7,), workspace=ws))
+    print(f"{huge:.1f} us, small windows {small:.1f} us; {few:.1f} us, window form {few_window:.1f} us", flush=True)
+    assert huge < 3.5 * small and few < 1.75 * few_window
