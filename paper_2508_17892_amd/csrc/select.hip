@@ -1053,6 +1053,11 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
         // window of 1024 cells took 3 - 5 times as long as the whole selection otherwise does)
         for (int q = 0, from = 0; q < ng;) {
             const int to = (int)of(l_size, q);
+            if (to - from <= 2) {  // sizes side by side
+                for (; from < to; ++from)
+#pragma unroll
+                    for (int k = 0; k < PER; ++k) sum[k] = sum[k] + buf[lane + 64 * k + from];
+            }
             for (int u = from; u < to; u += kAvgAhead) {
                 float x[PER][kAvgAhead];
 #pragma unroll
