@@ -72,7 +72,8 @@ constexpr int kPoolThreads = 256;                 // passes over the scores: fou
 constexpr int kPoolWaves = kPoolThreads / 64;
 constexpr int kPerThread = kSelFine / 64;         // 4 tokens per lane
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
-constexpr uint32_t kSortSmall = 4096;             // printed form: lists up to this long are sorted whole
+constexpr uint32_t kSortSmall = 4096;             // printed form: lists up to this long are sorted whole,
+constexpr uint32_t kSortLarge = 10240;            // and up to this long where more than kSortSmall elements are wanted
 
 // Per-combination description, host -> sel_init (by value).
 struct SelParams {
@@ -1420,11 +1421,12 @@ __device__ void rank_network(uint64_t *srt, uint32_t total, uint32_t want, uint3
 }
 
 // Printed form: the list of a combination in rank order, cut to the K_j best elements.  A list too long to sort (many
-// equal averages) is radix-selected down first.  Up to kSortSmall elements go by the counting sort: bound by the latency
+// equal averages) is radix-selected down first.  The rest goes by the counting sort: bound by the latency
 // of its few rounds through LDS on one workgroup a combination, where the network takes a round and a barrier for each of
 // 55 - 78 stages.  Measured (kernel trace): 9001 tokens 8.7 -> 4.8 us, 128K 15.6 -> 5.8 us, 1M
-// 14.4 -> 4.8 us; values in two clusters (spans just as many as are wanted, and the background's top) 47 -> 19 us.  Where a bin
-// is deep (equal averages in number) or the list is longer, the network is the faster one still.
+// 14.4 -> 4.8 us; values in two clusters (spans just as many as are wanted, and the background's top) 47 -> 19 us; the best
+// 8192 of 3M 118 us by radix selection and network.  Where a bin is deep (equal averages in number) the network, for up to
+// sort_n elements, is the faster one still.
 __global__ __launch_bounds__(kThreads) void refine(const SelCtrl *ctrl, uint64_t *cand, uint64_t *tie, uint32_t sort_n)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1436,13 +1438,14 @@ __global__ __launch_bounds__(kThreads) void refine(const SelCtrl *ctrl, uint64_t
     uint64_t *B = A + ctrl[j].len;
     const uint32_t want = ctrl[j].want;
     uint32_t nA = ctrl[j].tie_n, need = want, candn = 0;
-    peel<kThreads>(A, B, nA, need, cand_j, candn, sort_n);
-    const uint32_t total = candn + nA;  // <= sort_n
+    const bool large = sort_n > kSortSmall;  // uniform: there is room for kSortLarge keys
+    peel<kThreads>(A, B, nA, need, cand_j, candn, large ? kSortLarge : kSortSmall);
+    uint32_t total = candn + nA;
     auto element = [&](uint32_t i) { return i < candn ? load_u64(&cand_j[i]) : load_u64(&A[i - candn]); };
     // the walk wants the elements in rank order; the list (uint32) takes over the storage of the keys
     uint32_t *ranked = (uint32_t *)cand_j;
-    if (total <= kSortSmall && total > 0) {  // uniform
-        constexpr int PER = (int)kSortSmall / kThreads;
+    auto by_counting = [&](auto per_tag) {
+        constexpr int PER = decltype(per_tag)::value;
         uint64_t key[PER];
         uint32_t top = 0, low = 0xFFFFFFFFu, have = 0;
 #pragma unroll
@@ -1454,10 +1457,15 @@ __global__ __launch_bounds__(kThreads) void refine(const SelCtrl *ctrl, uint64_t
             low = min(low, (uint32_t)(key[k] >> 32));
         }
         rank_range(sh, top, low);
-        if (rank_keys(sh, srt, key, have, top, low, want, ranked)) return;
-    } else {
-        for (uint32_t i = threadIdx.x; i < total; i += kThreads) srt[i] = element(i);
-    }
+        return rank_keys(sh, srt, key, have, top, low, want, ranked);
+    };
+    if (total == 0) return;  // uniform
+    if (total <= kSortSmall ? by_counting(std::integral_constant<int, (int)kSortSmall / kThreads>{})
+                            : by_counting(std::integral_constant<int, (int)kSortLarge / kThreads>{}))
+        return;
+    if (total > sort_n) peel<kThreads>(A, B, nA, need, cand_j, candn, sort_n);
+    total = candn + nA;
+    for (uint32_t i = threadIdx.x; i < total; i += kThreads) srt[i] = element(i);
     rank_network(srt, total, want, ranked);
 }
 
@@ -2441,7 +2449,8 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
         launch_averages<1, kAvgNarrow, true>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
     else
         launch_averages<1, kAvgNarrow, false>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
-    hipLaunchKernelGGL(refine, dim3(n), dim3(kThreads), (size_t)sort_n * sizeof(uint64_t), s, ctrl, cand, tie, sort_n);
+    const uint32_t sort_keys = sort_n > kSortSmall ? std::max(sort_n, kSortLarge) : sort_n;
+    hipLaunchKernelGGL(refine, dim3(n), dim3(kThreads), (size_t)sort_keys * sizeof(uint64_t), s, ctrl, cand, tie, sort_n);
     walk.n = n;
     bool word_cells = true;  // cells lie inside words of the set: sizes 1, 2, 4, 8, 16, 32
     for (int j = 0; j < n; ++j) {
