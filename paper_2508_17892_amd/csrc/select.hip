@@ -9,8 +9,8 @@
 // whatever the earlier ones took; in the printed form K_m is given), so the candidate sets are built
 // for all combinations at once:
 //
-//   pool_cells   (cells of more than 8 tokens, or windows of more than 64 cells) the strided max pooling, one cell array
-//                per max kernel
+//   pool_cells   (cells of other than 1, 2, 3, 4 and 8 tokens, or long windows) the strided max pooling, one cell array per
+//                max kernel
 //   sel_init     clears histograms and counters, and per combination places the histogram's bins by a sample of its averages
 //   pool_averages<0>   the strided max pooling, if not there yet, and per combination a histogram of the averages;
 //                the last workgroup of a max kernel finds its combinations' cuts, the bin that holds the K_j-th best
@@ -2412,9 +2412,15 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
         at = ap.at[k];
     }
     const bool wide = small && coarse;
-    int m_top = 1;
-    for (int i = 0; i < job.n_max; ++i) m_top = std::max(m_top, job.max_kernels[i]);
-    ap.pooled = m_top > 8 || n_top > 64;
+    // Cells are pooled where their windows are summed while that is a straight line of loads (1, 2, 4 and 8 tokens) and few cells
+    // are in two chunks, else by a kernel of their own.  One average kernel, 128K tokens, there and apart: cells of 8, windows
+    // of 5 28.2 and 31.2 us, of 64 32.0 and 33.2, of 96 47.3 and 37.4; cells of 6 32.8 and 31.9, 52.6 and 33.6; cells of 16
+    // 53.5 and 31.7, 115 and 32.4; cells of 3 30.2 and 31.5, with windows of 33 34.5 and 31.9.
+    ap.pooled = n_top > 64;
+    for (int i = 0; i < job.n_max; ++i) {
+        const int m = job.max_kernels[i];
+        ap.pooled = ap.pooled || !(m == 1 || m == 2 || m == 4 || m == 8 || (m == 3 && n_top <= 16));
+    }
     prm.src = ap.pooled ? cells : scores;
     for (int j = 0; j < n; ++j) {
         if (ap.pooled) {

@@ -935,11 +935,11 @@ def test_scores_that_are_not_numbers_leave_a_valid_index_list(n_nan):
     assert (np.diff(got) > 0).all() and got[0] >= 0 and got[-1] < 9000
 
 
-@pytest.mark.parametrize("L,mk", [(9000, (9, 15)), (9001, (16, 17, 1)), (40000, (63, 64)), (70001, (65, 2)), (70000, (1024, 1023)), (1000, (1024, 8)), (1025, (1024,))],
+@pytest.mark.parametrize("L,mk", [(9000, (9, 15)), (9001, (3,)), (9001, (3, 5, 7)), (9002, (6, 2)), (9001, (16, 17, 1)), (40000, (63, 64)), (70001, (65, 2)), (70000, (1024, 1023)), (1000, (1024, 8)), (1025, (1024,))],
                          ids=lambda x: str(x).replace(" ", ""))
 def test_large_cells_and_long_windows(L, mk):
-    """Cells of more than 8 tokens, or windows of more than 64 cells, are pooled by a kernel of their own: sizes around its 4,
-    16 and 64 lanes a cell, bodies that end inside a cell or are shorter than one, windows around the eight cells that are
+    """Cells of other than 1, 2, 4 and 8 tokens (3 with windows of up to 16), or windows of more than 64 cells, are pooled by a
+    kernel of their own: sizes around its 1, 4, 16 and 64 lanes a cell, bodies that end inside a cell or are shorter than one, windows around the eight cells that are
     read together; bit-exact with the oracle."""
     for ak in ((1, 16), (7, 8, 9), (64, 65), (1024, 3), (5, 5, 1000)):
         for budget in (50, min(3000, L - 1)):
