@@ -19,7 +19,8 @@
 //                averages) is radix-selected down first, 8 bits a pass, survivors compacted
 //   allocate_walk   one workgroup walks the combinations in order over their ranked cells: the allocated set is
 //                a bitmap in LDS, tokens that it holds are skipped, the first B_j others are taken; the ascending
-//                output is then read off the bitmap
+//                output is then read off the bitmap.  allocate_relay: the same, the wavefronts taking turns, for many
+//                combinations with small shares
 //   emit_sorted  contexts whose bitmap does not fit the LDS: the allocated set in ascending order (each token
 //                counts the tokens below it)
 //
@@ -1580,8 +1581,7 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // returns a value, a combination's numbers come from a register lane, its list is in LDS before it is needed, and
 // there is one scan and two barriers per 1024 intervals.  Two wavefronts a SIMD: with one (four intervals a thread)
 // nothing hides the LDS latency, with four (one interval a thread) the scan is repeated by as many.
-// Measured (kernel trace): 48 printed combinations at budget 4096 on 128K tokens 135.9 -> 36.8 us, on 1M 124 -> 40.6 us,
-// four kernel sizes at budget 4096 on 32K tokens 11.4 us and five on 1M 20.2 us, where the predecessor took 15.0 and
+// Measured (kernel trace): four kernel sizes at budget 4096 on 32K tokens 11.4 us and five on 1M 20.2 us, where the predecessor took 15.0 and
 // 19.5 us and two more kernels of 5.7 - 9.5 us each (one to write every kernel size's ranked tokens out, one to put the
 // result in order); it walked single tokens through a hash set, a wavefront's round trip per token and probe.
 constexpr int kWalkThreads = 512;
@@ -1642,6 +1642,98 @@ __device__ __forceinline__ uint32_t nth_set_bit(uint32_t x, uint32_t k)
         at += up ? half : 0;
     }
     return at;
+}
+
+// The allocated set in ascending order, read off its bitmap by the walk's workgroup.  slot_word: per place in the output the
+// word (number + 1) whose first token goes there, or 0.
+__device__ __forceinline__ void emit_bitmap(const WalkArgs &a, const uint32_t *mask, uint16_t *slot_word, uint32_t *chunk_n, uint32_t nsel)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t chunks = (a.len + 32 * kBitmapChunk - 1) / (32 * kBitmapChunk);
+    // The tokens per chunk (a lane counts four neighbouring words) and
+    // their running sum place every word's first token; the place notes the word.  Then one lane a place: the nearest
+    // noted place at or before its own is at most 31 back and names the word, the distance the bit in it.
+    // All of it is latency: kEmitBatch chunks (groups of 64 places) of a wavefront advance together.
+    constexpr int kEmitBatch = 4;
+    __syncthreads();  // every wavefront is done with the set, and with what slot_word held
+    for (uint32_t i = tid * 8; i < (uint32_t)a.n_out; i += kWalkThreads * 8) *(uint4 *)&slot_word[i] = make_uint4(0, 0, 0, 0);
+    auto words4 = [&](uint32_t c) {  // the lane's four words of a chunk, none past the last chunk
+        return c < chunks ? *(const uint4 *)&mask[c * kBitmapChunk + 4 * lane] : make_uint4(0, 0, 0, 0);
+    };
+    for (uint32_t c0 = wave; c0 < chunks; c0 += kWalkWaves * kEmitBatch) {
+        uint32_t sum[kEmitBatch];
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) {
+            const uint4 x = words4(c0 + b * kWalkWaves);
+            sum[b] = __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w);
+        }
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) sum[b] = wave_scan_add(sum[b]);
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b)
+            if (lane == 63 && c0 + b * kWalkWaves < chunks) chunk_n[c0 + b * kWalkWaves] = sum[b];
+    }
+    __syncthreads();
+    // every wavefront sums the chunks before each of its own by itself (lane l holds chunks l, l + 64, l + 128)
+    uint32_t cn[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) cn[i] = (uint32_t)(lane + 64 * i) < chunks ? chunk_n[lane + 64 * i] : 0u;
+    static_assert(kBitmapChunks <= 3 * 64, "three chunks a lane");
+    for (uint32_t c0 = wave; c0 < chunks; c0 += kWalkWaves * kEmitBatch) {
+        uint4 x[kEmitBatch];
+        uint32_t n3[kEmitBatch], at[kEmitBatch];
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) {
+            const uint32_t c = c0 + b * kWalkWaves;
+            x[b] = words4(c);
+            n3[b] = __popc(x[b].x) + __popc(x[b].y) + __popc(x[b].z) + __popc(x[b].w);
+            at[b] = ((uint32_t)lane < c ? cn[0] : 0u) + ((uint32_t)lane + 64 < c ? cn[1] : 0u) + ((uint32_t)lane + 128 < c ? cn[2] : 0u);
+        }
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) at[b] = wave_total(wave_scan_add(at[b])) + wave_scan_add(n3[b]) - n3[b];
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) {
+            const uint32_t w = (c0 + b * kWalkWaves) * kBitmapChunk + 4 * lane;
+            if (x[b].x) slot_word[at[b]] = (uint16_t)(w + 1);
+            at[b] += __popc(x[b].x);
+            if (x[b].y) slot_word[at[b]] = (uint16_t)(w + 2);
+            at[b] += __popc(x[b].y);
+            if (x[b].z) slot_word[at[b]] = (uint16_t)(w + 3);
+            at[b] += __popc(x[b].z);
+            if (x[b].w) slot_word[at[b]] = (uint16_t)(w + 4);
+        }
+    }
+    __syncthreads();
+    int32_t *out = a.out_idx + a.sink;
+    // a wavefront's places lie side by side: the last note of one group of 64 serves the next
+    const uint32_t span = (nsel + kWalkThreads - 1) / kWalkThreads * 64, s_begin = wave * span, s_end = min(s_begin + span, nsel);
+    auto note_of = [&](uint32_t s) {  // place and word in one number, larger for a later place
+        const uint32_t x = s < nsel ? slot_word[s] : 0u;
+        return x ? (s & 0xFFFFu) << 16 | x : 0u;
+    };
+    uint32_t carry = 0;
+    if (s_begin >= 64 && s_begin < nsel) carry = wave_total(wave_scan_max(note_of(s_begin - 64 + lane)));
+    for (uint32_t s0 = s_begin; s0 < s_end; s0 += 64 * kEmitBatch) {
+        uint32_t note[kEmitBatch], bits[kEmitBatch];
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) note[b] = note_of(s0 + 64 * b + lane);
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) note[b] = wave_scan_max(note[b]);
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) {
+            note[b] = max(note[b], carry);
+            carry = wave_total(note[b]);
+            bits[b] = mask[(note[b] & 0xFFFFu) - 1u];  // (place 0 is noted: there is always one)
+        }
+#pragma unroll
+        for (int b = 0; b < kEmitBatch; ++b) {
+            const uint32_t s = s0 + 64 * b + lane;
+            if (s < s_end) out[s] = (int32_t)(((note[b] & 0xFFFFu) - 1u) * 32 + nth_set_bit(bits[b], s - (note[b] >> 16)) + (uint32_t)a.sink);
+        }
+    }
+    for (uint32_t i = tid; i < (uint32_t)a.sink; i += kWalkThreads) a.out_idx[i] = (int32_t)i;
+    for (uint32_t i = nsel + tid; i < (uint32_t)a.n_out; i += kWalkThreads) out[i] = -1;
+    if (tid == 0 && a.out_count) *a.out_count = a.sink + (int32_t)nsel;
 }
 
 template <int ITEMS, bool HASHED>
@@ -1905,92 +1997,172 @@ __global__ __launch_bounds__(kWalkThreads) void allocate_walk(const WalkArgs a)
         return;
     }
 
-    // Ascending output straight from the bitmap.  The tokens per chunk (a lane counts four neighbouring words) and
-    // their running sum place every word's first token; the place notes the word.  Then one lane a place: the nearest
-    // noted place at or before its own is at most 31 back and names the word, the distance the bit in it.
-    // All of it is latency: kEmitBatch chunks (groups of 64 places) of a wavefront advance together.
-    constexpr int kEmitBatch = 4;
-    // per place in the output: the word (number + 1) whose first token goes there, or 0
-    uint16_t *slot_word = (uint16_t *)ring;
-    __syncthreads();  // every wavefront is done with the ring
-    for (uint32_t i = tid * 8; i < (uint32_t)a.n_out; i += kWalkThreads * 8) *(uint4 *)&slot_word[i] = make_uint4(0, 0, 0, 0);
-    auto words4 = [&](uint32_t c) {  // the lane's four words of a chunk, none past the last chunk
-        return c < chunks ? *(const uint4 *)&set.mask[c * kBitmapChunk + 4 * lane] : make_uint4(0, 0, 0, 0);
+    emit_bitmap(a, set.mask, (uint16_t *)ring, chunk_n, nsel);
+}
+
+// The same walk where many combinations share the budget: the wavefronts take turns, a combination each, and nothing but the
+// turn itself is serial.  Until it has the turn a wavefront sorts out its list on its own: cells whose tokens are all
+// allocated already stay so, whatever the others do meanwhile, and are dropped, first from the whole list (while the seven before
+// it have their turns), again from the front of what is left when its turn is near.  With the turn it looks at the first
+// cells left once more: one gather, one scan and the marks for the usual share, without a barrier.  What was dropped before only
+// saves time, the turn decides on what the set holds then.
+// Bound: the chain of a turn, about 650 cycles, half of them LDS round trips (see the turn, fetch the words, mark, pass it on),
+// where a pass of the workgroup over the whole list took 1300.  Measured (kernel trace), 48 combinations: 9001 tokens, budget
+// 1000 33.9 -> 19.4 us; 1M, budget 4096 40.8 -> 26.7 us.
+constexpr int kRelayCombos = 4;                                 // from that many combinations on, and where ..
+constexpr uint32_t kRelayShare = 96;                            // .. no share is more cells
+constexpr int kRelayRaw = 16;                                   // cells of a list a lane fetches ahead
+constexpr int kRelayKept = kRingBytes / 4 / kWalkWaves;         // cells a wavefront keeps
+constexpr uint32_t kRelayChunk = 64 * kWalkPer;                 // cells it looks at at a time with the turn
+template <bool HASHED>
+__global__ __launch_bounds__(kWalkThreads) void allocate_relay(const WalkArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ uint32_t chunk_n[kBitmapChunks];
+    __shared__ uint32_t turn;  // whose turn it is, and the number of tokens allocated, above 8 bits
+    const TokenSet<HASHED> set{(uint32_t *)smem, (uint32_t *)smem + (HASHED ? kWordSlots : 0)};
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t chunks = (a.len + 32 * kBitmapChunk - 1) / (32 * kBitmapChunk);
+    const uint32_t clear = HASHED ? kWordSlots : chunks * kBitmapChunk;
+    uint32_t *ring = set.mask + clear, *kept = ring + wave * kRelayKept;
+
+    uint32_t l_share = a.share[lane], l_reach = a.reach[lane], l_cells = a.cells[lane];
+    asm volatile("" : "+v"(l_share), "+v"(l_reach), "+v"(l_cells));
+    auto of = [](uint32_t x, int j) { return (uint32_t)__builtin_amdgcn_readlane((int)x, j); };
+    auto list_of = [&](int j) { return (const uint32_t *)(a.cand + (size_t)j * kCandCap); };
+    uint32_t raw[kRelayRaw];
+    auto fetch = [&](int j) {
+        const uint32_t cn = of(l_cells, j);
+#pragma unroll
+        for (int k = 0; k < kRelayRaw; ++k)
+            if (64u * k < cn) raw[k] = list_of(j)[min(64u * k + lane, cn - 1)];  // uniform
     };
-    for (uint32_t c0 = wave; c0 < chunks; c0 += kWalkWaves * kEmitBatch) {
-        uint32_t sum[kEmitBatch];
+    if (wave < a.n) fetch(wave);
+    for (uint32_t i = tid * 4; i < clear; i += kWalkThreads * 4) {
+        if (HASHED) *(uint4 *)&set.key[i] = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
+        *(uint4 *)&set.mask[i] = make_uint4(0, 0, 0, 0);
+    }
+    if (tid == 0) turn = 0;
+    __syncthreads();
+    auto whose = [&]() { return __hip_atomic_load(&turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+
+    for (int j = wave; j < a.n; j += kWalkWaves) {
+        const uint32_t cn = of(l_cells, j), reach = of(l_reach, j), ones = 0xFFFFFFFFu >> (32 - reach);
+        const uint32_t *list = list_of(j);
+        auto word_of = [&](uint32_t c) { return c * reach >> 5; };
+        auto bits_of = [&](uint32_t c) { return ones << (c * reach & 31); };
+        auto keep = [&](uint32_t c, bool some, uint32_t &n) {  // the next of the cells kept
+            const uint64_t mask = __ballot(some);
+            const uint32_t at = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+            if (some) kept[at] = c;
+            n += (uint32_t)__popcll(mask);
+        };
+        // the list's cells that still have something free
+        uint32_t n = 0, seen = 0;  // kept; cells of the list looked at
+        {
+            uint32_t word[kRelayRaw];
 #pragma unroll
-        for (int b = 0; b < kEmitBatch; ++b) {
-            const uint4 x = words4(c0 + b * kWalkWaves);
-            sum[b] = __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w);
+            for (int k = 0; k < kRelayRaw; ++k)
+                if (64u * k < cn) word[k] = set.get(word_of(raw[k]));  // uniform
+#pragma unroll
+            for (int k = 0; k < kRelayRaw; ++k) {
+                if (64u * k < cn && n + 64 <= (uint32_t)kRelayKept) {  // uniform
+                    keep(raw[k], (64u * k + lane < cn) & ((~word[k] & bits_of(raw[k])) != 0), n);
+                    seen = min(64u * (k + 1), cn);
+                }
+            }
         }
+        if (j + kWalkWaves < a.n) fetch(j + kWalkWaves);
+        // close to its turn: once more, as many as it looks at at a time
+        while ((int)(whose() & 255u) < j - 2) __builtin_amdgcn_s_sleep(1);
+        uint32_t front = 0, rest = 0;
+        for (; rest < n && front < kRelayChunk; rest += 64) {
+            const uint32_t c = kept[min(rest + lane, n - 1)];
+            keep(c, (rest + lane < n) & ((~set.get(word_of(c)) & bits_of(c)) != 0), front);
+        }
+        // Two neighbouring cells a lane: their words of the set, the bits of their tokens, and what is free.
+        uint32_t word[kWalkPer], bits[kWalkPer], free[kWalkPer];
+        static_assert(kWalkPer == 2, "two cells a lane");
+        auto look = [&](uint2 c, uint32_t left) __attribute__((always_inline)) {
+            word[0] = word_of(c.x), word[1] = word_of(c.y);
+            bits[0] = lane * 2 < left ? bits_of(c.x) : 0u, bits[1] = lane * 2 + 1 < left ? bits_of(c.y) : 0u;
+            word[0] = bits[0] ? word[0] : 0u, word[1] = bits[1] ? word[1] : 0u;
+            asm volatile("" : "+v"(word[0]), "+v"(word[1]), "+v"(bits[0]), "+v"(bits[1]));  // (now, not when they are used)
+        };
+        uint32_t nsel = 0, taken = 0, share = 0;
+        auto take = [&]() __attribute__((always_inline)) {
+            free[0] = ~free[0] & bits[0], free[1] = ~free[1] & bits[1];
+            const uint32_t n0 = __popc(free[0]), n1 = __popc(free[1]);
+            const uint32_t upto = wave_scan_add(n0 + n1), total = wave_total(upto), room = share - taken;
+            if (HASHED || total > room) {  // uniform: the share ends here
+                const uint32_t before = upto - n0 - n1;
+                const uint32_t q0 = room > before ? room - before : 0u, q1 = room > before + n0 ? room - before - n0 : 0u;
+                free[0] = q0 ? free[0] : 0u, free[1] = q1 ? free[1] : 0u;
+                // in the cell where it ends the lowest tokens are taken: lane i counts the free ones below token i
+                const bool here0 = (q0 != 0) & (q0 < n0), here1 = (q1 != 0) & (q1 < n1);
+                const uint64_t ends = __ballot(here0 | here1);
+                if (ends) {  // uniform
+                    const int l = __ffsll((unsigned long long)ends) - 1;
+                    const uint32_t x = of(here0 ? free[0] : free[1], l), q = of(here0 ? q0 : q1, l);
+                    const uint32_t some = (uint32_t)__ballot((x >> (lane & 31) & 1u) & (__builtin_amdgcn_mbcnt_lo(x, 0u) < q ? 1u : 0u));
+                    free[0] = here0 ? some : free[0];
+                    free[1] = here1 ? some : free[1];
+                }
+                if (HASHED) {
+                    uint32_t place = nsel + taken + before;
 #pragma unroll
-        for (int b = 0; b < kEmitBatch; ++b) sum[b] = wave_scan_add(sum[b]);
-#pragma unroll
-        for (int b = 0; b < kEmitBatch; ++b)
-            if (lane == 63 && c0 + b * kWalkWaves < chunks) chunk_n[c0 + b * kWalkWaves] = sum[b];
+                    for (int i = 0; i < kWalkPer; ++i)
+                        for (uint32_t x = free[i]; x; x &= x - 1) a.picked[place++] = word[i] * 32 + (uint32_t)__ffs((int)x) - 1;
+                }
+            }
+            if (free[0]) set.set(word[0], free[0]);
+            if (free[1]) set.set(word[1], free[1]);
+            taken += min(total, room);
+        };
+        look(*(const uint2 *)&kept[2 * lane], front);
+        __builtin_amdgcn_s_setprio(3);
+        // (a wavefront's LDS operations are performed in order: the words are read after the turn is, and the turn is
+        // passed on after the marks)
+        uint32_t now;
+        do {
+            now = whose();
+            asm volatile("" ::: "memory");
+            free[0] = set.get(word[0]), free[1] = set.get(word[1]);
+            asm volatile("" : "+v"(free[0]), "+v"(free[1]));
+            now = (uint32_t)__builtin_amdgcn_readfirstlane((int)now);
+        } while ((int)(now & 255u) != j);
+        nsel = now >> 8;
+        share = min(of(l_share, j), (uint32_t)a.n_out - nsel);
+        take();
+        if (taken < share) {
+            // the cells behind them, and those of the list that were not looked at
+            uint32_t at = kRelayChunk, end = front;
+            if (at >= front) at = rest, end = n;
+            while (taken < share && at < n) {
+                look(make_uint2(kept[min(at + 2 * lane, end - 1)], kept[min(at + 2 * lane + 1, end - 1)]), end - at);
+                free[0] = set.get(word[0]), free[1] = set.get(word[1]);
+                take();
+                at += kRelayChunk;
+                if (at >= end && end == front) at = rest, end = n;
+            }
+            for (; taken < share && seen < cn; seen += kRelayChunk) {
+                look(make_uint2(list[min(seen + 2 * lane, cn - 1)], list[min(seen + 2 * lane + 1, cn - 1)]), cn - seen);
+                free[0] = set.get(word[0]), free[1] = set.get(word[1]);
+                take();
+            }
+        }
+        nsel += taken;
+        asm volatile("" ::: "memory");
+        if (lane == 0) __hip_atomic_store(&turn, (nsel << 8) | (uint32_t)(j + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __builtin_amdgcn_s_setprio(0);
     }
     __syncthreads();
-    // every wavefront sums the chunks before each of its own by itself (lane l holds chunks l, l + 64, l + 128)
-    uint32_t cn[3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) cn[i] = (uint32_t)(lane + 64 * i) < chunks ? chunk_n[lane + 64 * i] : 0u;
-    static_assert(kBitmapChunks <= 3 * 64, "three chunks a lane");
-    for (uint32_t c0 = wave; c0 < chunks; c0 += kWalkWaves * kEmitBatch) {
-        uint4 x[kEmitBatch];
-        uint32_t n3[kEmitBatch], at[kEmitBatch];
-#pragma unroll
-        for (int b = 0; b < kEmitBatch; ++b) {
-            const uint32_t c = c0 + b * kWalkWaves;
-            x[b] = words4(c);
-            n3[b] = __popc(x[b].x) + __popc(x[b].y) + __popc(x[b].z) + __popc(x[b].w);
-            at[b] = ((uint32_t)lane < c ? cn[0] : 0u) + ((uint32_t)lane + 64 < c ? cn[1] : 0u) + ((uint32_t)lane + 128 < c ? cn[2] : 0u);
-        }
-#pragma unroll
-        for (int b = 0; b < kEmitBatch; ++b) at[b] = wave_total(wave_scan_add(at[b])) + wave_scan_add(n3[b]) - n3[b];
-#pragma unroll
-        for (int b = 0; b < kEmitBatch; ++b) {
-            const uint32_t w = (c0 + b * kWalkWaves) * kBitmapChunk + 4 * lane;
-            if (x[b].x) slot_word[at[b]] = (uint16_t)(w + 1);
-            at[b] += __popc(x[b].x);
-            if (x[b].y) slot_word[at[b]] = (uint16_t)(w + 2);
-            at[b] += __popc(x[b].y);
-            if (x[b].z) slot_word[at[b]] = (uint16_t)(w + 3);
-            at[b] += __popc(x[b].z);
-            if (x[b].w) slot_word[at[b]] = (uint16_t)(w + 4);
-        }
+    const uint32_t nsel = turn >> 8;
+    if (HASHED) {
+        if (tid == 0) *a.picked_n = nsel;
+        return;
     }
-    __syncthreads();
-    int32_t *out = a.out_idx + a.sink;
-    // a wavefront's places lie side by side: the last note of one group of 64 serves the next
-    const uint32_t span = (nsel + kWalkThreads - 1) / kWalkThreads * 64, s_begin = wave * span, s_end = min(s_begin + span, nsel);
-    auto note_of = [&](uint32_t s) {  // place and word in one number, larger for a later place
-        const uint32_t x = s < nsel ? slot_word[s] : 0u;
-        return x ? (s & 0xFFFFu) << 16 | x : 0u;
-    };
-    uint32_t carry = 0;
-    if (s_begin >= 64 && s_begin < nsel) carry = wave_total(wave_scan_max(note_of(s_begin - 64 + lane)));
-    for (uint32_t s0 = s_begin; s0 < s_end; s0 += 64 * kEmitBatch) {
-        uint32_t note[kEmitBatch], bits[kEmitBatch];
-#pragma unroll
-        for (int b = 0; b < kEmitBatch; ++b) note[b] = note_of(s0 + 64 * b + lane);
-#pragma unroll
-        for (int b = 0; b < kEmitBatch; ++b) note[b] = wave_scan_max(note[b]);
-#pragma unroll
-        for (int b = 0; b < kEmitBatch; ++b) {
-            note[b] = max(note[b], carry);
-            carry = wave_total(note[b]);
-            bits[b] = set.mask[(note[b] & 0xFFFFu) - 1u];  // (place 0 is noted: there is always one)
-        }
-#pragma unroll
-        for (int b = 0; b < kEmitBatch; ++b) {
-            const uint32_t s = s0 + 64 * b + lane;
-            if (s < s_end) out[s] = (int32_t)(((note[b] & 0xFFFFu) - 1u) * 32 + nth_set_bit(bits[b], s - (note[b] >> 16)) + (uint32_t)a.sink);
-        }
-    }
-    for (uint32_t i = tid; i < (uint32_t)a.sink; i += kWalkThreads) a.out_idx[i] = (int32_t)i;
-    for (uint32_t i = nsel + tid; i < (uint32_t)a.n_out; i += kWalkThreads) out[i] = -1;
-    if (tid == 0 && a.out_count) *a.out_count = a.sink + (int32_t)nsel;
+    emit_bitmap(a, set.mask, (uint16_t *)ring, chunk_n, nsel);
 }
 
 
@@ -2174,7 +2346,8 @@ hipError_t set_select_attributes()
         hipError_t e;
         for (const void *walk : {(const void *)allocate_walk<kWalkSeeds, false>, (const void *)allocate_walk<kWalkSeeds, true>,
                                  (const void *)allocate_walk<kWalkWordCells, false>, (const void *)allocate_walk<kWalkWordCells, true>,
-                                 (const void *)allocate_walk<kWalkCells, false>, (const void *)allocate_walk<kWalkCells, true>})
+                                 (const void *)allocate_walk<kWalkCells, false>, (const void *)allocate_walk<kWalkCells, true>,
+                                 (const void *)allocate_relay<false>, (const void *)allocate_relay<true>})
             if ((e = hipFuncSetAttribute(walk, hipFuncAttributeMaxDynamicSharedMemorySize, kWalkLds)) != hipSuccess) return e;
         if ((e = raise_avg_lds<0, kAvgWide, true>()) != hipSuccess || (e = raise_avg_lds<0, kAvgNarrow, true>()) != hipSuccess ||
             (e = raise_avg_lds<0, kAvgNarrow, false>()) != hipSuccess || (e = raise_avg_lds<1, kAvgNarrow, true>()) != hipSuccess ||
@@ -2206,12 +2379,19 @@ void launch_walk(WalkArgs &w, const SelectJob &job, int n_out, unsigned char *ws
     w.picked_n = w.picked + ILRE_MAX_BUDGET;
     w.out_idx = out_idx;
     w.out_count = out_count;
+    // Taking turns pays while a turn is one look at kRelayChunk cells, of which those of the turns just before it are taken by
+    // then, and there are other turns to prepare in.  Whole selection, workgroup -> turns: 48 combinations, shares of 85, 42 and
+    // 21 cells 91.4 -> 81.0 us, 27 of 152, 76 and 38 59.2 -> 59.7; 32 of 128 and 64 94.3 -> 94.3 (with the word table 141.6 ->
+    // 165.6); 4 of 125 30.1 -> 31.0, of 37 28.8 -> 28.8, of 19 and 10 31.6 -> 30.8; one of 16 26.3 -> 26.8.
+    bool relay = ITEMS == kWalkWordCells && w.n >= kRelayCombos;
+    for (int j = 0; j < w.n; ++j) relay = relay && w.share[j] <= kRelayShare * w.reach[j];
     if (job.L <= kBitmapTokens) {
         const size_t chunks = ((size_t)job.L + 32 * kBitmapChunk - 1) / (32 * kBitmapChunk);
         const size_t lds = chunks * kBitmapChunk * sizeof(uint32_t) + kRingBytes;
-        hipLaunchKernelGGL((allocate_walk<ITEMS, false>), dim3(1), dim3(kWalkThreads), lds, s, w);
+        hipLaunchKernelGGL((relay ? allocate_relay<false> : allocate_walk<ITEMS, false>), dim3(1), dim3(kWalkThreads), lds, s, w);
     } else {
-        hipLaunchKernelGGL((allocate_walk<ITEMS, true>), dim3(1), dim3(kWalkThreads), 2 * (size_t)kWordSlots * sizeof(uint32_t) + kRingBytes, s, w);
+        hipLaunchKernelGGL((relay ? allocate_relay<true> : allocate_walk<ITEMS, true>), dim3(1), dim3(kWalkThreads),
+                           2 * (size_t)kWordSlots * sizeof(uint32_t) + kRingBytes, s, w);
         hipLaunchKernelGGL(emit_sorted, dim3((unsigned)((n_out + kEmitPerBlock - 1) / kEmitPerBlock) + 1u), dim3(kEmitThreads), 0, s,
                            w.picked, w.picked_n, n_out, job.sink, out_idx, out_count);
     }

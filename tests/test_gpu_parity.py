@@ -626,6 +626,34 @@ def test_walk_over_bitmap_and_word_table(L, sink, budget, windows, mk, ak):
     assert got_p[:n].tolist() == oracle.allocate_max_avg(s, mk, ak, budget, sink=sink).tolist() and (got_p[n:] == -1).all()
 
 
+ALL16 = tuple(range(1, 17))
+RELAY_CASES = [
+    # L, sink, budget, max sizes, average sizes, kind: combinations that take turns (shares of at most 96 cells, four of them or more)
+    (9000, 4, 1000, (2, 4, 8), ALL16, "needles"), (9001, 0, 30, (2, 4, 8), ALL16, "random"),  # .. fewer tokens than combinations
+    (40000, 0, 64 * 96, (1,), tuple(range(1, 65)), "needles"),    # 64 of them, lists of more cells than are fetched ahead (1024)
+    (40001, 1, 64 * 96, (1,), (5,) * 64, "random"),               # .. all alike: every list's front is taken
+    (40000, 0, 64 * 96 + 1, (1,), (5,) * 64, "random"),           # .. one token more: not by turns
+    (40000, 2, 8192, (32, 8, 4, 2), ALL16, "equal"), (30000, 0, 5000, (16, 32), (3, 4), "narrow"),
+    (700, 0, 700, (2, 4, 8), ALL16, "few_values"), (20, 3, 17, (32, 1, 16), (1, 2, 9), "random"),  # lists that run out, empty ones
+    (9000, 0, 4 * 95 + 1, (1,), (1, 2, 3, 4), "random"), (9000, 0, 300, (8,), (1, 2, 3), "random"),
+    (1200000, 4, 4096, (2, 4, 8), ALL16, "needles"), (1200001, 0, 3000, (1,), (7,) * 33, "two_values"),  # the word table
+]
+
+
+@pytest.mark.parametrize("L,sink,budget,mk,ak,kind", RELAY_CASES, ids=[f"L{c[0]}_B{c[2]}_{c[5]}" for c in RELAY_CASES])
+def test_walk_by_turns(L, sink, budget, mk, ak, kind):
+    _announce(f"turns L={L} sink={sink} budget={budget} max={mk} avg={len(ak)} {kind}")
+    s = _scores_for(kind, L, np.random.default_rng(L + budget))
+    want = oracle.allocate_max_avg(s, mk, ak, budget, sink=sink)
+    dev = torch.from_numpy(s).cuda()
+    for _ in range(3):
+        got, count = il.ilre_select_max_avg(dev, budget, mk, ak, sink)
+        torch.cuda.synchronize()
+        n = int(count.item())
+        got = got.cpu().numpy()
+        assert got[:n].tolist() == want.tolist() and (got[n:] == -1).all()
+
+
 AVERAGE_CASES = [
     # L, budget, max sizes, average sizes, kind: chunks of 128 / 256 windows and their remainders, the straight-line code for
     # sizes 1..16 and the loop for others (over 16, repeated), shares that want little, much or all of the cells
