@@ -17,6 +17,8 @@
 //   pool_averages<1>   the averages at or above the cut, into the combination's list
 //   refine       per combination: the list ranked, the first K_j elements kept; a list too long to sort (many equal
 //                averages) is radix-selected down first, 8 bits a pass, survivors compacted
+//   rank_short   few windows: a workgroup a combination does all of that in one launch; or one for each part of its cells, and
+//                refine_parts ranks what they leave
 //   allocate_walk   one workgroup walks the combinations in order over their ranked cells: the allocated set is
 //                a bitmap in LDS, tokens that it holds are skipped, the first B_j others are taken; the ascending
 //                output is then read off the bitmap.  allocate_relay: the same, the wavefronts taking turns, for many
@@ -1323,17 +1325,18 @@ __global__ __launch_bounds__(THREADS) void collect(const float *vals, int64_t le
 
 // Elements in rank order by a counting sort of one workgroup: kRankBins bins over the range of the values' key bits,
 // descending, a scan of the counts places every bin, and inside a bin an element counts the ones that rank ahead of it.
-// Thread t holds PER keys, of which the ones in `have` exist (`total` in all; `top` and `low` enclose their value bits);
-// the elements of the first `want` go out in order.  False where one of the bins they are in holds more than kRankDeep:
-// the keys then lie in srt[0 .. total) in some order, for the network.
+// Where a bin is crowded (a few values far above the others stretch the range) every bin is split in proportion to what it holds,
+// and the elements are counted once more.  Thread t holds PER keys, of which the ones in `have` exist (`all` in all; `top` and
+// `low` enclose their value bits); the elements of the first `want` go out in order.  False where one of the bins they are in
+// still holds more than kRankDeep (equal values): the keys then lie in srt[0 .. all) in some order, for the network.
 // (A list of 4096 elements all in bins of 128: the whole call 50 us, of 256: 67, of 512: 100; by the network 68.)
 constexpr int kRankBins = 2048;
-constexpr uint32_t kRankDeep = 256;
+constexpr uint32_t kRankCrowd = 160, kRankDeep = 256;
 struct RankShared {
-    uint32_t bin_n[kRankBins];
+    uint32_t bin_n[2 * kRankBins];
+    uint32_t split[kRankBins];  // first of a bin's parts, and their number's logarithm in 5 bits
     uint32_t wmax[kThreads / 64], wmin[kThreads / 64], wsum[kThreads / 64];
-    uint32_t cut;  // last bin that is wanted, and the elements up to it
-    uint32_t upto;
+    uint32_t cut;  // last bin that is wanted
 };
 
 // the range's top 11 bits number the bins
@@ -1361,32 +1364,59 @@ __device__ __forceinline__ void rank_range(RankShared &sh, uint32_t &top, uint32
 
 template <int PER>
 __device__ bool rank_keys(RankShared &sh, uint64_t *srt, const uint64_t (&key)[PER], uint32_t have, uint32_t top, uint32_t low, uint32_t want,
-                          uint32_t *ranked)
+                          uint32_t *ranked, uint32_t &all)
 {
     const uint32_t shift = rank_shift(top, low);
-    uint32_t bin[PER], place[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        bin[k] = (top - (uint32_t)(key[k] >> 32)) >> shift;
-        if (have >> k & 1u) place[k] = atomicAdd(&sh.bin_n[bin[k]], 1u);
-    }
-    __syncthreads();
-    const uint2 n2 = *(const uint2 *)&sh.bin_n[2 * threadIdx.x];
-    uint32_t all;
-    const uint32_t before = block_scan_inclusive<kThreads>(n2.x + n2.y, sh.wsum, all) - n2.x - n2.y;
-    // a bin's word: how many elements rank ahead of it, and its own number
-    static_assert(PER * kThreads < 1 << 14, "14 bits a count");
-    *(uint2 *)&sh.bin_n[2 * threadIdx.x] = make_uint2(before << 14 | n2.x, (before + n2.x) << 14 | n2.y);
-    const bool deep = __syncthreads_or((n2.x > kRankDeep && before < want) || (n2.y > kRankDeep && before + n2.x < want));
+    uint32_t place[PER];
 #pragma unroll
     for (int k = 0; k < PER; ++k)
-        if (have >> k & 1u) srt[(sh.bin_n[bin[k]] >> 14) + place[k]] = key[k];
+        if (have >> k & 1u) place[k] = atomicAdd(&sh.bin_n[(top - (uint32_t)(key[k] >> 32)) >> shift], 1u);
+    __syncthreads();
+    // a bin's word: how many elements rank ahead of it, and its own number
+    static_assert(PER * kThreads < 1 << 15, "15 bits a count");
+    const uint2 n2 = *(const uint2 *)&sh.bin_n[2 * threadIdx.x];
+    const uint32_t before = block_scan_inclusive<kThreads>(n2.x + n2.y, sh.wsum, all) - n2.x - n2.y;
+    *(uint2 *)&sh.bin_n[2 * threadIdx.x] = make_uint2(before << 15 | n2.x, (before + n2.x) << 15 | n2.y);
+    const bool crowd = __syncthreads_or((n2.x > kRankCrowd && before < want) || (n2.y > kRankCrowd && before + n2.x < want));
+    const bool split = crowd && shift;
+    auto bin_of = [&](uint64_t x) {
+        const uint32_t d = top - (uint32_t)(x >> 32), b = d >> shift;
+        if (!split) return b;
+        const uint32_t w = sh.split[b], e = w & 31u;
+        return (w >> 5) + ((d & ((1u << shift) - 1u)) >> (shift - e));
+    };
+    bool deep = false;
+    if (split) {  // uniform
+        // 2^e parts, about as many as a bin's elements are of the whole list's 2048ths
+        auto parts = [&](uint32_t n) { return n ? min(31u - (uint32_t)__clz((int)max(n * (uint32_t)kRankBins / all, 1u)), shift) : 0u; };
+        const uint32_t e0 = parts(n2.x), e1 = parts(n2.y), p0 = n2.x ? 1u << e0 : 0u, p1 = n2.y ? 1u << e1 : 0u;
+        uint32_t total;
+        const uint32_t first = block_scan_inclusive<kThreads>(p0 + p1, sh.wsum, total) - p0 - p1;  // (at most 2 kRankBins in all)
+        *(uint2 *)&sh.split[2 * threadIdx.x] = make_uint2(first << 5 | e0, (first + p0) << 5 | e1);
+        *(uint4 *)&sh.bin_n[4 * threadIdx.x] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if (have >> k & 1u) place[k] = atomicAdd(&sh.bin_n[bin_of(key[k])], 1u);
+        __syncthreads();
+        const uint4 n4 = *(const uint4 *)&sh.bin_n[4 * threadIdx.x];
+        const uint32_t sum = n4.x + n4.y + n4.z + n4.w, b0 = block_scan_inclusive<kThreads>(sum, sh.wsum, all) - sum;
+        const uint32_t b1 = b0 + n4.x, b2 = b1 + n4.y, b3 = b2 + n4.z;
+        *(uint4 *)&sh.bin_n[4 * threadIdx.x] = make_uint4(b0 << 15 | n4.x, b1 << 15 | n4.y, b2 << 15 | n4.z, b3 << 15 | n4.w);
+        deep = __syncthreads_or((n4.x > kRankDeep && b0 < want) || (n4.y > kRankDeep && b1 < want) || (n4.z > kRankDeep && b2 < want) ||
+                                (n4.w > kRankDeep && b3 < want));
+    } else if (crowd) {
+        deep = __syncthreads_or((n2.x > kRankDeep && before < want) || (n2.y > kRankDeep && before + n2.x < want));
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+        if (have >> k & 1u) srt[(sh.bin_n[bin_of(key[k])] >> 15) + place[k]] = key[k];
     __syncthreads();
     if (deep) return false;
     // neighbouring threads, neighbouring places: a deep bin is the work of the few wavefronts that hold it, from one address
     for (uint32_t x = threadIdx.x; x < all; x += kThreads) {
         const uint64_t mine = srt[x];
-        const uint32_t at = sh.bin_n[(top - (uint32_t)(mine >> 32)) >> shift], first = at >> 14, n = at & 16383u;
+        const uint32_t at = sh.bin_n[bin_of(mine)], first = at >> 15, n = at & 32767u;
         if (first >= want) break;  // (so are those behind it)
         uint32_t rank = first;
 #pragma unroll 8
@@ -1458,7 +1488,8 @@ __global__ __launch_bounds__(kThreads) void refine(const SelCtrl *ctrl, uint64_t
             low = min(low, (uint32_t)(key[k] >> 32));
         }
         rank_range(sh, top, low);
-        return rank_keys(sh, srt, key, have, top, low, want, ranked);
+        uint32_t all;
+        return rank_keys(sh, srt, key, have, top, low, want, ranked, all);
     };
     if (total == 0) return;  // uniform
     if (total <= kSortSmall ? by_counting(std::integral_constant<int, (int)kSortSmall / kThreads>{})
@@ -1468,6 +1499,235 @@ __global__ __launch_bounds__(kThreads) void refine(const SelCtrl *ctrl, uint64_t
     total = candn + nA;
     for (uint32_t i = threadIdx.x; i < total; i += kThreads) srt[i] = element(i);
     rank_network(srt, total, want, ranked);
+}
+
+// The same where several workgroups have collected a combination's elements, each the best of its part of the cells: part c's
+// lie in the list from c * size on.
+constexpr int kShortParts = 64;  // most parts
+static_assert(kShortParts <= kAvgBins, "their counts lie where the histograms do otherwise");
+__global__ __launch_bounds__(kThreads) void refine_parts(const SelParams prm, uint32_t size, const uint32_t *part_n, uint64_t *cand, uint64_t *tie,
+                                                         uint32_t sort_n)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ __align__(16) RankShared sh;
+    __shared__ uint32_t part_at[kShortParts + 1];
+    uint64_t *srt = (uint64_t *)smem;
+    const int j = blockIdx.x;
+    const uint32_t want = prm.want[j], len = prm.len[j], parts = (len + size - 1) / size;
+    if (want == 0) return;  // uniform
+    if (threadIdx.x < 64) {
+        static_assert(kShortParts == 64, "a lane a part");
+        part_at[threadIdx.x + 1] = wave_scan_add(threadIdx.x < parts ? part_n[j * kShortParts + threadIdx.x] : 0u);
+        if (threadIdx.x == 0) part_at[0] = 0;
+    }
+    __syncthreads();
+    const uint64_t *list = tie + prm.tie_off[j];
+    uint64_t *cand_j = cand + (size_t)j * kCandCap;
+    uint32_t *ranked = (uint32_t *)cand_j;
+    uint32_t nA = part_at[kShortParts];
+    uint32_t half = 1;  // of a power of two of parts
+    while (2 * half < parts) half *= 2;
+    auto by_counting = [&](auto per_tag) {
+        constexpr int PER = decltype(per_tag)::value;
+        uint64_t key[PER];
+        uint32_t c[PER], top = 0, low = 0xFFFFFFFFu, have = 0, all;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            c[k] = 0;
+            have |= threadIdx.x + k * kThreads < nA ? 1u << k : 0u;
+        }
+        for (uint32_t step = half; step; step >>= 1) {  // the parts they are in
+#pragma unroll
+            for (int k = 0; k < PER; ++k) c[k] += part_at[c[k] + step] <= min(threadIdx.x + k * kThreads, nA - 1) ? step : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < PER; ++k) key[k] = list[min(threadIdx.x + k * kThreads, nA - 1) - part_at[c[k]] + c[k] * size];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) top = max(top, (uint32_t)(key[k] >> 32)), low = min(low, (uint32_t)(key[k] >> 32));
+        rank_range(sh, top, low);
+        return rank_keys(sh, srt, key, have, top, low, want, ranked, all);
+    };
+    if (nA <= kSortLarge && (nA <= kSortSmall ? by_counting(std::integral_constant<int, (int)kSortSmall / kThreads>{})
+                                              : by_counting(std::integral_constant<int, (int)kSortLarge / kThreads>{})))
+        return;
+    // (many equal averages: put together, shortened, and to the network)
+    uint64_t *B = tie + prm.tie_off[j], *A = B + len;
+    for (uint32_t c = 0; c < parts; ++c)
+        for (uint32_t i = threadIdx.x; i < part_at[c + 1] - part_at[c]; i += kThreads) store_u64(&A[part_at[c] + i], list[i + (size_t)c * size]);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    uint32_t need = want, candn = 0;
+    peel<kThreads>(A, B, nA, need, cand_j, candn, sort_n);
+    const uint32_t total = candn + nA;
+    for (uint32_t i = threadIdx.x; i < total; i += kThreads) srt[i] = i < candn ? load_u64(&cand_j[i]) : load_u64(&A[i - candn]);
+    rank_network(srt, total, want, ranked);
+}
+
+// Printed form, few windows: the cut of a combination is not looked for by all workgroups over all windows but by one, or by one
+// for each part of the cells.  It pools the cells into LDS, sums the windows (four neighbouring ones a thread, from
+// 16-byte reads; in the order of the definition), finds the cut with a histogram over the range of the sums' keys, and ranks what
+// reaches it; a part's elements are left for refine_parts.  Where few are wanted only the largest of a thread's four neighbours is
+// counted: the K_j-th best of those is at most the K_j-th best of all.
+// Bound: latency (one round of loads, a dozen barriers); a workgroup a combination and 4096 windows share nothing, so that the
+// number of windows decides, see the launch.  Against sel_init, both passes over the averages and refine (kernel trace, 48
+// combinations, budget 4096 resp. 1000): 9001 tokens 6.9 + 10.1 + 8.8 + 4.5 -> 10.4 us, 128K 6.7 + 11.6 + 10.7 + 4.7 -> 16.8 + 8.5.
+constexpr uint32_t kShortCells = 16384;  // most cells a combination may have, ..
+constexpr int kShortMax = 8, kShortAvg = 64;  // .. tokens a cell, and cells a window
+constexpr size_t short_lds(uint32_t len, int n_top, bool ranks)
+{
+    size_t keys = ranks ? 2 : 0;
+    while (ranks && keys < len) keys *= 2;
+    const size_t cells = (size_t)((len + 3) & ~3u) + (size_t)n_top + 8;
+    return std::max(keys * sizeof(uint64_t), cells * sizeof(float));
+}
+template <int QUADS, bool PARTS>
+__global__ __launch_bounds__(kThreads) void rank_short(const SelParams prm, uint64_t *cand, uint64_t *tie, uint32_t *part_n)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ __align__(16) RankShared sh;
+    constexpr int PER = 4 * QUADS;
+    const int j = blockIdx.y, tid = threadIdx.x;
+    const uint32_t cells = prm.len[j], m = prm.m[j], n = prm.avg[j], first = blockIdx.x * (PER * kThreads);
+    if (first >= cells || prm.want[j] == 0) return;  // uniform
+    const uint32_t len = min(cells - first, (uint32_t)(PER * kThreads)), want = min(prm.want[j], len);
+    float *buf = (float *)smem;
+    const uint32_t lead = (n - 1) / 2, padded = ((len + 3) & ~3u) + n + 8;  // cell p lies at p - first + lead, zeros around all
+    auto pool = [&](auto size_tag) {
+        constexpr int M = decltype(size_tag)::value;  // 0: any
+        constexpr int kBatch = 4;
+        for (uint32_t i0 = tid; i0 < padded; i0 += kThreads * kBatch) {
+            float v[kBatch];
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b) {
+                const uint32_t p = first + i0 + b * kThreads - lead;  // (modulo 2^32)
+                const float *src = prm.src + (size_t)min(p, cells - 1) * (M ? (uint32_t)M : m);
+                v[b] = src[0];
+                if (M != 0) {
+#pragma unroll
+                    for (int u = 1; u < M; ++u) v[b] = fmaxf(v[b], src[u]);
+                } else {
+                    for (uint32_t u = 1; u < m; ++u) v[b] = fmaxf(v[b], src[u]);
+                }
+                if (p >= cells) v[b] = 0.0f;
+            }
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b)
+                if (i0 + b * kThreads < padded) buf[i0 + b * kThreads] = v[b];
+        }
+    };
+    using std::integral_constant;
+    if (m == 1)
+        pool(integral_constant<int, 1>{});
+    else if (m == 2)
+        pool(integral_constant<int, 2>{});
+    else if (m == 4)
+        pool(integral_constant<int, 4>{});
+    else if (m == 8)
+        pool(integral_constant<int, 8>{});
+    else
+        pool(integral_constant<int, 0>{});
+    __syncthreads();
+    const float size = (float)n, rcp = __fdiv_rn(1.0f, size);
+    uint64_t key[PER];
+    uint32_t have = 0, best[QUADS];
+#pragma unroll
+    for (int q = 0; q < QUADS; ++q) {
+        const uint32_t el = 4 * (tid + q * kThreads);
+        float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (el < len) {
+            for (uint32_t u = 0; u < n + 3; u += 4) {  // window i of the four holds cells i .. i + n - 1 from here
+                const float4 x4 = *(const float4 *)&buf[el + u];
+                const float x[4] = {x4.x, x4.y, x4.z, x4.w};
+                if (u >= 4 && u + 3 < n) {  // uniform
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) sum[i] += x[r];
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (u + r >= (uint32_t)i && u + r - i < n) sum[i] += x[r];  // uniform
+                }
+            }
+        }
+        best[q] = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            key[4 * q + i] = make_key(divide_small(sum[i], size, rcp), first + el + i);
+            if (el + i < len) {
+                have |= 1u << (4 * q + i);
+                best[q] = max(best[q], (uint32_t)(key[4 * q + i] >> 32));
+            }
+        }
+    }
+    // the bin that holds the K_j-th best, of all or of the best of each four
+    const bool fours = 2 * want <= (len + 3) / 4;  // uniform
+    uint32_t top = 0, low = 0xFFFFFFFFu;
+#pragma unroll
+    for (int q = 0; q < QUADS; ++q) {
+        if ((have >> (4 * q) & 1u) == 0) continue;
+        top = max(top, best[q]);
+        if (fours) low = min(low, best[q]);
+    }
+    if (!fours) {
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if (have >> k & 1u) low = min(low, (uint32_t)(key[k] >> 32));
+    }
+    rank_range(sh, top, low);
+    uint32_t shift = rank_shift(top, low);
+    if (fours) {
+#pragma unroll
+        for (int q = 0; q < QUADS; ++q)
+            if (have >> (4 * q) & 1u) atomicAdd(&sh.bin_n[(top - best[q]) >> shift], 1u);
+    } else {
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if (have >> k & 1u) atomicAdd(&sh.bin_n[(top - (uint32_t)(key[k] >> 32)) >> shift], 1u);
+    }
+    // the elements down to the bin that holds the K_j-th best, and the least of their keys
+    uint32_t subset = have, sub_low;
+    auto cut_off = [&]() __attribute__((always_inline)) {
+        __syncthreads();
+        const uint2 n2 = *(const uint2 *)&sh.bin_n[2 * tid];
+        uint32_t all;
+        const uint32_t upto = block_scan_inclusive<kThreads>(n2.x + n2.y, sh.wsum, all), before = upto - n2.x - n2.y;
+        if (before < want && want <= upto) sh.cut = 2 * tid + (before + n2.x < want ? 1u : 0u);  // one thread
+        __syncthreads();
+        const uint32_t cut = sh.cut;
+        sub_low = 0xFFFFFFFFu;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const uint32_t v = (uint32_t)(key[k] >> 32);
+            if ((top - v) >> shift > cut) subset &= ~(1u << k);
+            if (subset >> k & 1u) sub_low = min(sub_low, v);
+        }
+    };
+    cut_off();
+    rank_range(sh, top, sub_low);
+    if (!PARTS) {
+        uint64_t *srt = (uint64_t *)smem;
+        uint32_t *ranked = (uint32_t *)(cand + (size_t)j * kCandCap);
+        uint32_t total = 0;
+        if (!rank_keys(sh, srt, key, subset, top, sub_low, want, ranked, total)) rank_network(srt, total, want, ranked);
+        return;
+    }
+    if (fours) {  // uniform: once more, all of them
+        shift = rank_shift(top, sub_low);
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if (subset >> k & 1u) atomicAdd(&sh.bin_n[(top - (uint32_t)(key[k] >> 32)) >> shift], 1u);
+        cut_off();
+    }
+    uint32_t total;
+    const uint32_t mine = (uint32_t)__popc(subset);
+    uint64_t *at = tie + prm.tie_off[j] + first + (block_scan_inclusive<kThreads>(mine, sh.wsum, total) - mine);
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+        if (subset >> k & 1u) *at++ = key[k];
+    if (tid == 0) part_n[j * kShortParts + blockIdx.x] = total;
 }
 
 // Last step of the allocation: the sink indices, then the nsel allocated tokens in ascending order, then -1
@@ -2010,7 +2270,7 @@ __global__ __launch_bounds__(kWalkThreads) void allocate_walk(const WalkArgs a)
 // where a pass of the workgroup over the whole list took 1300.  Measured (kernel trace), 48 combinations: 9001 tokens, budget
 // 1000 33.9 -> 19.4 us; 1M, budget 4096 40.8 -> 26.7 us.
 constexpr int kRelayCombos = 4;                                 // from that many combinations on, and where ..
-constexpr uint32_t kRelayShare = 96;                            // .. no share is more cells
+constexpr uint32_t kRelayShare = 96, kRelayShareTable = 48;      // .. no share is more cells (with the word table)
 constexpr int kRelayRaw = 16;                                   // cells of a list a lane fetches ahead
 constexpr int kRelayKept = kRingBytes / 4 / kWalkWaves;         // cells a wavefront keeps
 constexpr uint32_t kRelayChunk = 64 * kWalkPer;                 // cells it looks at at a time with the turn
@@ -2353,7 +2613,11 @@ hipError_t set_select_attributes()
             (e = raise_avg_lds<0, kAvgNarrow, false>()) != hipSuccess || (e = raise_avg_lds<1, kAvgNarrow, true>()) != hipSuccess ||
             (e = raise_avg_lds<1, kAvgNarrow, false>()) != hipSuccess)
             return e;
-        if ((e = hipFuncSetAttribute((const void *)refine, hipFuncAttributeMaxDynamicSharedMemorySize, kSortLdsMax)) != hipSuccess) return e;
+        for (const void *rank : {(const void *)rank_short<1, false>, (const void *)rank_short<2, false>, (const void *)rank_short<4, false>,
+                                 (const void *)rank_short<1, true>, (const void *)rank_short<2, true>})
+            if ((e = hipFuncSetAttribute(rank, hipFuncAttributeMaxDynamicSharedMemorySize, (int)short_lds(kShortCells, kShortAvg, true))) != hipSuccess) return e;
+        for (const void *rank : {(const void *)refine, (const void *)refine_parts})
+            if ((e = hipFuncSetAttribute(rank, hipFuncAttributeMaxDynamicSharedMemorySize, kSortLdsMax)) != hipSuccess) return e;
         if ((e = hipFuncSetAttribute((const void *)seed_rank, hipFuncAttributeMaxDynamicSharedMemorySize, kSeedRankLds)) != hipSuccess) return e;
         return hipSuccess;
     }();
@@ -2383,9 +2647,11 @@ void launch_walk(WalkArgs &w, const SelectJob &job, int n_out, unsigned char *ws
     // then, and there are other turns to prepare in.  Whole selection, workgroup -> turns: 48 combinations, shares of 85, 42 and
     // 21 cells 91.4 -> 81.0 us, 27 of 152, 76 and 38 59.2 -> 59.7; 32 of 128 and 64 94.3 -> 94.3 (with the word table 141.6 ->
     // 165.6); 4 of 125 30.1 -> 31.0, of 37 28.8 -> 28.8, of 19 and 10 31.6 -> 30.8; one of 16 26.3 -> 26.8.
+    // With the word table, where looking through a list is a probe per cell: 20 of 51 91.0 -> 100.6, 48 of up to 42 141.5 -> 122.4.
+    const bool bitmap = job.L <= kBitmapTokens;
     bool relay = ITEMS == kWalkWordCells && w.n >= kRelayCombos;
-    for (int j = 0; j < w.n; ++j) relay = relay && w.share[j] <= kRelayShare * w.reach[j];
-    if (job.L <= kBitmapTokens) {
+    for (int j = 0; j < w.n; ++j) relay = relay && w.share[j] <= (bitmap ? kRelayShare : kRelayShareTable) * w.reach[j];
+    if (bitmap) {
         const size_t chunks = ((size_t)job.L + 32 * kBitmapChunk - 1) / (32 * kBitmapChunk);
         const size_t lds = chunks * kBitmapChunk * sizeof(uint32_t) + kRingBytes;
         hipLaunchKernelGGL((relay ? allocate_relay<false> : allocate_walk<ITEMS, false>), dim3(1), dim3(kWalkThreads), lds, s, w);
@@ -2616,27 +2882,63 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
     uint32_t sort_n = kSortSmall;  // elements are sorted in LDS, up to a power of two of them
     for (int j = 0; j < n; ++j)
         while (sort_n < prm.want[j]) sort_n *= 2;
-    if (ap.pooled) {
-        uint32_t wgs = 1;
-        for (int i = 0; i < job.n_max; ++i) {
-            const uint32_t per_wg = 64u / cell_lanes(ap.m[i]) * kCellBatch * kPoolWaves;
-            wgs = std::max(wgs, std::min((ap.len[i] + per_wg - 1) / per_wg, 4u * kNumCU));
-        }
-        hipLaunchKernelGGL(pool_cells, dim3(wgs, job.n_max), dim3(kPoolThreads), 0, s, scores, ap, cells);
+    // Few windows: see rank_short.  A workgroup a combination up to kShortCells cells; beyond, one for 4096 of them (up to 2M windows in
+    // all) or 8192 (4M), as long as what the parts may hand on, with some room, can be sorted at once.  Whole selection, by
+    // all workgroups -> so: 48 combinations 20000 tokens (0.8M windows) 68.6 -> 38.8 us, 128K (1.8M) 55.4 -> 47.4, 256K (3.7M) 50.4 -> 46.7,
+    // 512K (7.3M) 55.6 -> 64.2; 27 combinations 256K (2.1M) 41.7 -> 36.8; one, cells of 4 128K 27.8 -> 18.1, 1M 33.6 -> 26.7.  Parts of 16384
+    // cells: 256K, budget 4096 55.2 -> 63.0 us, one combination of 32K cells 28.7 -> 29.9.
+    int quads = 0;  // 4096 cells each
+    bool parts = false;
+    uint32_t most = 0;
+    int64_t windows = 0;
+    for (int j = 0; j < n; ++j) most = std::max(most, prm.want[j]), windows += prm.len[j];
+    bool brief = n_top <= kShortAvg;
+    for (int i = 0; i < job.n_max; ++i) brief = brief && job.max_kernels[i] <= kShortMax;
+    auto shared_by = [&](int64_t len, int q) { return (len + q * 4 * kThreads - 1) / (q * 4 * kThreads); };
+    if (brief && len_max <= (int64_t)kShortCells) {
+        quads = len_max <= 4 * kThreads ? 1 : len_max <= 8 * kThreads ? 2 : 4;
+    } else if (brief) {
+        for (int q = 1; q <= 2 && !quads; q *= 2)
+            if (windows <= (q << 21) && shared_by(len_max, q) <= kShortParts && 9 * shared_by(len_max, q) * most <= 8 * (int64_t)kSortLarge) quads = q;
+        parts = quads != 0;
     }
-    hipLaunchKernelGGL(sel_init, dim3(n), dim3(kThreads), 0, s, prm, hist, ctrl, done);
-    if (wide)
-        launch_averages<0, kAvgWide, true>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
-    else if (small)
-        launch_averages<0, kAvgNarrow, true>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
-    else
-        launch_averages<0, kAvgNarrow, false>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
-    if (small)
-        launch_averages<1, kAvgNarrow, true>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
-    else
-        launch_averages<1, kAvgNarrow, false>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
-    const uint32_t sort_keys = sort_n > kSortSmall ? std::max(sort_n, kSortLarge) : sort_n;
-    hipLaunchKernelGGL(refine, dim3(n), dim3(kThreads), (size_t)sort_keys * sizeof(uint64_t), s, ctrl, cand, tie, sort_n);
+    if (quads) {
+        for (int j = 0; j < n; ++j) prm.m[j] = (uint32_t)cell_of[j];
+        prm.src = scores;
+        if (!parts) {
+            auto kernel = quads == 1 ? rank_short<1, false> : quads == 2 ? rank_short<2, false> : rank_short<4, false>;
+            hipLaunchKernelGGL(kernel, dim3(1, n), dim3(kThreads), short_lds((uint32_t)len_max, n_top, true), s, prm, cand, tie, hist);
+        } else {
+            const uint32_t size = (uint32_t)quads * 4 * kThreads;
+            auto kernel = quads == 1 ? rank_short<1, true> : rank_short<2, true>;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)shared_by(len_max, quads), n), dim3(kThreads), short_lds(size, n_top, false), s, prm, cand, tie, hist);
+            const uint32_t sort_most = std::max(sort_n, 2 * kSortSmall);
+            hipLaunchKernelGGL(refine_parts, dim3(n), dim3(kThreads), (size_t)std::max(sort_most, kSortLarge) * sizeof(uint64_t), s, prm, size, hist,
+                               cand, tie, sort_most);
+        }
+    } else {
+        if (ap.pooled) {
+            uint32_t wgs = 1;
+            for (int i = 0; i < job.n_max; ++i) {
+                const uint32_t per_wg = 64u / cell_lanes(ap.m[i]) * kCellBatch * kPoolWaves;
+                wgs = std::max(wgs, std::min((ap.len[i] + per_wg - 1) / per_wg, 4u * kNumCU));
+            }
+            hipLaunchKernelGGL(pool_cells, dim3(wgs, job.n_max), dim3(kPoolThreads), 0, s, scores, ap, cells);
+        }
+        hipLaunchKernelGGL(sel_init, dim3(n), dim3(kThreads), 0, s, prm, hist, ctrl, done);
+        if (wide)
+            launch_averages<0, kAvgWide, true>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
+        else if (small)
+            launch_averages<0, kAvgNarrow, true>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
+        else
+            launch_averages<0, kAvgNarrow, false>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
+        if (small)
+            launch_averages<1, kAvgNarrow, true>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
+        else
+            launch_averages<1, kAvgNarrow, false>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
+        const uint32_t sort_keys = sort_n > kSortSmall ? std::max(sort_n, kSortLarge) : sort_n;
+        hipLaunchKernelGGL(refine, dim3(n), dim3(kThreads), (size_t)sort_keys * sizeof(uint64_t), s, ctrl, cand, tie, sort_n);
+    }
     walk.n = n;
     bool word_cells = true;  // cells lie inside words of the set: sizes 1, 2, 4, 8, 16, 32
     for (int j = 0; j < n; ++j) {

@@ -626,6 +626,45 @@ def test_walk_over_bitmap_and_word_table(L, sink, budget, windows, mk, ak):
     assert got_p[:n].tolist() == oracle.allocate_max_avg(s, mk, ak, budget, sink=sink).tolist() and (got_p[n:] == -1).all()
 
 
+SHORT_CASES = [
+    # L, sink, budget, max sizes, average sizes, kind: combinations ranked by a workgroup each (up to 16384 cells, cells of up to 8 tokens,
+    # windows of up to 64) or by one for each 4096 or 8192 cells, at the edges of what a thread, a workgroup and the rule take
+    (4096, 0, 700, (1,), (1, 2, 3), "random"), (4097, 0, 700, (1,), (4, 5), "needles"), (8192, 0, 64, (1,), (16, 63, 64), "random"),
+    (8193, 1, 64, (1, 2), (2, 64, 65), "random"), (16384, 0, 3000, (1,), (7,), "narrow"), (16385, 0, 3000, (1,), (7,), "narrow"),
+    (16386, 1, 8192, (1,), (1,), "equal"), (13, 0, 5, (3, 5, 7), (1, 64), "random"), (4, 4, 3, (2,), (2,), "random"), (3, 0, 2, (8, 2), (3,), "random"),
+    (8000, 0, 999, (1,), (3,), "needles"), (8000, 0, 1000, (1,), (3,), "needles"),       # the best of each four counted, all counted
+    (9000, 0, 8192, (6, 7, 8), (1, 6), "few_values"), (9000, 0, 500, (9, 8), (1, 6), "random"), (12000, 3, 8191, (1,), (5, 9), "half_zero"),
+    (16000, 0, 300, (2, 4), (1, 9), "signed"), (16000, 0, 4000, (1,), (2, 8), "outliers"), (9000, 0, 900, (2,), (1, 3), "denormal"),
+    (3 * 4096, 0, 4096, (1,), (2,), "one_far"), (16380, 0, 8192, (1, 2), (8,), "one_far"),  # crowded bins
+    (20000, 0, 500, (1,), (1, 16), "needles"), (20481, 0, 60, (1,), (64,), "logarithms"), (40000, 0, 100, (1,), (3,), "equal"),  # in parts
+    (40000, 2, 1500, (1, 8), (4, 5), "two_values"), (40000, 0, 8192, (2,), (4,), "one_far"), (64 * 4096, 0, 64, (1,), (5,), "random"),
+    (64 * 4096 + 1, 0, 64, (1,), (5,), "random"), (70000, 0, 4096, (2,), (1, 2, 3, 4), "narrow"), (300001, 0, 64, (2, 4, 8), (1, 2, 3, 4, 5, 6), "flat"),
+    (100003, 0, 4000, (8,), (1, 2, 3, 17, 33), "needles"), (60000, 0, 2000, (3,), (15,), "mostly_equal"),
+]
+
+
+@pytest.mark.parametrize("L,sink,budget,mk,ak,kind", SHORT_CASES, ids=[f"L{c[0]}_B{c[2]}_{c[5]}" for c in SHORT_CASES])
+def test_few_windows_are_ranked_by_a_workgroup(L, sink, budget, mk, ak, kind):
+    _announce(f"few windows L={L} sink={sink} budget={budget} max={mk} avg={ak} {kind}")
+    rng = np.random.default_rng(L + budget)
+    if kind == "one_far":          # a range that leaves nearly everything in a few bins
+        s = (1.0 + 0.01 * rng.random(L)).astype(np.float32)
+        s[L // 3] = 1e30
+    elif kind == "mostly_equal":   # parts that hand on all they have
+        s = np.full(L, 0.5, dtype=np.float32)
+        s[rng.integers(0, L, 300)] = 0.75
+    elif kind in ("random", "few_values", "two_values", "equal", "narrow", "needles"):
+        s = _scores_for(kind, L, rng)
+    else:
+        s = _any_scores(kind, L, rng)
+    want = oracle.allocate_max_avg(s, mk, ak, budget, sink=sink)
+    got, count = il.ilre_select_max_avg(torch.from_numpy(s).cuda(), budget, mk, ak, sink)
+    torch.cuda.synchronize()
+    n = int(count.item())
+    got = got.cpu().numpy()
+    assert got[:n].tolist() == want.tolist() and (got[n:] == -1).all()
+
+
 ALL16 = tuple(range(1, 17))
 RELAY_CASES = [
     # L, sink, budget, max sizes, average sizes, kind: combinations that take turns (shares of at most 96 cells, four of them or more)
@@ -663,6 +702,10 @@ AVERAGE_CASES = [
     (70000, 300, (1,), (64, 1, 2), "needles"), (70000, 8000, (4, 2), tuple(range(1, 17)), "random"), (30000, 200, (2,), (1, 2, 3), "equal"),
     (30000, 200, (2,), (17, 18), "equal"), (9000, 100, (1, 2), (3, 7), "tiny"), (9000, 100, (1, 2), (3, 7, 16), "negative"),
     (9000, 100, (2, 3), (1, 6), "huge_range"),
+    # .. of more windows, or larger ones, than a workgroup or a few rank on their own
+    (16385, 8000, (1,), (1, 16), "random"), (16511, 8000, (1,), (2, 15), "needles"), (33000, 7000, (2, 1), (3, 16, 7), "random"),
+    (20001, 8192, (1,), (16,), "few_values"), (4096, 60, (2, 16), (1, 7, 16), "random"), (9216, 300, (9,), (2, 16), "random"),
+    (33001, 8000, (1,), (3, 7, 16), "negative"), (33001, 8192, (1, 2), (1, 6), "huge_range"), (33001, 8000, (1,), (3, 7), "tiny"),
 ]
 
 
