@@ -1331,12 +1331,14 @@ __global__ __launch_bounds__(THREADS) void collect(const float *vals, int64_t le
 // still holds more than kRankDeep (equal values): the keys then lie in srt[0 .. all) in some order, for the network.
 // (A list of 4096 elements all in bins of 128: the whole call 50 us, of 256: 67, of 512: 100; by the network 68.)
 constexpr int kRankBins = 2048;
+// Counting once more takes 1.5 us (27 combinations, 20000 tokens, budget 4096, bins split that hold more than 48 33.6 us, 160 32.2,
+// 255 32.2; 4 combinations, 40000 tokens, budget 4096 31.3, 31.5, 36.2).
 constexpr uint32_t kRankCrowd = 160, kRankDeep = 256;
 struct RankShared {
     uint32_t bin_n[2 * kRankBins];
     uint32_t split[kRankBins];  // first of a bin's parts, and their number's logarithm in 5 bits
     uint32_t wmax[kThreads / 64], wmin[kThreads / 64], wsum[kThreads / 64];
-    uint32_t cut;  // last bin that is wanted
+    uint32_t cut, above, within;  // last bin that is wanted, elements ahead of it and in it
 };
 
 // the range's top 11 bits number the bins
@@ -1362,15 +1364,69 @@ __device__ __forceinline__ void rank_range(RankShared &sh, uint32_t &top, uint32
     low = ~not_low;
 }
 
+// The bin that holds the `want`-th of the elements counted in bin_n, in descending order.
+__device__ __forceinline__ void rank_cut(RankShared &sh, uint32_t want)
+{
+    __syncthreads();
+    const uint2 n2 = *(const uint2 *)&sh.bin_n[2 * threadIdx.x];
+    uint32_t all;
+    const uint32_t upto = block_scan_inclusive<kThreads>(n2.x + n2.y, sh.wsum, all), before = upto - n2.x - n2.y;
+    if (before < want && want <= upto) {  // one thread
+        const bool second = before + n2.x < want;
+        sh.cut = 2 * threadIdx.x + (second ? 1u : 0u);
+        sh.above = second ? before + n2.x : before;
+        sh.within = second ? n2.y : n2.x;
+    }
+    __syncthreads();
+}
+
+// Of the keys in `have` the `want` best, and no more than `slack` others: 11 bits a pass of what the keys at the cut differ in, first
+// of their values, then of their elements.
+template <int PER, typename KEY>
+__device__ __forceinline__ uint32_t narrow(RankShared &sh, const KEY &key, uint32_t have, uint32_t want, uint32_t slack)
+{
+    uint32_t taken = 0;
+    bool by_value = true;
+    while (true) {
+        auto word = [&](int k) { return by_value ? (uint32_t)(key(k) >> 32) : (uint32_t)key(k); };
+        uint32_t top = 0, low = 0xFFFFFFFFu;
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if (have >> k & 1u) top = max(top, word(k)), low = min(low, word(k));
+        rank_range(sh, top, low);
+        if (by_value && top == low) {  // uniform: equal values
+            by_value = false;
+            __syncthreads();
+            continue;
+        }
+        const uint32_t shift = rank_shift(top, low);
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if (have >> k & 1u) atomicAdd(&sh.bin_n[(top - word(k)) >> shift], 1u);
+        rank_cut(sh, want);
+        const uint32_t cut = sh.cut;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const uint32_t bin = (top - word(k)) >> shift;
+            if ((have >> k & 1u) && bin < cut) taken |= 1u << k;
+            if (bin != cut) have &= ~(1u << k);
+        }
+        want -= sh.above;
+        if (sh.within - want <= slack) return taken | have;
+    }
+}
+
 template <int PER>
 __device__ bool rank_keys(RankShared &sh, uint64_t *srt, const uint64_t (&key)[PER], uint32_t have, uint32_t top, uint32_t low, uint32_t want,
                           uint32_t *ranked, uint32_t &all)
 {
     const uint32_t shift = rank_shift(top, low);
-    uint32_t place[PER];
+    uint32_t bin[PER], place[PER];
 #pragma unroll
-    for (int k = 0; k < PER; ++k)
-        if (have >> k & 1u) place[k] = atomicAdd(&sh.bin_n[(top - (uint32_t)(key[k] >> 32)) >> shift], 1u);
+    for (int k = 0; k < PER; ++k) {
+        bin[k] = (top - (uint32_t)(key[k] >> 32)) >> shift;
+        if (have >> k & 1u) place[k] = atomicAdd(&sh.bin_n[bin[k]], 1u);
+    }
     __syncthreads();
     // a bin's word: how many elements rank ahead of it, and its own number
     static_assert(PER * kThreads < 1 << 15, "15 bits a count");
@@ -1379,14 +1435,12 @@ __device__ bool rank_keys(RankShared &sh, uint64_t *srt, const uint64_t (&key)[P
     *(uint2 *)&sh.bin_n[2 * threadIdx.x] = make_uint2(before << 15 | n2.x, (before + n2.x) << 15 | n2.y);
     const bool crowd = __syncthreads_or((n2.x > kRankCrowd && before < want) || (n2.y > kRankCrowd && before + n2.x < want));
     const bool split = crowd && shift;
-    auto bin_of = [&](uint64_t x) {
-        const uint32_t d = top - (uint32_t)(x >> 32), b = d >> shift;
-        if (!split) return b;
-        const uint32_t w = sh.split[b], e = w & 31u;
+    auto part_of = [&](uint64_t x) {
+        const uint32_t d = top - (uint32_t)(x >> 32), w = sh.split[d >> shift], e = w & 31u;
         return (w >> 5) + ((d & ((1u << shift) - 1u)) >> (shift - e));
     };
     bool deep = false;
-    if (split) {  // uniform
+    if (__builtin_expect(split, 0)) {  // uniform
         // 2^e parts, about as many as a bin's elements are of the whole list's 2048ths
         auto parts = [&](uint32_t n) { return n ? min(31u - (uint32_t)__clz((int)max(n * (uint32_t)kRankBins / all, 1u)), shift) : 0u; };
         const uint32_t e0 = parts(n2.x), e1 = parts(n2.y), p0 = n2.x ? 1u << e0 : 0u, p1 = n2.y ? 1u << e1 : 0u;
@@ -1396,8 +1450,10 @@ __device__ bool rank_keys(RankShared &sh, uint64_t *srt, const uint64_t (&key)[P
         *(uint4 *)&sh.bin_n[4 * threadIdx.x] = make_uint4(0, 0, 0, 0);
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < PER; ++k)
-            if (have >> k & 1u) place[k] = atomicAdd(&sh.bin_n[bin_of(key[k])], 1u);
+        for (int k = 0; k < PER; ++k) {
+            bin[k] = part_of(key[k]);
+            if (have >> k & 1u) place[k] = atomicAdd(&sh.bin_n[bin[k]], 1u);
+        }
         __syncthreads();
         const uint4 n4 = *(const uint4 *)&sh.bin_n[4 * threadIdx.x];
         const uint32_t sum = n4.x + n4.y + n4.z + n4.w, b0 = block_scan_inclusive<kThreads>(sum, sh.wsum, all) - sum;
@@ -1410,13 +1466,13 @@ __device__ bool rank_keys(RankShared &sh, uint64_t *srt, const uint64_t (&key)[P
     }
 #pragma unroll
     for (int k = 0; k < PER; ++k)
-        if (have >> k & 1u) srt[(sh.bin_n[bin_of(key[k])] >> 15) + place[k]] = key[k];
+        if (have >> k & 1u) srt[(sh.bin_n[bin[k]] >> 15) + place[k]] = key[k];
     __syncthreads();
     if (deep) return false;
     // neighbouring threads, neighbouring places: a deep bin is the work of the few wavefronts that hold it, from one address
     for (uint32_t x = threadIdx.x; x < all; x += kThreads) {
         const uint64_t mine = srt[x];
-        const uint32_t at = sh.bin_n[bin_of(mine)], first = at >> 15, n = at & 32767u;
+        const uint32_t at = sh.bin_n[split ? part_of(mine) : (top - (uint32_t)(mine >> 32)) >> shift], first = at >> 15, n = at & 32767u;
         if (first >= want) break;  // (so are those behind it)
         uint32_t rank = first;
 #pragma unroll 8
@@ -1505,8 +1561,7 @@ __global__ __launch_bounds__(kThreads) void refine(const SelCtrl *ctrl, uint64_t
 // lie in the list from c * size on.
 constexpr int kShortParts = 64;  // most parts
 static_assert(kShortParts <= kAvgBins, "their counts lie where the histograms do otherwise");
-__global__ __launch_bounds__(kThreads) void refine_parts(const SelParams prm, uint32_t size, const uint32_t *part_n, uint64_t *cand, uint64_t *tie,
-                                                         uint32_t sort_n)
+__global__ __launch_bounds__(kThreads) void refine_parts(const SelParams prm, uint32_t size, const uint32_t *part_n, uint64_t *cand, const uint64_t *tie)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ __align__(16) RankShared sh;
@@ -1524,7 +1579,7 @@ __global__ __launch_bounds__(kThreads) void refine_parts(const SelParams prm, ui
     const uint64_t *list = tie + prm.tie_off[j];
     uint64_t *cand_j = cand + (size_t)j * kCandCap;
     uint32_t *ranked = (uint32_t *)cand_j;
-    uint32_t nA = part_at[kShortParts];
+    const uint32_t total = part_at[kShortParts];  // kSortLarge at most
     uint32_t half = 1;  // of a power of two of parts
     while (2 * half < parts) half *= 2;
     auto by_counting = [&](auto per_tag) {
@@ -1534,39 +1589,33 @@ __global__ __launch_bounds__(kThreads) void refine_parts(const SelParams prm, ui
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             c[k] = 0;
-            have |= threadIdx.x + k * kThreads < nA ? 1u << k : 0u;
+            have |= threadIdx.x + k * kThreads < total ? 1u << k : 0u;
         }
         for (uint32_t step = half; step; step >>= 1) {  // the parts they are in
 #pragma unroll
-            for (int k = 0; k < PER; ++k) c[k] += part_at[c[k] + step] <= min(threadIdx.x + k * kThreads, nA - 1) ? step : 0u;
+            for (int k = 0; k < PER; ++k) c[k] += part_at[c[k] + step] <= min(threadIdx.x + k * kThreads, total - 1) ? step : 0u;
         }
 #pragma unroll
-        for (int k = 0; k < PER; ++k) key[k] = list[min(threadIdx.x + k * kThreads, nA - 1) - part_at[c[k]] + c[k] * size];
+        for (int k = 0; k < PER; ++k) key[k] = list[min(threadIdx.x + k * kThreads, total - 1) - part_at[c[k]] + c[k] * size];
 #pragma unroll
         for (int k = 0; k < PER; ++k) top = max(top, (uint32_t)(key[k] >> 32)), low = min(low, (uint32_t)(key[k] >> 32));
         rank_range(sh, top, low);
-        return rank_keys(sh, srt, key, have, top, low, want, ranked, all);
+        if (rank_keys(sh, srt, key, have, top, low, want, ranked, all)) return;
+        // many equal averages
+        const uint32_t subset = narrow<PER>(sh, [&](int k) { return key[k]; }, have, want, 0);
+        rank_range(sh, top, low);
+        if (!rank_keys(sh, srt, key, subset, top, low, want, ranked, all)) rank_network(srt, all, want, ranked);
     };
-    if (nA <= kSortLarge && (nA <= kSortSmall ? by_counting(std::integral_constant<int, (int)kSortSmall / kThreads>{})
-                                              : by_counting(std::integral_constant<int, (int)kSortLarge / kThreads>{})))
-        return;
-    // (many equal averages: put together, shortened, and to the network)
-    uint64_t *B = tie + prm.tie_off[j], *A = B + len;
-    for (uint32_t c = 0; c < parts; ++c)
-        for (uint32_t i = threadIdx.x; i < part_at[c + 1] - part_at[c]; i += kThreads) store_u64(&A[part_at[c] + i], list[i + (size_t)c * size]);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    uint32_t need = want, candn = 0;
-    peel<kThreads>(A, B, nA, need, cand_j, candn, sort_n);
-    const uint32_t total = candn + nA;
-    for (uint32_t i = threadIdx.x; i < total; i += kThreads) srt[i] = i < candn ? load_u64(&cand_j[i]) : load_u64(&A[i - candn]);
-    rank_network(srt, total, want, ranked);
+    if (total <= kSortSmall)
+        by_counting(std::integral_constant<int, (int)kSortSmall / kThreads>{});
+    else
+        by_counting(std::integral_constant<int, (int)kSortLarge / kThreads>{});
 }
 
 // Printed form, few windows: the cut of a combination is not looked for by all workgroups over all windows but by one, or by one
 // for each part of the cells.  It pools the cells into LDS, sums the windows (four neighbouring ones a thread, from
 // 16-byte reads; in the order of the definition), finds the cut with a histogram over the range of the sums' keys, and ranks what
-// reaches it; a part's elements are left for refine_parts.  Where few are wanted only the largest of a thread's four neighbours is
+// reaches it; a part's elements are left for refine_parts.  Equal sums are narrowed down by their places before that.  Where few are wanted only the largest of a thread's four neighbours is
 // counted: the K_j-th best of those is at most the K_j-th best of all.
 // Bound: latency (one round of loads, a dozen barriers); a workgroup a combination and 4096 windows share nothing, so that the
 // number of windows decides, see the launch.  Against sel_init, both passes over the averages and refine (kernel trace, 48
@@ -1581,7 +1630,7 @@ constexpr size_t short_lds(uint32_t len, int n_top, bool ranks)
     return std::max(keys * sizeof(uint64_t), cells * sizeof(float));
 }
 template <int QUADS, bool PARTS>
-__global__ __launch_bounds__(kThreads) void rank_short(const SelParams prm, uint64_t *cand, uint64_t *tie, uint32_t *part_n)
+__global__ __launch_bounds__(kThreads, PARTS ? 8 : 4) void rank_short(const SelParams prm, uint32_t slack, uint64_t *cand, uint64_t *tie, uint32_t *part_n)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ __align__(16) RankShared sh;
@@ -1628,8 +1677,9 @@ __global__ __launch_bounds__(kThreads) void rank_short(const SelParams prm, uint
         pool(integral_constant<int, 0>{});
     __syncthreads();
     const float size = (float)n, rcp = __fdiv_rn(1.0f, size);
-    uint64_t key[PER];
+    uint32_t value[PER];  // ordered
     uint32_t have = 0, best[QUADS];
+    auto key = [&](int k) { return (uint64_t)value[k] << 32 | (0xFFFFFFFFu - (first + 4 * (tid + k / 4 * kThreads) + k % 4)); };  // as make_key
 #pragma unroll
     for (int q = 0; q < QUADS; ++q) {
         const uint32_t el = 4 * (tid + q * kThreads);
@@ -1655,78 +1705,52 @@ __global__ __launch_bounds__(kThreads) void rank_short(const SelParams prm, uint
         best[q] = 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            key[4 * q + i] = make_key(divide_small(sum[i], size, rcp), first + el + i);
+            value[4 * q + i] = ordered_bits(divide_small(sum[i], size, rcp));
             if (el + i < len) {
                 have |= 1u << (4 * q + i);
-                best[q] = max(best[q], (uint32_t)(key[4 * q + i] >> 32));
+                best[q] = max(best[q], value[4 * q + i]);
             }
         }
     }
-    // the bin that holds the K_j-th best, of all or of the best of each four
-    const bool fours = 2 * want <= (len + 3) / 4;  // uniform
-    uint32_t top = 0, low = 0xFFFFFFFFu;
+    uint32_t subset = have;
+    bool many = true;
+    if (2 * want <= (len + 3) / 4) {  // uniform: down to the bin that holds the K_j-th of the best of each four
+        uint32_t top = 0, low = 0xFFFFFFFFu;
 #pragma unroll
-    for (int q = 0; q < QUADS; ++q) {
-        if ((have >> (4 * q) & 1u) == 0) continue;
-        top = max(top, best[q]);
-        if (fours) low = min(low, best[q]);
-    }
-    if (!fours) {
-#pragma unroll
-        for (int k = 0; k < PER; ++k)
-            if (have >> k & 1u) low = min(low, (uint32_t)(key[k] >> 32));
-    }
-    rank_range(sh, top, low);
-    uint32_t shift = rank_shift(top, low);
-    if (fours) {
+        for (int q = 0; q < QUADS; ++q)
+            if (have >> (4 * q) & 1u) top = max(top, best[q]), low = min(low, best[q]);
+        rank_range(sh, top, low);
+        const uint32_t shift = rank_shift(top, low);
 #pragma unroll
         for (int q = 0; q < QUADS; ++q)
             if (have >> (4 * q) & 1u) atomicAdd(&sh.bin_n[(top - best[q]) >> shift], 1u);
-    } else {
-#pragma unroll
-        for (int k = 0; k < PER; ++k)
-            if (have >> k & 1u) atomicAdd(&sh.bin_n[(top - (uint32_t)(key[k] >> 32)) >> shift], 1u);
-    }
-    // the elements down to the bin that holds the K_j-th best, and the least of their keys
-    uint32_t subset = have, sub_low;
-    auto cut_off = [&]() __attribute__((always_inline)) {
-        __syncthreads();
-        const uint2 n2 = *(const uint2 *)&sh.bin_n[2 * tid];
-        uint32_t all;
-        const uint32_t upto = block_scan_inclusive<kThreads>(n2.x + n2.y, sh.wsum, all), before = upto - n2.x - n2.y;
-        if (before < want && want <= upto) sh.cut = 2 * tid + (before + n2.x < want ? 1u : 0u);  // one thread
-        __syncthreads();
+        rank_cut(sh, want);
         const uint32_t cut = sh.cut;
-        sub_low = 0xFFFFFFFFu;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const uint32_t v = (uint32_t)(key[k] >> 32);
-            if ((top - v) >> shift > cut) subset &= ~(1u << k);
-            if (subset >> k & 1u) sub_low = min(sub_low, v);
-        }
-    };
-    cut_off();
-    rank_range(sh, top, sub_low);
-    if (!PARTS) {
-        uint64_t *srt = (uint64_t *)smem;
-        uint32_t *ranked = (uint32_t *)(cand + (size_t)j * kCandCap);
-        uint32_t total = 0;
-        if (!rank_keys(sh, srt, key, subset, top, sub_low, want, ranked, total)) rank_network(srt, total, want, ranked);
-        return;
-    }
-    if (fours) {  // uniform: once more, all of them
-        shift = rank_shift(top, sub_low);
+        many = PARTS || sh.above + sh.within > want + slack;
 #pragma unroll
         for (int k = 0; k < PER; ++k)
-            if (subset >> k & 1u) atomicAdd(&sh.bin_n[(top - (uint32_t)(key[k] >> 32)) >> shift], 1u);
-        cut_off();
+            if ((top - value[k]) >> shift > cut) subset &= ~(1u << k);
+    }
+    if (many) subset = narrow<PER>(sh, key, subset, want, slack);
+    if (!PARTS) {
+        uint32_t top = 0, low = 0xFFFFFFFFu, total;
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if (subset >> k & 1u) top = max(top, value[k]), low = min(low, value[k]);
+        rank_range(sh, top, low);
+        uint64_t *srt = (uint64_t *)smem, keys[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) keys[k] = key(k);
+        uint32_t *ranked = (uint32_t *)(cand + (size_t)j * kCandCap);
+        if (!rank_keys(sh, srt, keys, subset, top, low, want, ranked, total)) rank_network(srt, total, want, ranked);
+        return;
     }
     uint32_t total;
     const uint32_t mine = (uint32_t)__popc(subset);
     uint64_t *at = tie + prm.tie_off[j] + first + (block_scan_inclusive<kThreads>(mine, sh.wsum, total) - mine);
 #pragma unroll
     for (int k = 0; k < PER; ++k)
-        if (subset >> k & 1u) *at++ = key[k];
+        if (subset >> k & 1u) *at++ = key(k);
     if (tid == 0) part_n[j * kShortParts + blockIdx.x] = total;
 }
 
@@ -2899,7 +2923,8 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
         quads = len_max <= 4 * kThreads ? 1 : len_max <= 8 * kThreads ? 2 : 4;
     } else if (brief) {
         for (int q = 1; q <= 2 && !quads; q *= 2)
-            if (windows <= (q << 21) && shared_by(len_max, q) <= kShortParts && 9 * shared_by(len_max, q) * most <= 8 * (int64_t)kSortLarge) quads = q;
+            if (windows <= (q << 21) && shared_by(len_max, q) <= kShortParts && shared_by(len_max, q) * (most + most / 8 + 32) <= (int64_t)kSortLarge)
+                quads = q;
         parts = quads != 0;
     }
     if (quads) {
@@ -2907,14 +2932,13 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
         prm.src = scores;
         if (!parts) {
             auto kernel = quads == 1 ? rank_short<1, false> : quads == 2 ? rank_short<2, false> : rank_short<4, false>;
-            hipLaunchKernelGGL(kernel, dim3(1, n), dim3(kThreads), short_lds((uint32_t)len_max, n_top, true), s, prm, cand, tie, hist);
+            hipLaunchKernelGGL(kernel, dim3(1, n), dim3(kThreads), short_lds((uint32_t)len_max, n_top, true), s, prm, 1024u, cand, tie, hist);
         } else {
             const uint32_t size = (uint32_t)quads * 4 * kThreads;
             auto kernel = quads == 1 ? rank_short<1, true> : rank_short<2, true>;
-            hipLaunchKernelGGL(kernel, dim3((unsigned)shared_by(len_max, quads), n), dim3(kThreads), short_lds(size, n_top, false), s, prm, cand, tie, hist);
-            const uint32_t sort_most = std::max(sort_n, 2 * kSortSmall);
-            hipLaunchKernelGGL(refine_parts, dim3(n), dim3(kThreads), (size_t)std::max(sort_most, kSortLarge) * sizeof(uint64_t), s, prm, size, hist,
-                               cand, tie, sort_most);
+            const uint32_t by = (uint32_t)shared_by(len_max, quads);
+            hipLaunchKernelGGL(kernel, dim3(by, n), dim3(kThreads), short_lds(size, n_top, false), s, prm, kSortLarge / by - most, cand, tie, hist);
+            hipLaunchKernelGGL(refine_parts, dim3(n), dim3(kThreads), (size_t)kSortLarge * sizeof(uint64_t), s, prm, size, hist, cand, tie);
         }
     } else {
         if (ap.pooled) {
