@@ -48,6 +48,7 @@
 //                interval [max(u-r, a+r+1), min(u+r, b-r-1)]; their pooled value is u's score.  Seeds in rank
 //                order, each interval ascending, is the kernel size's ranked token list: the walk takes the
 //                intervals as they are, no list is written
+//   select_brief short contexts: one workgroup does all of that in one launch
 //
 // Long contexts in the window-max form (L >= 4M and >= 1024 tokens per budgeted token) start with a
 // pruning pre-pass: the maximum of every fine chunk (one streaming read of the scores), the bin that
@@ -2020,10 +2021,10 @@ __device__ __forceinline__ void emit_bitmap(const WalkArgs &a, const uint32_t *m
     if (tid == 0 && a.out_count) *a.out_count = a.sink + (int32_t)nsel;
 }
 
-template <int ITEMS, bool HASHED>
-__global__ __launch_bounds__(kWalkThreads) void allocate_walk(const WalkArgs a)
+// `load` gives a thread its seeds of a pass; there are `nseeds`, in PASSES passes at most.
+template <int ITEMS, bool HASHED, int PASSES, typename LOAD>
+__device__ __forceinline__ void walk_items(const WalkArgs &a, unsigned char *smem, uint32_t nseeds, const LOAD &load)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t wsum[2][kWalkWaves], wlen[kWalkWaves];
     __shared__ uint32_t chunk_n[kBitmapChunks];
     constexpr bool SEEDS = ITEMS == kWalkSeeds;
@@ -2037,19 +2038,17 @@ __global__ __launch_bounds__(kWalkThreads) void allocate_walk(const WalkArgs a)
     auto of = [](uint32_t x, int j) { return (uint32_t)__builtin_amdgcn_readlane((int)x, j); };
 
     // The seeds serve every kernel size: a thread keeps the ones it looks at in registers.
-    uint32_t seed[SEEDS ? kWalkPasses : 1][kWalkPer], dom[SEEDS ? kWalkPasses : 1][kWalkPer];
-    uint32_t nseeds = 0;
+    uint32_t seed[SEEDS ? PASSES : 1][kWalkPer], dom[SEEDS ? PASSES : 1][kWalkPer];
     if (SEEDS) {
-        nseeds = seed_count(*a.seeds);
 #pragma unroll
-        for (int p = 0; p < kWalkPasses; ++p) {
-            const int r2 = p * kWalkThreads + tid;
-            const uint2 x = ((const uint2 *)a.pos)[r2], d = ((const uint2 *)a.dom)[r2];
+        for (int p = 0; p < PASSES; ++p) {
+            uint2 x, d;
+            load(p * kWalkThreads + tid, x, d);
             seed[p][0] = x.x, seed[p][1] = x.y;
             dom[p][0] = d.x, dom[p][1] = d.y;
         }
 #pragma unroll
-        for (int p = 0; p < kWalkPasses; ++p)
+        for (int p = 0; p < PASSES; ++p)
 #pragma unroll
             for (int i = 0; i < kWalkPer; ++i)
                 if ((uint32_t)((p * kWalkThreads + tid) * kWalkPer + i) >= nseeds) seed[p][i] = dom[p][i] = 0;  // owns nothing at any radius
@@ -2248,7 +2247,7 @@ __global__ __launch_bounds__(kWalkThreads) void allocate_walk(const WalkArgs a)
         for (int j = 0; j < a.n; ++j) {
             start(j);
 #pragma unroll
-            for (int p = 0; p < kWalkPasses; ++p)
+            for (int p = 0; p < PASSES; ++p)
                 if (taken < share && (uint32_t)(p * kWalkSpan) < nseeds) pass(0, 0, seed[p], dom[p]);
             nsel += taken;
             lds_barrier();  // the set is complete before the next kernel size counts in it
@@ -2282,6 +2281,16 @@ __global__ __launch_bounds__(kWalkThreads) void allocate_walk(const WalkArgs a)
     }
 
     emit_bitmap(a, set.mask, (uint16_t *)ring, chunk_n, nsel);
+}
+
+template <int ITEMS, bool HASHED>
+__global__ __launch_bounds__(kWalkThreads) void allocate_walk(const WalkArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    walk_items<ITEMS, HASHED, kWalkPasses>(a, smem, ITEMS == kWalkSeeds ? seed_count(*a.seeds) : 0u, [&](int r2, uint2 &x, uint2 &d) {
+        x = ((const uint2 *)a.pos)[r2];
+        d = ((const uint2 *)a.dom)[r2];
+    });
 }
 
 // The same walk where many combinations share the budget: the wavefronts take turns, a combination each, and nothing but the
@@ -2524,6 +2533,125 @@ __global__ __launch_bounds__(kSeedRankThreads) void seed_rank(const float *score
     }
 }
 
+// Window-max form, short contexts: the whole selection in one launch of one workgroup, with the last scoring step where it is
+// fused (as in reduce_count).  The scores' keys stay in registers and in LDS: the seeds are cut and ranked there, a
+// thread a seed looks for its outranking neighbours, eight wavefronts walk.
+// Bound: latency (loads, a few dozen barriers), where the launches it replaces each start with memory round trips of their own.
+// Measured (whole calls, budget a quarter of the tokens at most): selection alone 4096 tokens, budget 256 28.3 -> 15 us, 16384, 256
+// 28.3 -> 21, 16384, 2048 29.6 -> 28.2; in a recall 1000 tokens 29.6 -> 23.9 us, 4096 41.8 -> 32.7, 8192, budget 2000 46.7 -> 44.5, and
+// 16384 50.4 -> 57.8, which is why a recall's limit is lower.  One compute unit adds up 8 vectors of 4096 partial scores in the time of a
+// launch (more are added up before it: 8 of 8192 45.9 -> 44.5 us).
+constexpr int kBriefTokens = 16384, kBriefFused = 8192, kBriefSeeds = 2048, kBriefReach = 64;
+constexpr int64_t kBriefPartial = 32768;  // partial scores that the one workgroup adds up itself
+constexpr int kBriefSpare = 1024;  // seeds' keys beyond the wanted ones that may be sorted with them
+constexpr size_t brief_lds(int64_t len)
+{
+    const size_t bitmap = ((size_t)len + 32 * kBitmapChunk - 1) / (32 * kBitmapChunk) * kBitmapChunk * 4;
+    return bitmap + kRingBytes + 2 * kBriefSeeds * 4 + 2 * kBriefSeeds * 8 + (size_t)len * 4;
+}
+template <int PER>
+__global__ __launch_bounds__(kThreads) void select_brief(const float *partial, int nunits, int rmax, float *score, const float *body, int sink, uint32_t want,
+                                                         int reach, const WalkArgs w)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ __align__(16) RankShared sh;
+    static_assert(kBriefSeeds + kBriefSpare <= 2 * kBriefSeeds, "the keys fit");
+    const int tid = threadIdx.x;
+    const uint32_t len = w.len, bitmap = (len + 32 * kBitmapChunk - 1) / (32 * kBitmapChunk) * kBitmapChunk;
+    uint32_t *ranked = (uint32_t *)smem + bitmap + kRingBytes / 4, *dom = ranked + kBriefSeeds;
+    uint64_t *srt = (uint64_t *)(dom + kBriefSeeds);
+    uint32_t *bits = (uint32_t *)(srt + 2 * kBriefSeeds);  // every token's ordered score
+    uint32_t value[PER], have = 0;
+    float v[PER];
+    if (partial) {  // uniform
+        const uint32_t L = len + (uint32_t)sink;
+        constexpr int kUnits = 64 / PER < 16 ? 64 / PER : 16;  // units whose loads are in flight together
+        for (int u0 = 0; u0 < nunits; u0 += kUnits) {
+            float x[kUnits][PER];
+#pragma unroll
+            for (int uu = 0; uu < kUnits; ++uu)
+#pragma unroll
+                for (int k = 0; k < PER; ++k)
+                    x[uu][k] = partial[(size_t)(u0 + uu < nunits ? u0 + uu : nunits - 1) * L + min((uint32_t)(tid + k * kThreads), L - 1)];
+#pragma unroll
+            for (int uu = 0; uu < kUnits; ++uu) {
+                if (u0 + uu >= nunits) break;  // uniform
+#pragma unroll
+                for (int k = 0; k < PER; ++k) v[k] = u0 + uu == 0 ? x[uu][k] : (rmax ? fmaxf(v[k], x[uu][k]) : v[k] + x[uu][k]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if ((uint32_t)(tid + k * kThreads) < L) score[tid + k * kThreads] = v[k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < PER; ++k) v[k] = body[min((uint32_t)(tid + k * kThreads), len - 1)];
+    }
+    const int first = tid - (partial ? sink : 0);  // token of the body
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int t = first + k * kThreads;
+        value[k] = ordered_bits(v[k]);
+        if (t >= 0 && t < (int)len) {
+            bits[t] = value[k];
+            have |= 1u << k;
+        }
+    }
+    auto key = [&](int k) { return (uint64_t)value[k] << 32 | (0xFFFFFFFFu - (uint32_t)(first + k * kThreads)); };  // as make_key
+    const uint32_t subset = narrow<PER>(sh, key, have, want, kBriefSpare);
+    uint32_t top = 0, low = 0xFFFFFFFFu, total;
+    uint64_t keys[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        keys[k] = key(k);
+        if (subset >> k & 1u) top = max(top, value[k]), low = min(low, value[k]);
+    }
+    rank_range(sh, top, low);
+    if (!rank_keys(sh, srt, keys, subset, top, low, want, ranked, total)) rank_network(srt, total, want, ranked);
+    __syncthreads();
+    // The distances to the nearest tokens that outrank a seed.  Those are seeds too: a thread goes through the seeds on either side,
+    // near ones first, by a bitmap of them (of the seed's own score only those before it outrank it).
+    uint32_t *seeds = (uint32_t *)smem;
+    for (uint32_t i = tid; i < bitmap; i += kThreads) seeds[i] = 0;
+    __syncthreads();
+    for (uint32_t r = tid; r < want; r += kThreads) atomicOr(&seeds[ranked[r] >> 5], 1u << (ranked[r] & 31));
+    __syncthreads();
+    for (uint32_t r = tid; r < want; r += kThreads) {
+        const uint32_t at = ranked[r], mine = bits[at], o = at & 31;
+        const int w = (int)(at >> 5);
+        auto word = [&](int i) { return (uint64_t)(i >= 0 && i < (int)bitmap ? seeds[max(min(i, (int)bitmap - 1), 0)] : 0u); };
+        const uint64_t here = word(w);
+        static_assert(kBriefReach <= 64, "a bit a token");
+        // bit 63: the token before, bit 0: the one behind
+        uint64_t l = (word(w - 1) << 32 | word(w - 2)) >> o | (o ? here << (64 - o) : 0ull);
+        uint64_t e = (word(w + 1) << 32 | here) >> (o + 1) | word(w + 2) << (63 - o);
+        l = reach ? l & ~0ull << (64 - reach) : 0ull;
+        e = reach ? e & ~0ull >> (64 - reach) : 0ull;
+        uint32_t left = kNoDom, right = kNoDom;
+        while (l | e) {
+            const uint32_t dl = l ? (uint32_t)__clzll((long long)l) + 1 : 0u, de = e ? (uint32_t)__ffsll((unsigned long long)e) : 0u;
+            const uint32_t vl = bits[at - dl], ve = bits[at + de];
+            if (dl) {
+                const bool found = vl >= mine;
+                left = found ? dl : left;
+                l = found ? 0ull : l & ~(1ull << (64 - dl));
+            }
+            if (de) {
+                const bool found = ve > mine;
+                right = found ? de : right;
+                e = found ? 0ull : e & (e - 1);
+            }
+        }
+        dom[r] = left | right << 16;
+    }
+    __syncthreads();
+    if (tid >= kWalkThreads) return;  // whole wavefronts; barriers count those that are left
+    walk_items<kWalkSeeds, false, kBriefSeeds / kWalkSpan>(w, smem, want, [&](int r2, uint2 &x, uint2 &d) {
+        x = ((const uint2 *)ranked)[r2];
+        d = ((const uint2 *)dom)[r2];
+    });
+}
+
 // Last line of Algorithm 1: the input IDs of the allocated tokens, C[I].  Unused index slots (-1) give -1.
 __global__ __launch_bounds__(kPoolThreads) void gather_ids_kernel(const int32_t *ids, int64_t L, const int32_t *idx, int n,
                                                                   int32_t *out)
@@ -2640,6 +2768,8 @@ hipError_t set_select_attributes()
         for (const void *rank : {(const void *)rank_short<1, false>, (const void *)rank_short<2, false>, (const void *)rank_short<4, false>,
                                  (const void *)rank_short<1, true>, (const void *)rank_short<2, true>})
             if ((e = hipFuncSetAttribute(rank, hipFuncAttributeMaxDynamicSharedMemorySize, (int)short_lds(kShortCells, kShortAvg, true))) != hipSuccess) return e;
+        for (const void *brief : {(const void *)select_brief<4>, (const void *)select_brief<8>, (const void *)select_brief<16>})
+            if ((e = hipFuncSetAttribute(brief, hipFuncAttributeMaxDynamicSharedMemorySize, (int)brief_lds(kBriefTokens))) != hipSuccess) return e;
         for (const void *rank : {(const void *)refine, (const void *)refine_parts})
             if ((e = hipFuncSetAttribute(rank, hipFuncAttributeMaxDynamicSharedMemorySize, kSortLdsMax)) != hipSuccess) return e;
         if ((e = hipFuncSetAttribute((const void *)seed_rank, hipFuncAttributeMaxDynamicSharedMemorySize, kSeedRankLds)) != hipSuccess) return e;
@@ -2694,6 +2824,14 @@ bool prunes(int64_t L, int n_out)
     return nfine >= 4 * (int64_t)n_out && nfine >= 16384;
 }
 
+// Whether one launch does a whole window-max selection, of scores that are there or still lie in partial vectors.
+bool in_brief(const SelectJob &job, bool fused)
+{
+    bool yes = job.L > 0 && job.L + job.sink <= (fused ? kBriefFused : kBriefTokens) && std::min<int64_t>(job.budget, job.L) <= kBriefSeeds;
+    for (int j = 0; j < job.n_max; ++j) yes = yes && job.max_kernels[j] - 1 <= kBriefReach;
+    return yes;
+}
+
 // Window-max form: the seeds (best raw scores), their ranks and neighbours, the walk.
 hipError_t launch_select_window(const float *scores, const SelectJob &job, int32_t *out_idx, int32_t *out_count,
                                 unsigned char *ws, const SelectLayout &lay, hipStream_t s, const FusedScores *fused)
@@ -2721,6 +2859,24 @@ hipError_t launch_select_window(const float *scores, const SelectJob &job, int32
     walk.seeds = st;
     walk.pos = by_rank;
     walk.dom = dom;
+
+    if (in_brief(job, fused != nullptr)) {
+        const int64_t tokens = L + job.sink;
+        if (fused && fused->nunits * tokens > kBriefPartial) {
+            const hipError_t e = launch_reduce_units(fused->partial, fused->nunits, fused->L, fused->rmax, fused->scores, s);
+            if (e != hipSuccess) return e;
+            fused = nullptr;
+        }
+        walk.n_out = n_out;
+        walk.sink = job.sink;
+        walk.len = (uint32_t)L;
+        walk.out_idx = out_idx;
+        walk.out_count = out_count;
+        auto kernel = tokens <= 4 * kThreads ? select_brief<4> : tokens <= 8 * kThreads ? select_brief<8> : select_brief<16>;
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(kThreads), brief_lds(L), s, fused ? fused->partial : nullptr, fused ? fused->nunits : 0,
+                           fused ? fused->rmax : 0, fused ? fused->scores : nullptr, scores, job.sink, want, 2 * r_max, walk);
+        return hipGetLastError();
+    }
 
     const uint32_t nfine = (uint32_t)((L + kSelFine - 1) / kSelFine);
     Entries ent{nullptr, nullptr};
@@ -2792,7 +2948,7 @@ hipError_t launch_select_window(const float *scores, const SelectJob &job, int32
 ClearWords select_clear_words(const SelectJob &job, const SelectLayout &lay, void *base)
 {
     const int n_out = (int)(job.budget < job.L ? job.budget : job.L);
-    if (job.mode != kSelWindowMax || job.L == 0 || prunes(job.L, n_out)) return ClearWords{};
+    if (job.mode != kSelWindowMax || job.L == 0 || in_brief(job, true) || prunes(job.L, n_out)) return ClearWords{};
     return ClearWords{(uint32_t *)((unsigned char *)base + lay.state), (uint32_t)(sizeof(SeedState) / sizeof(uint32_t))};
 }
 

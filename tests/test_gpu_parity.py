@@ -626,6 +626,51 @@ def test_walk_over_bitmap_and_word_table(L, sink, budget, windows, mk, ak):
     assert got_p[:n].tolist() == oracle.allocate_max_avg(s, mk, ak, budget, sink=sink).tolist() and (got_p[n:] == -1).all()
 
 
+BRIEF_CASES = [
+    # L, sink, budget, windows, kind: selections that one workgroup does (up to 16384 tokens, 2048 kept, windows of up to 65), at the edges
+    # of what its threads take and of the rule
+    (1, 0, 1, (1,), "random"), (2, 2, 1, (3,), "random"), (70, 0, 70, (65, 1), "random"), (1023, 1, 300, (3, 7, 15), "needles"), (1025, 0, 64, (65,), "equal"),
+    (4096, 0, 2048, (31, 3, 1), "few_values"), (4097, 0, 1025, (7,), "needles"), (8192, 0, 2048, (65, 63, 1), "random"), (8193, 4, 2047, (3, 7, 15, 31), "narrow"),
+    (16384, 0, 2048, (1, 3, 7, 15, 31), "needles"), (16384, 1, 2048, (65,), "two_values"), (16385, 0, 2048, (65,), "random"), (16380, 4, 2049, (3,), "random"),
+    (9000, 0, 500, (67, 3), "random"), (5000, 0, 2000, (5, 5, 5), "equal"), (12000, 3, 900, (3, 33), "outliers"), (16000, 0, 1500, (1, 3), "denormal"),
+    (6000, 2, 700, (9, 31), "signed"), (6000, 2, 2048, (9, 65), "half_zero"), (16384, 0, 2048, (3, 31), "one_far"), (7000, 0, 40, tuple(range(1, 65, 2)) * 2, "flat"),
+]
+
+
+@pytest.mark.parametrize("L,sink,budget,windows,kind", BRIEF_CASES, ids=[f"L{c[0]}_B{c[2]}_{c[4]}" for c in BRIEF_CASES])
+def test_short_selections_in_one_launch(L, sink, budget, windows, kind):
+    _announce(f"short selection L={L} sink={sink} budget={budget} {kind}")
+    rng = np.random.default_rng(L + budget)
+    if kind == "one_far":
+        s = (1.0 + 0.01 * rng.random(L)).astype(np.float32)
+        s[L // 3] = 1e30
+    elif kind in ("random", "few_values", "two_values", "equal", "narrow", "needles"):
+        s = _scores_for(kind, L, rng)
+    else:
+        s = _any_scores(kind, L, rng)
+    got = il.ilre_select(torch.from_numpy(s).cuda(), budget, windows, sink=sink)
+    torch.cuda.synchronize()
+    assert got.cpu().numpy().tolist() == oracle.allocate(s, windows, budget, sink=sink).tolist()
+
+
+@pytest.mark.parametrize("mode", [il.ILRE_SCORE_SUM, il.ILRE_SCORE_MAX], ids=["sum", "max"])
+@pytest.mark.parametrize("L,Lq,Hq,Hkv,sink", [(5, 1, 2, 2, 0), (1000, 8, 8, 2, 3), (4096, 16, 32, 8, 0), (4097, 8, 32, 8, 1), (8192, 16, 16, 4, 0), (8193, 8, 8, 2, 0), (3000, 200, 64, 8, 2)])
+def test_short_recalls_add_up_their_partial_scores(L, Lq, Hq, Hkv, sink, mode):
+    """The whole path up to 8192 tokens: one workgroup adds up the partial score vectors (or, of many, a kernel before it): the
+    same scores as from the staged call, and the oracle's indices for them."""
+    _announce(f"short recall L={L} Lq={Lq} {Hq}/{Hkv} sink={sink}")
+    inp = inputs.custom(L=L, Lq=Lq, Hq=Hq, Hkv=Hkv, d=128, dtype="bf16", n_spans=2 if L > 200 else 0, span_len=(8, 24), channel_scale=True, seed=L)
+    q, k = to_device(inp.q), to_device(inp.k)
+    budget = max(1, L // 5)
+    idx, scores = il.ilre_recall(q, k, budget, (3, 7, 15), score_mode=mode, sink=sink)
+    row_max, row_sum = il.ilre_row_stats(q, k)
+    staged = il.ilre_col_scores(q, k, row_max, row_sum, score_mode=mode)
+    torch.cuda.synchronize()
+    scores = scores.cpu().numpy()
+    np.testing.assert_allclose(scores, staged.cpu().numpy(), rtol=1e-6, atol=0)  # (the row offsets are merged elsewhere: an ulp of the exponent)
+    assert idx.cpu().numpy().tolist() == oracle.allocate(scores, (3, 7, 15), budget, sink=sink).tolist()
+
+
 SHORT_CASES = [
     # L, sink, budget, max sizes, average sizes, kind: combinations ranked by a workgroup each (up to 16384 cells, cells of up to 8 tokens,
     # windows of up to 64) or by one for each 4096 or 8192 cells, at the edges of what a thread, a workgroup and the rule take
