@@ -1,6 +1,7 @@
 // Scoring kernels of the token-recall path (paper Section 3.2, Eq. 4 and Eq. 5) for gfx950.
 //
-// Two passes over the key cache, both built on one MFMA skeleton:
+// Two passes over the key cache, both built on one MFMA skeleton (this is the one for bf16 states; the one for fp32 states,
+// score_f32_kernel, splits them into bf16 parts):
 //   pass 1 (MODE 0, row statistics)  S^T = K_tile . Q^T : tokens are the MFMA rows, query rows the
 //           columns, so each lane owns one query row and sees 16 tokens of it per 32x32 block; the
 //           running maximum and sum of exponentials of Eq. 4's softmax stay in that lane's registers.
@@ -19,6 +20,7 @@
 
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include <type_traits>
@@ -37,13 +39,9 @@ constexpr float kFrozenSumLimit = 1.0e30f;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
-template <int DT>
-struct Traits;
-
 // bf16: one 16-byte chunk holds 8 elements; v_mfma_f32_32x32x16_bf16 contracts 16 per issue
 // (lanes 0-31 supply k = 0..7, lanes 32-63 k = 8..15 of the same row).
-template <>
-struct Traits<ILRE_BF16> {
+struct Bf16 {
     static constexpr int kElemBytes = 2;
     static constexpr int kSteps = 8;
     static constexpr int kChunksPerRow = 16;
@@ -53,24 +51,6 @@ struct Traits<ILRE_BF16> {
     {
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
                                                       acc, 0, 0, 0);
-    }
-};
-
-// fp32: one chunk holds 4 elements; v_mfma_f32_32x32x2_f32 contracts 2 per issue (lanes 0-31 supply
-// k = 0, lanes 32-63 k = 1).  Element j of both operands' chunks is contracted by issue j, which pairs
-// identical k on the A and B side whatever order the k are visited in.
-template <>
-struct Traits<ILRE_F32> {
-    static constexpr int kElemBytes = 4;
-    static constexpr int kSteps = 16;
-    static constexpr int kChunksPerRow = 32;
-    static constexpr int tile_tokens(int waves) { return 16 * waves; }
-    static __device__ __forceinline__ void mma(f32x16 &acc, const uint4 &a, const uint4 &b)
-    {
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
     }
 };
 
@@ -173,10 +153,10 @@ __device__ __forceinline__ float merged_offset(const float *pm, const float *pz,
 }
 
 // MODE 0: row statistics.  MODE 1: column scores (RMAX = 0 sum over rows, 1 max over rows).
-template <int DT, int NB, int WAVES, int MODE, int RMAX>
+template <int NB, int WAVES, int MODE, int RMAX>
 __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
 {
-    using T = Traits<DT>;
+    using T = Bf16;
     constexpr int ES = T::kElemBytes;
     constexpr int STEPS = T::kSteps;
     constexpr int TN = T::tile_tokens(WAVES);
@@ -495,11 +475,11 @@ __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
             // ask the scheduler for: one MFMA (group), a slice of the vector work, and a fragment
             // read after every NB-th MFMA
 #pragma unroll
-            for (int st = 0; st < 8; ++st) {
+            for (int st = 0; st < STEPS; ++st) {
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, DT == ILRE_BF16 ? 1 : STEPS / 2, 0);
-                    if (b == NB - 1) __builtin_amdgcn_sched_group_barrier(0x100, STEPS / 8, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    if (b == NB - 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                     __builtin_amdgcn_sched_group_barrier(0x002, (MODE == 0 && !FROZEN) ? 8 : 6, 0);
                 }
             }
@@ -578,6 +558,215 @@ __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
         if (timed) {
             const unsigned long long dt = wall_clock64() - t_begin;  // 10 ns ticks
             a.wg_time[blockIdx.x] = dt < 0xFFFFFFFFull ? (uint32_t)(dt ? dt : 1) : 0xFFFFFFFFu;
+        }
+    }
+}
+
+// ---------------------------------------------------------------- fp32 states
+//
+// The fp32 matrix instructions run at a sixteenth of the bf16 rate.  An fp32 number is the sum of three bf16 numbers, exactly
+// (24 bits of significand, 8 each: x = h + m + l with h cut off, m and l rounded), and a product of two such sums is the nine
+// products of their parts, each exact in fp32.  Six of them are taken, added up in fp32: what is left out (m l, l m and l l) is
+// 2^-26 of a product at most, less than the rounding of one addition.  The large products (h h) have an accumulator of their own and
+// the others two, so that a logit sees 8 roundings at its own size, where the fp32 instructions took 64.  (Splitting into parts:
+// Dekker, Numerische Mathematik 18 (1971); several low-precision products for one of high precision: Henry, Tang and Heinecke,
+// ARITH 2019.)
+//
+// A workgroup owns 128 query rows of a kv head, 32 a wavefront, whose parts stay in registers, and streams 32 tokens of K at a
+// time: a thread fetches 64 bytes a tile ahead, splits them and writes the three parts to LDS, chunks swizzled as above.  Two
+// workgroups a compute unit work in each other's shadow; the split is done once for four wavefronts.
+// Bound: 48 matrix instructions of 32 cycles for 32 x 32 logits (the fp32 instructions: 4096 cycles), 1.2 PFLOP/s of them on 32768 tokens
+// and 8192 rows, what the matrix pipe reaches beside such vector work.  Measured, whole recall, fp32 instructions -> so: 4096
+// tokens, 32/8 heads, 32 queries 62.9 -> 40.3 us; 32768 tokens, 256 queries 1107 -> 713 us.  Errors against 64 bits, logarithms of
+// the rows' sums: 4.1e-7 -> 3.0e-7 rms, 1.5e-6 -> 0.9e-6 largest; scores 2.4e-6 -> 1.1e-6 largest.  (The softmax arithmetic a tile
+// behind the matrix instructions, as in score_kernel: 3 % faster on 32768 tokens, 3 % slower on 4096.)
+constexpr int kF32Waves = 4, kF32Tokens = 32;
+constexpr int kF32Plane = kF32Tokens * 256, kF32Buffer = 3 * kF32Plane;  // bytes
+constexpr int kF32Parts = 2 * kF32Waves, kF32Pitch = kF32Tokens + 4;    // pass 2's partial column results, floats
+constexpr size_t kF32Lds = 2 * kF32Buffer + 2 * kF32Parts * kF32Pitch * sizeof(float);
+static_assert(2 * kF32Parts * kF32Pitch >= kF32Waves * 32, "holds the rows' offsets first");
+
+struct Parts {
+    uint4 h, m, l;
+};
+__device__ __forceinline__ Parts split3(const float4 &a, const float4 &b)
+{
+    typedef __attribute__((ext_vector_type(2))) float f32x2;
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    uint32_t h[4], m[4], l[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t x0 = __float_as_uint(x[2 * i]), x1 = __float_as_uint(x[2 * i + 1]);
+        h[i] = __builtin_amdgcn_perm(x1, x0, 0x07060302);  // the upper halves
+        const float r0 = x[2 * i] - __uint_as_float(x0 & 0xFFFF0000u), r1 = x[2 * i + 1] - __uint_as_float(x1 & 0xFFFF0000u);
+        m[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){r0, r1}, bf16x2));
+        const float l0 = r0 - __uint_as_float(m[i] << 16), l1 = r1 - __uint_as_float(m[i] & 0xFFFF0000u);
+        l[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){l0, l1}, bf16x2));
+    }
+    return {make_uint4(h[0], h[1], h[2], h[3]), make_uint4(m[0], m[1], m[2], m[3]), make_uint4(l[0], l[1], l[2], l[3])};
+}
+
+template <int MODE, int RMAX>
+__global__ __launch_bounds__(kF32Waves * 64, 2) void score_f32_kernel(const ScoreArgs a)
+{
+    using T = Bf16;
+    constexpr int THREADS = kF32Waves * 64, ROWS = kF32Waves * 32, STEPS = 8;
+    constexpr int CHUNKS = kF32Tokens * 16 / THREADS;  // of 8 elements a thread fetches of a tile
+    extern __shared__ __align__(16) unsigned char smem[];
+    // workgroups that stream the same K range run on one XCD (see score_kernel)
+    const int xcd = blockIdx.x % kNumXCD, slot = blockIdx.x / kNumXCD, qb = slot % a.nqb;
+    const int64_t pair = (int64_t)(slot / a.nqb) * kNumXCD + xcd;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    if (MODE == 1 && blockIdx.x == 0)
+        for (uint32_t i = tid * 4; i < a.clear.n; i += THREADS * 4) *(uint4 *)&a.clear.at[i] = make_uint4(0, 0, 0, 0);
+    if (pair >= (int64_t)a.Hkv * a.nsplit) return;
+    const int g = (int)(pair / a.nsplit), split = (int)(pair % a.nsplit);
+    const int64_t tile0 = (int64_t)split * a.tiles_per_split;
+    const int64_t tile1 = tile0 + a.tiles_per_split < a.ntiles ? tile0 + a.tiles_per_split : a.ntiles;
+    if (tile0 >= tile1) return;
+    const int64_t nrows = (int64_t)a.Hq * a.Lq;
+    const int rl = qb * ROWS + wave * 32 + l32;  // the lane's query row in the group
+    float *red = (float *)(smem + 2 * kF32Buffer);  // [2][kF32Parts][kF32Pitch], pass 2 only
+
+    const unsigned char *kbase = (const unsigned char *)a.k + (int64_t)g * a.k_stride_head * 4;
+    auto first_token = [&](int64_t tile) { return (MODE == 1 ? tile0 + tile1 - 1 - tile : tile) * kF32Tokens; };
+    float4 raw[CHUNKS][2];
+    auto fetch = [&](int64_t tile) {
+#pragma unroll
+        for (int j = 0; j < CHUNKS; ++j) {
+            const int id = j * THREADS + tid;
+            const int64_t tok = first_token(tile) + (id >> 4);
+            const unsigned char *src = kbase + (tok < a.L ? tok : a.L - 1) * (a.k_stride_token * 4) + (id & 15) * 32;
+            raw[j][0] = *(const float4 *)src;
+            raw[j][1] = *(const float4 *)(src + 16);
+        }
+    };
+    auto stage = [&](int buf) {
+#pragma unroll
+        for (int j = 0; j < CHUNKS; ++j) {
+            const int id = j * THREADS + tid, row = id >> 4;
+            unsigned char *dst = smem + buf * kF32Buffer + row * 256 + ((id & 15) ^ (row & 15)) * 16;
+            const Parts x = split3(raw[j][0], raw[j][1]);
+            *(uint4 *)dst = x.h;
+            *(uint4 *)(dst + kF32Plane) = x.m;
+            *(uint4 *)(dst + 2 * kF32Plane) = x.l;
+        }
+    };
+    fetch(tile0);
+
+    Parts qf[STEPS];
+    {
+        const bool real = rl < a.rows_per_group;
+        const int at = real ? rl : 0, h = g * a.G + at / a.Lq, i = at % a.Lq;
+        const unsigned char *src = (const unsigned char *)a.q + ((int64_t)h * a.q_stride_head + (int64_t)i * a.q_stride_token) * 4;
+        float4 x[STEPS][2];
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) {
+            x[st][0] = *(const float4 *)(src + (st * 2 + half) * 32);
+            x[st][1] = *(const float4 *)(src + (st * 2 + half) * 32 + 16);
+        }
+        const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) qf[st] = split3(real ? x[st][0] : zero, real ? x[st][1] : zero);
+    }
+
+    float m = kNegBig, z[4] = {0.f, 0.f, 0.f, 0.f};  // pass 1
+    float noff[MODE == 1 ? 16 : 1];                  // pass 2, see score_kernel
+    if (MODE == 1) {
+        constexpr int SHARERS = THREADS / ROWS;
+        const int local = tid / SHARERS, r0 = qb * ROWS + local;
+        const bool real = r0 < a.rows_per_group;
+        const int64_t r = (int64_t)g * a.rows_per_group + (real ? r0 : a.rows_per_group - 1);
+        float off;
+        if (a.merge)
+            off = merged_offset<SHARERS>(a.part_m + r, a.part_z + r, a.nsplit, nrows, tid % SHARERS);
+        else
+            off = row_offset(a.row_max[r], a.row_sumexp[r]);
+        if (tid % SHARERS == 0) red[local] = real ? off : -INFINITY;
+    }
+    stage(0);
+    if (tile0 + 1 < tile1) fetch(tile0 + 1);
+    __syncthreads();
+    if (MODE == 1) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float4 x = *(const float4 *)&red[wave * 32 + 8 * j + 4 * half];
+            noff[4 * j] = x.x, noff[4 * j + 1] = x.y, noff[4 * j + 2] = x.z, noff[4 * j + 3] = x.w;
+        }
+        __syncthreads();  // the buffers are written from here on
+    }
+
+    unsigned frag[STEPS];
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) frag[st] = (unsigned)(l32 * 256 + (((2 * st + half) ^ (l32 & 15)) * 16));
+    const int unit = g * a.nqb + qb;
+    for (int64_t tile = tile0; tile < tile1; ++tile) {
+        const int buf = (int)(tile - tile0) & 1;
+        if (tile + 1 < tile1) {
+            stage(buf ^ 1);
+            if (tile + 2 < tile1) fetch(tile + 2);
+        }
+        f32x16 big, s1, s2;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) big[v] = s1[v] = s2[v] = 0.f;
+        const unsigned char *kb = smem + buf * kF32Buffer;
+        auto mma = [](f32x16 &acc, const uint4 &k, const uint4 &q) {
+            if (MODE == 0)
+                T::mma(acc, k, q);
+            else
+                T::mma(acc, q, k);
+        };
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) {
+            const uint4 kh = *(const uint4 *)(kb + frag[st]), km = *(const uint4 *)(kb + frag[st] + kF32Plane),
+                        kl = *(const uint4 *)(kb + frag[st] + 2 * kF32Plane);
+            mma(s1, kh, qf[st].l);
+            mma(s2, kl, qf[st].h);
+            mma(s1, km, qf[st].m);
+            mma(s2, km, qf[st].h);
+            mma(s1, kh, qf[st].m);
+            mma(big, kh, qf[st].h);
+        }
+        const int64_t tok0 = first_token(tile);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) big[v] += s1[v] + s2[v];
+        if (MODE == 0) {
+            if (tok0 + kF32Tokens > a.L)  // uniform
+                row_update<true>(big, a.c, m, z, tok0 + 4 * half, a.L);
+            else
+                row_update<false>(big, a.c, m, z, tok0 + 4 * half, a.L);
+        } else {
+            float p[4];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float e = fast_exp2(fmaf(big[v], a.c, noff[v]));
+                p[v & 3] = v < 4 ? e : RMAX ? fmaxf(p[v & 3], e) : p[v & 3] + e;
+            }
+            red[(buf * kF32Parts + wave * 2 + half) * kF32Pitch + l32] =
+                RMAX ? fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3])) : (p[0] + p[1]) + (p[2] + p[3]);
+        }
+        __syncthreads();
+        // the wavefronts' results of the tile's tokens, in a fixed order, by one of them
+        if (MODE == 1 && wave == (int)((tile - tile0) & 3) && half == 0) {
+            float x[kF32Parts];
+#pragma unroll
+            for (int i = 0; i < kF32Parts; ++i) x[i] = red[(buf * kF32Parts + i) * kF32Pitch + l32];
+#pragma unroll
+            for (int o = 1; o < kF32Parts; o <<= 1)
+#pragma unroll
+                for (int i = 0; i < kF32Parts; i += 2 * o) x[i] = RMAX ? fmaxf(x[i], x[i + o]) : x[i] + x[i + o];
+            if (tok0 + l32 < a.L) a.partial[(int64_t)unit * a.L + tok0 + l32] = x[0];
+        }
+    }
+    if (MODE == 0) {  // the half-waves saw disjoint tokens of the same rows
+        const float zb = (z[0] + z[1]) + (z[2] + z[3]);
+        const float mo = __shfl_xor(m, 32), zo = __shfl_xor(zb, 32), mm = fmaxf(m, mo);
+        const float zz = zb * fast_exp2(m - mm) + zo * fast_exp2(mo - mm);
+        if (half == 0 && rl < a.rows_per_group) {
+            const int64_t r = (int64_t)g * a.rows_per_group + rl;
+            a.part_m[(int64_t)split * nrows + r] = mm;
+            a.part_z[(int64_t)split * nrows + r] = zz;
         }
     }
 }
@@ -741,11 +930,7 @@ __global__ void reduce_units(const float *partial, int nunits, int64_t L, float 
     score[t] = acc;
 }
 
-template <int DT>
-constexpr size_t tile_lds_bytes(int waves)
-{
-    return 3 * (size_t)Traits<DT>::tile_tokens(waves) * (Traits<DT>::kChunksPerRow * 16);
-}
+constexpr size_t tile_lds_bytes(int waves) { return 3 * (size_t)Bf16::tile_tokens(waves) * (Bf16::kChunksPerRow * 16); }
 
 // The dynamic-LDS ceiling of a kernel is raised once per process (to the most any plan asks of it: the
 // 8-wavefront tiles plus the partial-result buffers of pass 2), not on every launch.
@@ -794,7 +979,7 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv)
         p.waves = pad4 < pad8 ? 4 : 8;
         p.nb = p.rows_per_group <= 128 ? 1 : 2;
     }
-    p.tile_tokens = dtype == ILRE_F32 ? Traits<ILRE_F32>::tile_tokens(p.waves) : Traits<ILRE_BF16>::tile_tokens(p.waves);
+    p.tile_tokens = dtype == ILRE_F32 ? kF32Tokens : Bf16::tile_tokens(p.waves);
     p.rows_per_wg = p.waves * p.nb * 32;
     p.nqb = (p.rows_per_group + p.rows_per_wg - 1) / p.rows_per_wg;
     p.ntiles = (L + p.tile_tokens - 1) / p.tile_tokens;
@@ -803,20 +988,26 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv)
     const int target = kNumCU * (p.waves == 8 ? 1 : 2);
     int64_t nsplit = (target + p.nunits / 2) / p.nunits;
     if (nsplit < 1) nsplit = 1;
-    if (nsplit > p.ntiles) nsplit = p.ntiles;
-    p.tiles_per_split = (p.ntiles + nsplit - 1) / nsplit;
+    const int64_t step = dtype == ILRE_F32 ? 2 : 1;  // a split's tiles come in twos there
+    nsplit = std::min(nsplit, (p.ntiles + step - 1) / step);
+    // few tiles: no more splits than pass 2 merges itself (4096 tokens, 32/8 heads, 32 queries 42.6 -> 40.3 us; with eight tiles 8192 tokens, 16/4
+    // heads, 16 queries 40.8 -> 49.7)
+    if (dtype == ILRE_F32 && nsplit > kMergeSplits && p.ntiles <= 4 * kMergeSplits) nsplit = kMergeSplits;
+    p.tiles_per_split = step * ((p.ntiles + step * nsplit - 1) / (step * nsplit));
     p.nsplit = (int)((p.ntiles + p.tiles_per_split - 1) / p.tiles_per_split);
     const int64_t pairs = (int64_t)Hkv * p.nsplit;
     p.grid = (int)(((pairs + kNumXCD - 1) / kNumXCD) * kNumXCD * p.nqb);
-    const size_t tiles = dtype == ILRE_F32 ? tile_lds_bytes<ILRE_F32>(p.waves) : tile_lds_bytes<ILRE_BF16>(p.waves);
     // pass 2's ranges follow the XCDs' speed where a range is long enough for that to matter
-    p.balanced = p.tiles_per_split >= 64 && p.nsplit >= kNumXCD && p.nsplit <= kMaxBalancedSplits;
+    p.balanced = dtype != ILRE_F32 && p.tiles_per_split >= 64 && p.nsplit >= kNumXCD && p.nsplit <= kMaxBalancedSplits;
     p.merge_in_cols = !p.balanced && p.nsplit <= kMergeSplits;
     uint64_t tag = 0x494c52652d584344ull;  // what a table has to have been made for
     for (uint64_t v : {(uint64_t)L, (uint64_t)p.ntiles, (uint64_t)p.nsplit, (uint64_t)p.nqb, (uint64_t)Hkv, (uint64_t)p.tile_tokens,
                        (uint64_t)p.grid})
         tag = (tag ^ v) * 0x9E3779B97F4A7C15ull + 0x7F4A7C15ull;
     p.table_tag = tag;
+    p.lds_bytes_stats = p.lds_bytes_cols = kF32Lds;
+    if (dtype == ILRE_F32) return p;
+    const size_t tiles = tile_lds_bytes(p.waves);
     p.lds_bytes_stats = tiles;
     p.lds_bytes_cols = tiles + 3 * 2 * (size_t)p.waves * (p.tile_tokens + 36) * sizeof(float);  // pitch <= tokens + 36
     return p;
@@ -830,13 +1021,13 @@ hipError_t launch_row_stats(const ScorePlan &p, const ScoreArgs &a, float *row_m
     const int64_t nrows = (int64_t)a.Hq * a.Lq;
     hipError_t e;
     if (p.dtype == ILRE_F32)
-        e = launch_score(score_kernel<ILRE_F32, 1, 4, 0, 0>, p.grid, 256, lds, a, s);
+        e = launch_score(score_f32_kernel<0, 0>, p.grid, kF32Waves * 64, lds, a, s);
     else if (p.nb == 1)
-        e = launch_score(score_kernel<ILRE_BF16, 1, 4, 0, 0>, p.grid, 256, lds, a, s);
+        e = launch_score(score_kernel<1, 4, 0, 0>, p.grid, 256, lds, a, s);
     else if (p.waves == 4)
-        e = launch_score(score_kernel<ILRE_BF16, 2, 4, 0, 0>, p.grid, 256, lds, a, s);
+        e = launch_score(score_kernel<2, 4, 0, 0>, p.grid, 256, lds, a, s);
     else
-        e = launch_score(score_kernel<ILRE_BF16, 2, 8, 0, 0>, p.grid, 512, lds, a, s);
+        e = launch_score(score_kernel<2, 8, 0, 0>, p.grid, 512, lds, a, s);
     if (e != hipSuccess) return e;
     if (a.merge) return hipSuccess;  // pass 2 takes the partials
     const bool balance = a.wg_time != nullptr && a.split_table != nullptr;
@@ -863,17 +1054,17 @@ hipError_t launch_col_scores(const ScorePlan &p, const ScoreArgs &a, int score_m
     const size_t lds = p.lds_bytes_cols;
     const bool mx = score_mode == ILRE_SCORE_MAX;
     if (p.dtype == ILRE_F32)
-        e = mx ? launch_score(score_kernel<ILRE_F32, 1, 4, 1, 1>, p.grid, 256, lds, a, s)
-               : launch_score(score_kernel<ILRE_F32, 1, 4, 1, 0>, p.grid, 256, lds, a, s);
+        e = mx ? launch_score(score_f32_kernel<1, 1>, p.grid, kF32Waves * 64, lds, a, s)
+               : launch_score(score_f32_kernel<1, 0>, p.grid, kF32Waves * 64, lds, a, s);
     else if (p.nb == 1)
-        e = mx ? launch_score(score_kernel<ILRE_BF16, 1, 4, 1, 1>, p.grid, 256, lds, a, s)
-               : launch_score(score_kernel<ILRE_BF16, 1, 4, 1, 0>, p.grid, 256, lds, a, s);
+        e = mx ? launch_score(score_kernel<1, 4, 1, 1>, p.grid, 256, lds, a, s)
+               : launch_score(score_kernel<1, 4, 1, 0>, p.grid, 256, lds, a, s);
     else if (p.waves == 4)
-        e = mx ? launch_score(score_kernel<ILRE_BF16, 2, 4, 1, 1>, p.grid, 256, lds, a, s)
-               : launch_score(score_kernel<ILRE_BF16, 2, 4, 1, 0>, p.grid, 256, lds, a, s);
+        e = mx ? launch_score(score_kernel<2, 4, 1, 1>, p.grid, 256, lds, a, s)
+               : launch_score(score_kernel<2, 4, 1, 0>, p.grid, 256, lds, a, s);
     else
-        e = mx ? launch_score(score_kernel<ILRE_BF16, 2, 8, 1, 1>, p.grid, 512, lds, a, s)
-               : launch_score(score_kernel<ILRE_BF16, 2, 8, 1, 0>, p.grid, 512, lds, a, s);
+        e = mx ? launch_score(score_kernel<2, 8, 1, 1>, p.grid, 512, lds, a, s)
+               : launch_score(score_kernel<2, 8, 1, 0>, p.grid, 512, lds, a, s);
     if (e != hipSuccess || !reduce) return e;
     return launch_reduce_units(a.partial, p.nunits, a.L, mx ? 1 : 0, out_scores, s);
 }

@@ -327,6 +327,34 @@ def _end_to_end(inp, kernels, budget):
     return idx, scores, rep
 
 
+@pytest.mark.parametrize("L,Lq,Hq,Hkv,spread", [(1, 1, 1, 1, 0), (31, 3, 2, 1, 0), (33, 33, 4, 1, 2), (64, 16, 8, 1, 0), (65, 129, 2, 2, 0), (1000, 8, 8, 2, 3),
+                                                (4097, 5, 28, 4, 0), (2100, 40, 16, 2, 1)])
+def test_fp32_states_keep_their_precision(L, Lq, Hq, Hkv, spread):
+    """fp32 states against 64 bits, at the edges of the kernels' tiles (32 tokens, 128 rows) and with channels of very different
+    scale.  A logit sees 8 additions at its own size, 40 at 2^-8 of it and a few more, each rounded to 2^-24, and products that
+    are 2^-26 short: within 16 * 2^-24 of the sum of its products' magnitudes.  A row's logarithm of a sum moves by no more
+    than the worst of its logits, the sum's own rounding (2^-24 for each of its levels, 64 tokens a lane and 16 splits at most) and
+    the exponentials' (2^-22 with the scaling)."""
+    _announce(f"fp32 precision L={L} Lq={Lq} {Hq}/{Hkv} spread {spread}")
+    rng = np.random.default_rng(L + Lq)
+    channel = np.exp(spread * rng.standard_normal(128))
+    q = (rng.standard_normal((Hq, Lq, 128)) * channel).astype(np.float32)
+    k = (rng.standard_normal((Hkv, L, 128)) / channel * np.exp(0.3 * spread * rng.standard_normal((Hkv, L, 1)))).astype(np.float32)
+    row_max, row_sum = il.ilre_row_stats(torch.from_numpy(q).cuda(), torch.from_numpy(k).cuda())
+    torch.cuda.synchronize()
+    got = row_max.cpu().numpy().astype(np.float64) + np.log(row_sum.cpu().numpy().astype(np.float64))
+    group = Hq // Hkv
+    scale = 1.0 / np.sqrt(128.0)
+    for h in range(Hq):
+        kk = k[h // group].astype(np.float64)
+        s = (q[h].astype(np.float64) @ kk.T) * scale
+        size = (np.abs(q[h]).astype(np.float64) @ np.abs(kk).T) * scale
+        top = s.max(axis=1)
+        want = top + np.log(np.exp(s - top[:, None]).sum(axis=1))
+        bound = 16 * 2.0 ** -24 * size.max(axis=1) + 2.0 ** -22 * (1 + np.abs(s).max(axis=1)) + 80 * 2.0 ** -24
+        assert (np.abs(got[h * Lq:(h + 1) * Lq] - want) <= bound).all(), (h, np.abs(got[h * Lq:(h + 1) * Lq] - want).max(), bound.min())
+
+
 def test_end_to_end_cfg1():
     _announce("end_to_end cfg1")
     inp = inputs.config(1)
