@@ -984,9 +984,12 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv)
     p.nqb = (p.rows_per_group + p.rows_per_wg - 1) / p.rows_per_wg;
     p.ntiles = (L + p.tile_tokens - 1) / p.tile_tokens;
     p.nunits = Hkv * p.nqb;
-    // enough splits for one workgroup of 8 waves (two of 4 waves) per compute unit
-    const int target = kNumCU * (p.waves == 8 ? 1 : 2);
-    int64_t nsplit = (target + p.nunits / 2) / p.nunits;
+    // As many splits as there is room for at a time: one workgroup of 8 waves (two of 4 waves) a compute unit, and on each XCD no
+    // more workgroups than that, because one too many runs behind all others, for as long as they do.  (Splits rounded up to
+    // the next number, 131072 tokens: 28/4 heads, 630 rows a kv head, 516 workgroups 287 us a call, 504 220; 64/8, 1360 rows, 528 1226
+    // us, 480 752; 28/4, 1050 rows, 500 workgroups, but 65 on some XCDs 443 us, 480, 60 an XCD, 363.)
+    const int room = kNumCU / kNumXCD * (p.waves == 8 ? 1 : 2);
+    int64_t nsplit = (int64_t)kNumXCD * (room / p.nqb) / Hkv;
     if (nsplit < 1) nsplit = 1;
     const int64_t step = dtype == ILRE_F32 ? 2 : 1;  // a split's tiles come in twos there
     nsplit = std::min(nsplit, (p.ntiles + step - 1) / step);

@@ -74,8 +74,9 @@ def test_staged_scoring(name, L, Lq, Hq, Hkv, dtype, cs):
     assert bad == 0, f"max mode: {bad} scores out of tolerance, worst {worst:.2f}x"
 
 
-@pytest.mark.parametrize("Lq,Hq,Hkv,L", [(1, 2, 2, 64), (1, 2, 2, 40001), (17, 28, 4, 9000), (32, 4, 1, 64 * 515), (32, 8, 2, 65), (43, 3, 1, 9000)],
-                         ids=["1_row", "1_row_many_splits", "119_rows", "128_rows", "128_rows_ragged", "129_rows"])
+@pytest.mark.parametrize("Lq,Hq,Hkv,L", [(1, 2, 2, 64), (1, 2, 2, 40001), (17, 28, 4, 9000), (32, 4, 1, 64 * 515), (32, 8, 2, 65), (43, 3, 1, 9000),
+                                         (150, 14, 2, 9000), (170, 16, 2, 3001), (90, 21, 3, 12000)],
+                         ids=["1_row", "1_row_many_splits", "119_rows", "128_rows", "128_rows_ragged", "129_rows", "1050_rows", "1360_rows", "630_rows"])
 def test_scoring_narrow_query_block(Lq, Hq, Hkv, L):
     """Up to 128 query rows a kv head go one 32-row block a wavefront, more go two: both sides of the line, tiles of 64
     tokens, one and several of them a split.  Tolerance as everywhere: what fp32 sums of bf16 products allow."""
