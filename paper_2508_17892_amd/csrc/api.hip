@@ -91,6 +91,14 @@ Layout make_layout(const ilre::ScorePlan &p, int64_t L, int64_t nrows, const ilr
     return l;
 }
 
+// The plan for `have` bytes of scratch, of which need(plan) are wanted: one that makes do with less where that is all there is.
+template <typename NEED>
+ilre::ScorePlan plan_within(size_t have, int dtype, int64_t L, int Lq, int Hq, int Hkv, const NEED &need)
+{
+    const ilre::ScorePlan p = ilre::make_score_plan(dtype, L, Lq, Hq, Hkv, true);
+    return p.mixed && have < need(p) ? ilre::make_score_plan(dtype, L, Lq, Hq, Hkv, false) : p;
+}
+
 int check_shape(int64_t L, int32_t Lq, int32_t Hq, int32_t Hkv, int32_t d, int32_t dtype)
 {
     if (L < 1 || Lq < 1 || Hq < 1 || Hkv < 1) return fail(ILRE_EINVAL, "L, Lq, Hq, Hkv must be positive");
@@ -217,6 +225,7 @@ int check_tile_span(const ilre::ScoreArgs &a, const ilre::ScorePlan &p, int dtyp
 void fill_plan(ilre::ScoreArgs &a, const ilre::ScorePlan &p)
 {
     a.rows_per_group = p.rows_per_group;
+    a.rows_per_wg = p.rows_per_wg;
     a.nqb = p.nqb;
     a.nsplit = p.nsplit;
     a.ntiles = p.ntiles;
@@ -261,9 +270,11 @@ int row_stats_into(const void *q, const void *k_cache, int64_t L, int32_t Lq, in
     if (rc) return rc;
     if ((rc = check_shape(L, Lq, Hq, Hkv, d, opts->dtype))) return rc;
     if (!row_max || !row_sumexp) return fail(ILRE_EINVAL, "row_max or row_sumexp is null");
-    const ilre::ScorePlan p = ilre::make_score_plan(opts->dtype, L, Lq, Hq, Hkv);
     const int64_t nrows = (int64_t)Hq * Lq;
-    const Layout lay = make_layout(p, L, nrows, window_job(L, 0, 1, nullptr, 0));
+    auto layout = [&](const ilre::ScorePlan &plan) { return make_layout(plan, L, nrows, window_job(L, 0, 1, nullptr, 0)); };
+    const size_t have = static_buf ? (size_t)ILRE_STATIC_SCRATCH_BYTES : opts->workspace_bytes;
+    const ilre::ScorePlan p = plan_within(have, opts->dtype, L, Lq, Hq, Hkv, [&](const ilre::ScorePlan &plan) { return layout(plan).row_max; });
+    const Layout lay = layout(p);
     unsigned char *ws;
     if (static_buf) {
         if (lay.row_max > (size_t)ILRE_STATIC_SCRATCH_BYTES)
@@ -307,7 +318,7 @@ int ilre_workspace_bytes(int64_t L, int32_t Lq, int32_t Hq, int32_t Hkv, int32_t
     if (rc) return rc;
     if (n_pool_kernels < 0 || n_pool_kernels > ILRE_MAX_POOL_KERNELS)
         return fail(ILRE_EINVAL, "n_pool_kernels out of range");
-    const ilre::ScorePlan p = ilre::make_score_plan(dtype, L, Lq, Hq, Hkv);
+    const ilre::ScorePlan p = ilre::make_score_plan(dtype, L, Lq, Hq, Hkv, true);
     *out_bytes = make_layout(p, L, (int64_t)Hq * Lq, window_job(L, 0, 1, nullptr, n_pool_kernels)).total;
     return ILRE_OK;
 }
@@ -320,7 +331,7 @@ int ilre_workspace_bytes_max_avg(int64_t L, int32_t Lq, int32_t Hq, int32_t Hkv,
     int rc = check_shape(L, Lq, Hq, Hkv, d, dtype);
     if (rc) return rc;
     if ((rc = check_max_avg(L, sink, 1, max_kernels, n_max, nullptr, n_avg, true))) return rc;
-    const ilre::ScorePlan p = ilre::make_score_plan(dtype, L, Lq, Hq, Hkv);
+    const ilre::ScorePlan p = ilre::make_score_plan(dtype, L, Lq, Hq, Hkv, true);
     *out_bytes = make_layout(p, L, (int64_t)Hq * Lq, max_avg_job(L, sink, 1, max_kernels, n_max, nullptr, n_avg)).total;
     return ILRE_OK;
 }
@@ -344,9 +355,10 @@ int ilre_col_scores(const void *q, const void *k_cache, int64_t L, int32_t Lq, i
     if (rc) return rc;
     if ((rc = check_shape(L, Lq, Hq, Hkv, d, opts->dtype))) return rc;
     if (!row_max || !row_sumexp || !out_scores) return fail(ILRE_EINVAL, "row_max, row_sumexp or out_scores is null");
-    const ilre::ScorePlan p = ilre::make_score_plan(opts->dtype, L, Lq, Hq, Hkv);
-    const int64_t nrows = (int64_t)Hq * Lq;
-    const Layout lay = make_layout(p, L, nrows, window_job(L, 0, 1, nullptr, 0));
+    auto layout = [&](const ilre::ScorePlan &plan) { return make_layout(plan, L, (int64_t)Hq * Lq, window_job(L, 0, 1, nullptr, 0)); };
+    const ilre::ScorePlan p =
+        plan_within(opts->workspace_bytes, opts->dtype, L, Lq, Hq, Hkv, [&](const ilre::ScorePlan &plan) { return layout(plan).select; });
+    const Layout lay = layout(p);
     if ((rc = check_workspace(opts, lay.select))) return rc;
     ilre::ScoreArgs a{};
     if ((rc = fill_qk(a, q, k_cache, L, Lq, Hq, Hkv, d, opts))) return rc;
@@ -522,9 +534,13 @@ int ilre_recall(const void *q, const void *k_cache, int64_t L, int32_t Lq, int32
     if ((uintptr_t)out_scores & 15) return fail(ILRE_EINVAL, "out_scores must be 16-byte aligned");
     if (opts->sink > L) return fail(ILRE_EINVAL, "sink must be in [0, L]");
     if ((rc = check_kernels(L - opts->sink, budget, pool_kernels, opts->n_pool_kernels))) return rc;
-    const ilre::ScorePlan p = ilre::make_score_plan(opts->dtype, L, Lq, Hq, Hkv);
     // workspace sized for the whole context (what ilre_workspace_bytes reports); the selection then runs on the body
-    const Layout lay = make_layout(p, L, (int64_t)Hq * Lq, window_job(L, 0, budget, pool_kernels, opts->n_pool_kernels));
+    auto layout = [&](const ilre::ScorePlan &plan) {
+        return make_layout(plan, L, (int64_t)Hq * Lq, window_job(L, 0, budget, pool_kernels, opts->n_pool_kernels));
+    };
+    const ilre::ScorePlan p =
+        plan_within(opts->workspace_bytes, opts->dtype, L, Lq, Hq, Hkv, [&](const ilre::ScorePlan &plan) { return layout(plan).total; });
+    const Layout lay = layout(p);
     if ((rc = check_workspace(opts, lay.total))) return rc;
     ilre::FusedScores fused{};
     unsigned char *ws = (unsigned char *)opts->workspace;
@@ -547,9 +563,11 @@ int ilre_recall_max_avg(const void *q, const void *k_cache, int64_t L, int32_t L
     if ((rc = check_shape(L, Lq, Hq, Hkv, d, opts->dtype))) return rc;
     if (!out_idx || !out_scores) return fail(ILRE_EINVAL, "out_idx or out_scores is null");
     if ((rc = check_max_avg(L, sink, budget, max_kernels, n_max, avg_kernels, n_avg, false))) return rc;
-    const ilre::ScorePlan p = ilre::make_score_plan(opts->dtype, L, Lq, Hq, Hkv);
     const ilre::SelectJob job = max_avg_job(L, sink, budget, max_kernels, n_max, avg_kernels, n_avg);
-    const Layout lay = make_layout(p, L, (int64_t)Hq * Lq, job);
+    auto layout = [&](const ilre::ScorePlan &plan) { return make_layout(plan, L, (int64_t)Hq * Lq, job); };
+    const ilre::ScorePlan p =
+        plan_within(opts->workspace_bytes, opts->dtype, L, Lq, Hq, Hkv, [&](const ilre::ScorePlan &plan) { return layout(plan).total; });
+    const Layout lay = layout(p);
     if ((rc = check_workspace(opts, lay.total))) return rc;
     ilre::FusedScores fused{};
     if ((rc = run_scoring(q, k_cache, L, Lq, Hq, Hkv, d, out_scores, opts, p, lay, ilre::ClearWords{}, fused))) return rc;

@@ -34,6 +34,7 @@ struct ScorePlan {
     int nb;               // 32-row query blocks per wavefront
     int rows_per_group;   // G * Lq query rows served by one kv head
     int rows_per_wg;      // waves * nb * 32
+    bool mixed;           // two query blocks a kv head, the second with one 32-row block a wavefront
     int nqb;              // query blocks per kv group
     int tile_tokens;      // tokens per LDS tile
     int64_t ntiles;       // ceil(L / tile_tokens)
@@ -60,7 +61,7 @@ struct ScoreArgs {
     int Lq, Hq, Hkv, G;
     int64_t q_stride_head, q_stride_token, k_stride_head, k_stride_token;  // in elements
     float c;  // scale * log2(e): logits leave the MFMA in raw units and are exponentiated base 2
-    int rows_per_group, nqb, nsplit;
+    int rows_per_group, rows_per_wg, nqb, nsplit;
     int64_t ntiles, tiles_per_split;
     // pass 1 (row statistics): per-split partial maxima (base-2 units) and sums
     float *part_m, *part_z;  // [nsplit][Hq*Lq]
@@ -76,7 +77,8 @@ struct ScoreArgs {
     float *dump;                        // 16 floats nobody reads: target of stores that have nothing to store
 };
 
-ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv);
+// `mix`: query blocks may be of unequal size, which can take one partial score vector more a kv head.
+ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv, bool mix);
 
 // With a.merge the partials are all that is left behind.
 hipError_t launch_row_stats(const ScorePlan &p, const ScoreArgs &a, float *row_max, float *row_sumexp, hipStream_t s);

@@ -152,9 +152,10 @@ __device__ __forceinline__ float merged_offset(const float *pm, const float *pz,
     return row_offset(mm * kLn2, sum[0]);
 }
 
+// One workgroup's share: NB 32-row blocks a wavefront of query block qb, tiles tile0 .. tile1 - 1 of kv head g.
 // MODE 0: row statistics.  MODE 1: column scores (RMAX = 0 sum over rows, 1 max over rows).
 template <int NB, int WAVES, int MODE, int RMAX>
-__global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
+__device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split, int qb, int64_t tile0, int64_t tile1, bool timed, unsigned long long t_begin)
 {
     using T = Bf16;
     constexpr int ES = T::kElemBytes;
@@ -178,53 +179,12 @@ __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
 
     extern __shared__ __align__(16) unsigned char smem[];
 
-    // blockIdx -> (kv head, token split, query block).  Workgroups are dealt round-robin to the 8
-    // XCDs, so the query blocks that stream the same K range are given ids with equal id % 8 and
-    // consecutive id / 8: they run on one XCD at about the same time and share its L2.
-    const int xcd = blockIdx.x % kNumXCD;
-    const int slot = blockIdx.x / kNumXCD;
-    const int qb = slot % a.nqb;
-    const int64_t pair = (int64_t)(slot / a.nqb) * kNumXCD + xcd;
-    // Pass 1 notes how long each workgroup ran (0: it had nothing to do); the merge kernel behind it turns the
-    // times into pass 2's token ranges.
-    const bool timed = MODE == 0 && a.wg_time != nullptr && threadIdx.x == 0;
-    const unsigned long long t_begin = timed ? wall_clock64() : 0ull;
-    if (timed) a.wg_time[blockIdx.x] = 0u;
-    // what the selection counts in is cleared on the side (a launch of its own took 4.7 us)
-    if (MODE == 1 && blockIdx.x == 0)
-        for (uint32_t i = threadIdx.x * 4; i < a.clear.n; i += WAVES * 64 * 4) *(uint4 *)&a.clear.at[i] = make_uint4(0, 0, 0, 0);
-    if (pair >= (int64_t)a.Hkv * a.nsplit) return;
-    const int g = (int)(pair / a.nsplit);
-    const int split = (int)(pair % a.nsplit);
-    int64_t tile_lo = (int64_t)split * a.tiles_per_split;
-    int64_t tile_hi = (tile_lo + a.tiles_per_split < a.ntiles) ? tile_lo + a.tiles_per_split : a.ntiles;
-    if (MODE == 1 && a.split_table != nullptr) {
-        // Pass 2's column results do not depend on how the tokens are cut into ranges, so the ranges may follow the
-        // speed of the XCD they run on (the table's header says which launch shape it was made for; the table is
-        // only used if it is a cut of the context, whatever the workspace holds).
-        const int32_t *tb = a.split_table;
-        if ((uint32_t)tb[0] == (uint32_t)a.table_tag && (uint32_t)tb[1] == (uint32_t)(a.table_tag >> 32)) {
-            // every wavefront checks the whole table (a few loads a lane): edges from 0 to ntiles that never
-            // step back cut the context into ranges that cover every tile once, whatever else they are
-            bool bad = false;
-            for (int i = threadIdx.x & 63; i <= a.nsplit; i += 64) {
-                const int64_t e0 = tb[2 + i], e1 = i < a.nsplit ? (int64_t)tb[3 + i] : a.ntiles;
-                bad = bad || e0 < 0 || e0 > e1 || e1 > a.ntiles || (i == 0 && e0 != 0) || (i == a.nsplit && e0 != a.ntiles);
-            }
-            if (!__any(bad)) {
-                tile_lo = tb[2 + split];
-                tile_hi = tb[3 + split];
-            }
-        }
-    }
-    const int64_t tile0 = tile_lo, tile1 = tile_hi;
-    if (tile0 >= tile1) return;
     const int tid = threadIdx.x;
     const int wave = tid >> 6;
     const int lane = tid & 63;
     const int l32 = lane & 31;
     const int half = lane >> 5;
-    const int rl0 = qb * (WAVES * NB * 32) + wave * (NB * 32);
+    const int rl0 = qb * a.rows_per_wg + wave * (NB * 32);
     const int64_t nrows = (int64_t)a.Hq * a.Lq;
 
     // Query fragments, resident for the whole kernel: lane holds, for each of its NB blocks, row
@@ -309,7 +269,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
         // get -inf: exp2(0*c - inf) = 0.
         issue_first();  // K and Q are on their way meanwhile
         constexpr int ROWS = WAVES * NB * 32, SHARERS = WAVES * 64 / ROWS;
-        const int local = tid / SHARERS, rl = qb * ROWS + local;
+        const int local = tid / SHARERS, rl = qb * a.rows_per_wg + local;
         const bool real = rl < a.rows_per_group;
         const int64_t r = (int64_t)g * a.rows_per_group + (real ? rl : a.rows_per_group - 1);
         float off;
@@ -560,6 +520,57 @@ __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
             a.wg_time[blockIdx.x] = dt < 0xFFFFFFFFull ? (uint32_t)(dt ? dt : 1) : 0xFFFFFFFFu;
         }
     }
+}
+
+// MIXED: two query blocks a kv head, of which the second is one 32-row block a wavefront.  Workgroups 32 slots apart share a compute
+// unit, so that every other 32 slots have the two blocks the other way round: one of each kind a compute unit.
+template <int NB, int WAVES, int MODE, int RMAX, bool MIXED>
+__global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
+{
+    // blockIdx -> (kv head, token split, query block).  Workgroups are dealt round-robin to the 8
+    // XCDs, so the query blocks that stream the same K range are given ids with equal id % 8 and
+    // consecutive id / 8: they run on one XCD at about the same time and share its L2.
+    const int xcd = blockIdx.x % kNumXCD;
+    const int slot = blockIdx.x / kNumXCD;
+    const int qb = MIXED ? (slot ^ slot >> 5) & 1 : slot % a.nqb;
+    const int64_t pair = (int64_t)(slot / a.nqb) * kNumXCD + xcd;
+    // Pass 1 notes how long each workgroup ran (0: it had nothing to do); the merge kernel behind it turns the
+    // times into pass 2's token ranges.
+    const bool timed = MODE == 0 && a.wg_time != nullptr && threadIdx.x == 0;
+    const unsigned long long t_begin = timed ? wall_clock64() : 0ull;
+    if (timed) a.wg_time[blockIdx.x] = 0u;
+    // what the selection counts in is cleared on the side (a launch of its own took 4.7 us)
+    if (MODE == 1 && blockIdx.x == 0)
+        for (uint32_t i = threadIdx.x * 4; i < a.clear.n; i += WAVES * 64 * 4) *(uint4 *)&a.clear.at[i] = make_uint4(0, 0, 0, 0);
+    if (pair >= (int64_t)a.Hkv * a.nsplit) return;
+    const int g = (int)(pair / a.nsplit);
+    const int split = (int)(pair % a.nsplit);
+    int64_t tile_lo = (int64_t)split * a.tiles_per_split;
+    int64_t tile_hi = (tile_lo + a.tiles_per_split < a.ntiles) ? tile_lo + a.tiles_per_split : a.ntiles;
+    if (MODE == 1 && a.split_table != nullptr) {
+        // Pass 2's column results do not depend on how the tokens are cut into ranges, so the ranges may follow the
+        // speed of the XCD they run on (the table's header says which launch shape it was made for; the table is
+        // only used if it is a cut of the context, whatever the workspace holds).
+        const int32_t *tb = a.split_table;
+        if ((uint32_t)tb[0] == (uint32_t)a.table_tag && (uint32_t)tb[1] == (uint32_t)(a.table_tag >> 32)) {
+            // every wavefront checks the whole table (a few loads a lane): edges from 0 to ntiles that never
+            // step back cut the context into ranges that cover every tile once, whatever else they are
+            bool bad = false;
+            for (int i = threadIdx.x & 63; i <= a.nsplit; i += 64) {
+                const int64_t e0 = tb[2 + i], e1 = i < a.nsplit ? (int64_t)tb[3 + i] : a.ntiles;
+                bad = bad || e0 < 0 || e0 > e1 || e1 > a.ntiles || (i == 0 && e0 != 0) || (i == a.nsplit && e0 != a.ntiles);
+            }
+            if (!__any(bad)) {
+                tile_lo = tb[2 + split];
+                tile_hi = tb[3 + split];
+            }
+        }
+    }
+    if (tile_lo >= tile_hi) return;
+    if (MIXED && qb == 1)
+        score_rows<1, WAVES, MODE, RMAX>(a, g, split, qb, tile_lo, tile_hi, timed, t_begin);
+    else
+        score_rows<NB, WAVES, MODE, RMAX>(a, g, split, qb, tile_lo, tile_hi, timed, t_begin);
 }
 
 // ---------------------------------------------------------------- fp32 states
@@ -959,7 +970,7 @@ hipError_t launch_score(K kernel, int grid, int threads, size_t lds, const Score
 
 }  // namespace
 
-ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv)
+ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv, bool mix)
 {
     ScorePlan p{};
     p.dtype = dtype;
@@ -978,6 +989,11 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv)
         const int64_t pad4 = ((p.rows_per_group + 255) / 256) * 256;
         p.waves = pad4 < pad8 ? 4 : 8;
         p.nb = p.rows_per_group <= 128 ? 1 : 2;
+        // 257 - 384 rows: a block of 256 and one of 128, which a quarter of 512 would be padding for (whole recall, 384 rows a kv head,
+        // 9000 tokens 64.5 -> 60.3 us, 50001 130.2 -> 124.0, 400000 799 -> 755; 280 rows, 131072 tokens 251 -> 240).  513 - 640 rows as
+        // two and one are no faster than three, the larger blocks decide: 600 rows, 131072 tokens 411 and 405 us, 800 of 4 heads 259 and 274.
+        p.mixed = mix && p.rows_per_group > 256 && p.rows_per_group <= 384;
+        if (p.mixed) p.waves = 4;
     }
     p.tile_tokens = dtype == ILRE_F32 ? kF32Tokens : Bf16::tile_tokens(p.waves);
     p.rows_per_wg = p.waves * p.nb * 32;
@@ -1026,11 +1042,13 @@ hipError_t launch_row_stats(const ScorePlan &p, const ScoreArgs &a, float *row_m
     if (p.dtype == ILRE_F32)
         e = launch_score(score_f32_kernel<0, 0>, p.grid, kF32Waves * 64, lds, a, s);
     else if (p.nb == 1)
-        e = launch_score(score_kernel<1, 4, 0, 0>, p.grid, 256, lds, a, s);
+        e = launch_score(score_kernel<1, 4, 0, 0, false>, p.grid, 256, lds, a, s);
+    else if (p.mixed)
+        e = launch_score(score_kernel<2, 4, 0, 0, true>, p.grid, 256, lds, a, s);
     else if (p.waves == 4)
-        e = launch_score(score_kernel<2, 4, 0, 0>, p.grid, 256, lds, a, s);
+        e = launch_score(score_kernel<2, 4, 0, 0, false>, p.grid, 256, lds, a, s);
     else
-        e = launch_score(score_kernel<2, 8, 0, 0>, p.grid, 512, lds, a, s);
+        e = launch_score(score_kernel<2, 8, 0, 0, false>, p.grid, 512, lds, a, s);
     if (e != hipSuccess) return e;
     if (a.merge) return hipSuccess;  // pass 2 takes the partials
     const bool balance = a.wg_time != nullptr && a.split_table != nullptr;
@@ -1060,14 +1078,17 @@ hipError_t launch_col_scores(const ScorePlan &p, const ScoreArgs &a, int score_m
         e = mx ? launch_score(score_f32_kernel<1, 1>, p.grid, kF32Waves * 64, lds, a, s)
                : launch_score(score_f32_kernel<1, 0>, p.grid, kF32Waves * 64, lds, a, s);
     else if (p.nb == 1)
-        e = mx ? launch_score(score_kernel<1, 4, 1, 1>, p.grid, 256, lds, a, s)
-               : launch_score(score_kernel<1, 4, 1, 0>, p.grid, 256, lds, a, s);
+        e = mx ? launch_score(score_kernel<1, 4, 1, 1, false>, p.grid, 256, lds, a, s)
+               : launch_score(score_kernel<1, 4, 1, 0, false>, p.grid, 256, lds, a, s);
+    else if (p.mixed)
+        e = mx ? launch_score(score_kernel<2, 4, 1, 1, true>, p.grid, 256, lds, a, s)
+               : launch_score(score_kernel<2, 4, 1, 0, true>, p.grid, 256, lds, a, s);
     else if (p.waves == 4)
-        e = mx ? launch_score(score_kernel<2, 4, 1, 1>, p.grid, 256, lds, a, s)
-               : launch_score(score_kernel<2, 4, 1, 0>, p.grid, 256, lds, a, s);
+        e = mx ? launch_score(score_kernel<2, 4, 1, 1, false>, p.grid, 256, lds, a, s)
+               : launch_score(score_kernel<2, 4, 1, 0, false>, p.grid, 256, lds, a, s);
     else
-        e = mx ? launch_score(score_kernel<2, 8, 1, 1>, p.grid, 512, lds, a, s)
-               : launch_score(score_kernel<2, 8, 1, 0>, p.grid, 512, lds, a, s);
+        e = mx ? launch_score(score_kernel<2, 8, 1, 1, false>, p.grid, 512, lds, a, s)
+               : launch_score(score_kernel<2, 8, 1, 0, false>, p.grid, 512, lds, a, s);
     if (e != hipSuccess || !reduce) return e;
     return launch_reduce_units(a.partial, p.nunits, a.L, mx ? 1 : 0, out_scores, s);
 }

@@ -75,11 +75,14 @@ def test_staged_scoring(name, L, Lq, Hq, Hkv, dtype, cs):
 
 
 @pytest.mark.parametrize("Lq,Hq,Hkv,L", [(1, 2, 2, 64), (1, 2, 2, 40001), (17, 28, 4, 9000), (32, 4, 1, 64 * 515), (32, 8, 2, 65), (43, 3, 1, 9000),
-                                         (150, 14, 2, 9000), (170, 16, 2, 3001), (90, 21, 3, 12000)],
-                         ids=["1_row", "1_row_many_splits", "119_rows", "128_rows", "128_rows_ragged", "129_rows", "1050_rows", "1360_rows", "630_rows"])
+                                         (150, 14, 2, 9000), (170, 16, 2, 3001), (90, 21, 3, 12000),
+                                         (257, 1, 1, 65), (64, 5, 1, 3000), (96, 32, 8, 9000), (48, 24, 3, 20001), (385, 1, 1, 200)],
+                         ids=["1_row", "1_row_many_splits", "119_rows", "128_rows", "128_rows_ragged", "129_rows", "1050_rows", "1360_rows", "630_rows",
+                              "257_rows", "320_rows", "384_rows", "384_rows_ragged", "385_rows"])
 def test_scoring_narrow_query_block(Lq, Hq, Hkv, L):
     """Up to 128 query rows a kv head go one 32-row block a wavefront, more go two: both sides of the line, tiles of 64
-    tokens, one and several of them a split.  Tolerance as everywhere: what fp32 sums of bf16 products allow."""
+    tokens, one and several of them a split.  257 to 384 rows are a block of 256 and one of 128 in one launch; more blocks a kv
+    head than divide the places on an XCD.  Tolerance as everywhere: what fp32 sums of bf16 products allow."""
     _announce(f"narrow query block Lq={Lq} Hq={Hq} Hkv={Hkv} L={L}")
     inp = inputs.custom(L=L, Lq=Lq, Hq=Hq, Hkv=Hkv, d=128, dtype="bf16", n_spans=2 if L > 200 else 0, span_len=(8, 24),
                         channel_scale=True, seed=Lq + L)
@@ -90,6 +93,30 @@ def test_scoring_narrow_query_block(Lq, Hq, Hkv, L):
         torch.cuda.synchronize()
         bad, worst = score_errors(got.cpu().numpy(), want)
         assert bad == 0, f"{bad} scores out of tolerance, worst {worst:.2f}x"
+
+
+def test_unequal_query_blocks_want_a_workspace_for_them():
+    """A block of 256 rows and one of 128 leave two partial score vectors a kv head.  A workspace that has room for one serves as
+    well: one padded block is taken then."""
+    L, Lq, Hq, Hkv = 9000, 96, 32, 8
+    _announce("unequal query blocks, small workspace")
+    inp = inputs.custom(L=L, Lq=Lq, Hq=Hq, Hkv=Hkv, d=128, dtype="bf16", n_spans=2, span_len=(8, 24), channel_scale=True, seed=3)
+    q, k = to_device(inp.q), to_device(inp.k)
+    full = il.alloc_workspace(L, Lq, Hq, Hkv, 128, 2, il.ILRE_BF16)
+    small = torch.empty(full.numel() - Hkv * L * 4, dtype=torch.uint8, device="cuda")
+    got = []
+    for ws in (full, small):
+        idx, scores = il.ilre_recall(q, k, 500, (3, 7), workspace=ws)
+        ref, total = il.ilre_row_stats(q, k, workspace=ws)
+        staged = il.ilre_col_scores(q, k, ref, total, workspace=ws)
+        torch.cuda.synchronize()
+        scores = scores.cpu().numpy()
+        assert idx.cpu().numpy().tolist() == oracle.allocate(scores, (3, 7), 500).tolist()
+        np.testing.assert_allclose(staged.cpu().numpy(), scores, rtol=4e-6, atol=0)
+        got.append(scores)
+    np.testing.assert_allclose(got[0], got[1], rtol=4e-6, atol=0)
+    with pytest.raises(il.IlreError):
+        il.ilre_recall(q, k, 500, (3, 7), workspace=small[: small.numel() // 2 // 256 * 256])
 
 
 @pytest.mark.parametrize("dtype,Lq,G,Hkv", [("bf16", 20, 2, 4), ("bf16", 50, 4, 4), ("bf16", 64, 8, 2), ("f32", 33, 2, 4)],
