@@ -726,6 +726,7 @@ struct AvgParams {
     uint64_t off[ILRE_MAX_POOL_KERNELS];                  // its cells
     uint16_t avg[ILRE_MAX_POOL_KERNELS], at[ILRE_MAX_POOL_KERNELS];  // average kernels ascending, and their number in the order given
     uint16_t at_of_size[kAvgGroup];                       // SMALL: number of the average kernel of size 1, 2, .. (kNoAvg: none)
+    uint32_t wg_end[ILRE_MAX_POOL_KERNELS];               // per max kernel: its workgroups end before that one (0xFFFFFFFF: not used)
 };
 
 // The strided max pooling on its own, where cells are large or windows reach over so many of them that each would be pooled
@@ -794,7 +795,7 @@ __device__ __forceinline__ uint32_t find_cut(const uint32_t *h, uint32_t need)
 
 // Both passes over the averages of Algorithm 1.  PASS 0: the strided max pooling (each cell computed where its windows
 // are, and written out), and per combination a histogram, whose cut the last workgroup finds.  PASS 1: the elements
-// at or above the cut, into the combination's list.  grid = (workgroups, max kernels x groups).
+// at or above the cut, into the combination's list.  grid = (workgroups of all max kernels, groups).
 //
 // A window's sum for average kernel n is its sum for n - 1 plus one cell if both windows start at the same cell, which is
 // also the order the definition sums in: a lane takes windows by their first cell and gets all average kernels' sums from
@@ -826,7 +827,14 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
     __shared__ uint32_t is_last;
     constexpr int CHUNK = 64 * PER;            // windows a wavefront sums at a time
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int i = blockIdx.y / ap.groups, g0 = (blockIdx.y % ap.groups) * kAvgGroup;
+    // the workgroup's max kernel (the first ends are at fixed places of the arguments, loaded together)
+    constexpr int kEnds = 8;
+    int i = 0;
+#pragma unroll
+    for (int k = 0; k < kEnds; ++k) i += blockIdx.x >= ap.wg_end[k] ? 1 : 0;
+    while (i >= kEnds && blockIdx.x >= ap.wg_end[i]) ++i;  // (the last end is the grid's)
+    const uint32_t wg0 = i ? ap.wg_end[i - 1] : 0u, wg = blockIdx.x - wg0, nwg = ap.wg_end[i] - wg0;
+    const int g0 = blockIdx.y * kAvgGroup;
     const int ng = min(kAvgGroup, ap.n_avg - g0), rows = SMALL ? kAvgGroup : ng;
     const uint32_t m = ap.m[i], len = ap.len[i];
     const int n_top = ap.avg[g0 + ng - 1], ahead = (n_top - 1) / 2;  // the first windows start before the first cell
@@ -874,7 +882,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
             all(std::integral_constant<int, 0>{});
     };
     float cell[PER + 1];
-    if (blockIdx.x * kAvgWaves < chunks) fetch(blockIdx.x * kAvgWaves + wave, cell);
+    if (wg * kAvgWaves < chunks) fetch(wg * kAvgWaves + wave, cell);
 
     // average kernel q's numbers are lane q's, in every wavefront (SMALL: the one of size n has number n - 1)
     uint32_t l_size, l_want, l_span0, l_span1, l_shift;
@@ -942,7 +950,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
             const uint32_t name = (uint32_t)e, q = name >> kKernelAt;
             const uint32_t to = (uint32_t)__shfl((int)l_to, (int)q) + (name >> kPlaceAt & ((1u << kPlaceBits) - 1u));
             const uint32_t size = SMALL ? q + 1 : (uint32_t)__shfl((int)l_size, (int)q);
-            const uint32_t chunk = blockIdx.x * kAvgWaves + wave + (first_round + (name >> kWindowBits & ((1u << kRoundBits) - 1u))) * (gridDim.x * kAvgWaves);
+            const uint32_t chunk = wg * kAvgWaves + wave + (first_round + (name >> kWindowBits & ((1u << kRoundBits) - 1u))) * (nwg * kAvgWaves);
             const uint32_t el = chunk * (uint32_t)CHUNK - (uint32_t)ahead + (name & ((1u << kWindowBits) - 1u)) + (size - 1) / 2;
             const float avg = divide_small(__uint_as_float((uint32_t)(e >> 32)), (float)size, c_rcp[q]);
             if (valid) lists[c_list[q] + to] = make_key(avg, el);
@@ -964,7 +972,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
         if (hit) queue[at] = (uint64_t)__float_as_uint(x) << 32 | (where + ((at + place) << kPlaceAt));
         queued += (uint32_t)__popcll(mask);
     };
-    for (uint32_t c0 = blockIdx.x * kAvgWaves; c0 < chunks; c0 += gridDim.x * kAvgWaves, ++round) {
+    for (uint32_t c0 = wg * kAvgWaves; c0 < chunks; c0 += nwg * kAvgWaves, ++round) {
         const uint32_t c = c0 + wave;  // a chunk past the last one has no elements
         const int64_t first = (int64_t)c * CHUNK - ahead;  // first cell of the chunk's first window
         lds_wave_sync();  // the previous chunk's reads of the buffer are done
@@ -989,7 +997,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
             }
         }
         lds_wave_sync();
-        if (c0 + gridDim.x * kAvgWaves < chunks) fetch(c + gridDim.x * kAvgWaves, cell);  // in flight while this chunk is summed
+        if (c0 + nwg * kAvgWaves < chunks) fetch(c + nwg * kAvgWaves, cell);  // in flight while this chunk is summed
 
         float sum[PER];
 #pragma unroll
@@ -1116,7 +1124,7 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
                 if (v[b]) atomicAdd(&hist[(size_t)c_comb[x / kAvgBins] * kAvgBins + x % kAvgBins], v[b]);
             }
         }
-        if (count_in(&done[blockIdx.y], gridDim.x, &is_last)) {
+        if (count_in(&done[i * ap.groups + blockIdx.y], nwg, &is_last)) {
             for (int q = wave; q < rows; q += kAvgWaves) {
                 if (c_comb[q] == 0xFFFFFFFFu) continue;
                 const uint32_t cut = find_cut(hist + (size_t)c_comb[q] * kAvgBins, of(l_want, q));
@@ -2734,16 +2742,25 @@ hipError_t raise_avg_lds()
 }
 
 // One chunk of windows a wavefront where that is at most two workgroups a compute unit, more of them beyond: a
-// workgroup carries the clearing and flushing of its 16 KiB of counts.
+// workgroup carries the clearing and flushing of its 16 KiB of counts.  Max kernels get workgroups in proportion to their
+// cells (as many each, cells of 2 had four times as much a workgroup as cells of 8: whole selection, budget 4096, 48 combinations 4M
+// scores 173.7 -> 160.3 us; max kernels 1, 2, 4, 8, 16 with four others 1M 142.5 -> 109.7; 64 max kernels 1M 355 -> 231).  Half as many
+// in all: 166, 120 and 231 us; the counts are added up a line at a time, but fewer workgroups sum longer.
 template <int PASS, int PER, bool SMALL>
-void launch_averages(const float *scores, float *cells, const AvgParams &ap, int n_max, int64_t len_max, int n_top, SelCtrl *ctrl, uint32_t *hist,
-                     uint32_t *done, uint64_t *lists, hipStream_t s)
+void launch_averages(const float *scores, float *cells, AvgParams &ap, int n_max, int n_top, SelCtrl *ctrl, uint32_t *hist, uint32_t *done,
+                     uint64_t *lists, hipStream_t s)
 {
-    const uint32_t rows = (uint32_t)(n_max * ap.groups), per_wg = kAvgWaves * 64 * PER;
-    const uint32_t want = (uint32_t)((len_max + n_top + per_wg - 1) / per_wg), most = 2 * kNumCU / rows;
-    const uint32_t gx = want < most ? want : (most > 16 ? most : 16u);
+    constexpr uint64_t per_wg = kAvgWaves * 64 * PER;
+    const uint64_t most = std::max(2 * kNumCU / ap.groups, 16 * n_max);
+    uint64_t all = 0;
+    for (int i = 0; i < n_max; ++i) all += ap.len[i];
+    uint32_t wgs = 0;
+    for (int i = 0; i < ILRE_MAX_POOL_KERNELS; ++i) {
+        if (i < n_max) wgs += (uint32_t)std::max<uint64_t>(std::min((ap.len[i] + n_top + per_wg - 1) / per_wg, most * ap.len[i] / std::max<uint64_t>(all, 1)), 1);
+        ap.wg_end[i] = i < n_max ? wgs : 0xFFFFFFFFu;
+    }
     const size_t lds = avg_lds(PASS, PER, SMALL, SMALL ? kAvgGroup : ap.rows, n_top);
-    hipLaunchKernelGGL((pool_averages<PASS, PER, SMALL>), dim3(gx, rows), dim3(kAvgThreads), lds, s, scores, cells, ap, ctrl, hist, done, lists);
+    hipLaunchKernelGGL((pool_averages<PASS, PER, SMALL>), dim3(wgs, ap.groups), dim3(kAvgThreads), lds, s, scores, cells, ap, ctrl, hist, done, lists);
 }
 
 // Dynamic LDS ceilings of the selection kernels: the same constants on every call, set once per process
@@ -3107,15 +3124,15 @@ hipError_t launch_select(const float *scores, const SelectJob &job, int32_t *out
         }
         hipLaunchKernelGGL(sel_init, dim3(n), dim3(kThreads), 0, s, prm, hist, ctrl, done);
         if (wide)
-            launch_averages<0, kAvgWide, true>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
+            launch_averages<0, kAvgWide, true>(scores, cells, ap, job.n_max, n_top, ctrl, hist, done, tie, s);
         else if (small)
-            launch_averages<0, kAvgNarrow, true>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
+            launch_averages<0, kAvgNarrow, true>(scores, cells, ap, job.n_max, n_top, ctrl, hist, done, tie, s);
         else
-            launch_averages<0, kAvgNarrow, false>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
+            launch_averages<0, kAvgNarrow, false>(scores, cells, ap, job.n_max, n_top, ctrl, hist, done, tie, s);
         if (small)
-            launch_averages<1, kAvgNarrow, true>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
+            launch_averages<1, kAvgNarrow, true>(scores, cells, ap, job.n_max, n_top, ctrl, hist, done, tie, s);
         else
-            launch_averages<1, kAvgNarrow, false>(scores, cells, ap, job.n_max, len_max, n_top, ctrl, hist, done, tie, s);
+            launch_averages<1, kAvgNarrow, false>(scores, cells, ap, job.n_max, n_top, ctrl, hist, done, tie, s);
         const uint32_t sort_keys = sort_n > kSortSmall ? std::max(sort_n, kSortLarge) : sort_n;
         hipLaunchKernelGGL(refine, dim3(n), dim3(kThreads), (size_t)sort_keys * sizeof(uint64_t), s, ctrl, cand, tie, sort_n);
     }

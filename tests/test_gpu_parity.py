@@ -807,6 +807,11 @@ AVERAGE_CASES = [
     (16385, 8000, (1,), (1, 16), "random"), (16511, 8000, (1,), (2, 15), "needles"), (33000, 7000, (2, 1), (3, 16, 7), "random"),
     (20001, 8192, (1,), (16,), "few_values"), (4096, 60, (2, 16), (1, 7, 16), "random"), (9216, 300, (9,), (2, 16), "random"),
     (33001, 8000, (1,), (3, 7, 16), "negative"), (33001, 8192, (1, 2), (1, 6), "huge_range"), (33001, 8000, (1,), (3, 7), "tiny"),
+    # .. max kernels with unequal numbers of workgroups: as many as have their place among the first ends, one more, the most, two groups
+    # of average kernels, one cell and none
+    (300000, 3000, tuple(range(1, 9)), (3, 5), "needles"), (300000, 3000, (9, 1, 64, 2, 33, 5, 1, 16, 128), (2, 16), "needles"),
+    (70000, 2000, tuple(range(1, 65)), (3,), "random"), (200000, 4000, (1, 24, 2), tuple(range(1, 22)), "needles"),
+    (1000, 100, (9, 1000, 1024, 2), (1, 3), "random"),
 ]
 
 
