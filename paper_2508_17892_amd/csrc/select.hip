@@ -1006,11 +1006,20 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
         if (SMALL) {
             auto size = [&](int u, const float(&x)[PER]) {
                 const float edge = of_f(l_edge, u);
+                if (PASS == 1) {  // most chunks hold nothing that reaches the cut
+                    bool any = false;
+#pragma unroll
+                    for (int k = 0; k < PER; ++k) {
+                        sum[k] = sum[k] + x[k];
+                        any = any | !(sum[k] < edge);
+                    }
+                    if (__ballot(any) == 0) return;  // uniform
+                }
                 const uint32_t before = queued, els = of(l_len, u), span0 = of(l_span0, u), span1 = of(l_span1, u), shifts = of(l_shift, u);
                 float best = -INFINITY;
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
-                    sum[k] = sum[k] + x[k];
+                    if (PASS == 0) sum[k] = sum[k] + x[k];
                     const bool in = el0 + 64u * k + u / 2 < els;
                     // (what is not counted goes to a word of the lane's own)
                     auto count = [&](float x, bool hit) {
@@ -1094,6 +1103,12 @@ __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, 
                 if (PASS == 1) spill(CHUNK);
                 const float edge = of_f(l_edge, q);
                 const uint32_t before = queued;
+                if (PASS == 1) {
+                    bool any = false;
+#pragma unroll
+                    for (int k = 0; k < PER; ++k) any = any | !(sum[k] < edge);
+                    if (__ballot(any) == 0) continue;  // uniform
+                }
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
                     const bool hit = !(sum[k] < edge) && el0 + 64u * k + (uint32_t)(to - 1) / 2 < len;
