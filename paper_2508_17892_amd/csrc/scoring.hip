@@ -114,13 +114,15 @@ __device__ __forceinline__ float row_offset(float row_max, float row_sumexp) { r
 // the first K tiles.  It saves a launch of 3.8 - 5 us; on the other hand every workgroup of a kv head reads all of the
 // head's partials.  Measured, merge kernel -> this, whole recall: 16 splits (1000 tokens) 33.1 -> 29.1 us, 32 splits
 // (40000 tokens, 32/8 heads, 128 queries) 115.4 -> 113.9 us; 64 splits (20000 tokens fp32) 132.4 -> 134.2 us,
-// 256 splits (100000 tokens, 8/2 heads, 64 queries) 72.2 -> 86.9 us: two splits a sum is where it stops to pay.
+// 256 splits (100000 tokens, 8/2 heads, 64 queries) 72.2 -> 86.9 us.  Two splits a sum is where it stops to pay; four where a workgroup
+// has 128 rows, half the partials (64 splits, 32/8 heads, 32 queries, 32768 tokens 62.5 -> 61.6 us, 100003 103.9 -> 102.6; 256 rows a workgroup,
+// 64 queries 76.8 and 142.4 either way; 128 rows and 128 splits, 28/4 heads, 17 queries, 74.8 -> 76.4).
 constexpr int kCombineLanes = 16;
 constexpr int kMergeSplits = 2 * kCombineLanes;
-template <int SHARERS>
+template <int SHARERS, int ROUNDS>
 __device__ __forceinline__ float merged_offset(const float *pm, const float *pz, int nsplit, int64_t pitch, int part)
 {
-    constexpr int OWN = kCombineLanes / SHARERS, ROUNDS = kMergeSplits / kCombineLanes;
+    constexpr int OWN = kCombineLanes / SHARERS;
     float m[ROUNDS][OWN], z[ROUNDS][OWN];
 #pragma unroll
     for (int k = 0; k < ROUNDS; ++k)
@@ -153,8 +155,8 @@ __device__ __forceinline__ float merged_offset(const float *pm, const float *pz,
 }
 
 // One workgroup's share: NB 32-row blocks a wavefront of query block qb, tiles tile0 .. tile1 - 1 of kv head g.
-// MODE 0: row statistics.  MODE 1: column scores (RMAX = 0 sum over rows, 1 max over rows).
-template <int NB, int WAVES, int MODE, int RMAX>
+// MODE 0: row statistics.  MODE 1: column scores (RMAX = 0 sum over rows, 1 max over rows; MANY: it may have to merge 2 kMergeSplits).
+template <int NB, int WAVES, int MODE, int RMAX, bool MANY>
 __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split, int qb, int64_t tile0, int64_t tile1, bool timed, unsigned long long t_begin)
 {
     using T = Bf16;
@@ -273,8 +275,10 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
         const bool real = rl < a.rows_per_group;
         const int64_t r = (int64_t)g * a.rows_per_group + (real ? rl : a.rows_per_group - 1);
         float off;
-        if (a.merge)
-            off = merged_offset<SHARERS>(a.part_m + r, a.part_z + r, a.nsplit, nrows, tid % SHARERS);
+        if (MANY && a.merge && a.nsplit > kMergeSplits)
+            off = merged_offset<SHARERS, 4>(a.part_m + r, a.part_z + r, a.nsplit, nrows, tid % SHARERS);
+        else if (a.merge)
+            off = merged_offset<SHARERS, 2>(a.part_m + r, a.part_z + r, a.nsplit, nrows, tid % SHARERS);
         else
             off = row_offset(a.row_max[r], a.row_sumexp[r]);
         if (tid % SHARERS == 0) red[local] = real ? off : -INFINITY;
@@ -568,9 +572,9 @@ __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
     }
     if (tile_lo >= tile_hi) return;
     if (MIXED && qb == 1)
-        score_rows<1, WAVES, MODE, RMAX>(a, g, split, qb, tile_lo, tile_hi, timed, t_begin);
+        score_rows<1, WAVES, MODE, RMAX, false>(a, g, split, qb, tile_lo, tile_hi, timed, t_begin);
     else
-        score_rows<NB, WAVES, MODE, RMAX>(a, g, split, qb, tile_lo, tile_hi, timed, t_begin);
+        score_rows<NB, WAVES, MODE, RMAX, NB == 1>(a, g, split, qb, tile_lo, tile_hi, timed, t_begin);
 }
 
 // ---------------------------------------------------------------- fp32 states
@@ -691,7 +695,7 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void score_f32_kernel(const Scor
         const int64_t r = (int64_t)g * a.rows_per_group + (real ? r0 : a.rows_per_group - 1);
         float off;
         if (a.merge)
-            off = merged_offset<SHARERS>(a.part_m + r, a.part_z + r, a.nsplit, nrows, tid % SHARERS);
+            off = merged_offset<SHARERS, 2>(a.part_m + r, a.part_z + r, a.nsplit, nrows, tid % SHARERS);
         else
             off = row_offset(a.row_max[r], a.row_sumexp[r]);
         if (tid % SHARERS == 0) red[local] = real ? off : -INFINITY;
@@ -1018,7 +1022,7 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv, bool mi
     p.grid = (int)(((pairs + kNumXCD - 1) / kNumXCD) * kNumXCD * p.nqb);
     // pass 2's ranges follow the XCDs' speed where a range is long enough for that to matter
     p.balanced = dtype != ILRE_F32 && p.tiles_per_split >= 64 && p.nsplit >= kNumXCD && p.nsplit <= kMaxBalancedSplits;
-    p.merge_in_cols = !p.balanced && p.nsplit <= kMergeSplits;
+    p.merge_in_cols = !p.balanced && p.nsplit <= (dtype == ILRE_F32 || p.nb != 1 ? 1 : 2) * kMergeSplits;
     uint64_t tag = 0x494c52652d584344ull;  // what a table has to have been made for
     for (uint64_t v : {(uint64_t)L, (uint64_t)p.ntiles, (uint64_t)p.nsplit, (uint64_t)p.nqb, (uint64_t)Hkv, (uint64_t)p.tile_tokens,
                        (uint64_t)p.grid})

@@ -122,8 +122,8 @@ def test_unequal_query_blocks_want_a_workspace_for_them():
 @pytest.mark.parametrize("dtype,Lq,G,Hkv", [("bf16", 20, 2, 4), ("bf16", 50, 4, 4), ("bf16", 64, 8, 2), ("f32", 33, 2, 4)],
                          ids=["pair_of_threads_a_row", "4_waves", "8_waves", "f32_two_query_blocks"])
 def test_second_pass_merges_the_partial_statistics(dtype, Lq, G, Hkv):
-    """In the whole path the second scoring pass merges the splits' partial row statistics itself, up to 32 splits, in
-    the order the merge kernel of the staged call uses: the scores are the same bits either way.  Numbers of splits
+    """In the whole path the second scoring pass merges the splits' partial row statistics itself, up to 32 splits (64 where a
+    workgroup has 128 rows), in the order the merge kernel of the staged call uses: the scores are the same bits either way.  Numbers of splits
     (one a tile on these lengths) around the 16 sums and the line; one row beyond every frozen reference, so that a
     split's partial has another reference."""
     tile = 128 if dtype == "bf16" and Lq * G == 512 else 64
@@ -131,7 +131,7 @@ def test_second_pass_merges_the_partial_statistics(dtype, Lq, G, Hkv):
     g.manual_seed(5)
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     q = torch.randn(Hkv * G, Lq, 128, device="cuda", generator=g).to(dt)
-    for n in (1, 2, 15, 16, 17, 24, 31, 32, 33, 100):
+    for n in (1, 2, 15, 16, 17, 24, 31, 32, 33, 48, 63, 64, 65, 100):
         L = tile * n - (n % 3)
         _announce(f"partials merged in pass 2: {dtype} Lq={Lq} G={G} Hkv={Hkv} L={L}")
         k = torch.randn(Hkv, L, 128, device="cuda", generator=g).to(dt)
