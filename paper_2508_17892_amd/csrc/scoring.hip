@@ -114,9 +114,10 @@ __device__ __forceinline__ float row_offset(float row_max, float row_sumexp) { r
 // the first K tiles.  It saves a launch of 3.8 - 5 us; on the other hand every workgroup of a kv head reads all of the
 // head's partials.  Measured, merge kernel -> this, whole recall: 16 splits (1000 tokens) 33.1 -> 29.1 us, 32 splits
 // (40000 tokens, 32/8 heads, 128 queries) 115.4 -> 113.9 us; 64 splits (20000 tokens fp32) 132.4 -> 134.2 us,
-// 256 splits (100000 tokens, 8/2 heads, 64 queries) 72.2 -> 86.9 us.  Two splits a sum is where it stops to pay; four where a workgroup
-// has 128 rows, half the partials (64 splits, 32/8 heads, 32 queries, 32768 tokens 62.5 -> 61.6 us, 100003 103.9 -> 102.6; 256 rows a workgroup,
-// 64 queries 76.8 and 142.4 either way; 128 rows and 128 splits, 28/4 heads, 17 queries, 74.8 -> 76.4).
+// 256 splits (100000 tokens, 8/2 heads, 64 queries) 72.2 -> 86.9 us.  Two splits a sum is where it stops to pay with 256 rows a
+// workgroup (64 queries, 32768 and 100003 tokens 76.8 and 142.4 us either way), four with 128, which are half the partials (64
+// splits, 32/8 heads, 32 queries 62.5 -> 61.6 and 103.9 -> 102.6; 128 splits, 28/4 heads, 17 queries, 100003 tokens 74.8 -> 76.4), and with
+// 512, where half as many workgroups read them (28/4 heads, 64 queries 74.6 -> 73.2 and 134.2 -> 133.3).
 constexpr int kCombineLanes = 16;
 constexpr int kMergeSplits = 2 * kCombineLanes;
 template <int SHARERS, int ROUNDS>
@@ -528,7 +529,7 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
 
 // MIXED: two query blocks a kv head, of which the second is one 32-row block a wavefront.  Workgroups 32 slots apart share a compute
 // unit, so that every other 32 slots have the two blocks the other way round: one of each kind a compute unit.
-template <int NB, int WAVES, int MODE, int RMAX, bool MIXED>
+template <int NB, int WAVES, int MODE, int RMAX, bool MIXED, bool MANY = false>
 __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
 {
     // blockIdx -> (kv head, token split, query block).  Workgroups are dealt round-robin to the 8
@@ -574,7 +575,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
     if (MIXED && qb == 1)
         score_rows<1, WAVES, MODE, RMAX, false>(a, g, split, qb, tile_lo, tile_hi, timed, t_begin);
     else
-        score_rows<NB, WAVES, MODE, RMAX, NB == 1>(a, g, split, qb, tile_lo, tile_hi, timed, t_begin);
+        score_rows<NB, WAVES, MODE, RMAX, MANY>(a, g, split, qb, tile_lo, tile_hi, timed, t_begin);
 }
 
 // ---------------------------------------------------------------- fp32 states
@@ -1022,7 +1023,7 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv, bool mi
     p.grid = (int)(((pairs + kNumXCD - 1) / kNumXCD) * kNumXCD * p.nqb);
     // pass 2's ranges follow the XCDs' speed where a range is long enough for that to matter
     p.balanced = dtype != ILRE_F32 && p.tiles_per_split >= 64 && p.nsplit >= kNumXCD && p.nsplit <= kMaxBalancedSplits;
-    p.merge_in_cols = !p.balanced && p.nsplit <= (dtype == ILRE_F32 || p.nb != 1 ? 1 : 2) * kMergeSplits;
+    p.merge_in_cols = !p.balanced && p.nsplit <= (dtype != ILRE_F32 && (p.nb == 1 || p.waves == 8) ? 2 : 1) * kMergeSplits;
     uint64_t tag = 0x494c52652d584344ull;  // what a table has to have been made for
     for (uint64_t v : {(uint64_t)L, (uint64_t)p.ntiles, (uint64_t)p.nsplit, (uint64_t)p.nqb, (uint64_t)Hkv, (uint64_t)p.tile_tokens,
                        (uint64_t)p.grid})
@@ -1082,14 +1083,17 @@ hipError_t launch_col_scores(const ScorePlan &p, const ScoreArgs &a, int score_m
         e = mx ? launch_score(score_f32_kernel<1, 1>, p.grid, kF32Waves * 64, lds, a, s)
                : launch_score(score_f32_kernel<1, 0>, p.grid, kF32Waves * 64, lds, a, s);
     else if (p.nb == 1)
-        e = mx ? launch_score(score_kernel<1, 4, 1, 1, false>, p.grid, 256, lds, a, s)
-               : launch_score(score_kernel<1, 4, 1, 0, false>, p.grid, 256, lds, a, s);
+        e = mx ? launch_score(score_kernel<1, 4, 1, 1, false, true>, p.grid, 256, lds, a, s)
+               : launch_score(score_kernel<1, 4, 1, 0, false, true>, p.grid, 256, lds, a, s);
     else if (p.mixed)
         e = mx ? launch_score(score_kernel<2, 4, 1, 1, true>, p.grid, 256, lds, a, s)
                : launch_score(score_kernel<2, 4, 1, 0, true>, p.grid, 256, lds, a, s);
     else if (p.waves == 4)
         e = mx ? launch_score(score_kernel<2, 4, 1, 1, false>, p.grid, 256, lds, a, s)
                : launch_score(score_kernel<2, 4, 1, 0, false>, p.grid, 256, lds, a, s);
+    else if (a.merge && a.nsplit > kMergeSplits)  // (of its own: with both in one kernel up to 32 splits took 0.4 % longer)
+        e = mx ? launch_score(score_kernel<2, 8, 1, 1, false, true>, p.grid, 512, lds, a, s)
+               : launch_score(score_kernel<2, 8, 1, 0, false, true>, p.grid, 512, lds, a, s);
     else
         e = mx ? launch_score(score_kernel<2, 8, 1, 1, false>, p.grid, 512, lds, a, s)
                : launch_score(score_kernel<2, 8, 1, 0, false>, p.grid, 512, lds, a, s);

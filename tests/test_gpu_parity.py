@@ -123,7 +123,7 @@ def test_unequal_query_blocks_want_a_workspace_for_them():
                          ids=["pair_of_threads_a_row", "4_waves", "8_waves", "f32_two_query_blocks"])
 def test_second_pass_merges_the_partial_statistics(dtype, Lq, G, Hkv):
     """In the whole path the second scoring pass merges the splits' partial row statistics itself, up to 32 splits (64 where a
-    workgroup has 128 rows), in the order the merge kernel of the staged call uses: the scores are the same bits either way.  Numbers of splits
+    workgroup has 128 or 512 rows), in the order the merge kernel of the staged call uses: the scores are the same bits either way.  Numbers of splits
     (one a tile on these lengths) around the 16 sums and the line; one row beyond every frozen reference, so that a
     split's partial has another reference."""
     tile = 128 if dtype == "bf16" and Lq * G == 512 else 64
