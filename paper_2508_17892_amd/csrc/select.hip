@@ -815,7 +815,8 @@ __device__ __forceinline__ uint32_t find_cut(const uint32_t *h, uint32_t need)
 // Bound: instructions and LDS round trips of few workgroups on short contexts, additions to the global counts on long ones.
 // Measured (kernel trace), 48 combinations, budget 4096, before -> after (before: every combination pooled its own
 // windows, two histogram passes): counting 29.6 + 26 -> 10.1 us on 128K tokens, 40.6 + 34.0 -> 15.9 us on 1M; collecting
-// 8.1 -> 10.5 us and 23.6 -> 21.1 us; the separate max pooling, 4.7 and 10.1 us, is gone.
+// 8.1 -> 10.5 us and 23.6 -> 21.1 us; the separate max pooling, 4.7 and 10.1 us, is gone.  (1M since workgroups follow the cells, and
+// collecting passes over what cannot reach the cut: 18.2 and 14.1.)
 template <int PASS, int PER, bool SMALL>
 __global__ __launch_bounds__(kAvgThreads) void pool_averages(const float *body, float *cells, const AvgParams ap, SelCtrl *ctrl,
                                                              uint32_t *hist, uint32_t *done, uint64_t *lists)
