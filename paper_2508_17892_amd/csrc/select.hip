@@ -2758,18 +2758,21 @@ hipError_t raise_avg_lds()
 }
 
 // One chunk of windows a wavefront where that is at most two workgroups a compute unit, more of them beyond: a
-// workgroup carries the clearing and flushing of its 16 KiB of counts.  Max kernels get workgroups in proportion to their
-// cells (as many each, cells of 2 had four times as much a workgroup as cells of 8: whole selection, budget 4096, 48 combinations 4M
-// scores 173.7 -> 160.3 us; max kernels 1, 2, 4, 8, 16 with four others 1M 142.5 -> 109.7; 64 max kernels 1M 355 -> 231).  Half as many
-// in all: 166, 120 and 231 us; the counts are added up a line at a time, but fewer workgroups sum longer.
+// workgroup carries the clearing and flushing of its 16 KiB of counts, and all want the same lines of the global ones.  Of chunks of
+// kAvgWide up to two a wavefront with one workgroup a compute unit (whole selection, budget 4096, 1M scores, two workgroups -> one: 48
+// combinations 88.7 -> 86.8 us, uniform scores 68.6 -> 66.8, one of cells of 1, windows of 7 74.4 -> 71.4; 4M scores, up to seven chunks, 148.9
+// -> 154.5; chunks of kAvgNarrow, 20 combinations of 512K 68.1 -> 72.5).
+// Max kernels get workgroups in proportion to their cells (as many each, cells of 2 had four times as much a workgroup as cells
+// of 8: 48 combinations 4M scores 173.7 -> 160.3 us; max kernels 1, 2, 4, 8, 16 with four others 1M 142.5 -> 109.7; 64 max kernels 1M 355 -> 231).
 template <int PASS, int PER, bool SMALL>
 void launch_averages(const float *scores, float *cells, AvgParams &ap, int n_max, int n_top, SelCtrl *ctrl, uint32_t *hist, uint32_t *done,
                      uint64_t *lists, hipStream_t s)
 {
     constexpr uint64_t per_wg = kAvgWaves * 64 * PER;
-    const uint64_t most = std::max(2 * kNumCU / ap.groups, 16 * n_max);
     uint64_t all = 0;
     for (int i = 0; i < n_max; ++i) all += ap.len[i];
+    const int per_cu = PASS == 0 && PER == kAvgWide && all <= 2 * kNumCU * per_wg ? 1 : 2;
+    const uint64_t most = std::max(per_cu * kNumCU / ap.groups, 16 * n_max);
     uint32_t wgs = 0;
     for (int i = 0; i < ILRE_MAX_POOL_KERNELS; ++i) {
         if (i < n_max) wgs += (uint32_t)std::max<uint64_t>(std::min((ap.len[i] + n_top + per_wg - 1) / per_wg, most * ap.len[i] / std::max<uint64_t>(all, 1)), 1);
