@@ -581,12 +581,13 @@ __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
 // ---------------------------------------------------------------- fp32 states
 //
 // The fp32 matrix instructions run at a sixteenth of the bf16 rate.  An fp32 number is the sum of three bf16 numbers, exactly
-// (24 bits of significand, 8 each: x = h + m + l with h cut off, m and l rounded), and a product of two such sums is the nine
-// products of their parts, each exact in fp32.  Six of them are taken, added up in fp32: what is left out (m l, l m and l l) is
-// 2^-26 of a product at most, less than the rounding of one addition.  The large products (h h) have an accumulator of their own and
-// the others two, so that a logit sees 8 roundings at its own size, where the fp32 instructions took 64.  (Splitting into parts:
-// Dekker, Numerische Mathematik 18 (1971); several low-precision products for one of high precision: Henry, Tang and Heinecke,
-// ARITH 2019.)
+// (24 bits of significand: x = h + m + l, each the rest rounded to nearest, so that m is 2^-8 of x at most and l 2^-17), and a
+// product of two such sums is the nine products of their parts, each exact in fp32.  Six of them are taken, added up in fp32: what
+// is left out (m l, l m and l l) is 2^-24 of a product at most, as much as the rounding of one addition, and 2^-27.5 rms (h cut off
+// instead of rounded: m reaches 2^-7, l 2^-16, and what is left out 2^-22).  The large products (h h) have an accumulator of their
+// own and the others two, so that a logit sees 8 roundings at its own size, where the fp32 instructions took 64.  (Splitting into
+// parts: Dekker, Numerische Mathematik 18 (1971); several low-precision products for one of high precision: Henry, Tang and
+// Heinecke, ARITH 2019.)
 //
 // A workgroup owns 128 query rows of a kv head, 32 a wavefront, whose parts stay in registers, and streams 32 tokens of K at a
 // time: a thread fetches 64 bytes a tile ahead, splits them and writes the three parts to LDS, chunks swizzled as above.  Two
@@ -594,7 +595,9 @@ __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
 // Bound: 48 matrix instructions of 32 cycles for 32 x 32 logits (the fp32 instructions: 4096 cycles), 1.2 PFLOP/s of them on 32768 tokens
 // and 8192 rows, what the matrix pipe reaches beside such vector work.  Measured, whole recall, fp32 instructions -> so: 4096
 // tokens, 32/8 heads, 32 queries 62.9 -> 40.3 us; 32768 tokens, 256 queries 1107 -> 713 us.  Errors against 64 bits, logarithms of
-// the rows' sums: 4.1e-7 -> 3.0e-7 rms, 1.5e-6 -> 0.9e-6 largest; scores 2.4e-6 -> 1.1e-6 largest.  (The softmax arithmetic a tile
+// the rows' sums: 4.1e-7 -> 3.0e-7 rms, 1.5e-6 -> 1.1e-6 largest; scores 2.4e-6 -> 1.1e-6 largest; single logits of normally distributed
+// states with 1, 2, 4, 16 and 128 channels at work 3.6e-8, 3.4e-8, 3.1e-8, 2.9e-8, 2.8e-8 -> 3.6e-8, 3.1e-8, 2.5e-8, 1.6e-8, 1.0e-8 rms of
+// the sum of their products' magnitudes, 1.6, 2.2, 2.9, 3.8, 3.9 -> 2.0, 2.2, 2.3, 2.7, 1.5 times 2^-24 largest.  (The softmax arithmetic a tile
 // behind the matrix instructions, as in score_kernel: 3 % faster on 32768 tokens, 3 % slower on 4096.)
 constexpr int kF32Waves = 4, kF32Tokens = 32;
 constexpr int kF32Plane = kF32Tokens * 256, kF32Buffer = 3 * kF32Plane;  // bytes
@@ -605,20 +608,22 @@ static_assert(2 * kF32Parts * kF32Pitch >= kF32Waves * 32, "holds the rows' offs
 struct Parts {
     uint4 h, m, l;
 };
+constexpr float kLargestBf16 = 0x1.fep127f;
 __device__ __forceinline__ Parts split3(const float4 &a, const float4 &b)
 {
     typedef __attribute__((ext_vector_type(2))) float f32x2;
     typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
     const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    auto round2 = [](float x0, float x1) { return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){x0, x1}, bf16x2)); };
+    auto near = [](float x) { return __builtin_amdgcn_fmed3f(x, -kLargestBf16, kLargestBf16); };  // (no finite number rounds to infinity)
     uint32_t h[4], m[4], l[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const uint32_t x0 = __float_as_uint(x[2 * i]), x1 = __float_as_uint(x[2 * i + 1]);
-        h[i] = __builtin_amdgcn_perm(x1, x0, 0x07060302);  // the upper halves
-        const float r0 = x[2 * i] - __uint_as_float(x0 & 0xFFFF0000u), r1 = x[2 * i + 1] - __uint_as_float(x1 & 0xFFFF0000u);
-        m[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){r0, r1}, bf16x2));
-        const float l0 = r0 - __uint_as_float(m[i] << 16), l1 = r1 - __uint_as_float(m[i] & 0xFFFF0000u);
-        l[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){l0, l1}, bf16x2));
+        const float x0 = x[2 * i], x1 = x[2 * i + 1];
+        h[i] = round2(near(x0), near(x1));
+        const float r0 = x0 - __uint_as_float(h[i] << 16), r1 = x1 - __uint_as_float(h[i] & 0xFFFF0000u);
+        m[i] = round2(r0, r1);
+        l[i] = round2(r0 - __uint_as_float(m[i] << 16), r1 - __uint_as_float(m[i] & 0xFFFF0000u));
     }
     return {make_uint4(h[0], h[1], h[2], h[3]), make_uint4(m[0], m[1], m[2], m[3]), make_uint4(l[0], l[1], l[2], l[3])};
 }

@@ -360,7 +360,7 @@ def _end_to_end(inp, kernels, budget):
 def test_fp32_states_keep_their_precision(L, Lq, Hq, Hkv, spread):
     """fp32 states against 64 bits, at the edges of the kernels' tiles (32 tokens, 128 rows) and with channels of very different
     scale.  A logit sees 8 additions at its own size, 40 at 2^-8 of it and a few more, each rounded to 2^-24, and products that
-    are 2^-26 short: within 16 * 2^-24 of the sum of its products' magnitudes.  A row's logarithm of a sum moves by no more
+    are 2^-24 short at most: within 16 * 2^-24 of the sum of its products' magnitudes.  A row's logarithm of a sum moves by no more
     than the worst of its logits, the sum's own rounding (2^-24 for each of its levels, 64 tokens a lane and 16 splits at most) and
     the exponentials' (2^-22 with the scaling)."""
     _announce(f"fp32 precision L={L} Lq={Lq} {Hq}/{Hkv} spread {spread}")
@@ -381,6 +381,45 @@ def test_fp32_states_keep_their_precision(L, Lq, Hq, Hkv, spread):
         want = top + np.log(np.exp(s - top[:, None]).sum(axis=1))
         bound = 16 * 2.0 ** -24 * size.max(axis=1) + 2.0 ** -22 * (1 + np.abs(s).max(axis=1)) + 80 * 2.0 ** -24
         assert (np.abs(got[h * Lq:(h + 1) * Lq] - want) <= bound).all(), (h, np.abs(got[h * Lq:(h + 1) * Lq] - want).max(), bound.min())
+
+
+@pytest.mark.parametrize("channels", [1, 2, 3, 4])
+@pytest.mark.parametrize("kind", ["normal", "worst"])
+def test_fp32_products_keep_their_precision(kind, channels):
+    """Single logits (one token, exact row maxima) of fp32 states with few channels at work, where rounding does not average out.
+    Each channel's large product is added with a rounding of 2^-24 but the first, the other parts with one more, what is left
+    out of a product is 2^-24 at most, and the maximum leaves the library with one multiplication by ln 2: channels + 2 of
+    them, with 2^-6 on top for the rounding of the small parts.  `worst`: significands that leave the most out where the parts are cut off
+    instead of rounded (2^-22 of a product)."""
+    _announce(f"fp32 products, {channels} channels {kind}")
+    rng = np.random.default_rng(channels)
+    Hkv, Lq, ln2 = 64, 256, np.float32(np.log(2.0))
+    assert np.float32(ln2 * np.float32(1.4426950408889634)) == 1  # the scale that makes logits of base 2 the products themselves
+    q, k = np.zeros((Hkv, Lq, 128), np.float32), np.zeros((Hkv, 1, 128), np.float32)
+    for x in (q, k):
+        some = rng.standard_normal(x.shape[:2] + (channels,))
+        x[..., rng.choice(128, channels, replace=False) if x is q else np.flatnonzero(q[0, 0])] = some if kind == "normal" else 1.0078 + 1e-5 * some
+    row_max, _ = il.ilre_row_stats(torch.from_numpy(q).cuda(), torch.from_numpy(k).cuda(), scale=float(ln2), flags=il.ILRE_FLAG_EXACT_ROW_MAX)
+    torch.cuda.synchronize()
+    got = row_max.cpu().numpy().astype(np.float64).reshape(Hkv, Lq) / np.float64(ln2)
+    products = q.astype(np.float64) * k.astype(np.float64)
+    off = np.abs(got - products.sum(-1)) / np.abs(products).sum(-1)
+    assert off.max() <= (channels + 2) * 2.0 ** -24 * (1 + 2.0 ** -6), off.max() * 2.0 ** 24
+
+
+def test_fp32_states_near_the_largest_float():
+    """The largest floats would round to an infinite bf16; products that are finite stay so."""
+    _announce("fp32 states near the largest float")
+    top = np.finfo(np.float32).max
+    k = np.zeros((1, 3, 128), np.float32)
+    k[0, 0, 0], k[0, 1, 0], k[0, 2, 0] = top, -top, np.float32(3.3961e38)
+    q = np.zeros((1, 2, 128), np.float32)
+    q[0, 0, 0], q[0, 1, 0] = 1.0, -0.3
+    row_max, row_sum = il.ilre_row_stats(torch.from_numpy(q).cuda(), torch.from_numpy(k).cuda(), scale=1e-37)
+    torch.cuda.synchronize()
+    got = row_max.cpu().numpy().astype(np.float64) + np.log(row_sum.cpu().numpy().astype(np.float64))
+    s = np.float64(np.float32(1e-37)) * (q[0].astype(np.float64) @ k[0].astype(np.float64).T)
+    np.testing.assert_allclose(got, np.log(np.exp(s).sum(axis=1)), rtol=1e-6)
 
 
 def test_end_to_end_cfg1():
