@@ -605,8 +605,11 @@ constexpr int kF32Parts = 2 * kF32Waves, kF32Pitch = kF32Tokens + 4;    // pass 
 constexpr size_t kF32Lds = 2 * kF32Buffer + 2 * kF32Parts * kF32Pitch * sizeof(float);
 static_assert(2 * kF32Parts * kF32Pitch >= kF32Waves * 32, "holds the rows' offsets first");
 
+// m and l lie in the range of x as well (without a scale a number below 2^-110 lost the bits below 2^-134, which a large partner
+// brings back: 1e-38 times 3.4e38 was 1e-3 off); 2^8 would take the largest floats' m to infinity.
+constexpr float kPartScale = 128.0f;
 struct Parts {
-    uint4 h, m, l;
+    uint4 h, m, l;  // x = h + m / kPartScale + l / kPartScale^2
 };
 constexpr float kLargestBf16 = 0x1.fep127f;
 __device__ __forceinline__ Parts split3(const float4 &a, const float4 &b)
@@ -622,8 +625,9 @@ __device__ __forceinline__ Parts split3(const float4 &a, const float4 &b)
         const float x0 = x[2 * i], x1 = x[2 * i + 1];
         h[i] = round2(near(x0), near(x1));
         const float r0 = x0 - __uint_as_float(h[i] << 16), r1 = x1 - __uint_as_float(h[i] & 0xFFFF0000u);
-        m[i] = round2(r0, r1);
-        l[i] = round2(r0 - __uint_as_float(m[i] << 16), r1 - __uint_as_float(m[i] & 0xFFFF0000u));
+        const float s0 = r0 * kPartScale, s1 = r1 * kPartScale;
+        m[i] = round2(s0, s1);
+        l[i] = round2((s0 - __uint_as_float(m[i] << 16)) * kPartScale, (s1 - __uint_as_float(m[i] & 0xFFFF0000u)) * kPartScale);
     }
     return {make_uint4(h[0], h[1], h[2], h[3]), make_uint4(m[0], m[1], m[2], m[3]), make_uint4(l[0], l[1], l[2], l[3])};
 }
@@ -728,7 +732,7 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void score_f32_kernel(const Scor
             stage(buf ^ 1);
             if (tile + 2 < tile1) fetch(tile + 2);
         }
-        f32x16 big, s1, s2;
+        f32x16 big, s1, s2;  // of the logits, kPartScale and kPartScale^2 times them
 #pragma unroll
         for (int v = 0; v < 16; ++v) big[v] = s1[v] = s2[v] = 0.f;
         const unsigned char *kb = smem + buf * kF32Buffer;
@@ -742,16 +746,16 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void score_f32_kernel(const Scor
         for (int st = 0; st < STEPS; ++st) {
             const uint4 kh = *(const uint4 *)(kb + frag[st]), km = *(const uint4 *)(kb + frag[st] + kF32Plane),
                         kl = *(const uint4 *)(kb + frag[st] + 2 * kF32Plane);
-            mma(s1, kh, qf[st].l);
+            mma(s2, kh, qf[st].l);
+            mma(s1, km, qf[st].h);
             mma(s2, kl, qf[st].h);
-            mma(s1, km, qf[st].m);
-            mma(s2, km, qf[st].h);
             mma(s1, kh, qf[st].m);
+            mma(s2, km, qf[st].m);
             mma(big, kh, qf[st].h);
         }
         const int64_t tok0 = first_token(tile);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) big[v] += s1[v] + s2[v];
+        for (int v = 0; v < 16; ++v) big[v] = fmaf(fmaf(s2[v], 1.0f / kPartScale, s1[v]), 1.0f / kPartScale, big[v]);
         if (MODE == 0) {
             if (tok0 + kF32Tokens > a.L)  // uniform
                 row_update<true>(big, a.c, m, z, tok0 + 4 * half, a.L);

@@ -407,6 +407,27 @@ def test_fp32_products_keep_their_precision(kind, channels):
     assert off.max() <= (channels + 2) * 2.0 ** -24 * (1 + 2.0 ** -6), off.max() * 2.0 ** 24
 
 
+@pytest.mark.parametrize("small", [1e-25, 1e-32, 3e-35, 2.0 ** -126, 2.0 ** -132])
+@pytest.mark.parametrize("which", ["keys", "queries"])
+def test_fp32_states_of_any_magnitude(small, which):
+    """Small states with partners as large as brings their products back to one: the products' errors are those of usual states (16 *
+    2^-24 of the sum of their magnitudes, as above; the two multiplications behind it 2 * 2^-24), and the parts of a number below
+    2^-126 are multiples of 2^-147."""
+    _announce(f"fp32 states, {which} of {small}")
+    rng = np.random.default_rng(7)
+    large = min(1.0 / small, 2.0 ** 120)
+    q, k = rng.standard_normal((8, 16, 128)), rng.standard_normal((8, 1, 128))
+    q, k = (q * large, k * small) if which == "keys" else (q * small, k * large)
+    q, k, ln2 = q.astype(np.float32), k.astype(np.float32), np.float32(np.log(2.0))
+    row_max, _ = il.ilre_row_stats(torch.from_numpy(q).cuda(), torch.from_numpy(k).cuda(), scale=float(ln2), flags=il.ILRE_FLAG_EXACT_ROW_MAX)
+    torch.cuda.synchronize()
+    got = row_max.cpu().numpy().astype(np.float64).reshape(8, 16) / np.float64(ln2)
+    products = q.astype(np.float64) * k.astype(np.float64)
+    bound = 18 * 2.0 ** -24 * np.abs(products).sum(-1) + 2.0 ** -148 * np.abs(q if which == "keys" else k).astype(np.float64).sum(-1)
+    off = np.abs(got - products.sum(-1))
+    assert (off <= bound).all(), (off / bound).max()
+
+
 def test_fp32_states_near_the_largest_float():
     """The largest floats would round to an infinite bf16; products that are finite stay so."""
     _announce("fp32 states near the largest float")
