@@ -1476,8 +1476,10 @@ __device__ bool rank_keys(RankShared &sh, uint64_t *srt, const uint64_t (&key)[P
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-            bin[k] = part_of(key[k]);
-            if (have >> k & 1u) place[k] = atomicAdd(&sh.bin_n[bin[k]], 1u);
+            if (have >> k & 1u) {  // (the other keys may lie outside the bins)
+                bin[k] = part_of(key[k]);
+                place[k] = atomicAdd(&sh.bin_n[bin[k]], 1u);
+            }
         }
         __syncthreads();
         const uint4 n4 = *(const uint4 *)&sh.bin_n[4 * threadIdx.x];

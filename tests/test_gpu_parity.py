@@ -742,6 +742,19 @@ def test_walk_over_bitmap_and_word_table(L, sink, budget, windows, mk, ak):
     assert got_p[:n].tolist() == oracle.allocate_max_avg(s, mk, ak, budget, sink=sink).tolist() and (got_p[n:] == -1).all()
 
 
+def _crowd_between(L, rng):
+    """A crowd in one of the ranking's bins, a few values so far above it that they stretch the bins, and the rest so far
+    below it that it would lie beyond the last bin: keys that are not ranked have no bin."""
+    s = (1e-6 * rng.random(L)).astype(np.float32)
+    at = rng.permutation(L)[:820]
+    s[at[:20]] = 1e6 * (1.0 + rng.random(20))
+    s[at[20:]] = 1.0 + 1e-4 * rng.random(800)
+    bits = np.sort(s.view(np.uint32))[::-1].astype(np.int64)  # positive floats rank as their bits do
+    shift = max(0, int(bits[0] - bits[819]).bit_length() - 11)
+    assert bits[20] - bits[819] < 1 << shift and bits[0] - bits[820] >> shift >= 2048
+    return s
+
+
 BRIEF_CASES = [
     # L, sink, budget, windows, kind: selections that one workgroup does (up to 16384 tokens, 2048 kept, windows of up to 65), at the edges
     # of what its threads take and of the rule
@@ -750,6 +763,7 @@ BRIEF_CASES = [
     (16384, 0, 2048, (1, 3, 7, 15, 31), "needles"), (16384, 1, 2048, (65,), "two_values"), (16385, 0, 2048, (65,), "random"), (16380, 4, 2049, (3,), "random"),
     (9000, 0, 500, (67, 3), "random"), (5000, 0, 2000, (5, 5, 5), "equal"), (12000, 3, 900, (3, 33), "outliers"), (16000, 0, 1500, (1, 3), "denormal"),
     (6000, 2, 700, (9, 31), "signed"), (6000, 2, 2048, (9, 65), "half_zero"), (16384, 0, 2048, (3, 31), "one_far"), (7000, 0, 40, tuple(range(1, 65, 2)) * 2, "flat"),
+    (9000, 0, 600, (3, 7), "crowd_between"), (3000, 1, 600, (1,), "crowd_between"),
 ]
 
 
@@ -760,6 +774,8 @@ def test_short_selections_in_one_launch(L, sink, budget, windows, kind):
     if kind == "one_far":
         s = (1.0 + 0.01 * rng.random(L)).astype(np.float32)
         s[L // 3] = 1e30
+    elif kind == "crowd_between":
+        s = _crowd_between(L, rng)
     elif kind in ("random", "few_values", "two_values", "equal", "narrow", "needles"):
         s = _scores_for(kind, L, rng)
     else:
@@ -801,6 +817,7 @@ SHORT_CASES = [
     (40000, 2, 1500, (1, 8), (4, 5), "two_values"), (40000, 0, 8192, (2,), (4,), "one_far"), (64 * 4096, 0, 64, (1,), (5,), "random"),
     (64 * 4096 + 1, 0, 64, (1,), (5,), "random"), (70000, 0, 4096, (2,), (1, 2, 3, 4), "narrow"), (300001, 0, 64, (2, 4, 8), (1, 2, 3, 4, 5, 6), "flat"),
     (100003, 0, 4000, (8,), (1, 2, 3, 17, 33), "needles"), (60000, 0, 2000, (3,), (15,), "mostly_equal"),
+    (4000, 0, 600, (1,), (1,), "crowd_between"), (13000, 0, 600, (1,), (1, 2), "crowd_between"), (40000, 0, 600, (1,), (1,), "crowd_between"),
 ]
 
 
@@ -811,6 +828,8 @@ def test_few_windows_are_ranked_by_a_workgroup(L, sink, budget, mk, ak, kind):
     if kind == "one_far":          # a range that leaves nearly everything in a few bins
         s = (1.0 + 0.01 * rng.random(L)).astype(np.float32)
         s[L // 3] = 1e30
+    elif kind == "crowd_between":
+        s = _crowd_between(L, rng)
     elif kind == "mostly_equal":   # parts that hand on all they have
         s = np.full(L, 0.5, dtype=np.float32)
         s[rng.integers(0, L, 300)] = 0.75
