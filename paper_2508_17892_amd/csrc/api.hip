@@ -96,7 +96,7 @@ template <typename NEED>
 ilre::ScorePlan plan_within(size_t have, int dtype, int64_t L, int Lq, int Hq, int Hkv, const NEED &need)
 {
     const ilre::ScorePlan p = ilre::make_score_plan(dtype, L, Lq, Hq, Hkv, true);
-    return p.mixed && have < need(p) ? ilre::make_score_plan(dtype, L, Lq, Hq, Hkv, false) : p;
+    return have < need(p) ? ilre::make_score_plan(dtype, L, Lq, Hq, Hkv, false) : p;
 }
 
 int check_shape(int64_t L, int32_t Lq, int32_t Hq, int32_t Hkv, int32_t d, int32_t dtype)

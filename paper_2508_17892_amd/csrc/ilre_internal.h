@@ -77,8 +77,9 @@ struct ScoreArgs {
     float *dump;                        // 16 floats nobody reads: target of stores that have nothing to store
 };
 
-// `mix`: query blocks may be of unequal size, which can take one partial score vector more a kv head.
-ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv, bool mix);
+// `roomy`: query blocks may be of unequal size, which can take one partial score vector more a kv head, and workgroups may run in
+// several rounds, which takes partial row statistics for each.
+ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv, bool roomy);
 
 // With a.merge the partials are all that is left behind.
 hipError_t launch_row_stats(const ScorePlan &p, const ScoreArgs &a, float *row_max, float *row_sumexp, hipStream_t s);

@@ -984,7 +984,7 @@ hipError_t launch_score(K kernel, int grid, int threads, size_t lds, const Score
 
 }  // namespace
 
-ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv, bool mix)
+ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv, bool roomy)
 {
     ScorePlan p{};
     p.dtype = dtype;
@@ -1006,7 +1006,7 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv, bool mi
         // 257 - 384 rows: a block of 256 and one of 128, which a quarter of 512 would be padding for (whole recall, 384 rows a kv head,
         // 9000 tokens 64.5 -> 60.3 us, 50001 130.2 -> 124.0, 400000 799 -> 755; 280 rows, 131072 tokens 251 -> 240).  513 - 640 rows as
         // two and one are no faster than three, the larger blocks decide: 600 rows, 131072 tokens 411 and 405 us, 800 of 4 heads 259 and 274.
-        p.mixed = mix && p.rows_per_group > 256 && p.rows_per_group <= 384;
+        p.mixed = roomy && p.rows_per_group > 256 && p.rows_per_group <= 384;
         if (p.mixed) p.waves = 4;
     }
     p.tile_tokens = dtype == ILRE_F32 ? kF32Tokens : Bf16::tile_tokens(p.waves);
@@ -1018,16 +1018,33 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv, bool mi
     // more workgroups than that, because one too many runs behind all others, for as long as they do.  (Splits rounded up to
     // the next number, 131072 tokens: 28/4 heads, 630 rows a kv head, 516 workgroups 287 us a call, 504 220; 64/8, 1360 rows, 528 1226
     // us, 480 752; 28/4, 1050 rows, 500 workgroups, but 65 on some XCDs 443 us, 480, 60 an XCD, 363.)
+    // Several rounds of workgroups where that takes a quarter off the tiles one place goes through, two a workgroup for its start
+    // counted in: query blocks that are many against an XCD's places leave most of them empty otherwise, or have no round of their own.
+    // (One round, then so, 131072 tokens: 16/2 heads, 2080 queries 10.81 -> 2.37 ms, 64/4, 1360 11.77 -> 5.69, 32/1, 540 12.17 -> 1.34, 40/5, 1280
+    // 6.11 -> 3.90; fp32, 32768 tokens, 32/1, 260 6.85 -> 0.91.  Splits rounded up: 2.90, 6.14, 1.79, 4.73, 1.63.)
     const int room = kNumCU / kNumXCD * (p.waves == 8 ? 1 : 2);
-    int64_t nsplit = (int64_t)kNumXCD * (room / p.nqb) / Hkv;
-    if (nsplit < 1) nsplit = 1;
     const int64_t step = dtype == ILRE_F32 ? 2 : 1;  // a split's tiles come in twos there
-    nsplit = std::min(nsplit, (p.ntiles + step - 1) / step);
-    // few tiles: no more splits than pass 2 merges itself (4096 tokens, 32/8 heads, 32 queries 42.6 -> 40.3 us; with eight tiles 8192 tokens, 16/4
-    // heads, 16 queries 40.8 -> 49.7)
-    if (dtype == ILRE_F32 && nsplit > kMergeSplits && p.ntiles <= 4 * kMergeSplits) nsplit = kMergeSplits;
-    p.tiles_per_split = step * ((p.ntiles + step * nsplit - 1) / (step * nsplit));
-    p.nsplit = (int)((p.ntiles + p.tiles_per_split - 1) / p.tiles_per_split);
+    auto cut = [&](int rounds) {
+        int64_t nsplit = std::max<int64_t>((int64_t)kNumXCD * ((int64_t)rounds * room / p.nqb) / Hkv, 1);
+        nsplit = std::min(nsplit, (p.ntiles + step - 1) / step);
+        // few tiles: no more splits than pass 2 merges itself (4096 tokens, 32/8 heads, 32 queries 42.6 -> 40.3 us; with eight tiles 8192 tokens,
+        // 16/4 heads, 16 queries 40.8 -> 49.7)
+        if (dtype == ILRE_F32 && nsplit > kMergeSplits && p.ntiles <= 4 * kMergeSplits) nsplit = kMergeSplits;
+        p.tiles_per_split = step * ((p.ntiles + step * nsplit - 1) / (step * nsplit));
+        p.nsplit = (int)((p.ntiles + p.tiles_per_split - 1) / p.tiles_per_split);
+        const int64_t on_xcd = ((int64_t)Hkv * p.nsplit + kNumXCD - 1) / kNumXCD * p.nqb;
+        return (on_xcd + room - 1) / room * (p.tiles_per_split + 2);
+    };
+    int rounds = 1;
+    int64_t least = cut(1);
+    for (int r = 2; roomy && r <= 4 + p.nqb / room; ++r) {
+        const int64_t tiles = cut(r);
+        if (4 * tiles < 3 * least) {
+            rounds = r;
+            least = tiles;
+        }
+    }
+    cut(rounds);
     const int64_t pairs = (int64_t)Hkv * p.nsplit;
     p.grid = (int)(((pairs + kNumXCD - 1) / kNumXCD) * kNumXCD * p.nqb);
     // pass 2's ranges follow the XCDs' speed where a range is long enough for that to matter

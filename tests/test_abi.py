@@ -159,6 +159,28 @@ def test_row_stats_static_rejects_shapes_beyond_its_buffer():
     assert lib.ilre_row_stats_static(fake, fake, 1000, 8, 8, 2, 64, fake, fake, ctypes.byref(o)) == il.ILRE_EUNSUPPORTED
 
 
+@pytest.mark.parametrize("dtype,Lq,Hq,Hkv,block,room,least,most", [
+    # query blocks that outnumber an XCD's places, or half of them: several rounds of workgroups
+    (il.ILRE_BF16, 2080, 16, 2, 256, 64, 512, 2048), (il.ILRE_BF16, 1360, 64, 4, 256, 64, 512, 2048), (il.ILRE_BF16, 540, 32, 1, 512, 32, 256, 1024),
+    (il.ILRE_BF16, 245, 71, 1, 512, 32, 256, 1024), (il.ILRE_F32, 260, 32, 1, 128, 64, 512, 2048), (il.ILRE_BF16, 1280, 40, 5, 512, 32, 256, 1024),
+    # one round, as many as an XCD holds
+    (il.ILRE_BF16, 90, 28, 4, 256, 64, 504, 504), (il.ILRE_BF16, 150, 28, 4, 256, 64, 480, 480), (il.ILRE_BF16, 170, 64, 8, 512, 32, 240, 240),
+    (il.ILRE_BF16, 256, 32, 8, 512, 32, 256, 256), (il.ILRE_F32, 176, 64, 8, 128, 64, 440, 440),
+])
+def test_scoring_fills_the_chip_whatever_the_query_blocks(dtype, Lq, Hq, Hkv, block, room, least, most):
+    """Workgroups of a scoring pass, read off the size of the workspace (partial row statistics, 8 bytes a row and split): no fewer than
+    the chip has places where query blocks are many, and no more than a round of them where one fills it."""
+    L = 131072
+    nqb = -(-(Hq // Hkv) * Lq // block)
+    bytes_of = lambda *shape: il.ilre_workspace_bytes(L, *shape, 128, 3, dtype)
+    # beside 64 splits of 8 rows, 8 score vectors and the same selection region
+    more = bytes_of(Lq, Hq, Hkv) - bytes_of(1, 8, 8) - 4 * L * (Hkv * nqb - 8) + 8 * 64 * 8
+    splits = round(more / (8 * Hq * Lq)) - 1  # (rows' merged statistics)
+    assert abs(more / (8 * Hq * Lq) - 1 - splits) < 0.3
+    assert least <= splits * nqb * Hkv <= most
+    assert 8 * room == (256 if block == 512 else 512)
+
+
 def test_walk_cases_sit_at_the_edge_of_the_bitmap():
     """The GPU cases of the walk name the number of tokens up to which its set is a bitmap; it is the library's."""
     import test_gpu_parity as parity_tests

@@ -119,6 +119,32 @@ def test_unequal_query_blocks_want_a_workspace_for_them():
         il.ilre_recall(q, k, 500, (3, 7), workspace=small[: small.numel() // 2 // 256 * 256])
 
 
+@pytest.mark.parametrize("L,Lq,Hq,Hkv,dtype", [(3001, 540, 32, 1, "bf16"), (1500, 2080, 16, 2, "bf16"), (1300, 260, 32, 1, "f32")],
+                         ids=["34_blocks_of_512", "65_blocks_of_256", "65_blocks_of_128"])
+def test_query_blocks_that_outnumber_an_xcds_places(L, Lq, Hq, Hkv, dtype):
+    """Many query blocks a kv head run in several rounds of workgroups, with more splits; a workspace that only has room for one
+    round's partial statistics serves as well.  Tolerances as everywhere, and between the two what another order of sums gives."""
+    _announce(f"many query blocks L={L} Lq={Lq} {Hq}/{Hkv} {dtype}")
+    inp = inputs.custom(L=L, Lq=Lq, Hq=Hq, Hkv=Hkv, d=128, dtype=dtype, n_spans=2, span_len=(8, 24), channel_scale=True, seed=L)
+    q, k = to_device(inp.q), to_device(inp.k)
+    full = il.alloc_workspace(L, Lq, Hq, Hkv, 128, 2, il.ILRE_BF16 if dtype == "bf16" else il.ILRE_F32)
+    small = torch.empty(full.numel() - 8 * Hq * Lq, dtype=torch.uint8, device="cuda")
+    want, _, _ = oracle.scores(inp.q, inp.k)
+    got = []
+    for ws in (full, small):
+        idx, scores = il.ilre_recall(q, k, 300, (3, 7), workspace=ws)
+        ref, total = il.ilre_row_stats(q, k, workspace=ws)
+        staged = il.ilre_col_scores(q, k, ref, total, workspace=ws)
+        torch.cuda.synchronize()
+        scores = scores.cpu().numpy()
+        bad, worst = score_errors(scores, want)
+        assert bad == 0, f"{bad} scores out of tolerance, worst {worst:.2f}x"
+        assert idx.cpu().numpy().tolist() == oracle.allocate(scores, (3, 7), 300).tolist()
+        np.testing.assert_allclose(staged.cpu().numpy(), scores, rtol=4e-6, atol=0)
+        got.append(scores)
+    np.testing.assert_allclose(got[0], got[1], rtol=4e-6, atol=0)
+
+
 @pytest.mark.parametrize("dtype,Lq,G,Hkv", [("bf16", 20, 2, 4), ("bf16", 50, 4, 4), ("bf16", 64, 8, 2), ("f32", 33, 2, 4)],
                          ids=["pair_of_threads_a_row", "4_waves", "8_waves", "f32_two_query_blocks"])
 def test_second_pass_merges_the_partial_statistics(dtype, Lq, G, Hkv):
