@@ -30,7 +30,7 @@ SHAPES = [
     ("bf16_exact_tiles", 4096, 32, 32, 8, "bf16", False),
     # head counts of the other models the paper evaluates (Section 4): GQA groups of 7 and of 8
     ("qwen2_5_7b_heads", 3000, 64, 28, 4, "bf16", True),       # 448 rows/group: one 8-wave query block, 64 rows padded
-    ("qwen3_32b_heads", 2500, 40, 64, 8, "bf16", True),        # 320 rows/group: two 4-wave query blocks
+    ("qwen3_32b_heads", 2500, 40, 64, 8, "bf16", True),        # 320 rows/group: a block of 256 and one of 128
 ]
 
 
@@ -119,6 +119,32 @@ def test_unequal_query_blocks_want_a_workspace_for_them():
         il.ilre_recall(q, k, 500, (3, 7), workspace=small[: small.numel() // 2 // 256 * 256])
 
 
+@pytest.mark.parametrize("L,Lq,Hq,Hkv", [(33001, 300, 32, 32), (60001, 2080, 16, 2)], ids=["blocks_of_256_and_128", "65_blocks_of_256"])
+def test_blocks_of_unequal_size_and_rounds_with_ranges_by_the_xcds_speed(L, Lq, Hq, Hkv):
+    """The second pass's token ranges follow the XCDs' speed where a split is 64 tiles and more, in launches of unequal query blocks (8 splits
+    of 65 tiles of 64 tokens) and of several rounds (12 of 79) as well: the same bits with the first pass's table, without one, and in the whole path,
+    and what 64 bits give."""
+    _announce(f"ranges by the XCDs' speed L={L} Lq={Lq} {Hq}/{Hkv}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(12)
+    q = torch.randn(Hq, Lq, 128, device="cuda", generator=g).to(torch.bfloat16)
+    k = torch.randn(Hkv, L, 128, device="cuda", generator=g).to(torch.bfloat16)
+    ws = il.alloc_workspace(L, Lq, Hq, Hkv, 128, 2, il.ILRE_BF16)
+    rmax, rsum = il.ilre_row_stats(q, k, workspace=ws)
+    with_table = il.ilre_col_scores(q, k, rmax, rsum, workspace=ws).clone()
+    without = il.ilre_col_scores(q, k, rmax, rsum, workspace=torch.zeros_like(ws))
+    _, whole = il.ilre_recall(q, k, 64, (3, 7), workspace=ws)
+    want = torch.zeros(L, dtype=torch.float64, device="cuda")
+    for h in range(Hq):
+        kk = k[h // (Hq // Hkv)].double().t().contiguous()
+        for part in q[h].double().split(256):
+            want += torch.softmax(part @ kk / 128 ** 0.5, dim=1).sum(0)
+    torch.cuda.synchronize()
+    assert torch.equal(with_table, without) and torch.equal(with_table, whole)
+    bad, worst = score_errors(whole.cpu().numpy(), want.cpu().numpy())
+    assert bad == 0, f"{bad} scores out of tolerance, worst {worst:.2f}x"
+
+
 @pytest.mark.parametrize("L,Lq,Hq,Hkv,dtype", [(3001, 540, 32, 1, "bf16"), (1500, 2080, 16, 2, "bf16"), (1300, 260, 32, 1, "f32")],
                          ids=["34_blocks_of_512", "65_blocks_of_256", "65_blocks_of_128"])
 def test_query_blocks_that_outnumber_an_xcds_places(L, Lq, Hq, Hkv, dtype):
@@ -145,12 +171,13 @@ def test_query_blocks_that_outnumber_an_xcds_places(L, Lq, Hq, Hkv, dtype):
     np.testing.assert_allclose(got[0], got[1], rtol=4e-6, atol=0)
 
 
-@pytest.mark.parametrize("dtype,Lq,G,Hkv", [("bf16", 20, 2, 4), ("bf16", 50, 4, 4), ("bf16", 64, 8, 2), ("f32", 33, 2, 4)],
-                         ids=["pair_of_threads_a_row", "4_waves", "8_waves", "f32_two_query_blocks"])
+@pytest.mark.parametrize("dtype,Lq,G,Hkv", [("bf16", 20, 2, 4), ("bf16", 50, 4, 4), ("bf16", 64, 8, 2), ("bf16", 96, 4, 4), ("f32", 33, 2, 4), ("f32", 80, 2, 4)],
+                         ids=["pair_of_threads_a_row", "4_waves", "8_waves", "blocks_of_256_and_128", "f32", "f32_two_query_blocks"])
 def test_second_pass_merges_the_partial_statistics(dtype, Lq, G, Hkv):
     """In the whole path the second scoring pass merges the splits' partial row statistics itself, up to 32 splits (64 where a
     workgroup has 128 or 512 rows), in the order the merge kernel of the staged call uses: the scores are the same bits either way.  Numbers of splits
-    (one a tile on these lengths) around the 16 sums and the line; one row beyond every frozen reference, so that a
+    around the 16 sums and the line (bf16: one a tile up to 64, fp32: one for two tiles of 32 tokens up to 32 of them, then 17 to 32 up to
+    128 tiles and more beyond, which the merge kernel takes); one row beyond every frozen reference, so that a
     split's partial has another reference."""
     tile = 128 if dtype == "bf16" and Lq * G == 512 else 64
     g = torch.Generator(device="cuda")
@@ -387,18 +414,23 @@ def test_fp32_states_keep_their_precision(L, Lq, Hq, Hkv, spread):
     """fp32 states against 64 bits, at the edges of the kernels' tiles (32 tokens, 128 rows) and with channels of very different
     scale.  A logit sees 8 additions at its own size, 40 at 2^-8 of it and a few more, each rounded to 2^-24, and products that
     are 2^-24 short at most: within 16 * 2^-24 of the sum of its products' magnitudes.  A row's logarithm of a sum moves by no more
-    than the worst of its logits, the sum's own rounding (2^-24 for each of its levels, 64 tokens a lane and 16 splits at most) and
-    the exponentials' (2^-22 with the scaling)."""
+    than the worst of its logits, the sum's own rounding (2^-24 for each of its levels: 64 tokens a lane at most, in four sums, and 65 splits, in 16; 80 is more than
+    all of them) and the exponentials' (2^-22 with the scaling).  A score's terms move by their logits, their rows' logarithms and the
+    exponent's roundings (2^-22 of its size with the row's offset); their sum is 16 a lane, 8 of a tile and up to 16 blocks, fewer than 40
+    levels.  Exponentials below the smallest normal number may be 0."""
     _announce(f"fp32 precision L={L} Lq={Lq} {Hq}/{Hkv} spread {spread}")
     rng = np.random.default_rng(L + Lq)
     channel = np.exp(spread * rng.standard_normal(128))
     q = (rng.standard_normal((Hq, Lq, 128)) * channel).astype(np.float32)
     k = (rng.standard_normal((Hkv, L, 128)) / channel * np.exp(0.3 * spread * rng.standard_normal((Hkv, L, 1)))).astype(np.float32)
-    row_max, row_sum = il.ilre_row_stats(torch.from_numpy(q).cuda(), torch.from_numpy(k).cuda())
+    qd, kd = torch.from_numpy(q).cuda(), torch.from_numpy(k).cuda()
+    row_max, row_sum = il.ilre_row_stats(qd, kd)
+    got_sum, got_top = (il.ilre_col_scores(qd, kd, row_max, row_sum, score_mode=mode) for mode in (il.ILRE_SCORE_SUM, il.ILRE_SCORE_MAX))
     torch.cuda.synchronize()
     got = row_max.cpu().numpy().astype(np.float64) + np.log(row_sum.cpu().numpy().astype(np.float64))
     group = Hq // Hkv
     scale = 1.0 / np.sqrt(128.0)
+    want_sum, off_sum, want_top, off_top = (np.zeros(L) for _ in range(4))
     for h in range(Hq):
         kk = k[h // group].astype(np.float64)
         s = (q[h].astype(np.float64) @ kk.T) * scale
@@ -407,6 +439,12 @@ def test_fp32_states_keep_their_precision(L, Lq, Hq, Hkv, spread):
         want = top + np.log(np.exp(s - top[:, None]).sum(axis=1))
         bound = 16 * 2.0 ** -24 * size.max(axis=1) + 2.0 ** -22 * (1 + np.abs(s).max(axis=1)) + 80 * 2.0 ** -24
         assert (np.abs(got[h * Lq:(h + 1) * Lq] - want) <= bound).all(), (h, np.abs(got[h * Lq:(h + 1) * Lq] - want).max(), bound.min())
+        prob = np.exp(s - want[:, None])
+        off = prob * np.expm1(16 * 2.0 ** -24 * size + bound[:, None] + 2.0 ** -22 * (1 + np.abs(s) + np.abs(want[:, None])))
+        want_sum, off_sum = want_sum + prob.sum(axis=0), off_sum + off.sum(axis=0)
+        want_top, off_top = np.maximum(want_top, prob.max(axis=0)), np.maximum(off_top, off.max(axis=0))
+    assert (np.abs(got_sum.cpu().numpy() - want_sum) <= off_sum + 40 * 2.0 ** -24 * want_sum + 1e-37).all()
+    assert (np.abs(got_top.cpu().numpy() - want_top) <= off_top + 1e-37).all()
 
 
 @pytest.mark.parametrize("channels", [1, 2, 3, 4])
