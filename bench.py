@@ -18,7 +18,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
-PEAK_F32_MFMA_TFLOPS = 157.3  # fp32 matrix path (cfg 1 only)
+PEAK_F32_SPLIT_TFLOPS = PEAK_BF16_TFLOPS / 6  # fp32 states: six bf16 products for one of theirs
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "score_kernel_cfg5_1m_hbm_traffic.md")
 
 
@@ -164,9 +164,10 @@ def run_workload(il, torch, np, inputs, cfg: int, steps: int, warmup: int, calib
 
     flops_per_pass = 2.0 * wl.Hq * wl.Lq * wl.L * wl.d
     dom = 0 if stage_ms[0] >= stage_ms[1] else 1
-    dom_name = ("row_stats (score_kernel MODE 0)", "col_scores (score_kernel MODE 1)")[dom]
+    kernel_name = "score_kernel" if wl.dtype == "bf16" else "score_f32_kernel"
+    dom_name = f"{('row_stats', 'col_scores')[dom]} ({kernel_name} MODE {dom})"
     achieved = flops_per_pass / (stage_ms[dom] * 1e-3) / 1e12
-    peak = PEAK_BF16_TFLOPS if wl.dtype == "bf16" else PEAK_F32_MFMA_TFLOPS
+    peak = PEAK_BF16_TFLOPS if wl.dtype == "bf16" else PEAK_F32_SPLIT_TFLOPS
     roofline = {"bound": "mfma", "kernel": dom_name, "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
                 "frac": round(achieved / peak, 4), "traffic": None,
                 "flops_per_launch": flops_per_pass, "launch_ms": round(stage_ms[dom], 4)}
