@@ -77,8 +77,8 @@ struct ScoreArgs {
     float *dump;                        // 16 floats nobody reads: target of stores that have nothing to store
 };
 
-// `roomy`: query blocks may be of unequal size, which can take one partial score vector more a kv head, and workgroups may run in
-// several rounds, which takes partial row statistics for each.
+// `roomy`: query blocks may be of unequal size, which can take one partial score vector more a kv head, and workgroups may be
+// more (in several rounds, and with few tiles of fp32 states), which takes more partial row statistics.
 ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv, bool roomy);
 
 // With a.merge the partials are all that is left behind.

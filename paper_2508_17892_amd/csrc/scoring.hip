@@ -1027,11 +1027,16 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv, bool ro
     auto cut = [&](int rounds) {
         int64_t nsplit = std::max<int64_t>((int64_t)kNumXCD * ((int64_t)rounds * room / p.nqb) / Hkv, 1);
         nsplit = std::min(nsplit, (p.ntiles + step - 1) / step);
-        // few tiles: no more splits than pass 2 merges itself (4096 tokens, 32/8 heads, 32 queries 42.6 -> 40.3 us; with eight tiles 8192 tokens,
-        // 16/4 heads, 16 queries 40.8 -> 49.7)
-        if (dtype == ILRE_F32 && nsplit > kMergeSplits && p.ntiles <= 4 * kMergeSplits) nsplit = kMergeSplits;
-        p.tiles_per_split = step * ((p.ntiles + step * nsplit - 1) / (step * nsplit));
-        p.nsplit = (int)((p.ntiles + p.tiles_per_split - 1) / p.tiles_per_split);
+        auto into = [&](int64_t n) {
+            p.tiles_per_split = step * ((p.ntiles + step * n - 1) / (step * n));
+            p.nsplit = (int)((p.ntiles + p.tiles_per_split - 1) / p.tiles_per_split);
+            return ((int64_t)p.nunits * p.nsplit + kNumCU - 1) / kNumCU * p.tiles_per_split;  // tiles of the busiest compute unit
+        };
+        const int64_t busiest = into(nsplit);
+        // fp32, few tiles: no more splits than pass 2 merges itself, unless a compute unit then has more to do (32 queries, 32/8 heads, 4096
+        // tokens 41.3 -> 38.8 us, 6000 52.2 -> 47.4; 24/6 heads, 3000 41.6 -> 38.4, but 2100, 4 tiles instead of 2, 35.2 -> 38.1; 16 queries, 16/4
+        // heads, 4096 34.0 -> 36.7).  Beyond 6 tiles a split it gains nothing: 24/6 heads, 6500 tokens 52.1 -> 53.6, 32/8, 8192 53.8 either way.
+        if (dtype == ILRE_F32 && p.nsplit > kMergeSplits && p.ntiles <= 6 * kMergeSplits && into(kMergeSplits) > busiest && roomy) into(nsplit);
         const int64_t on_xcd = ((int64_t)Hkv * p.nsplit + kNumXCD - 1) / kNumXCD * p.nqb;
         return (on_xcd + room - 1) / room * (p.tiles_per_split + 2);
     };

@@ -159,6 +159,21 @@ def test_row_stats_static_rejects_shapes_beyond_its_buffer():
     assert lib.ilre_row_stats_static(fake, fake, 1000, 8, 8, 2, 64, fake, fake, ctypes.byref(o)) == il.ILRE_EUNSUPPORTED
 
 
+def _splits(L, Lq, Hq, Hkv, block, dtype):
+    """Token splits of a scoring pass, read off the size of the workspace."""
+    nqb = -(-(Hq // Hkv) * Lq // block)
+
+    def beside_the_selection(n, rows, heads, blocks):  # row statistics, a word a workgroup, edges of the splits, score vectors
+        return 8 * rows * (n + 1) + 4 * (8 * -(-heads * n // 8) * blocks + n) + 4 * L * heads * blocks
+
+    one = il.ilre_workspace_bytes(L, 1, 8, 8, 128, 3, il.ILRE_BF16)  # a split a tile of 64 tokens, up to 64
+    selection = one - beside_the_selection(min(64, -(-L // 64)), 8, 8, 1)
+    rest = il.ilre_workspace_bytes(L, Lq, Hq, Hkv, 128, 3, dtype) - selection
+    n = min(range(1, 600), key=lambda n: abs(beside_the_selection(n, Hq * Lq, Hkv, nqb) - rest))
+    assert abs(beside_the_selection(n, Hq * Lq, Hkv, nqb) - rest) < 3 * Hq * Lq  # (a split is 8 bytes a row, each region ends on 256)
+    return n
+
+
 @pytest.mark.parametrize("dtype,Lq,Hq,Hkv,block,room,least,most", [
     # query blocks that outnumber an XCD's places, or half of them: several rounds of workgroups
     (il.ILRE_BF16, 2080, 16, 2, 256, 64, 512, 2048), (il.ILRE_BF16, 1360, 64, 4, 256, 64, 512, 2048), (il.ILRE_BF16, 540, 32, 1, 512, 32, 256, 1024),
@@ -168,17 +183,20 @@ def test_row_stats_static_rejects_shapes_beyond_its_buffer():
     (il.ILRE_BF16, 256, 32, 8, 512, 32, 256, 256), (il.ILRE_F32, 176, 64, 8, 128, 64, 440, 440),
 ])
 def test_scoring_fills_the_chip_whatever_the_query_blocks(dtype, Lq, Hq, Hkv, block, room, least, most):
-    """Workgroups of a scoring pass, read off the size of the workspace (partial row statistics, 8 bytes a row and split): no fewer than
-    the chip has places where query blocks are many, and no more than a round of them where one fills it."""
-    L = 131072
+    """Workgroups of a scoring pass: no fewer than the chip has places where query blocks are many, and no more than a round of them where one fills it."""
     nqb = -(-(Hq // Hkv) * Lq // block)
-    bytes_of = lambda *shape: il.ilre_workspace_bytes(L, *shape, 128, 3, dtype)
-    # beside 64 splits of 8 rows, 8 score vectors and the same selection region
-    more = bytes_of(Lq, Hq, Hkv) - bytes_of(1, 8, 8) - 4 * L * (Hkv * nqb - 8) + 8 * 64 * 8
-    splits = round(more / (8 * Hq * Lq)) - 1  # (rows' merged statistics)
-    assert abs(more / (8 * Hq * Lq) - 1 - splits) < 0.3
-    assert least <= splits * nqb * Hkv <= most
+    assert least <= _splits(131072, Lq, Hq, Hkv, block, dtype) * nqb * Hkv <= most
     assert 8 * room == (256 if block == 512 else 512)
+
+
+@pytest.mark.parametrize("L,Lq,Hq,Hkv,splits", [
+    # as few as the second pass merges itself (32) where no compute unit has more tiles of 32 tokens to do for it ...
+    (4096, 32, 32, 8, 32), (2100, 32, 32, 8, 17), (4128, 32, 32, 8, 22), (6144, 128, 8, 2, 32), (3000, 32, 24, 6, 24),
+    # ... and all there are where one would, or with many tiles
+    (4096, 32, 16, 4, 64), (2100, 32, 24, 6, 33), (5000, 64, 20, 5, 40), (8192, 32, 32, 8, 64),
+])
+def test_fp32_splits_of_short_contexts(L, Lq, Hq, Hkv, splits):
+    assert _splits(L, Lq, Hq, Hkv, 128, il.ILRE_F32) == splits
 
 
 def test_walk_cases_sit_at_the_edge_of_the_bitmap():

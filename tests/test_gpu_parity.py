@@ -145,11 +145,11 @@ def test_blocks_of_unequal_size_and_rounds_with_ranges_by_the_xcds_speed(L, Lq, 
     assert bad == 0, f"{bad} scores out of tolerance, worst {worst:.2f}x"
 
 
-@pytest.mark.parametrize("L,Lq,Hq,Hkv,dtype", [(3001, 540, 32, 1, "bf16"), (1500, 2080, 16, 2, "bf16"), (1300, 260, 32, 1, "f32")],
-                         ids=["34_blocks_of_512", "65_blocks_of_256", "65_blocks_of_128"])
+@pytest.mark.parametrize("L,Lq,Hq,Hkv,dtype", [(3001, 540, 32, 1, "bf16"), (1500, 2080, 16, 2, "bf16"), (1300, 260, 32, 1, "f32"), (2100, 32, 24, 6, "f32")],
+                         ids=["34_blocks_of_512", "65_blocks_of_256", "65_blocks_of_128", "fp32_33_splits"])
 def test_query_blocks_that_outnumber_an_xcds_places(L, Lq, Hq, Hkv, dtype):
-    """Many query blocks a kv head run in several rounds of workgroups, with more splits; a workspace that only has room for one
-    round's partial statistics serves as well.  Tolerances as everywhere, and between the two what another order of sums gives."""
+    """Many query blocks a kv head run in several rounds of workgroups, with more splits, and fp32 states of few tiles take more splits than the
+    second pass merges where that is less work for each; a workspace that only has room for the fewer splits' partial statistics serves as well.  Tolerances as everywhere, and between the two what another order of sums gives."""
     _announce(f"many query blocks L={L} Lq={Lq} {Hq}/{Hkv} {dtype}")
     inp = inputs.custom(L=L, Lq=Lq, Hq=Hq, Hkv=Hkv, d=128, dtype=dtype, n_spans=2, span_len=(8, 24), channel_scale=True, seed=L)
     q, k = to_device(inp.q), to_device(inp.k)
@@ -176,8 +176,8 @@ def test_query_blocks_that_outnumber_an_xcds_places(L, Lq, Hq, Hkv, dtype):
 def test_second_pass_merges_the_partial_statistics(dtype, Lq, G, Hkv):
     """In the whole path the second scoring pass merges the splits' partial row statistics itself, up to 32 splits (64 where a
     workgroup has 128 or 512 rows), in the order the merge kernel of the staged call uses: the scores are the same bits either way.  Numbers of splits
-    around the 16 sums and the line (bf16: one a tile up to 64, fp32: one for two tiles of 32 tokens up to 32 of them, then 17 to 32 up to
-    128 tiles and more beyond, which the merge kernel takes); one row beyond every frozen reference, so that a
+    around the 16 sums and the line (bf16: one a tile up to 64; fp32: one for two tiles of 32 tokens, or fewer of more tiles where that keeps
+    every compute unit as busy: 17 to 32 of 66 to 128 tiles with two blocks of rows); one row beyond every frozen reference, so that a
     split's partial has another reference."""
     tile = 128 if dtype == "bf16" and Lq * G == 512 else 64
     g = torch.Generator(device="cuda")
