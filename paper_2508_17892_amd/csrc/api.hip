@@ -261,8 +261,8 @@ int static_scratch(void **out)
     return ILRE_OK;
 }
 
-// Eq. 4 row statistics with the partial results in `scratch_base` (scratch_bytes long; a caller's workspace or
-// the static array).  static_buf only words the error message.
+// Eq. 4 row statistics with the partial results in `scratch_base` (a caller's workspace or the static
+// array).  static_buf says which: the plan is made for its size, and the error message names it.
 int row_stats_into(const void *q, const void *k_cache, int64_t L, int32_t Lq, int32_t Hq, int32_t Hkv, int32_t d,
                    float *row_max, float *row_sumexp, const ilre_opts *opts, bool static_buf)
 {

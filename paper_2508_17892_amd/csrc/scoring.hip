@@ -594,7 +594,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void score_kernel(const ScoreArgs a)
 // workgroups a compute unit work in each other's shadow; the split is done once for four wavefronts.
 // Bound: 48 matrix instructions of 32 cycles for 32 x 32 logits (the fp32 instructions: 4096 cycles), 1.2 PFLOP/s of them on 32768 tokens
 // and 8192 rows, what the matrix pipe reaches beside such vector work.  Measured, whole recall, fp32 instructions -> so: 4096
-// tokens, 32/8 heads, 32 queries 62.9 -> 40.3 us; 32768 tokens, 256 queries 1107 -> 713 us.  Errors against 64 bits, logarithms of
+// tokens, 32/8 heads, 32 queries 61.0 -> 38.6 us; 32768 tokens, 256 queries 1102 -> 717 us; 20000, 28/4, 64 209 -> 140.  Errors against 64 bits, logarithms of
 // the rows' sums: 4.1e-7 -> 3.0e-7 rms, 1.5e-6 -> 1.1e-6 largest; scores 2.4e-6 -> 1.1e-6 largest; single logits of normally distributed
 // states with 1, 2, 4, 16 and 128 channels at work 3.6e-8, 3.4e-8, 3.1e-8, 2.9e-8, 2.8e-8 -> 3.6e-8, 3.1e-8, 2.5e-8, 1.6e-8, 1.0e-8 rms of
 // the sum of their products' magnitudes, 1.6, 2.2, 2.9, 3.8, 3.9 -> 2.0, 2.2, 2.3, 2.7, 1.5 times 2^-24 largest.  (The softmax arithmetic a tile
@@ -1016,8 +1016,8 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv, bool ro
     p.nunits = Hkv * p.nqb;
     // As many splits as there is room for at a time: one workgroup of 8 waves (two of 4 waves) a compute unit, and on each XCD no
     // more workgroups than that, because one too many runs behind all others, for as long as they do.  (Splits rounded up to
-    // the next number, 131072 tokens: 28/4 heads, 630 rows a kv head, 516 workgroups 287 us a call, 504 220; 64/8, 1360 rows, 528 1226
-    // us, 480 752; 28/4, 1050 rows, 500 workgroups, but 65 on some XCDs 443 us, 480, 60 an XCD, 363.)
+    // the next number, 131072 tokens: 28/4 heads, 630 rows a kv head, 516 workgroups 299 us a call, 504 232; 64/8, 1360 rows, 528 1282
+    // us, 480 816; 28/4, 1050 rows, 500 workgroups, but 65 on some XCDs 468 us, 480, 60 an XCD, 381.)
     // Several rounds of workgroups where that takes a quarter off the tiles one place goes through, two a workgroup for its start
     // counted in: query blocks that are many against an XCD's places leave most of them empty otherwise, or have no round of their own.
     // (One round, then so, 131072 tokens: 16/2 heads, 2080 queries 10.81 -> 2.37 ms, 64/4, 1360 11.77 -> 5.69, 32/1, 540 12.17 -> 1.34, 40/5, 1280

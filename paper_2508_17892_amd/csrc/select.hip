@@ -2762,8 +2762,9 @@ hipError_t raise_avg_lds()
 // One chunk of windows a wavefront where that is at most two workgroups a compute unit, more of them beyond: a
 // workgroup carries the clearing and flushing of its 16 KiB of counts, and all want the same lines of the global ones.  Of chunks of
 // kAvgWide up to two a wavefront with one workgroup a compute unit (whole selection, budget 4096, 1M scores, two workgroups -> one: 48
-// combinations 88.7 -> 86.8 us, uniform scores 68.6 -> 66.8, one of cells of 1, windows of 7 74.4 -> 71.4; 4M scores, up to seven chunks, 148.9
-// -> 154.5; chunks of kAvgNarrow, 20 combinations of 512K 68.1 -> 72.5).
+// combinations, three draws of a background with a few dozen spans far above it, whose places decide how many elements share a bin and a
+// list, 89.4 -> 86.8, 69.9 -> 68.6 and 67.7 -> 67.8 us, uniform scores 69.2 -> 67.3; cells of 1, windows of 7, the same draws 74.0 -> 71.3, 64.7
+// -> 61.8, 58.5 -> 57.6; 4M scores, up to seven chunks, 148.9 -> 154.5; chunks of kAvgNarrow, 20 combinations of 512K 68.1 -> 72.5).
 // Max kernels get workgroups in proportion to their cells (as many each, cells of 2 had four times as much a workgroup as cells
 // of 8: 48 combinations 4M scores 173.7 -> 160.3 us; max kernels 1, 2, 4, 8, 16 with four others 1M 142.5 -> 109.7; 64 max kernels 1M 355 -> 231).
 template <int PASS, int PER, bool SMALL>
