@@ -1042,7 +1042,7 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv, bool ro
     };
     int rounds = 1;
     int64_t least = cut(1);
-    for (int r = 2; roomy && r <= 4 + p.nqb / room; ++r) {
+    for (int r = std::max(2, p.nqb / room); roomy && r <= 4 + p.nqb / room; ++r) {  // (fewer hold no split of every query block)
         const int64_t tiles = cut(r);
         if (4 * tiles < 3 * least) {
             rounds = r;
