@@ -319,7 +319,7 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
         const float x1 = quad_swap1(acc);
         acc = RMAX ? fmaxf(acc, x1) : acc + x1;
         const float x2 = quad_swap2(acc);
-        acc = RMAX ? fmaxf(acc, x2) : acc + x2;
+        acc = RMAX ? fast_exp2(fmaxf(acc, x2)) : acc + x2;
         const int64_t tok = first_token(tile) + tl;
         // after the quad reduction the four lanes of a token hold the same value and all store it
         float *dst = (live && tok < a.L) ? a.partial + ((int64_t)unit * a.L + tok) : a.dump + (lane & 15);
@@ -344,9 +344,15 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
             else
                 row_update<MASKED>(acc, a.c, m[b], z[b], tile * TN + tb * 32 + 4 * half, a.L);
         } else {
+            // RMAX: the exponents' maximum, of which flush_finish takes the one exp2 a token (exp2 being monotonic).  Two fma and two maxima a
+            // matrix instruction keep up with it, two exp2 more do not: 131072 tokens, 128 queries, 32/8 heads 138 -> 111 us this pass, 1M
+            // tokens, 256 queries 1980 -> 1625.
             float e[16];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) e[v] = fast_exp2(fmaf(acc[v], a.c, noff[b][v]));
+            for (int v = 0; v < 16; ++v) {
+                const float x = fmaf(acc[v], a.c, noff[b][v]);
+                e[v] = RMAX ? x : fast_exp2(x);
+            }
             float p0 = e[0], p1 = e[1], p2 = e[2], p3 = e[3];
 #pragma unroll
             for (int v = 4; v < 16; v += 4) {
@@ -445,7 +451,7 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
                 for (int b = 0; b < NB; ++b) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                     if (b == NB - 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, (MODE == 0 && !FROZEN) ? 8 : 6, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, (MODE == 0 && !FROZEN) ? 8 : RMAX ? 4 : 6, 0);
                 }
             }
         }
@@ -765,7 +771,8 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void score_f32_kernel(const Scor
             float p[4];
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const float e = fast_exp2(fmaf(big[v], a.c, noff[v]));
+                const float x = fmaf(big[v], a.c, noff[v]);
+                const float e = RMAX ? x : fast_exp2(x);
                 p[v & 3] = v < 4 ? e : RMAX ? fmaxf(p[v & 3], e) : p[v & 3] + e;
             }
             red[(buf * kF32Parts + wave * 2 + half) * kF32Pitch + l32] =
@@ -781,7 +788,7 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void score_f32_kernel(const Scor
             for (int o = 1; o < kF32Parts; o <<= 1)
 #pragma unroll
                 for (int i = 0; i < kF32Parts; i += 2 * o) x[i] = RMAX ? fmaxf(x[i], x[i + o]) : x[i] + x[i + o];
-            if (tok0 + l32 < a.L) a.partial[(int64_t)unit * a.L + tok0 + l32] = x[0];
+            if (tok0 + l32 < a.L) a.partial[(int64_t)unit * a.L + tok0 + l32] = RMAX ? fast_exp2(x[0]) : x[0];
         }
     }
     if (MODE == 0) {  // the half-waves saw disjoint tokens of the same rows
