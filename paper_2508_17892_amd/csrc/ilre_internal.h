@@ -20,8 +20,13 @@ constexpr int kNumXCD = 8;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 __device__ __forceinline__ void lds_dma16(i32x4 rsrc, unsigned lds_addr, int voffset)
 {
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voffset), "s"(rsrc)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voffset), "s"(rsrc)
                  : "memory", "m0");
+}
+// The same from an address a lane.
+__device__ __forceinline__ void lds_dma16(uint64_t src, unsigned lds_addr)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(src) : "memory", "m0");
 }
 
 // ---------------------------------------------------------------- scoring (Eq. 4 / Eq. 5)

@@ -106,7 +106,7 @@ __device__ __forceinline__ void row_accumulate(const f32x16 &acc, float c, float
 }
 
 // A row's exponent offset in pass 2 from its statistics in the natural-log units of Eq. 4.
-__device__ __forceinline__ float row_offset(float row_max, float row_sumexp) { return -(row_max * kLog2e + __log2f(row_sumexp)); }
+__device__ __forceinline__ float row_offset(float row_max, float row_sumexp) { return -fmaf(row_max, kLog2e, __log2f(row_sumexp)); }
 
 // The same straight from the per-split partials m[s*pitch], z[s*pitch], added up in the order of combine_row_stats: the
 // splits are dealt to kCombineLanes sums, which a tree of neighbours reduces.  SHARERS threads (1, or 2 neighbouring
@@ -120,40 +120,47 @@ __device__ __forceinline__ float row_offset(float row_max, float row_sumexp) { r
 // 512, where half as many workgroups read them (28/4 heads, 64 queries 74.6 -> 73.2 and 134.2 -> 133.3).
 constexpr int kCombineLanes = 16;
 constexpr int kMergeSplits = 2 * kCombineLanes;
+// The loads are issued before those of Q and K, which arrive while the sums are made (K first: the wait for the partials was one for Q
+// and two tiles as well, and the sums came after it).
 template <int SHARERS, int ROUNDS>
-__device__ __forceinline__ float merged_offset(const float *pm, const float *pz, int nsplit, int64_t pitch, int part)
-{
-    constexpr int OWN = kCombineLanes / SHARERS;
+struct RowParts {
+    static constexpr int OWN = kCombineLanes / SHARERS;
     float m[ROUNDS][OWN], z[ROUNDS][OWN];
+    __device__ __forceinline__ void load(const float *pm, const float *pz, int nsplit, int64_t pitch, int part)
+    {
 #pragma unroll
-    for (int k = 0; k < ROUNDS; ++k)
+        for (int k = 0; k < ROUNDS; ++k)
 #pragma unroll
-        for (int i = 0; i < OWN; ++i) {
-            const int s = k * kCombineLanes + part * OWN + i;
-            const int64_t at = (int64_t)(s < nsplit ? s : nsplit - 1) * pitch;
-            m[k][i] = pm[at];
-            z[k][i] = pz[at];
-        }
-    float mm = kNegBig, sum[OWN];
+            for (int i = 0; i < OWN; ++i) {
+                const int s = k * kCombineLanes + part * OWN + i;
+                const int64_t at = (int64_t)(s < nsplit ? s : nsplit - 1) * pitch;
+                m[k][i] = pm[at];
+                z[k][i] = pz[at];
+            }
+    }
+    __device__ __forceinline__ float offset(int nsplit, int part) const
+    {
+        float mm = kNegBig, sum[OWN];
 #pragma unroll
-    for (int k = 0; k < ROUNDS; ++k)
+        for (int k = 0; k < ROUNDS; ++k)
 #pragma unroll
-        for (int i = 0; i < OWN; ++i) mm = fmaxf(mm, m[k][i]);
-    if (SHARERS == 2) mm = fmaxf(mm, quad_swap1(mm));
+            for (int i = 0; i < OWN; ++i) mm = fmaxf(mm, m[k][i]);
+        if (SHARERS == 2) mm = fmaxf(mm, quad_swap1(mm));
 #pragma unroll
-    for (int i = 0; i < OWN; ++i) sum[i] = 0.f;
+        for (int i = 0; i < OWN; ++i) sum[i] = 0.f;
 #pragma unroll
-    for (int k = 0; k < ROUNDS; ++k)
+        for (int k = 0; k < ROUNDS; ++k)
 #pragma unroll
-        for (int i = 0; i < OWN; ++i)
-            if (k * kCombineLanes + part * OWN + i < nsplit) sum[i] += z[k][i] * fast_exp2(m[k][i] - mm);
+            for (int i = 0; i < OWN; ++i)
+                if (k * kCombineLanes + part * OWN + i < nsplit) sum[i] = fmaf(z[k][i], fast_exp2(m[k][i] - mm), sum[i]);  // (as combine_row_stats, bit for bit)
 #pragma unroll
-    for (int o = 1; o < OWN; o <<= 1)
+        for (int o = 1; o < OWN; o <<= 1)
 #pragma unroll
-        for (int i = 0; i < OWN; i += 2 * o) sum[i] += sum[i + o];
-    if (SHARERS == 2) sum[0] += quad_swap1(sum[0]);
-    return row_offset(mm * kLn2, sum[0]);
-}
+            for (int i = 0; i < OWN; i += 2 * o) sum[i] += sum[i + o];
+        if (SHARERS == 2) sum[0] += quad_swap1(sum[0]);
+        return row_offset(mm * kLn2, sum[0]);
+    }
+};
 
 // One workgroup's share: NB 32-row blocks a wavefront of query block qb, tiles tile0 .. tile1 - 1 of kv head g.
 // MODE 0: row statistics.  MODE 1: column scores (RMAX = 0 sum over rows, 1 max over rows; MANY: it may have to merge 2 kMergeSplits).
@@ -190,29 +197,68 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
     const int rl0 = qb * a.rows_per_wg + wave * (NB * 32);
     const int64_t nrows = (int64_t)a.Hq * a.Lq;
 
-    // Query fragments, resident for the whole kernel: lane holds, for each of its NB blocks, row
-    // l32 of the block, 16-byte chunk (2*step + half) of that row.
-    uint4 qf[NB][STEPS];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int rl = rl0 + b * 32 + l32;
-        if (rl < a.rows_per_group) {
-            const int h = g * a.G + rl / a.Lq;
-            const int i = rl % a.Lq;
-            const unsigned char *src =
-                (const unsigned char *)a.q + ((int64_t)h * a.q_stride_head + (int64_t)i * a.q_stride_token) * ES;
-#pragma unroll
-            for (int st = 0; st < STEPS; ++st) qf[b][st] = *(const uint4 *)(src + (st * 2 + half) * 16);
+    // Pass 2: what the exponent offset of a row is made of, one row a thread (NB = 1: a pair of threads).
+    constexpr int ROWS = WAVES * NB * 32, SHARERS = WAVES * 64 / ROWS;
+    const int off_row = qb * a.rows_per_wg + tid / SHARERS;
+    RowParts<SHARERS, 2> parts;
+    RowParts<SHARERS, 4> more_parts;
+    float stat_m, stat_z;
+    const bool many = MANY && (NB == 2 || (a.merge && a.nsplit > kMergeSplits));  // (the kernel for NB = 2 is launched for nothing else)
+    if (MODE == 1) {
+        const int64_t r = (int64_t)g * a.rows_per_group + min(off_row, a.rows_per_group - 1);
+        if (many) {
+            more_parts.load(a.part_m + r, a.part_z + r, a.nsplit, nrows, tid % SHARERS);
+        } else if (a.merge) {
+            parts.load(a.part_m + r, a.part_z + r, a.nsplit, nrows, tid % SHARERS);
         } else {
-#pragma unroll
-            for (int st = 0; st < STEPS; ++st) qf[b][st] = make_uint4(0, 0, 0, 0);
+            stat_m = a.row_max[r];
+            stat_z = a.row_sumexp[r];
         }
     }
+
+    // Query fragments, resident for the whole kernel: lane holds, for each of its NB blocks, row
+    // l32 of the block, 16-byte chunk (2*step + half) of that row.  Rows past the group's last one repeat it: pass 1 does not
+    // store their statistics, pass 2 gives them the offset -inf.
+    // They come by way of LDS, where a wavefront's copy of 32 rows is the size of half a tile's share (behind the first two tile buffers,
+    // laid out as a tile is), one block after the other.  Read straight into the registers a load takes 16 bytes from each of 64
+    // cache lines, and the K tiles queue up behind 16 of them a wavefront: 131072 tokens, 512 rows a workgroup, the tiles were there 6.7 us
+    // after the start.  Passes before -> after (with the partials and the flag of the redo below): 32768 tokens, 32/8 heads, 64 queries 24.4 + 22.9
+    // -> 22.5 + 21.8 us, 100003, 28/4, 17 21.3 -> 19.5 the first, 20000, 16/4, 40 13.1 + 11.9 -> 12.0 + 11.5, 1M no change.
+    uint4 qf[NB][STEPS];
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
+    const unsigned qlds = lds0 + 2 * TILE_BYTES + wave * (32 * ROWB);
+    const bool in_line = a.q_stride_head == (int64_t)a.Lq * a.q_stride_token;  // a head's rows follow the one's before
+    auto issue_queries = [&](int b) {
+        const int64_t row_bytes = a.q_stride_token * ES, head_bytes = a.q_stride_head * ES;
+        constexpr int ISSUES = 32 * CPR / 64;  // four rows at a time
+        auto issue = [&](int j, uint64_t row_at) {
+            const int row = j * 4 + (lane >> 4);
+            lds_dma16(row_at + (((lane & 15) ^ (row & 15)) * 16), __builtin_amdgcn_readfirstlane(qlds + j * 1024));
+        };
+        if (in_line) {  // uniform
+            const uint64_t first = (uint64_t)a.q + (uint64_t)((int64_t)g * a.G * head_bytes);
+#pragma unroll
+            for (int j = 0; j < ISSUES; ++j)
+                issue(j, first + (uint64_t)(min(rl0 + b * 32 + j * 4 + (lane >> 4), a.rows_per_group - 1) * row_bytes));
+        } else {  // lane l32 works out where row l32 lies
+            const int rl = min(rl0 + b * 32 + l32, a.rows_per_group - 1);
+            const uint64_t own = (uint64_t)a.q + (uint64_t)((int64_t)(g * a.G + rl / a.Lq) * head_bytes + (int64_t)(rl % a.Lq) * row_bytes);
+#pragma unroll
+            for (int j = 0; j < ISSUES; ++j) {
+                const int row = j * 4 + (lane >> 4);
+                issue(j, (uint64_t)(uint32_t)__shfl((int)(uint32_t)(own >> 32), row) << 32 | (uint32_t)__shfl((int)(uint32_t)own, row));
+            }
+        }
+    };
+    auto read_queries = [&](int b) {
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st)
+            qf[b][st] = *(const uint4 *)(__attribute__((address_space(3))) unsigned char *)(size_t)(qlds + l32 * ROWB + (((2 * st + half) ^ (l32 & 15)) * 16));
+    };
 
     // K tiles: three LDS buffers of TN rows, row r's 16-byte chunk c stored at chunk position
     // c ^ (r & 15), so that the fragment reads of 16 consecutive rows fall in distinct banks while a
     // wavefront's DMA still fills 1 KiB of consecutive LDS.
-    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
     const unsigned char *kbase = (const unsigned char *)a.k + (int64_t)g * a.k_stride_head * ES;
     const int64_t krow_bytes = a.k_stride_token * ES;
     int dma_voff[NLW];
@@ -258,6 +304,19 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
     float *red = (float *)(smem + 3 * TILE_BYTES);  // [3][NPART][RSTR], pass 2 only
     const int unit = g * a.nqb + qb;
 
+    uint32_t *behind = (uint32_t *)(smem + 4 * TILE_BYTES);  // behind the wavefronts' query rows
+    issue_queries(0);
+    issue_first();
+    if (tile0 + 1 < tile1)  // (the tiles may stay on their way)
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NLW) : "memory");
+    else
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NLW) : "memory");
+    read_queries(0);
+    if (NB == 2) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        issue_queries(1);
+    }
+
     if (MODE == 0) {
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
@@ -265,38 +324,33 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
 #pragma unroll
             for (int k = 0; k < 4; ++k) z[b][k] = 0.f;
         }
+        if (tid == 0) *behind = 0;  // set where a split has to be walked again
     } else {
-        // The exponent offsets of the workgroup's rows, one row a thread (NB = 1: a pair of threads), handed out through
-        // LDS (a kernel that wrote them to a table before took 4.7 us of a staged call: 50001 tokens 149.9 -> 146.9 us):
-        // accumulator registers 4j .. 4j+3 of a lane are four consecutive rows.  Rows past the group's last one, whose q = 0,
-        // get -inf: exp2(0*c - inf) = 0.
-        issue_first();  // K and Q are on their way meanwhile
-        constexpr int ROWS = WAVES * NB * 32, SHARERS = WAVES * 64 / ROWS;
-        const int local = tid / SHARERS, rl = qb * a.rows_per_wg + local;
-        const bool real = rl < a.rows_per_group;
-        const int64_t r = (int64_t)g * a.rows_per_group + (real ? rl : a.rows_per_group - 1);
-        float off;
-        if (MANY && a.merge && a.nsplit > kMergeSplits)
-            off = merged_offset<SHARERS, 4>(a.part_m + r, a.part_z + r, a.nsplit, nrows, tid % SHARERS);
-        else if (a.merge)
-            off = merged_offset<SHARERS, 2>(a.part_m + r, a.part_z + r, a.nsplit, nrows, tid % SHARERS);
-        else
-            off = row_offset(a.row_max[r], a.row_sumexp[r]);
-        if (tid % SHARERS == 0) red[local] = real ? off : -INFINITY;
+        // The exponent offsets of the workgroup's rows, handed out through LDS (a kernel that wrote them to a table before took
+        // 4.7 us of a staged call: 50001 tokens 149.9 -> 146.9 us):
+        // accumulator registers 4j .. 4j+3 of a lane are four consecutive rows.  Rows past the group's last one
+        // get -inf: exp2(x*c - inf) = 0.
+        float *offs = (float *)behind;
+        const float off = many      ? more_parts.offset(a.nsplit, tid % SHARERS)
+                          : a.merge ? parts.offset(a.nsplit, tid % SHARERS)
+                                    : row_offset(stat_m, stat_z);
+        if (tid % SHARERS == 0) offs[tid / SHARERS] = off_row < a.rows_per_group ? off : -INFINITY;
         __syncthreads();
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const float4 x = *(const float4 *)&red[wave * (NB * 32) + b * 32 + 8 * j + 4 * half];
+                const float4 x = *(const float4 *)&offs[wave * (NB * 32) + b * 32 + 8 * j + 4 * half];
                 noff[b][4 * j + 0] = x.x;
                 noff[b][4 * j + 1] = x.y;
                 noff[b][4 * j + 2] = x.z;
                 noff[b][4 * j + 3] = x.w;
             }
         }
-        // (the buffers are written again only behind the barrier in front of the first tile)
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (NB == 2) read_queries(NB - 1);
+    // (the barrier in front of the first tile lies between these reads and what else goes there: the third tile, pass 2's partial results)
 
     // Pass 2: combine the NPART partial column results of a finished tile in a fixed order.  Wave w
     // takes tokens 16w..16w+15, four lanes per token, each lane NPART/4 partials, then the quad.
@@ -378,7 +432,6 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
     auto start_split = [&]() {
 #pragma unroll
         for (int st = 0; st < STEPS; ++st) frag_addr[st] = lds0 + l32 * ROWB + (((2 * st + half) ^ (l32 & 15)) * 16);
-        if (MODE == 0) issue_first();
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
 
@@ -494,7 +547,10 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
         for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int k = 0; k < 4; ++k) bad = bad || !(z[b][k] <= kFrozenSumLimit);
-        if (__syncthreads_or(bad)) {  // uniform; also orders the last reads of the tile buffers before the new DMA
+        if (bad) *behind = 1;
+        __syncthreads();
+        if (*behind) {  // uniform; the barrier also orders the last reads of the tile buffers before the new DMA
+            issue_first();
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 m[b] = kNegBig;
@@ -521,7 +577,7 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
             const float zz = zb * fast_exp2(m[b] - mm) + zo * fast_exp2(mo - mm);
             const int rl = rl0 + b * 32 + l32;
             if (half == 0 && rl < a.rows_per_group) {
-                const int64_t r = (int64_t)(g * a.G + rl / a.Lq) * a.Lq + rl % a.Lq;
+                const int64_t r = (int64_t)g * a.rows_per_group + rl;
                 a.part_m[(int64_t)split * nrows + r] = mm;
                 a.part_z[(int64_t)split * nrows + r] = zz;
             }
@@ -684,6 +740,20 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void score_f32_kernel(const Scor
             *(uint4 *)(dst + 2 * kF32Plane) = x.l;
         }
     };
+    // pass 2: see score_rows
+    constexpr int SHARERS = THREADS / ROWS;
+    const int off_row = qb * ROWS + tid / SHARERS;
+    RowParts<SHARERS, 2> parts;
+    float stat_m, stat_z;
+    if (MODE == 1) {
+        const int64_t r = (int64_t)g * a.rows_per_group + min(off_row, a.rows_per_group - 1);
+        if (a.merge) {
+            parts.load(a.part_m + r, a.part_z + r, a.nsplit, nrows, tid % SHARERS);
+        } else {
+            stat_m = a.row_max[r];
+            stat_z = a.row_sumexp[r];
+        }
+    }
     fetch(tile0);
 
     Parts qf[STEPS];
@@ -705,16 +775,8 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void score_f32_kernel(const Scor
     float m = kNegBig, z[4] = {0.f, 0.f, 0.f, 0.f};  // pass 1
     float noff[MODE == 1 ? 16 : 1];                  // pass 2, see score_kernel
     if (MODE == 1) {
-        constexpr int SHARERS = THREADS / ROWS;
-        const int local = tid / SHARERS, r0 = qb * ROWS + local;
-        const bool real = r0 < a.rows_per_group;
-        const int64_t r = (int64_t)g * a.rows_per_group + (real ? r0 : a.rows_per_group - 1);
-        float off;
-        if (a.merge)
-            off = merged_offset<SHARERS, 2>(a.part_m + r, a.part_z + r, a.nsplit, nrows, tid % SHARERS);
-        else
-            off = row_offset(a.row_max[r], a.row_sumexp[r]);
-        if (tid % SHARERS == 0) red[local] = real ? off : -INFINITY;
+        const float off = a.merge ? parts.offset(a.nsplit, tid % SHARERS) : row_offset(stat_m, stat_z);
+        if (tid % SHARERS == 0) red[tid / SHARERS] = off_row < a.rows_per_group ? off : -INFINITY;
     }
     stage(0);
     if (tile0 + 1 < tile1) fetch(tile0 + 1);
@@ -928,7 +990,7 @@ __global__ __launch_bounds__(256) void combine_row_stats(const float *part_m, co
         }
 #pragma unroll
         for (int i = 0; i < kBlock; ++i)
-            if (s0 + i * kCombineLanes < nsplit) zz += z[i] * fast_exp2(m[i] - mm);
+            if (s0 + i * kCombineLanes < nsplit) zz = fmaf(z[i], fast_exp2(m[i] - mm), zz);
     }
 #pragma unroll
     for (int o = 1; o < kCombineLanes; o <<= 1) zz += __shfl_xor(zz, o);
@@ -962,7 +1024,8 @@ __global__ void reduce_units(const float *partial, int nunits, int64_t L, float 
     score[t] = acc;
 }
 
-constexpr size_t tile_lds_bytes(int waves) { return 3 * (size_t)Bf16::tile_tokens(waves) * (Bf16::kChunksPerRow * 16); }
+// of three tiles, of two tiles and 32 query rows a wavefront (as much as two tiles)
+constexpr size_t tile_lds_bytes(int waves, int tiles) { return tiles * (size_t)Bf16::tile_tokens(waves) * (Bf16::kChunksPerRow * 16); }
 
 // The dynamic-LDS ceiling of a kernel is raised once per process (to the most any plan asks of it: the
 // 8-wavefront tiles plus the partial-result buffers of pass 2), not on every launch.
@@ -1069,9 +1132,10 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv, bool ro
     p.table_tag = tag;
     p.lds_bytes_stats = p.lds_bytes_cols = kF32Lds;
     if (dtype == ILRE_F32) return p;
-    const size_t tiles = tile_lds_bytes(p.waves);
-    p.lds_bytes_stats = tiles;
-    p.lds_bytes_cols = tiles + 3 * 2 * (size_t)p.waves * (p.tile_tokens + 36) * sizeof(float);  // pitch <= tokens + 36
+    const size_t start = tile_lds_bytes(p.waves, 4);  // and behind it pass 1's flag or pass 2's row offsets
+    p.lds_bytes_stats = start + 16;
+    p.lds_bytes_cols = std::max(start + (size_t)p.rows_per_wg * sizeof(float),
+                                tile_lds_bytes(p.waves, 3) + 3 * 2 * (size_t)p.waves * (p.tile_tokens + 36) * sizeof(float));  // pitch <= tokens + 36
     return p;
 }
 

@@ -95,6 +95,32 @@ def test_scoring_narrow_query_block(Lq, Hq, Hkv, L):
         assert bad == 0, f"{bad} scores out of tolerance, worst {worst:.2f}x"
 
 
+@pytest.mark.parametrize("L,Lq,Hq,Hkv", [(300, 1, 8, 8), (9000, 17, 28, 4), (700, 40, 16, 4), (9000, 87, 16, 4), (5000, 131, 12, 4), (40000, 65, 28, 4)],
+                         ids=["1_row", "119_rows", "160_rows", "348_rows", "393_rows", "455_rows_64_splits"])
+def test_query_rows_however_they_lie(L, Lq, Hq, Hkv):
+    """Query rows reach the kernels' registers by two ways, one for heads that follow each other without a gap.  Blocks of 128, 256, 256 + 128 and 512
+    rows, the last of them partly filled, one row and many splits: the same bits from rows with gaps between them,
+    with gaps between the heads and with the heads side by side, and the oracle's scores."""
+    _announce(f"query rows L={L} Lq={Lq} {Hq}/{Hkv}")
+    inp = inputs.custom(L=L, Lq=Lq, Hq=Hq, Hkv=Hkv, d=128, dtype="bf16", n_spans=1, span_len=(8, 24), channel_scale=True, seed=Lq)
+    q, k = to_device(inp.q), to_device(inp.k)
+    wide = torch.zeros(Hq, Lq + 3, 136, dtype=q.dtype, device="cuda")
+    token_major = torch.zeros(Lq, Hq, 128, dtype=q.dtype, device="cuda").permute(1, 0, 2)
+    layouts = [wide[:, :Lq, :128], wide.new_zeros(Hq, Lq + 1, 128)[:, 1:], token_major]
+    for x in layouts:
+        x.copy_(q)
+    for gpu_mode, mode in ((il.ILRE_SCORE_SUM, oracle.MODE_SUM), (il.ILRE_SCORE_MAX, oracle.MODE_MAX)):
+        idx, scores = il.ilre_recall(q, k, 64, (3, 7), score_mode=gpu_mode)
+        want, _, _ = oracle.scores(inp.q, inp.k, mode=mode)
+        torch.cuda.synchronize()
+        bad, worst = score_errors(scores.cpu().numpy(), want)
+        assert bad == 0, f"{bad} scores out of tolerance, worst {worst:.2f}x"
+        for x in layouts:
+            other = il.ilre_recall(x, k, 64, (3, 7), score_mode=gpu_mode)
+            torch.cuda.synchronize()
+            assert torch.equal(idx, other[0]) and torch.equal(scores, other[1]), x.stride()
+
+
 def test_unequal_query_blocks_want_a_workspace_for_them():
     """A block of 256 rows and one of 128 leave two partial score vectors a kv head.  A workspace that has room for one serves as
     well: one padded block is taken then."""
