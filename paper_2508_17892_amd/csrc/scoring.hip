@@ -217,8 +217,8 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
     }
 
     // Query fragments, resident for the whole kernel: lane holds, for each of its NB blocks, row
-    // l32 of the block, 16-byte chunk (2*step + half) of that row.  Rows past the group's last one repeat it: pass 1 does not
-    // store their statistics, pass 2 gives them the offset -inf.
+    // l32 of the block, 16-byte chunk (2*step + half) of that row.  Rows past the group's last one are read as that one and become
+    // zeros: pass 1 does not store their statistics, pass 2 gives them the offset -inf.
     // They come by way of LDS, where a wavefront's copy of 32 rows is the size of half a tile's share (behind the first two tile buffers,
     // laid out as a tile is), one block after the other.  Read straight into the registers a load takes 16 bytes from each of 64
     // cache lines, and the K tiles queue up behind 16 of them a wavefront: 131072 tokens, 512 rows a workgroup, the tiles were there 6.7 us
@@ -254,6 +254,11 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
 #pragma unroll
         for (int st = 0; st < STEPS; ++st)
             qf[b][st] = *(const uint4 *)(__attribute__((address_space(3))) unsigned char *)(size_t)(qlds + l32 * ROWB + (((2 * st + half) ^ (l32 & 15)) * 16));
+        if (rl0 + b * 32 + 32 > a.rows_per_group) {  // uniform
+            // (matrix instructions draw less power on zeros, and the clock follows: 60000 tokens, 64 of 128 rows 62.1 -> 60.7 us a recall)
+#pragma unroll
+            for (int st = 0; st < STEPS; ++st) qf[b][st] = rl0 + b * 32 + l32 < a.rows_per_group ? qf[b][st] : make_uint4(0, 0, 0, 0);
+        }
     };
 
     // K tiles: three LDS buffers of TN rows, row r's 16-byte chunk c stored at chunk position
@@ -329,7 +334,7 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
         // The exponent offsets of the workgroup's rows, handed out through LDS (a kernel that wrote them to a table before took
         // 4.7 us of a staged call: 50001 tokens 149.9 -> 146.9 us):
         // accumulator registers 4j .. 4j+3 of a lane are four consecutive rows.  Rows past the group's last one
-        // get -inf: exp2(x*c - inf) = 0.
+        // (q = 0) get -inf: exp2(0*c - inf) = 0.
         float *offs = (float *)behind;
         const float off = many      ? more_parts.offset(a.nsplit, tid % SHARERS)
                           : a.merge ? parts.offset(a.nsplit, tid % SHARERS)
