@@ -95,14 +95,15 @@ def test_scoring_narrow_query_block(Lq, Hq, Hkv, L):
         assert bad == 0, f"{bad} scores out of tolerance, worst {worst:.2f}x"
 
 
-@pytest.mark.parametrize("L,Lq,Hq,Hkv", [(300, 1, 8, 8), (9000, 17, 28, 4), (700, 40, 16, 4), (9000, 87, 16, 4), (5000, 131, 12, 4), (40000, 65, 28, 4)],
-                         ids=["1_row", "119_rows", "160_rows", "348_rows", "393_rows", "455_rows_64_splits"])
-def test_query_rows_however_they_lie(L, Lq, Hq, Hkv):
-    """Query rows reach the kernels' registers by two ways, one for heads that follow each other without a gap.  Blocks of 128, 256, 256 + 128 and 512
+@pytest.mark.parametrize("L,Lq,Hq,Hkv,dtype", [(300, 1, 8, 8, "bf16"), (9000, 17, 28, 4, "bf16"), (700, 40, 16, 4, "bf16"), (9000, 87, 16, 4, "bf16"),
+                                               (5000, 131, 12, 4, "bf16"), (40000, 65, 28, 4, "bf16"), (300, 1, 8, 8, "f32"), (2000, 43, 12, 4, "f32")],
+                         ids=["1_row", "119_rows", "160_rows", "348_rows", "393_rows", "455_rows_64_splits", "f32_1_row", "f32_129_rows"])
+def test_query_rows_however_they_lie(L, Lq, Hq, Hkv, dtype):
+    """Query rows reach the kernels' registers by two ways, one for heads that follow each other without a gap (bf16).  Blocks of 128, 256, 256 + 128 and 512
     rows, the last of them partly filled, one row and many splits: the same bits from rows with gaps between them,
     with gaps between the heads and with the heads side by side, and the oracle's scores."""
-    _announce(f"query rows L={L} Lq={Lq} {Hq}/{Hkv}")
-    inp = inputs.custom(L=L, Lq=Lq, Hq=Hq, Hkv=Hkv, d=128, dtype="bf16", n_spans=1, span_len=(8, 24), channel_scale=True, seed=Lq)
+    _announce(f"query rows L={L} Lq={Lq} {Hq}/{Hkv} {dtype}")
+    inp = inputs.custom(L=L, Lq=Lq, Hq=Hq, Hkv=Hkv, d=128, dtype=dtype, n_spans=1, span_len=(8, 24), channel_scale=True, seed=Lq)
     q, k = to_device(inp.q), to_device(inp.k)
     wide = torch.zeros(Hq, Lq + 3, 136, dtype=q.dtype, device="cuda")
     token_major = torch.zeros(Lq, Hq, 128, dtype=q.dtype, device="cuda").permute(1, 0, 2)
