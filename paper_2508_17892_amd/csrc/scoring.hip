@@ -114,10 +114,10 @@ __device__ __forceinline__ float row_offset(float row_max, float row_sumexp) { r
 // the first K tiles.  It saves a launch of 3.8 - 5 us; on the other hand every workgroup of a kv head reads all of the
 // head's partials.  Measured, merge kernel -> this, whole recall: 16 splits (1000 tokens) 33.1 -> 29.1 us, 32 splits
 // (40000 tokens, 32/8 heads, 128 queries) 115.4 -> 113.9 us; 64 splits (20000 tokens fp32) 132.4 -> 134.2 us,
-// 256 splits (100000 tokens, 8/2 heads, 64 queries) 72.2 -> 86.9 us.  Two splits a sum is where it stops to pay with 256 rows a
-// workgroup (64 queries, 32768 and 100003 tokens 76.8 and 142.4 us either way), four with 128, which are half the partials (64
-// splits, 32/8 heads, 32 queries 62.5 -> 61.6 and 103.9 -> 102.6; 128 splits, 28/4 heads, 17 queries, 100003 tokens 74.8 -> 76.4), and with
-// 512, where half as many workgroups read them (28/4 heads, 64 queries 74.6 -> 73.2 and 134.2 -> 133.3).
+// 256 splits (100000 tokens, 8/2 heads, 64 queries) 72.2 -> 86.9 us.  Four splits a sum is where it stops to pay (64 splits, 32/8 heads: 64 queries,
+// 32768 tokens 78.0 -> 76.2 us, 100003 147.7 -> 146.9; 32 queries, 128 rows a workgroup 62.5 -> 61.6; 28/4 heads, 64 queries, 512 rows 74.6 -> 73.2;
+// 128 splits of 128 rows 73.5 -> 75.0 and, 20000 tokens, 54.0 -> 56.5), in blocks of 256 and 128 rows two (96 queries, 30000 tokens, 64 splits 90.0
+// -> 90.7).
 constexpr int kCombineLanes = 16;
 constexpr int kMergeSplits = 2 * kCombineLanes;
 // The loads are issued before those of Q and K, which arrive while the sums are made (K first: the wait for the partials was one for Q
@@ -1137,7 +1137,7 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv, bool ro
     p.grid = (int)(((pairs + kNumXCD - 1) / kNumXCD) * kNumXCD * p.nqb);
     // pass 2's ranges follow the XCDs' speed where a range is long enough for that to matter
     p.balanced = dtype != ILRE_F32 && p.tiles_per_split >= 64 && p.nsplit >= kNumXCD && p.nsplit <= kMaxBalancedSplits;
-    p.merge_in_cols = !p.balanced && p.nsplit <= (dtype != ILRE_F32 && (p.nb == 1 || p.waves == 8) ? 2 : 1) * kMergeSplits;
+    p.merge_in_cols = !p.balanced && p.nsplit <= (dtype == ILRE_F32 || p.mixed ? 1 : 2) * kMergeSplits;
     uint64_t tag = 0x494c52652d584344ull;  // what a table has to have been made for
     for (uint64_t v : {(uint64_t)L, (uint64_t)p.ntiles, (uint64_t)p.nsplit, (uint64_t)p.nqb, (uint64_t)Hkv, (uint64_t)p.tile_tokens,
                        (uint64_t)p.grid})
@@ -1203,10 +1203,13 @@ hipError_t launch_col_scores(const ScorePlan &p, const ScoreArgs &a, int score_m
     else if (p.mixed)
         e = mx ? launch_score(score_kernel<2, 4, 1, 1, true>, p.grid, 256, lds, a, s)
                : launch_score(score_kernel<2, 4, 1, 0, true>, p.grid, 256, lds, a, s);
+    else if (p.waves == 4 && a.merge && a.nsplit > kMergeSplits)  // (of its own: with both in one kernel up to 32 splits took 0.4 % longer)
+        e = mx ? launch_score(score_kernel<2, 4, 1, 1, false, true>, p.grid, 256, lds, a, s)
+               : launch_score(score_kernel<2, 4, 1, 0, false, true>, p.grid, 256, lds, a, s);
     else if (p.waves == 4)
         e = mx ? launch_score(score_kernel<2, 4, 1, 1, false>, p.grid, 256, lds, a, s)
                : launch_score(score_kernel<2, 4, 1, 0, false>, p.grid, 256, lds, a, s);
-    else if (a.merge && a.nsplit > kMergeSplits)  // (of its own: with both in one kernel up to 32 splits took 0.4 % longer)
+    else if (a.merge && a.nsplit > kMergeSplits)
         e = mx ? launch_score(score_kernel<2, 8, 1, 1, false, true>, p.grid, 512, lds, a, s)
                : launch_score(score_kernel<2, 8, 1, 0, false, true>, p.grid, 512, lds, a, s);
     else

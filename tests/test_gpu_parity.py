@@ -201,8 +201,8 @@ def test_query_blocks_that_outnumber_an_xcds_places(L, Lq, Hq, Hkv, dtype):
 @pytest.mark.parametrize("dtype,Lq,G,Hkv", [("bf16", 20, 2, 4), ("bf16", 50, 4, 4), ("bf16", 64, 8, 2), ("bf16", 96, 4, 4), ("f32", 33, 2, 4), ("f32", 80, 2, 4)],
                          ids=["pair_of_threads_a_row", "4_waves", "8_waves", "blocks_of_256_and_128", "f32", "f32_two_query_blocks"])
 def test_second_pass_merges_the_partial_statistics(dtype, Lq, G, Hkv):
-    """In the whole path the second scoring pass merges the splits' partial row statistics itself, up to 32 splits (64 where a
-    workgroup has 128 or 512 rows), in the order the merge kernel of the staged call uses: the scores are the same bits either way.  Numbers of splits
+    """In the whole path the second scoring pass merges the splits' partial row statistics itself, up to 32 splits (64 where all
+    workgroups have as many rows, bf16), in the order the merge kernel of the staged call uses: the scores are the same bits either way.  Numbers of splits
     around the 16 sums and the line (bf16: one a tile up to 64; fp32: one for two tiles of 32 tokens, or fewer of more tiles where that keeps
     every compute unit as busy: 17 to 32 of 66 to 128 tiles with two blocks of rows); one row beyond every frozen reference, so that a
     split's partial has another reference."""
