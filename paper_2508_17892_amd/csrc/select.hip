@@ -1957,8 +1957,10 @@ __device__ __forceinline__ uint32_t nth_set_bit(uint32_t x, uint32_t k)
 
 // The allocated set in ascending order, read off its bitmap by the walk's workgroup.  slot_word: per place in the output the
 // word (number + 1) whose first token goes there, or 0.
+template <int THREADS>
 __device__ __forceinline__ void emit_bitmap(const WalkArgs &a, const uint32_t *mask, uint16_t *slot_word, uint32_t *chunk_n, uint32_t nsel)
 {
+    constexpr int WAVES = THREADS / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t chunks = (a.len + 32 * kBitmapChunk - 1) / (32 * kBitmapChunk);
     // The tokens per chunk (a lane counts four neighbouring words) and
@@ -1967,22 +1969,22 @@ __device__ __forceinline__ void emit_bitmap(const WalkArgs &a, const uint32_t *m
     // All of it is latency: kEmitBatch chunks (groups of 64 places) of a wavefront advance together.
     constexpr int kEmitBatch = 4;
     __syncthreads();  // every wavefront is done with the set, and with what slot_word held
-    for (uint32_t i = tid * 8; i < (uint32_t)a.n_out; i += kWalkThreads * 8) *(uint4 *)&slot_word[i] = make_uint4(0, 0, 0, 0);
+    for (uint32_t i = tid * 8; i < (uint32_t)a.n_out; i += THREADS * 8) *(uint4 *)&slot_word[i] = make_uint4(0, 0, 0, 0);
     auto words4 = [&](uint32_t c) {  // the lane's four words of a chunk, none past the last chunk
         return c < chunks ? *(const uint4 *)&mask[c * kBitmapChunk + 4 * lane] : make_uint4(0, 0, 0, 0);
     };
-    for (uint32_t c0 = wave; c0 < chunks; c0 += kWalkWaves * kEmitBatch) {
+    for (uint32_t c0 = wave; c0 < chunks; c0 += WAVES * kEmitBatch) {
         uint32_t sum[kEmitBatch];
 #pragma unroll
         for (int b = 0; b < kEmitBatch; ++b) {
-            const uint4 x = words4(c0 + b * kWalkWaves);
+            const uint4 x = words4(c0 + b * WAVES);
             sum[b] = __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w);
         }
 #pragma unroll
         for (int b = 0; b < kEmitBatch; ++b) sum[b] = wave_scan_add(sum[b]);
 #pragma unroll
         for (int b = 0; b < kEmitBatch; ++b)
-            if (lane == 63 && c0 + b * kWalkWaves < chunks) chunk_n[c0 + b * kWalkWaves] = sum[b];
+            if (lane == 63 && c0 + b * WAVES < chunks) chunk_n[c0 + b * WAVES] = sum[b];
     }
     __syncthreads();
     // every wavefront sums the chunks before each of its own by itself (lane l holds chunks l, l + 64, l + 128)
@@ -1990,12 +1992,12 @@ __device__ __forceinline__ void emit_bitmap(const WalkArgs &a, const uint32_t *m
 #pragma unroll
     for (int i = 0; i < 3; ++i) cn[i] = (uint32_t)(lane + 64 * i) < chunks ? chunk_n[lane + 64 * i] : 0u;
     static_assert(kBitmapChunks <= 3 * 64, "three chunks a lane");
-    for (uint32_t c0 = wave; c0 < chunks; c0 += kWalkWaves * kEmitBatch) {
+    for (uint32_t c0 = wave; c0 < chunks; c0 += WAVES * kEmitBatch) {
         uint4 x[kEmitBatch];
         uint32_t n3[kEmitBatch], at[kEmitBatch];
 #pragma unroll
         for (int b = 0; b < kEmitBatch; ++b) {
-            const uint32_t c = c0 + b * kWalkWaves;
+            const uint32_t c = c0 + b * WAVES;
             x[b] = words4(c);
             n3[b] = __popc(x[b].x) + __popc(x[b].y) + __popc(x[b].z) + __popc(x[b].w);
             at[b] = ((uint32_t)lane < c ? cn[0] : 0u) + ((uint32_t)lane + 64 < c ? cn[1] : 0u) + ((uint32_t)lane + 128 < c ? cn[2] : 0u);
@@ -2004,7 +2006,7 @@ __device__ __forceinline__ void emit_bitmap(const WalkArgs &a, const uint32_t *m
         for (int b = 0; b < kEmitBatch; ++b) at[b] = wave_total(wave_scan_add(at[b])) + wave_scan_add(n3[b]) - n3[b];
 #pragma unroll
         for (int b = 0; b < kEmitBatch; ++b) {
-            const uint32_t w = (c0 + b * kWalkWaves) * kBitmapChunk + 4 * lane;
+            const uint32_t w = (c0 + b * WAVES) * kBitmapChunk + 4 * lane;
             if (x[b].x) slot_word[at[b]] = (uint16_t)(w + 1);
             at[b] += __popc(x[b].x);
             if (x[b].y) slot_word[at[b]] = (uint16_t)(w + 2);
@@ -2017,7 +2019,7 @@ __device__ __forceinline__ void emit_bitmap(const WalkArgs &a, const uint32_t *m
     __syncthreads();
     int32_t *out = a.out_idx + a.sink;
     // a wavefront's places lie side by side: the last note of one group of 64 serves the next
-    const uint32_t span = (nsel + kWalkThreads - 1) / kWalkThreads * 64, s_begin = wave * span, s_end = min(s_begin + span, nsel);
+    const uint32_t span = (nsel + THREADS - 1) / THREADS * 64, s_begin = wave * span, s_end = min(s_begin + span, nsel);
     auto note_of = [&](uint32_t s) {  // place and word in one number, larger for a later place
         const uint32_t x = s < nsel ? slot_word[s] : 0u;
         return x ? (s & 0xFFFFu) << 16 | x : 0u;
@@ -2042,8 +2044,8 @@ __device__ __forceinline__ void emit_bitmap(const WalkArgs &a, const uint32_t *m
             if (s < s_end) out[s] = (int32_t)(((note[b] & 0xFFFFu) - 1u) * 32 + nth_set_bit(bits[b], s - (note[b] >> 16)) + (uint32_t)a.sink);
         }
     }
-    for (uint32_t i = tid; i < (uint32_t)a.sink; i += kWalkThreads) a.out_idx[i] = (int32_t)i;
-    for (uint32_t i = nsel + tid; i < (uint32_t)a.n_out; i += kWalkThreads) out[i] = -1;
+    for (uint32_t i = tid; i < (uint32_t)a.sink; i += THREADS) a.out_idx[i] = (int32_t)i;
+    for (uint32_t i = nsel + tid; i < (uint32_t)a.n_out; i += THREADS) out[i] = -1;
     if (tid == 0 && a.out_count) *a.out_count = a.sink + (int32_t)nsel;
 }
 
@@ -2303,7 +2305,7 @@ __device__ __forceinline__ void walk_items(const WalkArgs &a, unsigned char *sme
         return;
     }
 
-    emit_bitmap(a, set.mask, (uint16_t *)ring, chunk_n, nsel);
+    emit_bitmap<kWalkThreads>(a, set.mask, (uint16_t *)ring, chunk_n, nsel);
 }
 
 template <int ITEMS, bool HASHED>
@@ -2324,14 +2326,16 @@ __global__ __launch_bounds__(kWalkThreads) void allocate_walk(const WalkArgs a)
 // saves time, the turn decides on what the set holds then.
 // Bound: the chain of a turn, about 650 cycles, half of them LDS round trips (see the turn, fetch the words, mark, pass it on),
 // where a pass of the workgroup over the whole list took 1300.  Measured (kernel trace), 48 combinations: 9001 tokens, budget
-// 1000 33.9 -> 19.4 us; 1M, budget 4096 40.8 -> 26.7 us.
+// 1000 33.9 -> 19.7 us; 1M, budget 4096 40.8 -> 26.5 us.
 constexpr int kRelayCombos = 4;                                 // from that many combinations on, and where ..
 constexpr uint32_t kRelayShare = 96, kRelayShareTable = 48;      // .. no share is more cells (with the word table)
 constexpr int kRelayRaw = 16;                                   // cells of a list a lane fetches ahead
 constexpr int kRelayKept = kRingBytes / 4 / kWalkWaves;         // cells a wavefront keeps
+// Eight wavefronts take turns, sixteen clear the set and read it off at the end (1M scores, 48 combinations 26.5 -> 24.4 us, 9001 19.7 -> 19.4).
+constexpr int kRelayThreads = 1024;
 constexpr uint32_t kRelayChunk = 64 * kWalkPer;                 // cells it looks at at a time with the turn
 template <bool HASHED>
-__global__ __launch_bounds__(kWalkThreads) void allocate_relay(const WalkArgs a)
+__global__ __launch_bounds__(kRelayThreads) void allocate_relay(const WalkArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t chunk_n[kBitmapChunks];
@@ -2353,8 +2357,8 @@ __global__ __launch_bounds__(kWalkThreads) void allocate_relay(const WalkArgs a)
         for (int k = 0; k < kRelayRaw; ++k)
             if (64u * k < cn) raw[k] = list_of(j)[min(64u * k + lane, cn - 1)];  // uniform
     };
-    if (wave < a.n) fetch(wave);
-    for (uint32_t i = tid * 4; i < clear; i += kWalkThreads * 4) {
+    if (wave < kWalkWaves && wave < a.n) fetch(wave);
+    for (uint32_t i = tid * 4; i < clear; i += kRelayThreads * 4) {
         if (HASHED) *(uint4 *)&set.key[i] = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
         *(uint4 *)&set.mask[i] = make_uint4(0, 0, 0, 0);
     }
@@ -2362,7 +2366,7 @@ __global__ __launch_bounds__(kWalkThreads) void allocate_relay(const WalkArgs a)
     __syncthreads();
     auto whose = [&]() { return __hip_atomic_load(&turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
 
-    for (int j = wave; j < a.n; j += kWalkWaves) {
+    for (int j = wave < kWalkWaves ? wave : a.n; j < a.n; j += kWalkWaves) {
         const uint32_t cn = of(l_cells, j), reach = of(l_reach, j), ones = 0xFFFFFFFFu >> (32 - reach);
         const uint32_t *list = list_of(j);
         auto word_of = [&](uint32_t c) { return c * reach >> 5; };
@@ -2478,7 +2482,7 @@ __global__ __launch_bounds__(kWalkThreads) void allocate_relay(const WalkArgs a)
         if (tid == 0) *a.picked_n = nsel;
         return;
     }
-    emit_bitmap(a, set.mask, (uint16_t *)ring, chunk_n, nsel);
+    emit_bitmap<kRelayThreads>(a, set.mask, (uint16_t *)ring, chunk_n, nsel);
 }
 
 
@@ -2844,9 +2848,9 @@ void launch_walk(WalkArgs &w, const SelectJob &job, int n_out, unsigned char *ws
     if (bitmap) {
         const size_t chunks = ((size_t)job.L + 32 * kBitmapChunk - 1) / (32 * kBitmapChunk);
         const size_t lds = chunks * kBitmapChunk * sizeof(uint32_t) + kRingBytes;
-        hipLaunchKernelGGL((relay ? allocate_relay<false> : allocate_walk<ITEMS, false>), dim3(1), dim3(kWalkThreads), lds, s, w);
+        hipLaunchKernelGGL((relay ? allocate_relay<false> : allocate_walk<ITEMS, false>), dim3(1), dim3(relay ? kRelayThreads : kWalkThreads), lds, s, w);
     } else {
-        hipLaunchKernelGGL((relay ? allocate_relay<true> : allocate_walk<ITEMS, true>), dim3(1), dim3(kWalkThreads),
+        hipLaunchKernelGGL((relay ? allocate_relay<true> : allocate_walk<ITEMS, true>), dim3(1), dim3(relay ? kRelayThreads : kWalkThreads),
                            2 * (size_t)kWordSlots * sizeof(uint32_t) + kRingBytes, s, w);
         hipLaunchKernelGGL(emit_sorted, dim3((unsigned)((n_out + kEmitPerBlock - 1) / kEmitPerBlock) + 1u), dim3(kEmitThreads), 0, s,
                            w.picked, w.picked_n, n_out, job.sink, out_idx, out_count);
