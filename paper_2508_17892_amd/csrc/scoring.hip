@@ -195,6 +195,10 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
     const int l32 = lane & 31;
     const int half = lane >> 5;
     const int rl0 = qb * a.rows_per_wg + wave * (NB * 32);
+    // One block a wavefront: a wavefront without a single row copies its share of the tiles, and in pass 2 adds up its tokens, but computes
+    // nothing (500000 tokens, 32/8 heads, 8 queries, 32 of 128 rows 443.5 -> 438.4 us a recall; 60000, 16/4, 16 60.4 -> 59.8).  With two
+    // blocks the branch costs full workgroups more than it saves the others (32768 tokens, 64 queries 75.4 -> 76.5; 65536, 28/4, 64 103.8 -> 101.6).
+    const bool idle = NB == 1 && __builtin_amdgcn_readfirstlane(rl0) >= a.rows_per_group;
     const int64_t nrows = (int64_t)a.Hq * a.Lq;
 
     // Pass 2: what the exponent offset of a row is made of, one row a thread (NB = 1: a pair of threads).
@@ -439,6 +443,9 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
         for (int st = 0; st < STEPS; ++st) frag_addr[st] = lds0 + l32 * ROWB + (((2 * st + half) ^ (l32 & 15)) * 16);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
+        if (MODE == 1 && idle)  // what it has to add, once for all tiles
+            for (int i = lane; i < 3 * 2 * TN; i += 64)
+                red[(i / (2 * TN) * NPART + wave * 2 + i / TN % 2) * RSTR + i % TN] = RMAX ? -INFINITY : 0.f;
 
         // acc[u & 1] receives unit u (a 32-token block against the wave's NB query blocks); the unit
         // before the very first one is all -inf, which the softmax arithmetic turns into zeros.
@@ -463,6 +470,15 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
         const int it = (int)(tile - tile0);
         const int rb_cur = it % 3, rb_prev = (it + 2) % 3;
         if (tile + 2 < tile1) issue_tile(tile + 2, (it + 2) % 3);
+        if (idle) {
+            if (MODE == 1) {
+                flush_load(it >= 2 ? tile - 2 : tile);
+                flush_finish(tile - 2, it >= 2);
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            return;
+        }
         // byte distance from this tile's buffer to the next tile's
         const int to_next = (it % 3 == 2) ? -2 * TILE_BYTES : TILE_BYTES;
 
@@ -533,6 +549,7 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
     if (MODE == 0)
         for (; tile < tile_full_end; ++tile) do_tile(tile, std::false_type{}, std::true_type{});
     if (last_ragged) do_tile(tile1 - 1, std::true_type{}, std::false_type{});
+    if (idle) return;
     // drain the pipeline: the last unit of the last tile
     const int rb_last = (int)((tile1 - 1 - tile0) % 3);
 #pragma unroll
