@@ -716,7 +716,13 @@ __device__ __forceinline__ Parts split3(const float4 &a, const float4 &b)
     return {make_uint4(h[0], h[1], h[2], h[3]), make_uint4(m[0], m[1], m[2], m[3]), make_uint4(l[0], l[1], l[2], l[3])};
 }
 
-template <int MODE, int RMAX>
+// BY_LDS: the query rows come by way of LDS.  Read straight into the registers, a load takes 32 bytes from each of 64 rows, and the loads of four
+// wavefronts queue up; those of one or two are there before a copy that is read again behind the whole workgroup's barrier.  Measured,
+// straight -> by LDS, the two passes: 128 rows a kv head, 4096 tokens, 32/8 heads 13.4 + 13.3 -> 12.8 + 12.5 us; 9220 tokens, 96 rows 22.4 + 21.6
+// -> 21.9 + 21.7, 72 21.8 + 21.0 -> 21.6 + 21.0, 64 21.1 + 20.3 -> 21.0 + 20.9, 32 19.7 + 19.8 -> 20.5 + 20.6; 40 rows, 30000 tokens, 16/4 26.7 + 25.8
+// -> 27.2 + 26.7.
+constexpr int kF32StraightRows = 64;
+template <int MODE, int RMAX, bool BY_LDS>
 __global__ __launch_bounds__(kF32Waves * 64, 2) void score_f32_kernel(const ScoreArgs a)
 {
     using T = Bf16;
@@ -778,29 +784,53 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void score_f32_kernel(const Scor
     }
     fetch(tile0);
 
-    // The wavefront's 32 query rows, by way of LDS as in score_rows (rows past the group's last one are read as that one): 16-byte chunks, chunk c of
-    // row r at c ^ r.  (Read straight into the registers, 32 bytes from each of 64 rows: 4096 tokens, 32 queries 40.3 -> 39.0 us a recall.)
-    const unsigned qlds = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)smem + wave * (32 * 512);
-    {
-        const int at = min(rl, a.rows_per_group - 1), h = g * a.G + at / a.Lq, i = at % a.Lq;
-        const uint64_t own = (uint64_t)a.q + (uint64_t)(((int64_t)h * a.q_stride_head + (int64_t)i * a.q_stride_token) * 4);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {  // two rows at a time
-            const int row = j * 2 + half;
-            const uint64_t src = (uint64_t)(uint32_t)__shfl((int)(uint32_t)(own >> 32), row) << 32 | (uint32_t)__shfl((int)(uint32_t)own, row);
-            lds_dma16(src + ((l32 ^ row) * 16), __builtin_amdgcn_readfirstlane(qlds + j * 1024));
-        }
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     Parts qf[STEPS];
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    if constexpr (BY_LDS) {
+        // As in score_rows: 16-byte chunks, chunk c of row r at c ^ r, rows past the group's last one read as that one.  A wavefront without a row
+        // copies none, it would only stand in the others' way.
+        const int rl0 = qb * ROWS + wave * 32;
+        const unsigned qlds = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)smem + wave * (32 * 512);
+        auto copy = [&](auto row_at) {
 #pragma unroll
-    for (int st = 0; st < STEPS; ++st) {
-        const unsigned char *src = smem + wave * (32 * 512) + l32 * 512;
-        const int c = 2 * (2 * st + half);
-        const float4 x = *(const float4 *)(src + (c ^ l32) * 16), y = *(const float4 *)(src + ((c + 1) ^ l32) * 16), zero = make_float4(0.f, 0.f, 0.f, 0.f);
-        qf[st] = split3(rl < a.rows_per_group ? x : zero, rl < a.rows_per_group ? y : zero);
+            for (int j = 0; j < 16; ++j) {  // two rows at a time
+                const int row = j * 2 + half;
+                lds_dma16(row_at(row) + ((l32 ^ row) * 16), __builtin_amdgcn_readfirstlane(qlds + j * 1024));
+            }
+        };
+        if (__builtin_amdgcn_readfirstlane(rl0) < a.rows_per_group) {
+            const int64_t row_bytes = a.q_stride_token * 4, head_bytes = a.q_stride_head * 4;
+            if (a.q_stride_head == (int64_t)a.Lq * a.q_stride_token) {  // uniform: a head's rows follow the one's before
+                const uint64_t first = (uint64_t)a.q + (uint64_t)((int64_t)g * a.G * head_bytes);
+                copy([&](int row) { return first + (uint64_t)(min(rl0 + row, a.rows_per_group - 1) * row_bytes); });
+            } else {  // lane l32 works out where row l32 lies
+                const int at = min(rl, a.rows_per_group - 1);
+                const uint64_t own = (uint64_t)a.q + (uint64_t)((int64_t)(g * a.G + at / a.Lq) * head_bytes + (int64_t)(at % a.Lq) * row_bytes);
+                copy([&](int row) { return (uint64_t)(uint32_t)__shfl((int)(uint32_t)(own >> 32), row) << 32 | (uint32_t)__shfl((int)(uint32_t)own, row); });
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) {
+            const unsigned char *src = smem + wave * (32 * 512) + l32 * 512;
+            const int c = 2 * (2 * st + half);
+            const float4 x = *(const float4 *)(src + (c ^ l32) * 16), y = *(const float4 *)(src + ((c + 1) ^ l32) * 16);
+            qf[st] = split3(rl < a.rows_per_group ? x : zero, rl < a.rows_per_group ? y : zero);
+        }
+        __syncthreads();  // the tiles go to the same place
+    } else {
+        const bool real = rl < a.rows_per_group;
+        const int at = real ? rl : 0, h = g * a.G + at / a.Lq, i = at % a.Lq;
+        const unsigned char *src = (const unsigned char *)a.q + ((int64_t)h * a.q_stride_head + (int64_t)i * a.q_stride_token) * 4;
+        float4 x[STEPS][2];
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) {
+            x[st][0] = *(const float4 *)(src + (st * 2 + half) * 32);
+            x[st][1] = *(const float4 *)(src + (st * 2 + half) * 32 + 16);
+        }
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) qf[st] = split3(real ? x[st][0] : zero, real ? x[st][1] : zero);
     }
-    __syncthreads();  // the tiles go to the same place
 
     float m = kNegBig, z[4] = {0.f, 0.f, 0.f, 0.f};  // pass 1
     float noff[MODE == 1 ? 16 : 1];                  // pass 2, see score_kernel
@@ -1177,7 +1207,8 @@ hipError_t launch_row_stats(const ScorePlan &p, const ScoreArgs &a, float *row_m
     const int64_t nrows = (int64_t)a.Hq * a.Lq;
     hipError_t e;
     if (p.dtype == ILRE_F32)
-        e = launch_score(score_f32_kernel<0, 0>, p.grid, kF32Waves * 64, lds, a, s);
+        e = p.rows_per_group > kF32StraightRows ? launch_score(score_f32_kernel<0, 0, true>, p.grid, kF32Waves * 64, lds, a, s)
+                                                : launch_score(score_f32_kernel<0, 0, false>, p.grid, kF32Waves * 64, lds, a, s);
     else if (p.nb == 1)
         e = launch_score(score_kernel<1, 4, 0, 0, false>, p.grid, 256, lds, a, s);
     else if (p.mixed)
@@ -1211,9 +1242,12 @@ hipError_t launch_col_scores(const ScorePlan &p, const ScoreArgs &a, int score_m
     hipError_t e;
     const size_t lds = p.lds_bytes_cols;
     const bool mx = score_mode == ILRE_SCORE_MAX;
-    if (p.dtype == ILRE_F32)
-        e = mx ? launch_score(score_f32_kernel<1, 1>, p.grid, kF32Waves * 64, lds, a, s)
-               : launch_score(score_f32_kernel<1, 0>, p.grid, kF32Waves * 64, lds, a, s);
+    if (p.dtype == ILRE_F32 && p.rows_per_group > kF32StraightRows)
+        e = mx ? launch_score(score_f32_kernel<1, 1, true>, p.grid, kF32Waves * 64, lds, a, s)
+               : launch_score(score_f32_kernel<1, 0, true>, p.grid, kF32Waves * 64, lds, a, s);
+    else if (p.dtype == ILRE_F32)
+        e = mx ? launch_score(score_f32_kernel<1, 1, false>, p.grid, kF32Waves * 64, lds, a, s)
+               : launch_score(score_f32_kernel<1, 0, false>, p.grid, kF32Waves * 64, lds, a, s);
     else if (p.nb == 1)
         e = mx ? launch_score(score_kernel<1, 4, 1, 1, false, true>, p.grid, 256, lds, a, s)
                : launch_score(score_kernel<1, 4, 1, 0, false, true>, p.grid, 256, lds, a, s);

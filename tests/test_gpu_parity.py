@@ -96,10 +96,13 @@ def test_scoring_narrow_query_block(Lq, Hq, Hkv, L):
 
 
 @pytest.mark.parametrize("L,Lq,Hq,Hkv,dtype", [(300, 1, 8, 8, "bf16"), (9000, 17, 28, 4, "bf16"), (700, 40, 16, 4, "bf16"), (9000, 87, 16, 4, "bf16"),
-                                               (5000, 131, 12, 4, "bf16"), (40000, 65, 28, 4, "bf16"), (300, 1, 8, 8, "f32"), (2000, 43, 12, 4, "f32")],
-                         ids=["1_row", "119_rows", "160_rows", "348_rows", "393_rows", "455_rows_64_splits", "f32_1_row", "f32_129_rows"])
+                                               (5000, 131, 12, 4, "bf16"), (40000, 65, 28, 4, "bf16"), (300, 1, 8, 8, "f32"), (2000, 43, 12, 4, "f32"),
+                                               (2000, 16, 16, 4, "f32"), (2000, 13, 20, 4, "f32")],
+                         ids=["1_row", "119_rows", "160_rows", "348_rows", "393_rows", "455_rows_64_splits", "f32_1_row", "f32_129_rows",
+                              "f32_64_rows", "f32_65_rows"])
 def test_query_rows_however_they_lie(L, Lq, Hq, Hkv, dtype):
-    """Query rows reach the kernels' registers by two ways, one for heads that follow each other without a gap (bf16).  Blocks of 128, 256, 256 + 128 and 512
+    """Query rows reach the kernels' registers by two ways, one for heads that follow each other without a gap; fp32 rows up to 64 a kv head
+    are read without LDS in between.  Blocks of 128, 256, 256 + 128 and 512
     rows, the last of them partly filled, one row and many splits: the same bits from rows with gaps between them,
     with gaps between the heads and with the heads side by side, and the oracle's scores."""
     _announce(f"query rows L={L} Lq={Lq} {Hq}/{Hkv} {dtype}")
