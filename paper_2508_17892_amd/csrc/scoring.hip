@@ -195,8 +195,10 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
     const int l32 = lane & 31;
     const int half = lane >> 5;
     const int rl0 = qb * a.rows_per_wg + wave * (NB * 32);
-    // One block a wavefront: a wavefront without a single row copies its share of the tiles, and in pass 2 adds up its tokens, but computes
-    // nothing (500000 tokens, 32/8 heads, 8 queries, 32 of 128 rows 443.5 -> 438.4 us a recall; 60000, 16/4, 16 60.4 -> 59.8).  With two
+    // One block a wavefront: a wavefront without a single row copies its share of the tiles, but no query rows, and in pass 2 adds up its tokens; it
+    // computes nothing.  Both passes, all wavefronts alike -> so (where rows it has no use for are copied all the same): 500000 tokens, 32/8 heads, 8
+    // queries (32 of 128 rows) 165.5 + 235 -> 161.7 + 224 us (161.9 + 225), staged 167 + 235 -> 161.4 + 224.5; 9000 tokens, 8/2, staged
+    // 5.4 + 5.8 -> 4.8 + 5.2 (5.2 + 5.6); 119 of 128 rows, none idle, 100003 tokens 20.1 + 21.7 -> 20.4 + 21.6.  With two
     // blocks the branch costs full workgroups more than it saves the others (32768 tokens, 64 queries 75.4 -> 76.5; 65536, 28/4, 64 103.8 -> 101.6).
     const bool idle = NB == 1 && __builtin_amdgcn_readfirstlane(rl0) >= a.rows_per_group;
     const int64_t nrows = (int64_t)a.Hq * a.Lq;
@@ -314,7 +316,7 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
     const int unit = g * a.nqb + qb;
 
     uint32_t *behind = (uint32_t *)(smem + 4 * TILE_BYTES);  // behind the wavefronts' query rows
-    issue_queries(0);
+    if (!idle) issue_queries(0);
     issue_first();
     if (tile0 + 1 < tile1)  // (the tiles may stay on their way)
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NLW) : "memory");
