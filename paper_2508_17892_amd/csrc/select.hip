@@ -1968,54 +1968,73 @@ __device__ __forceinline__ void emit_bitmap(const WalkArgs &a, const uint32_t *m
     // noted place at or before its own is at most 31 back and names the word, the distance the bit in it.
     // All of it is latency: kEmitBatch chunks (groups of 64 places) of a wavefront advance together.
     constexpr int kEmitBatch = 4;
+    // Sixteen wavefronts take no more at a time than they have: chunks that are not there make their scans all the same, with four wavefronts a
+    // SIMD in each other's way (48 combinations, budget 1000, the whole walk with eight wavefronts, sixteen in batches of four, so:
+    // 116363 scores 19.7, 20.1, 19.1 us, 200000 19.8, 20.3, 19.6, 300000, still four, 21.2, 20.6, 20.6).
+    auto by_batches = [&](auto loop) {
+        if (WAVES > kWalkWaves && chunks <= WAVES)  // uniform
+            loop(std::integral_constant<int, 1>{});
+        else if (WAVES > kWalkWaves && chunks <= 2 * WAVES)
+            loop(std::integral_constant<int, 2>{});
+        else
+            loop(std::integral_constant<int, kEmitBatch>{});
+    };
     __syncthreads();  // every wavefront is done with the set, and with what slot_word held
     for (uint32_t i = tid * 8; i < (uint32_t)a.n_out; i += THREADS * 8) *(uint4 *)&slot_word[i] = make_uint4(0, 0, 0, 0);
     auto words4 = [&](uint32_t c) {  // the lane's four words of a chunk, none past the last chunk
         return c < chunks ? *(const uint4 *)&mask[c * kBitmapChunk + 4 * lane] : make_uint4(0, 0, 0, 0);
     };
-    for (uint32_t c0 = wave; c0 < chunks; c0 += WAVES * kEmitBatch) {
-        uint32_t sum[kEmitBatch];
+    auto count = [&](auto batch) {
+        constexpr int BATCH = decltype(batch)::value;
+        for (uint32_t c0 = wave; c0 < chunks; c0 += WAVES * BATCH) {
+            uint32_t sum[BATCH];
 #pragma unroll
-        for (int b = 0; b < kEmitBatch; ++b) {
-            const uint4 x = words4(c0 + b * WAVES);
-            sum[b] = __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w);
+            for (int b = 0; b < BATCH; ++b) {
+                const uint4 x = words4(c0 + b * WAVES);
+                sum[b] = __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w);
+            }
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b) sum[b] = wave_scan_add(sum[b]);
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b)
+                if (lane == 63 && c0 + b * WAVES < chunks) chunk_n[c0 + b * WAVES] = sum[b];
         }
-#pragma unroll
-        for (int b = 0; b < kEmitBatch; ++b) sum[b] = wave_scan_add(sum[b]);
-#pragma unroll
-        for (int b = 0; b < kEmitBatch; ++b)
-            if (lane == 63 && c0 + b * WAVES < chunks) chunk_n[c0 + b * WAVES] = sum[b];
-    }
+    };
+    by_batches(count);
     __syncthreads();
     // every wavefront sums the chunks before each of its own by itself (lane l holds chunks l, l + 64, l + 128)
     uint32_t cn[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i) cn[i] = (uint32_t)(lane + 64 * i) < chunks ? chunk_n[lane + 64 * i] : 0u;
     static_assert(kBitmapChunks <= 3 * 64, "three chunks a lane");
-    for (uint32_t c0 = wave; c0 < chunks; c0 += WAVES * kEmitBatch) {
-        uint4 x[kEmitBatch];
-        uint32_t n3[kEmitBatch], at[kEmitBatch];
+    auto note_places = [&](auto batch) {
+        constexpr int BATCH = decltype(batch)::value;
+        for (uint32_t c0 = wave; c0 < chunks; c0 += WAVES * BATCH) {
+            uint4 x[BATCH];
+            uint32_t n3[BATCH], at[BATCH];
 #pragma unroll
-        for (int b = 0; b < kEmitBatch; ++b) {
-            const uint32_t c = c0 + b * WAVES;
-            x[b] = words4(c);
-            n3[b] = __popc(x[b].x) + __popc(x[b].y) + __popc(x[b].z) + __popc(x[b].w);
-            at[b] = ((uint32_t)lane < c ? cn[0] : 0u) + ((uint32_t)lane + 64 < c ? cn[1] : 0u) + ((uint32_t)lane + 128 < c ? cn[2] : 0u);
+            for (int b = 0; b < BATCH; ++b) {
+                const uint32_t c = c0 + b * WAVES;
+                x[b] = words4(c);
+                n3[b] = __popc(x[b].x) + __popc(x[b].y) + __popc(x[b].z) + __popc(x[b].w);
+                at[b] = ((uint32_t)lane < c ? cn[0] : 0u) + ((uint32_t)lane + 64 < c ? cn[1] : 0u) + ((uint32_t)lane + 128 < c ? cn[2] : 0u);
+            }
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b) at[b] = wave_total(wave_scan_add(at[b])) + wave_scan_add(n3[b]) - n3[b];
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b) {
+                const uint32_t w = (c0 + b * WAVES) * kBitmapChunk + 4 * lane;
+                if (x[b].x) slot_word[at[b]] = (uint16_t)(w + 1);
+                at[b] += __popc(x[b].x);
+                if (x[b].y) slot_word[at[b]] = (uint16_t)(w + 2);
+                at[b] += __popc(x[b].y);
+                if (x[b].z) slot_word[at[b]] = (uint16_t)(w + 3);
+                at[b] += __popc(x[b].z);
+                if (x[b].w) slot_word[at[b]] = (uint16_t)(w + 4);
+            }
         }
-#pragma unroll
-        for (int b = 0; b < kEmitBatch; ++b) at[b] = wave_total(wave_scan_add(at[b])) + wave_scan_add(n3[b]) - n3[b];
-#pragma unroll
-        for (int b = 0; b < kEmitBatch; ++b) {
-            const uint32_t w = (c0 + b * WAVES) * kBitmapChunk + 4 * lane;
-            if (x[b].x) slot_word[at[b]] = (uint16_t)(w + 1);
-            at[b] += __popc(x[b].x);
-            if (x[b].y) slot_word[at[b]] = (uint16_t)(w + 2);
-            at[b] += __popc(x[b].y);
-            if (x[b].z) slot_word[at[b]] = (uint16_t)(w + 3);
-            at[b] += __popc(x[b].z);
-            if (x[b].w) slot_word[at[b]] = (uint16_t)(w + 4);
-        }
-    }
+    };
+    by_batches(note_places);
     __syncthreads();
     int32_t *out = a.out_idx + a.sink;
     // a wavefront's places lie side by side: the last note of one group of 64 serves the next
@@ -2331,7 +2350,7 @@ constexpr int kRelayCombos = 4;                                 // from that man
 constexpr uint32_t kRelayShare = 96, kRelayShareTable = 48;      // .. no share is more cells (with the word table)
 constexpr int kRelayRaw = 16;                                   // cells of a list a lane fetches ahead
 constexpr int kRelayKept = kRingBytes / 4 / kWalkWaves;         // cells a wavefront keeps
-// Eight wavefronts take turns, sixteen clear the set and read it off at the end (1M scores, 48 combinations 26.5 -> 24.4 us, 9001 19.7 -> 19.4).
+// Eight wavefronts take turns, sixteen clear the set and read it off at the end (1M scores, 48 combinations 26.5 -> 24.4 us, 9001 19.4 -> 18.7).
 constexpr int kRelayThreads = 1024;
 constexpr uint32_t kRelayChunk = 64 * kWalkPer;                 // cells it looks at at a time with the turn
 template <bool HASHED>

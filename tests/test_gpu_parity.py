@@ -949,6 +949,8 @@ RELAY_CASES = [
     (40000, 2, 8192, (32, 8, 4, 2), ALL16, "equal"), (30000, 0, 5000, (16, 32), (3, 4), "narrow"),
     (700, 0, 700, (2, 4, 8), ALL16, "few_values"), (20, 3, 17, (32, 1, 16), (1, 2, 9), "random"),  # lists that run out, empty ones
     (9000, 0, 4 * 95 + 1, (1,), (1, 2, 3, 4), "random"), (9000, 0, 300, (8,), (1, 2, 3), "random"),
+    (131072, 0, 4096, (2, 4, 8), ALL16, "random"), (131073, 0, 900, (2, 4, 8), ALL16, "random"),  # 16 chunks of the set, one more
+    (262144, 0, 900, (2, 4, 8), ALL16, "random"), (262145, 0, 4096, (2, 4, 8), ALL16, "random"),  # 32, one more
     (1200000, 4, 4096, (2, 4, 8), ALL16, "needles"), (1200001, 0, 3000, (1,), (7,) * 33, "two_values"),  # the word table
 ]
 
