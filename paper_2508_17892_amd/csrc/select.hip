@@ -61,6 +61,7 @@
 // is deterministic.  An element of m tokens ranks its tokens in ascending order, which is the order
 // the same key gives them once the element index is replaced by the token index.
 #include "ilre_internal.h"
+#include "seed_interval.h"
 
 #include <float.h>
 #include <string.h>
@@ -2160,13 +2161,10 @@ __device__ __forceinline__ void walk_items(const WalkArgs &a, unsigned char *sme
         for (int i = 0; i < kWalkPer; ++i) {
             bool some;
             if (SEEDS) {
-                // the tokens whose window holds the seed and nothing that outranks it
-                const int32_t r = (int32_t)reach, at = (int32_t)it[i];
-                const int32_t l = min(min(r, (int32_t)(dm[i] & 0xFFFFu) - r - 1), at);
-                const int32_t e = min(min(r, (int32_t)(dm[i] >> 16) - r - 1), (int32_t)a.len - 1 - at);
-                some = (l + e >= 0) & (base + tid * kWalkPer + i < nseeds);
-                first[i] = some ? (uint32_t)(at - l) : 0u;
-                last[i] = some ? (uint32_t)(at + e) : 0u;
+                const SeedInterval own = seed_interval(base + tid * kWalkPer + i < nseeds, it[i], dm[i], reach, a.len);
+                some = own.some;
+                first[i] = own.first;
+                last[i] = own.last;
             } else {
                 some = base + tid * kWalkPer + i < cn;
                 first[i] = some ? it[i] * reach : 0u;

@@ -100,3 +100,16 @@ def test_library_host_code_runs_clean_under_sanitizers():
     assert run.returncode == 0, (run.stdout[-3000:], run.stderr[-3000:])
     assert "0 failures" in run.stdout
     assert "runtime error" not in run.stderr and "AddressSanitizer" not in run.stderr, run.stderr[-3000:]
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
+def test_seed_interval_is_defined_for_whatever_lies_behind_the_last_seed():
+    from paper_2508_17892_amd import build as hip_build
+
+    os.makedirs(OUT, exist_ok=True)
+    exe = os.path.join(OUT, "seed_interval_driver")
+    subprocess.run(["hipcc", *hip_build.FLAGS, "-Xarch_host", "-fsanitize=undefined", "-Xarch_host", "-fno-sanitize-recover=all", "-fno-gpu-sanitize",
+                    "-o", exe, os.path.join(HERE, "seed_interval_driver.hip"), "-Xarch_host", "-fsanitize=undefined"], check=True, capture_output=True)
+    run = subprocess.run([exe], env=SAN_ENV, capture_output=True, text=True, timeout=60)
+    assert run.returncode == 0 and "0 failures" in run.stdout, (run.stdout[-2000:], run.stderr[-2000:])
+    assert "runtime error" not in run.stderr, run.stderr[-2000:]
