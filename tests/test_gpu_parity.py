@@ -207,8 +207,8 @@ def test_second_pass_merges_the_partial_statistics(dtype, Lq, G, Hkv):
     """In the whole path the second scoring pass merges the splits' partial row statistics itself, up to 32 splits (64 where all
     workgroups have as many rows, bf16), in the order the merge kernel of the staged call uses: the scores are the same bits either way.  Numbers of splits
     around the 16 sums and the line (bf16: one a tile up to 64; fp32: one for two tiles of 32 tokens, or fewer of more tiles where that keeps
-    every compute unit as busy: 17 to 32 of 66 to 128 tiles with two blocks of rows); one row beyond every frozen reference, so that a
-    split's partial has another reference."""
+    every compute unit as busy: 17 to 32 of 66 to 128 tiles with two blocks of rows); one row of a head far above the others in one split, so
+    that its partial has another reference."""
     tile = 128 if dtype == "bf16" and Lq * G == 512 else 64
     g = torch.Generator(device="cuda")
     g.manual_seed(5)
@@ -695,8 +695,8 @@ def test_custom_scale():
 
 @pytest.mark.parametrize("dtype,Lq", [("f32", 16), ("bf16", 64), ("bf16", 256)])
 def test_extreme_logits_take_the_safe_row_statistics_path(dtype, Lq):
-    """A key far above everything seen in the first tiles of its split: sums against a frozen
-    reference leave the fp32 range, and the row statistics must come from the always-safe redo."""
+    """A key far above everything else, in contexts of one tile a split, which follow the running maximum throughout (splits that freeze
+    their references have a test of their own)."""
     _announce(f"extreme logits {dtype} Lq={Lq}")
     L, Hq, Hkv = 6000, 4, 2
     inp = inputs.custom(L=L, Lq=Lq, Hq=Hq, Hkv=Hkv, d=128, dtype=dtype, seed=31)
@@ -719,6 +719,47 @@ def test_extreme_logits_take_the_safe_row_statistics_path(dtype, Lq):
     np.testing.assert_allclose(gm + np.log(gz), want_max + np.log(want_sum), rtol=2e-5, atol=2e-4)
     bad, worst = score_errors(scores.cpu().numpy(), want_score)
     assert bad == 0, f"{bad} scores out of tolerance, worst {worst:.2f}x"
+
+
+@pytest.mark.parametrize("Lq,tile,tiles", [(40, 64, 4), (256, 64, 4), (330, 64, 8), (512, 128, 4)],
+                         ids=["128_rows_idle_waves", "256_rows", "256_and_128_rows_idle_wave", "512_rows"])
+def test_a_split_is_walked_again_where_a_frozen_reference_does_not_hold(Lq, tile, tiles):
+    """The first pass freezes every row's reference after two tiles of a split.  64 kv heads leave 8 splits of 4 tiles (blocks of 256 and
+    128 rows: 4 of 8, blocks of 512: 4 of 4); the large key lies in the fourth tile of the second split, of every other head against the
+    first row and of the others against the last.  22 nats: the reference stays below the maximum, which shows that the tile is one
+    of the frozen ones.  79 nats (a finite sum beyond the limit) and 158 nats (an infinite one): the split is walked again and the reference is
+    the maximum itself.  Tolerances as everywhere."""
+    H, L = 64, 2045
+    rng = np.random.default_rng(Lq)
+    qf = rng.standard_normal((H, Lq, 128), dtype=np.float32)
+    base = rng.standard_normal((H, L, 128), dtype=np.float32)
+    at = (tiles + 3) * tile + 10
+    row = np.where(np.arange(H) % 2 == 0, 0, Lq - 1)
+    qf[np.arange(H), row] *= (np.sqrt(128.0) / np.linalg.norm(qf[np.arange(H), row], axis=1))[:, None].astype(np.float32)
+    loud = np.arange(H) * Lq + row  # of the statistics, head by head
+    for factor in (2.0, 7.0, 14.0):
+        _announce(f"frozen references Lq={Lq} factor={factor}")
+        kf = base.copy()
+        kf[:, at] = factor * qf[np.arange(H), row]
+        q_in, k_in = inputs.f32_to_bf16_bits(qf), inputs.f32_to_bf16_bits(kf)
+        want_score, want_max, want_sum = oracle.scores(q_in, k_in)
+        q, k = to_device(q_in), to_device(k_in)
+        row_max, row_sumexp = il.ilre_row_stats(q, k)
+        staged = il.ilre_col_scores(q, k, row_max, row_sumexp)
+        _, whole = il.ilre_recall(q, k, 64, (3, 7))
+        torch.cuda.synchronize()
+        gm, gz = row_max.cpu().numpy().astype(np.float64).ravel(), row_sumexp.cpu().numpy().astype(np.float64).ravel()
+        want_max, want_sum = np.asarray(want_max).ravel(), np.asarray(want_sum).ravel()
+        assert np.isfinite(gm).all() and np.isfinite(gz).all()
+        np.testing.assert_allclose(gm + np.log(gz), want_max + np.log(want_sum), rtol=2e-5, atol=2e-4)
+        if factor == 2.0:
+            assert (gm[loud] < want_max[loud] - 5).all()
+        else:
+            np.testing.assert_allclose(gm[loud], want_max[loud], rtol=2e-5)
+        for got in (staged, whole):
+            bad, worst = score_errors(got.cpu().numpy(), want_score)
+            assert bad == 0, f"{bad} scores out of tolerance, worst {worst:.2f}x"
+        assert torch.equal(staged, whole)
 
 
 def test_recall_replays_from_a_captured_graph():
