@@ -16,7 +16,8 @@ constexpr int kNumXCD = 8;
 // Asynchronous 16-byte-per-lane copy from a buffer resource straight into LDS: lane l of the
 // wavefront lands at lds_addr + 16*l; bytes past the resource's num_records read as zero.  Tracked
 // by vmcnt.  Issued as inline assembly so that the compiler's conservative alias handling does not
-// put a full vmcnt wait in front of every later LDS read.
+// put a full vmcnt wait in front of every later LDS read.  (s_nop: a copy to LDS has to be one wait state behind a scalar write
+// of M0, which the assembler does not insert by itself.)
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 __device__ __forceinline__ void lds_dma16(i32x4 rsrc, unsigned lds_addr, int voffset)
 {

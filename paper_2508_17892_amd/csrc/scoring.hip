@@ -226,11 +226,13 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
     // Query fragments, resident for the whole kernel: lane holds, for each of its NB blocks, row
     // l32 of the block, 16-byte chunk (2*step + half) of that row.  Rows past the group's last one are read as that one and become
     // zeros: pass 1 does not store their statistics, pass 2 gives them the offset -inf.
-    // They come by way of LDS, where a wavefront's copy of 32 rows is the size of half a tile's share (behind the first two tile buffers,
-    // laid out as a tile is), one block after the other.  Read straight into the registers a load takes 16 bytes from each of 64
-    // cache lines, and the K tiles queue up behind 16 of them a wavefront: 131072 tokens, 512 rows a workgroup, the tiles were there 6.7 us
-    // after the start.  Passes before -> after (with the partials and the flag of the redo below): 32768 tokens, 32/8 heads, 64 queries 24.4 + 22.9
-    // -> 22.5 + 21.8 us, 100003, 28/4, 17 21.3 -> 19.5 the first, 20000, 16/4, 40 13.1 + 11.9 -> 12.0 + 11.5, 1M no change.
+    // They come by way of LDS, where a wavefront's copy of 32 rows is twice its share of a tile, so that all of them fill two tile buffers (behind the
+    // first two, laid out as a tile is), one block after the other.  Read straight into the registers a load takes 16 bytes from each of 64
+    // cache lines, and the K tiles queue up behind 16 of them a wavefront: 131072 tokens, 512 rows a workgroup, the tiles were there 5.2 us
+    // after the start of a first pass and 7.7 of a second, 3.0 and 5.3 now (1M 6.8 and 6.3, 5.0 and 4.8).  Passes before -> after, together with the
+    // order of the partials, the flag of the redo below and sums as fma, which were not timed one by one: 32768 tokens, 32/8 heads, 64 queries 24.4 + 22.9
+    // -> 22.5 + 21.8 us, 100003, 28/4, 17 21.3 -> 20.4 the first, 20000, 16/4, 40 13.1 + 11.9 -> 12.0 + 11.5, 1M no change.
+    static_assert(WAVES * 32 * ROWB == 2 * TILE_BYTES, "the query rows end where `behind` begins");
     uint4 qf[NB][STEPS];
     const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
     const unsigned qlds = lds0 + 2 * TILE_BYTES + wave * (32 * ROWB);
@@ -411,8 +413,8 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
                 row_update<MASKED>(acc, a.c, m[b], z[b], tile * TN + tb * 32 + 4 * half, a.L);
         } else {
             // RMAX: the exponents' maximum, of which flush_finish takes the one exp2 a token (exp2 being monotonic).  Two fma and two maxima a
-            // matrix instruction keep up with it, two exp2 more do not: 131072 tokens, 128 queries, 32/8 heads 138 -> 111 us this pass, 1M
-            // tokens, 256 queries 1980 -> 1625.
+            // matrix instruction keep up with it, two exp2 more do not: 131072 tokens, 128 queries, 32/8 heads 144 -> 114 us this pass, 1M
+            // tokens, 256 queries 1981 -> 1621.
             float e[16];
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -433,7 +435,7 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
                 col = part;
             else
                 col = RMAX ? fmaxf(col, part) : col + part;
-            // (the unit before a split's very first one stores zeros into a buffer that is rewritten
+            // (the unit before a split's very first one stores zeros, max: -inf, into a buffer that is rewritten
             // before it is read: no condition here, the tile body stays free of branches)
             if (b == NB - 1) red[(rb * NPART + wave * 2 + half) * RSTR + tb * 32 + l32] = col;
         }
@@ -451,7 +453,7 @@ __device__ __forceinline__ void score_rows(const ScoreArgs &a, int g, int split,
                 red[(i / (2 * TN) * NPART + wave * 2 + i / TN % 2) * RSTR + i % TN] = RMAX ? -INFINITY : 0.f;
 
         // acc[u & 1] receives unit u (a 32-token block against the wave's NB query blocks); the unit
-        // before the very first one is all -inf, which the softmax arithmetic turns into zeros.
+        // before the very first one is all -inf, which the softmax arithmetic turns into zeros (max over rows: leaves).
     #pragma unroll
         for (int b = 0; b < NB; ++b) {
     #pragma unroll
@@ -1090,9 +1092,18 @@ __global__ void reduce_units(const float *partial, int nunits, int64_t L, float 
 // of three tiles, of two tiles and 32 query rows a wavefront (as much as two tiles)
 constexpr size_t tile_lds_bytes(int waves, int tiles) { return tiles * (size_t)Bf16::tile_tokens(waves) * (Bf16::kChunksPerRow * 16); }
 
-// The dynamic-LDS ceiling of a kernel is raised once per process (to the most any plan asks of it: the
-// 8-wavefront tiles plus the partial-result buffers of pass 2), not on every launch.
+// Behind the query rows, which start behind two tiles: pass 1's flag, or the offsets of pass 2's rows.
+constexpr size_t stats_lds_bytes(int waves) { return tile_lds_bytes(waves, 4) + 16; }
+constexpr size_t cols_lds_bytes(int waves, int rows)
+{
+    return std::max(tile_lds_bytes(waves, 4) + rows * sizeof(float),
+                    tile_lds_bytes(waves, 3) + 3 * 2 * (size_t)waves * (Bf16::tile_tokens(waves) + 36) * sizeof(float));  // pitch <= tokens + 36
+}
+
+// The dynamic-LDS ceiling of a kernel is raised once per process (beyond the most any plan asks of it: 8 wavefronts' query rows
+// behind two tiles, and their offsets), not on every launch.
 constexpr int kMaxDynamicLds = 144 * 1024;  // leaves room for the few bytes of static LDS a kernel may hold
+static_assert(std::max(stats_lds_bytes(8), cols_lds_bytes(8, 512)) <= kMaxDynamicLds && kF32Lds <= kMaxDynamicLds, "room for every plan");
 hipError_t raise_lds_limit_once(const void *kernel)
 {
     static std::mutex mutex;
@@ -1195,10 +1206,8 @@ ScorePlan make_score_plan(int dtype, int64_t L, int Lq, int Hq, int Hkv, bool ro
     p.table_tag = tag;
     p.lds_bytes_stats = p.lds_bytes_cols = kF32Lds;
     if (dtype == ILRE_F32) return p;
-    const size_t start = tile_lds_bytes(p.waves, 4);  // and behind it pass 1's flag or pass 2's row offsets
-    p.lds_bytes_stats = start + 16;
-    p.lds_bytes_cols = std::max(start + (size_t)p.rows_per_wg * sizeof(float),
-                                tile_lds_bytes(p.waves, 3) + 3 * 2 * (size_t)p.waves * (p.tile_tokens + 36) * sizeof(float));  // pitch <= tokens + 36
+    p.lds_bytes_stats = stats_lds_bytes(p.waves);
+    p.lds_bytes_cols = cols_lds_bytes(p.waves, p.rows_per_wg);
     return p;
 }
 
