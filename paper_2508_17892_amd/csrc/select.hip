@@ -1973,12 +1973,12 @@ __device__ __forceinline__ void emit_bitmap(const WalkArgs &a, const uint32_t *m
     // SIMD in each other's way (48 combinations, budget 1000, the whole walk with eight wavefronts, sixteen in batches of four, so:
     // 116363 scores 19.7, 20.1, 19.1 us, 200000 19.8, 20.3, 19.6, 300000, still four, 21.2, 20.6, 20.6).
     auto by_batches = [&](auto loop) {
-        if (WAVES > kWalkWaves && chunks <= WAVES)  // uniform
-            loop(std::integral_constant<int, 1>{});
-        else if (WAVES > kWalkWaves && chunks <= 2 * WAVES)
+        if (WAVES == kWalkWaves || chunks > 2 * WAVES)  // uniform
+            loop(std::integral_constant<int, kEmitBatch>{});
+        else if (chunks > WAVES)
             loop(std::integral_constant<int, 2>{});
         else
-            loop(std::integral_constant<int, kEmitBatch>{});
+            loop(std::integral_constant<int, 1>{});
     };
     __syncthreads();  // every wavefront is done with the set, and with what slot_word held
     for (uint32_t i = tid * 8; i < (uint32_t)a.n_out; i += THREADS * 8) *(uint4 *)&slot_word[i] = make_uint4(0, 0, 0, 0);
